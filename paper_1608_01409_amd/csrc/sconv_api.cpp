@@ -48,7 +48,20 @@ struct sconv_csr {
     DeviceDirect dev_direct;
     bool lds_uploaded = false, direct_uploaded = false;
     int planned_n = 0;       // batch size the current LDS tiling was chosen for
-    std::map<int, sconv_plan> plan_of_n;     // tilings already chosen, by batch size
+    struct Planned {
+        sconv_plan plan;
+        double us;           // the cost model's time for it
+    };
+    std::map<int, Planned> plan_of_n;        // tilings already chosen, by batch size
+    // small launches: the gather kernels, and the batch sizes they serve (by the cost models, or as measured)
+    struct GatherChoice {
+        bool use;
+        GatherShape shape;
+    };
+    DeviceGather gather;                     // convolution entry points
+    DeviceGather fc_gather;
+    std::map<int, GatherChoice> gather_of_n, fc_gather_of_n;
+    int max_row_nnz = 0;
     std::vector<StashedPacking> stash;       // earlier packings, oldest first
     // the layer the LDS kernels run: the layer itself, or for stride > 1 its stride-1 form over phase images
     bool phased = false;
@@ -147,12 +160,12 @@ static int plan_lds(sconv_csr *h, int n, bool resident_only = false)
     auto known = h->plan_of_n.find(n);
     const bool fresh = known == h->plan_of_n.end();
     if (fresh && resident_only) return SCONV_ERR_PLAN; // never planned for this batch size
-    rc = make_lds_tiling(d, fresh ? h->requested : known->second, n, avg, t, h->phase_cg()); // a known tiling has every field: no search
+    rc = make_lds_tiling(d, fresh ? h->requested : known->second.plan, n, avg, t, h->phase_cg()); // a known tiling has every field: no search
     if (rc) return rc;
     auto remember = [&]() {
         if (!fresh) return;
         if (h->plan_of_n.size() >= kPlansRemembered) h->plan_of_n.clear();
-        h->plan_of_n[n] = t.p;
+        h->plan_of_n[n] = {t.p, t.us};
     };
     if (h->has_lds && same_plan(t.p, h->flat ? h->lds_flat.t.p : h->lds.t.p)) {
         remember();
@@ -209,6 +222,7 @@ static int finish_create(sconv_csr *h, const sconv_plan *plan)
     if (plan) h->requested = *plan;
     if (h->requested.kernel < 0 || h->requested.kernel > 4) return SCONV_ERR_PLAN;
     const sconv_desc &d = h->desc;
+    for (int k = 0; k < d.K; ++k) h->max_row_nnz = std::max(h->max_row_nnz, h->canon.rowptr[k + 1] - h->canon.rowptr[k]);
     int rc = pack_direct(d, h->canon, h->direct);
     if (rc) return rc;
     h->kdesc = d;
@@ -434,6 +448,88 @@ extern "C" int sconv_forward_fused(sconv_csr *h, const float *in, float *out, in
     return forward_impl(h, in, out, N, ep, hip_stream);
 }
 
+// No field of the tiling was requested: the library follows the batch size, and may leave the LDS kernels alone.
+static bool free_choice(const sconv_csr *h)
+{
+    const sconv_plan &rq = h->requested;
+    return !rq.nt && !rq.cb && !rq.waves && !rq.cg && !rq.rows_w && !rq.t && !rq.band && !rq.strip && !rq.splits;
+}
+
+// The gather kernels are taken when they are expected to win by this much.  Of 75 convolutions run both ways the models
+// then lose none by more than 10 % (at 1.05: four, the worst 31 us instead of 23.5; the LDS model reads up to 40 % high
+// on launches of 5-20 us); of 25 fully connected layers none at 1.1.
+static const double kGatherMargin = 1.25, kFcGatherMargin = 1.1;
+
+static double avg_row_nnz(const sconv_csr *h) { return h->desc.K ? (double)h->canon.val.size() / h->desc.K : 0.0; }
+
+// The LDS path's time for N images: the flat-stream kernel's, and for layers that need phase images the pass that writes
+// them (a launch, and their bytes written and read).
+static double planned_us(const sconv_csr *h, int N, double flat_us)
+{
+    if (!h->phased || flat_us <= 0 || f_tiling(h).phase_cg > 0) return flat_us;
+    return flat_us + 4.0 + 2.0 * N * h->kdesc.C * h->kdesc.H * h->kdesc.W * 4.0 / 4.0e6;
+}
+
+// Whether a call with N images goes to the gather kernel.  Only launches with little arithmetic do: its multiply-adds
+// cost about three times the LDS kernels' (4.4 against 10-20 million per microsecond), its fixed price is a third of
+// theirs (3.5 us against 6-15).  Both cost models are asked; `lds_us` is the LDS kernel's time.
+static const sconv_csr::GatherChoice &gather_choice(sconv_csr *h, int N, double lds_us)
+{
+    auto known = h->gather_of_n.find(N);
+    if (known != h->gather_of_n.end()) return known->second;
+    sconv_csr::GatherChoice c = {false, {0, 0, 0.0}};
+    if (gather_fits(h->desc, N)) {
+        c.shape = choose_gather(h->desc, N, avg_row_nnz(h), h->max_row_nnz);
+        c.use = c.shape.us * kGatherMargin < lds_us;
+    }
+    if (h->gather_of_n.size() >= kPlansRemembered) h->gather_of_n.clear();
+    return h->gather_of_n[N] = c;
+}
+
+// Set-up on this device: the address of the library's static scratch is looked up with the first upload, so that
+// sconv_forward_noalloc finds it known (a failure here is that entry point's to report).
+static void find_static_scratch()
+{
+    void *base;
+    size_t bytes;
+    int ignored = 0;
+    (void)static_scratch(&base, &bytes, &ignored);
+}
+
+static int upload_gather(sconv_csr *h, DeviceGather &dev, bool fc)
+{
+    if (dev.uploaded) return SCONV_OK;
+    try {
+        PackedGather p;
+        int rc = fc ? pack_fc_gather(h->desc, h->canon, p) : pack_gather(h->desc, h->canon, p);
+        if (!rc) rc = upload(p.ent.data(), p.ent.size() * 8, &dev.ent, &h->hip_err);
+        if (!rc) rc = upload(p.rowptr.data(), p.rowptr.size() * 4, &dev.rowptr, &h->hip_err);
+        if (rc) {
+            release(dev.ent);
+            release(dev.rowptr);
+            dev = DeviceGather();
+            return rc;
+        }
+    } catch (const std::bad_alloc &) {
+        return SCONV_ERR_NOMEM;
+    }
+    dev.uploaded = true;
+    return SCONV_OK;
+}
+
+static int upload_flat(sconv_csr *h)
+{
+    if (h->lds_uploaded) return SCONV_OK;
+    const PackedFlat &f = h->lds_flat;
+    int rc = upload(f.pairs.data(), f.pairs.size() * 8, &h->dev_lds.pairs, &h->hip_err);
+    if (!rc) rc = upload(f.seg.data(), f.seg.size() * 4, &h->dev_lds.seg_ptr, &h->hip_err);
+    if (!rc) rc = upload(f.row_of.data(), f.row_of.size() * 4, &h->dev_lds.row_of, &h->hip_err);
+    if (!rc) rc = upload(f.store_tbl.data(), f.store_tbl.size() * 4, &h->dev_lds.store_tbl, &h->hip_err);
+    if (rc) return rc;
+    h->lds_uploaded = true;
+    return SCONV_OK;
+}
+
 // ws != nullptr: the caller forbids allocation.  Scratch then comes out of ws, and everything else the launch
 // needs (the tiling for N, its packing, the device copies) must already exist: SCONV_ERR_PLAN otherwise.
 static int forward_impl(sconv_csr *h, const float *in, float *out, int32_t N, const Epilogue &ep, void *hip_stream,
@@ -445,14 +541,37 @@ static int forward_impl(sconv_csr *h, const float *in, float *out, int32_t N, co
     const int64_t out_rows = (int64_t)N * h->desc.K, out_inner = (int64_t)og.OH * og.OW;
     bool use_lds = h->has_lds;
     // a tiling the library chose itself follows the batch size (only when none of its fields was requested)
-    const sconv_plan &rq = h->requested;
-    const bool free_choice = !rq.nt && !rq.cb && !rq.waves && !rq.cg && !rq.rows_w && !rq.t && !rq.band && !rq.strip && !rq.splits;
     // (batches below 4 use the tiling of batch 4: one tile of 4 images, not all of them present)
     const int n_plan = N < 4 ? 4 : N;
-    if (use_lds && free_choice && n_plan != h->planned_n) {
+    const bool choose = use_lds && free_choice(h);
+    const bool may_gather = choose && h->requested.kernel == 0 && h->flat;
+    if (ws && may_gather && h->gather.uploaded) {
+        // the gather kernel's arrays are the same for every batch size, so nothing has to be looked up or switched
+        const auto planned = h->plan_of_n.find(n_plan);
+        const auto known = h->gather_of_n.find(N);
+        if (planned != h->plan_of_n.end() && known != h->gather_of_n.end() && known->second.use)
+            return launch_gather(h->desc, h->gather, known->second.shape, in, out, N, ep, hip_stream, &h->hip_err);
+    }
+    if (choose && n_plan != h->planned_n) {
         try {
             const int prc = plan_lds(h, n_plan, ws != nullptr);
             if (prc) return prc;
+        } catch (const std::bad_alloc &) {
+            return SCONV_ERR_NOMEM;
+        }
+    }
+    if (!ws && may_gather && h->flat) {
+        try {
+            const auto planned = h->plan_of_n.find(n_plan);
+            const sconv_csr::GatherChoice &c = gather_choice(h, N, planned == h->plan_of_n.end() ? 0.0 : planned_us(h, N, planned->second.us));
+            if (c.use) {
+                if (!h->gather.uploaded) find_static_scratch();
+                int rc = upload_gather(h, h->gather, false);
+                // batches of 1-3 share a tiling: a later call with another of them may want the LDS kernel without uploading
+                if (!rc && N < 4) rc = upload_flat(h);
+                if (rc) return rc;
+                return launch_gather(h->desc, h->gather, c.shape, in, out, N, ep, hip_stream, &h->hip_err);
+            }
         } catch (const std::bad_alloc &) {
             return SCONV_ERR_NOMEM;
         }
@@ -481,19 +600,9 @@ static int forward_impl(sconv_csr *h, const float *in, float *out, int32_t N, co
     }
     if (use_lds && h->flat) {
         if (!h->lds_uploaded) {
-            const PackedFlat &f = h->lds_flat;
-            rc = upload(f.pairs.data(), f.pairs.size() * 8, &h->dev_lds.pairs, &h->hip_err);
-            if (!rc) rc = upload(f.seg.data(), f.seg.size() * 4, &h->dev_lds.seg_ptr, &h->hip_err);
-            if (!rc) rc = upload(f.row_of.data(), f.row_of.size() * 4, &h->dev_lds.row_of, &h->hip_err);
-            if (!rc) rc = upload(f.store_tbl.data(), f.store_tbl.size() * 4, &h->dev_lds.store_tbl, &h->hip_err);
+            rc = upload_flat(h);
             if (rc) return rc;
-            h->lds_uploaded = true;
-            // set-up on this device: the address of the library's static scratch is looked up now, so that
-            // sconv_forward_noalloc finds it known (a failure here is that entry point's to report)
-            void *base;
-            size_t bytes;
-            int ignored = 0;
-            (void)static_scratch(&base, &bytes, &ignored);
+            find_static_scratch();
         }
         const LdsTiling &ft = f_tiling(h);
         Lds2Layout lay = nchw_layout(h->kdesc, ft);
@@ -661,6 +770,20 @@ static int plan_fc(sconv_csr *h, int N, const sconv_plan *force = nullptr)
     return SCONV_OK;
 }
 
+// The same decision for the fully connected entry point: up to SCONV_FC_GATHER_MAX_N images, against the tiling just packed.
+static const sconv_csr::GatherChoice &fc_gather_choice(sconv_csr *h, int N)
+{
+    auto known = h->fc_gather_of_n.find(N);
+    if (known != h->fc_gather_of_n.end()) return known->second;
+    sconv_csr::GatherChoice c = {false, {0, 0, 0.0}};
+    if (free_choice(h) && h->requested.kernel == 0 && fc_gather_fits(h->desc, N)) {
+        c.shape = choose_fc_gather(h->desc, N, avg_row_nnz(h), h->max_row_nnz);
+        c.use = c.shape.us * kFcGatherMargin < h->fc_flat.t.us;
+    }
+    if (h->fc_gather_of_n.size() >= kPlansRemembered) h->fc_gather_of_n.clear();
+    return h->fc_gather_of_n[N] = c;
+}
+
 extern "C" int sconv_fc_plan(sconv_csr *h, int32_t N, sconv_plan *plan)
 {
     if (!h || !plan) return SCONV_ERR_NULL;
@@ -686,6 +809,18 @@ extern "C" int sconv_fc_forward(sconv_csr *h, const float *in_t, float *out_t, i
         return SCONV_ERR_NOMEM;
     }
     if (rc) return rc;
+    Epilogue ep;
+    ep.bias = bias;
+    ep.relu = relu != 0;
+    try {
+        const sconv_csr::GatherChoice &c = fc_gather_choice(h, N);
+        if (c.use) {
+            rc = upload_gather(h, h->fc_gather, true);
+            return rc ? rc : launch_fc_gather(h->desc, h->fc_gather, c.shape, in_t, out_t, N, ep, hip_stream, &h->hip_err);
+        }
+    } catch (const std::bad_alloc &) {
+        return SCONV_ERR_NOMEM;
+    }
     if (!h->fc_uploaded) {
         const PackedFlat &f = h->fc_flat;
         rc = upload(f.pairs.data(), f.pairs.size() * 8, &h->fc_dev.pairs, &h->hip_err);
@@ -704,26 +839,24 @@ extern "C" int sconv_fc_forward(sconv_csr *h, const float *in_t, float *out_t, i
     lay.in_tile = nc; lay.in_img = 1; lay.in_ch = (int64_t)h->fc_desc.H * N; lay.in_pos = 4;
     lay.in_rec_fixed = C * N * 4; lay.in_rec_img = 0; lay.in_rec_tile = nc * 4;
     lay.out_tile = nc; lay.out_band = 0; lay.out_row = N; lay.out_img = 1; lay.out_pos = 4;
-    Epilogue ep;
-    ep.bias = bias;
-    ep.relu = relu != 0;
     return run_flat(h, h->fc_desc, t, h->fc_dev, lay, in_t, out_t, 4 * h->fc_tiles, K, N, ep, hip_stream);
 }
 
 // ---- measured choice of the tiling ----------------------------------------------------------------------
 
-// Times run() after install(candidate) for every candidate and returns the index of the fastest in *best
-// (-1 if none could be installed and run).  A candidate that cannot be packed or launched is skipped.
+// Times run() after install(i) for candidates 0 .. n-1 and returns the index of the fastest in *best
+// (-1 if none could be installed and run).  A candidate that cannot be packed or launched is skipped; candidate
+// `own` is the one an untuned call uses.
 // All candidates are packed and uploaded first and stay in the handle's stash, so that the timed part only
 // switches between them: the GPU's clocks drop while the host packs, and a candidate timed right after
 // that would look 10-15 % slower than one timed later.
 template <class Install, class Run>
-static int time_candidates(sconv_csr *h, const std::vector<LdsTiling> &cands, Install install, Run run, void *stream, int *best)
+static int time_candidates(sconv_csr *h, size_t n, size_t own, Install install, Run run, void *stream, int *best)
 {
     *best = -1;
     std::vector<size_t> ok;
-    for (size_t i = 0; i < cands.size(); ++i)
-        if (install(cands[i].p) == SCONV_OK && run() == SCONV_OK) ok.push_back(i);
+    for (size_t i = 0; i < n; ++i)
+        if (install(i) == SCONV_OK && run() == SCONV_OK) ok.push_back(i);
     if (ok.empty()) return SCONV_OK;
     StreamTimer timer;
     int rc = timer_create(timer, &h->hip_err);
@@ -738,7 +871,7 @@ static int time_candidates(sconv_csr *h, const std::vector<LdsTiling> &cands, In
     };
     // warm-up, about 30 ms of the first candidate
     float ms = 0, spent = 0;
-    rc = install(cands[ok[0]].p);
+    rc = install(ok[0]);
     for (int k = 0; k < 200 && !rc && spent < 30.0f; ++k) {
         rc = timed(4, &ms);
         spent += 4 * ms;
@@ -747,7 +880,7 @@ static int time_candidates(sconv_csr *h, const std::vector<LdsTiling> &cands, In
     std::vector<float> t(ok.size(), std::numeric_limits<float>::max());
     for (int round = 0; round < 3 && !rc; ++round)
         for (size_t j = 0; j < ok.size() && !rc; ++j) {
-            rc = install(cands[ok[j]].p);
+            rc = install(ok[j]);
             if (!rc) rc = timed(1, &ms);
             if (rc) break;
             const int reps = std::max(3, std::min(40, (int)(2.0f / std::max(ms, 0.01f))));
@@ -760,7 +893,8 @@ static int time_candidates(sconv_csr *h, const std::vector<LdsTiling> &cands, In
     for (size_t j = 1; j < ok.size(); ++j)
         if (t[j] < t[arg]) arg = j;
     // the timings repeat to 1-2 %: the cost model's own choice stands unless another is clearly faster
-    if (ok[0] == 0 && t[arg] > 0.985f * t[0]) arg = 0;
+    for (size_t j = 0; j < ok.size(); ++j)
+        if (ok[j] == own && t[arg] > 0.985f * t[j]) arg = j;
     *best = (int)ok[arg];
     return SCONV_OK;
 }
@@ -807,9 +941,7 @@ extern "C" int sconv_tune(sconv_csr *h, const float *in, float *out, int32_t N, 
 {
     if (!h || !in || !out) return SCONV_ERR_NULL;
     if (N < 1) return SCONV_ERR_BATCH;
-    const sconv_plan &rq = h->requested;
-    const bool free_choice = !rq.nt && !rq.cb && !rq.waves && !rq.cg && !rq.rows_w && !rq.t && !rq.band && !rq.strip && !rq.splits;
-    if (!h->has_lds || !free_choice) return SCONV_ERR_PLAN;
+    if (!h->has_lds || !free_choice(h)) return SCONV_ERR_PLAN;
     const int n_plan = N < 4 ? 4 : N;
     const Epilogue none;
     try {
@@ -819,15 +951,28 @@ extern "C" int sconv_tune(sconv_csr *h, const float *in, float *out, int32_t N, 
         if (rc) return rc;
         int best = -1;
         StashRoom room(h, cands.size());
+        // the gather kernel is one more candidate where it can run (and the untuned choice where the models pick it)
+        h->gather_of_n.erase(N);
+        const size_t n_lds = cands.size();
+        sconv_csr::GatherChoice gc = {false, {0, 0, 0.0}};
+        const bool may_gather = h->requested.kernel == 0 && h->flat && gather_fits(h->desc, N);
+        if (may_gather) gc = gather_choice(h, N, planned_us(h, N, cands[0].us));
+        const bool own_gather = gc.use;
         rc = time_candidates(
-            h, cands,
-            [&](const sconv_plan &p) {
-                h->plan_of_n[n_plan] = p;
+            h, n_lds + (may_gather ? 1 : 0), own_gather ? n_lds : 0,
+            [&](size_t i) {
+                gc.use = i >= n_lds;
+                h->gather_of_n[N] = gc;
+                const LdsTiling &c = cands[i < n_lds ? i : 0];
+                h->plan_of_n[n_plan] = {c.p, c.us};
                 return plan_lds(h, n_plan);
             },
             [&]() { return forward_impl(h, in, out, N, none, hip_stream); }, hip_stream, &best);
         // the fastest, or the cost model's choice if nothing could be timed
-        h->plan_of_n[n_plan] = cands[best < 0 ? 0 : (size_t)best].p;
+        gc.use = best < 0 ? own_gather : (size_t)best >= n_lds;
+        h->gather_of_n[N] = gc;
+        const LdsTiling &c = cands[best < 0 || gc.use ? 0 : (size_t)best];
+        h->plan_of_n[n_plan] = {c.p, c.us};
         const int prc = plan_lds(h, n_plan);
         if (rc) return rc;
         if (prc) return prc;
@@ -853,11 +998,25 @@ extern "C" int sconv_fc_tune(sconv_csr *h, const float *in_t, float *out_t, int3
         int best = -1;
         StashRoom room(h, cands.size());
         h->fc_plan_of_n.erase(N);
+        h->fc_gather_of_n.erase(N);
+        rc = plan_fc(h, N, &cands[0].p);
+        if (rc) return rc;
+        h->fc_flat.t.us = cands[0].us;
+        const size_t n_lds = cands.size();
+        sconv_csr::GatherChoice gc = fc_gather_choice(h, N);
+        const bool may_gather = gc.shape.t > 0, own_gather = gc.use;
         rc = time_candidates(
-            h, cands, [&](const sconv_plan &p) { return plan_fc(h, N, &p); },
+            h, n_lds + (may_gather ? 1 : 0), own_gather ? n_lds : 0,
+            [&](size_t i) {
+                gc.use = i >= n_lds;
+                h->fc_gather_of_n[N] = gc;
+                return plan_fc(h, N, &cands[i < n_lds ? i : 0].p);
+            },
             [&]() { return sconv_fc_forward(h, in_t, out_t, N, nullptr, 0, hip_stream); }, hip_stream, &best);
         if (rc) return rc;
-        h->fc_plan_of_n[N] = cands[best < 0 ? 0 : (size_t)best].p;
+        gc.use = best < 0 ? own_gather : (size_t)best >= n_lds;
+        h->fc_gather_of_n[N] = gc;
+        h->fc_plan_of_n[N] = cands[best < 0 || gc.use ? 0 : (size_t)best].p;
         rc = plan_fc(h, N); // while the candidates' packings are still at hand
         if (rc) return rc;
     } catch (const std::bad_alloc &) {
@@ -882,6 +1041,10 @@ extern "C" void sconv_destroy_csr(sconv_csr *h)
     for (auto &sp : h->fc_stash) release_arrays(sp.dev);
     release(h->dev_direct.rowptr);
     release(h->dev_direct.trip);
+    for (DeviceGather *g : {&h->gather, &h->fc_gather}) {
+        release(g->ent);
+        release(g->rowptr);
+    }
     delete h;
 }
 

@@ -126,6 +126,7 @@ static int fill_tiling(const sconv_desc &d, const sconv_plan &p, LdsTiling &t, i
     if (p.band < 0 || p.band > g.OH) return SCONV_ERR_PLAN;
     if (p.waves % p.cg) return SCONV_ERR_PLAN;
     t.p = p;
+    t.us = 0.0;
     if (!is_flat_kernel(p.kernel)) t.p.kernel = 1;
     const bool flat = is_flat_kernel(t.p.kernel), flow = t.p.kernel == 4;
     t.vec = (p.nt % 4 == 0) ? 4 : 1;
@@ -418,6 +419,7 @@ static int search_lds_tilings(const sconv_desc &d, const sconv_plan &req, int N_
                         if (!req.splits && t.p.splits != sp) continue; // the same as a smaller choice
                         const double c = flat ? tiling_cost_flat(d, t, N_hint, avg_row_nnz, wide)
                                                    : tiling_cost(d, t, N_hint, avg_row_nnz);
+                        t.us = flat ? c : 0.0;
                         if (all) all->emplace_back(c, t);
                         if (best < 0 || c < best) {
                             best = c;
@@ -865,6 +867,101 @@ int unpack_direct(const sconv_desc &d, const PackedDirect &p, Canonical &out)
     }
     sort_rows_by_offset(d, rows, out);
     return SCONV_OK;
+}
+
+// ------------------------------------------------------------------ gather kernels (small launches)
+
+int pack_gather(const sconv_desc &d, const Canonical &c, PackedGather &out)
+{
+    const Geometry g = geometry(d);
+    out.ent.clear();
+    out.ent.reserve(c.val.size() + (size_t)d.K * SCONV_GATHER_CHUNK);
+    out.rowptr.assign(d.K + 1, 0);
+    for (int k = 0; k < d.K; ++k) {
+        for (int j = c.rowptr[k]; j < c.rowptr[k + 1]; ++j) {
+            const int off = c.off[j];
+            const int s = off % g.Wp, r = (off / g.Wp) % g.Hp, ca = off / (g.Wp * g.Hp);
+            const uint32_t byte_off = (uint32_t)((ca * d.H + r) * d.W + s) * 4u;
+            uint32_t vb;
+            std::memcpy(&vb, &c.val[j], 4);
+            out.ent.push_back((uint64_t)vb | ((uint64_t)(byte_off << 3 | (uint32_t)(31 - (r * d.S + s))) << 32));
+        }
+        while (out.ent.size() % SCONV_GATHER_CHUNK) out.ent.push_back(0);
+        if (out.ent.size() >= ((size_t)1 << 31)) return SCONV_ERR_RANGE;
+        out.rowptr[k + 1] = (int32_t)out.ent.size();
+    }
+    out.ent.resize(out.ent.size() + SCONV_GATHER_CHUNK, 0); // the kernel reads one chunk ahead
+    return SCONV_OK;
+}
+
+int pack_fc_gather(const sconv_desc &d, const Canonical &c, PackedGather &out)
+{
+    out.rowptr = c.rowptr;
+    out.ent.resize(c.val.size());
+    for (size_t j = 0; j < c.val.size(); ++j) {
+        uint32_t vb;
+        std::memcpy(&vb, &c.val[j], 4);
+        out.ent[j] = (uint64_t)vb | ((uint64_t)(uint32_t)c.off[j] << 32); // 1x1 image: the offset is the feature
+    }
+    return SCONV_OK;
+}
+
+// The kernel's own limits: a tap per bit of the lane mask, the image's byte offsets in 29 bits, everything else in 31.
+bool gather_fits(const sconv_desc &d, int N)
+{
+    const Geometry g = geometry(d);
+    const int64_t HW = (int64_t)d.H * d.W, OHW = (int64_t)g.OH * g.OW;
+    if ((int64_t)d.R * d.S > SCONV_GATHER_MAX_TAPS) return false;
+    if ((d.C * HW + ((int64_t)d.R * d.W + d.S)) * 4 >= ((int64_t)1 << 29)) return false;
+    return (int64_t)N * d.C * HW * 4 < ((int64_t)1 << 30) && (int64_t)N * OHW < ((int64_t)1 << 28) &&
+           ((int64_t)d.pad * d.W + d.pad) * 4 < ((int64_t)1 << 28);
+}
+
+bool fc_gather_fits(const sconv_desc &d, int N)
+{
+    return N >= 4 && N % 4 == 0 && N <= SCONV_FC_GATHER_MAX_N && (int64_t)d.C * N * 4 < ((int64_t)1 << 32);
+}
+
+// What a gather launch takes, in microseconds, fitted to 37 convolutions and 11 fully connected layers (0.1-480 million
+// multiply-adds) run in every shape: 3 us for a launch whatever it does, then the longer of two terms and a third of the
+// shorter one.  Throughput: a wave costs 0.12 us per thousand (index arithmetic, 30 % more for a second chunk of
+// positions), a 64-lane load 18 us per million (25 % more when the lanes are a stride apart).  Latency: a wave's
+// chunks of 8 nonzeros follow each other at 0.28 us; the longest row counts.
+GatherShape choose_gather(const sconv_desc &d, int N, double avg_row_nnz, int max_row_nnz)
+{
+    const Geometry g = geometry(d);
+    const double P = (double)N * g.OH * g.OW;
+    GatherShape best = {0, 0, 0.0};
+    for (int t = 1; t <= 2; ++t)
+        for (int split = 1; split <= 8; split *= 2) {
+            const double tiles = std::ceil(P / (64.0 * t)), chunks = std::max(1.0, std::ceil(avg_row_nnz / SCONV_GATHER_CHUNK + 0.4));
+            const double waves = d.K * tiles * split, loads = d.K * tiles * t * chunks * SCONV_GATHER_CHUNK;
+            const double thr = 0.12e-3 * waves * (1.0 + 0.3 * (t - 1)) + 0.018e-3 * loads * (d.stride > 1 ? 1.25 : 1.0);
+            const double lat = 0.28 * std::ceil((double)max_row_nnz / (SCONV_GATHER_CHUNK * split)) * std::sqrt((double)t);
+            const double us = 3.0 + std::max(thr, lat) + 0.35 * std::min(thr, lat);
+            if (best.t == 0 || us < best.us) best = GatherShape{t, split, us};
+        }
+    return best;
+}
+
+// The same for the fully connected kernel; t is the number of lanes (16-byte pieces of the batch) that share a nonzero.
+// A load instruction costs 50 us per million and up to 230 us more, the more separate pieces of memory its lanes read
+// (64 / t); a round of four nonzeros per lane group takes 0.28 us of latency.
+GatherShape choose_fc_gather(const sconv_desc &d, int N, double avg_row_nnz, int max_row_nnz)
+{
+    const int n4 = N / 4;
+    GatherShape best = {0, 0, 0.0};
+    for (int t = 1; t <= 32 && t < 2 * n4; t *= 2)
+        for (int split = 1; split <= 16; split *= 4) {
+            const double per_round = 4.0 * (64 / t) * split;
+            const double waves = (double)d.K * split * std::ceil((double)n4 / t);
+            const double rounds = std::max(1.0, std::ceil(avg_row_nnz / per_round + 0.3));
+            const double thr = 0.03e-3 * waves + (0.05e-3 + 0.23e-3 / t) * waves * rounds * 4.0;
+            const double lat = 0.28 * std::ceil(max_row_nnz / per_round);
+            const double us = 2.9 + std::max(thr, lat) + 0.35 * std::min(thr, lat);
+            if (best.t == 0 || us < best.us) best = GatherShape{t, split, us};
+        }
+    return best;
 }
 
 } // namespace sconv

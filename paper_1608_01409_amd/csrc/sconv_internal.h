@@ -66,6 +66,7 @@ struct LdsTiling {
     int page_cells;     // size of that page in cells of nt floats
     int strip_rows;     // strip layout: rows of the block of positions one chunk covers (64 / strip), else 0
     int out_pos;        // floats from one output position to the next in the caller's layout (1 for NCHW)
+    double us;          // what the cost model expects a launch to take (flat-stream tilings the search chose, else 0)
 };
 
 struct PackedLds {
@@ -105,6 +106,29 @@ struct Canonical {
     std::vector<int32_t> rowptr, colidx, off;
     std::vector<float> val;
 };
+
+// Packing for the gather kernels (small launches), the same for every batch size.  Convolutions: rows padded to whole
+// chunks, entry = (value bits, byte offset of (c, r, s) in the unpadded image << 3 | (31 - tap)); padding entries are
+// (0, 0).  Fully connected layers (taps = 0): entry = (value bits, feature), rows not padded.
+#define SCONV_GATHER_CHUNK 8
+#define SCONV_GATHER_MAX_TAPS 31
+#define SCONV_FC_GATHER_MAX_N 256
+struct PackedGather {
+    std::vector<uint64_t> ent;
+    std::vector<int32_t> rowptr;   // [K + 1], in entries
+};
+// What one wave of a gather kernel covers: t x 64 output positions (fully connected: t pieces of 4 images); split waves
+// share a row.
+struct GatherShape {
+    int t, split;
+    double us;                     // what the launch is expected to take
+};
+int pack_gather(const sconv_desc &d, const Canonical &c, PackedGather &out);
+int pack_fc_gather(const sconv_desc &d, const Canonical &c, PackedGather &out);
+bool gather_fits(const sconv_desc &d, int N);
+bool fc_gather_fits(const sconv_desc &d, int N);
+GatherShape choose_gather(const sconv_desc &d, int N, double avg_row_nnz, int max_row_nnz);
+GatherShape choose_fc_gather(const sconv_desc &d, int N, double avg_row_nnz, int max_row_nnz);
 
 int validate_desc(const sconv_desc &d);
 // rowptr starts at 0 and never falls, columns inside [0, Cg*R*S) and strictly ascending in each row
@@ -150,12 +174,31 @@ void phase_desc(const sconv_desc &d, sconv_desc &v);
 int phase_canonical(const sconv_desc &d, const Canonical &c, Canonical &vc);
 int unphase_canonical(const sconv_desc &d, const Canonical &vc, Canonical &out);
 
-// Device side (sconv_kernels.hip)
+// Division of a small non-negative number by a divisor fixed per launch: a multiply-high with
+// magic = ceil(2^32 / d), exact while n * d < 2^32 (the launcher checks the largest n of each use and passes
+// magic = 0, meaning "divide", where that does not hold or d is 1).  The generic 32-bit division costs some 30
+// instructions per use, and the kernel's first microsecond was mostly these.
+struct FastDiv {
+    unsigned d, magic;
+};
+inline FastDiv make_fastdiv(int d, int64_t n_max)
+{
+    FastDiv f;
+    f.d = (unsigned)d;
+    f.magic = (d > 1 && n_max * (int64_t)d < ((int64_t)1 << 32)) ? (unsigned)((((uint64_t)1 << 32) + d - 1) / (uint64_t)d) : 0u;
+    return f;
+}
+
+// Device side (sconv_kernels.hip, sconv_gather.hip)
 struct DeviceLds {
     void *pairs = nullptr, *seg_ptr = nullptr, *row_of = nullptr, *store_tbl = nullptr;
 };
 struct DeviceDirect {
     void *rowptr = nullptr, *trip = nullptr;
+};
+struct DeviceGather {
+    void *ent = nullptr, *rowptr = nullptr;
+    bool uploaded = false;
 };
 int launch_lds(const sconv_desc &d, const LdsTiling &t, const DeviceLds &dev, const float *in, float *out,
                int N, void *stream, int *hip_err);
@@ -164,6 +207,10 @@ struct Epilogue {
     const float *bias = nullptr;
     bool relu = false;
 };
+int launch_gather(const sconv_desc &d, const DeviceGather &dev, const GatherShape &gs, const float *in, float *out, int N,
+                  const Epilogue &ep, void *stream, int *hip_err);
+int launch_fc_gather(const sconv_desc &d, const DeviceGather &dev, const GatherShape &gs, const float *in_t, float *out_t, int N,
+                     const Epilogue &ep, void *stream, int *hip_err);
 // Where the flat-stream kernel finds its operands, in floats.  Input element (image i of tile m, channel c,
 // position p = Y*W + X of the unpadded image): m*in_tile + i*in_img + c*in_ch + p*in_pos.  Output (image i
 // of tile m, row k, band b, position q inside the band): m*out_tile + b*out_band + k*out_row + i*out_img +

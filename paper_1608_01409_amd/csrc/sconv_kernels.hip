@@ -18,7 +18,7 @@
 #include <set>
 #include <utility>
 
-#include "sconv_internal.h"
+#include "sconv_device.h"
 
 namespace sconv {
 
@@ -211,25 +211,6 @@ __global__ void __launch_bounds__(1024) sconv_lds_kernel(const LdsArgs a)
 //     blocks, stores) runs inside one asm statement that owns a fixed block of registers;
 //   * staging uses buffer loads into LDS whose range check returns 0 for the padding cells, so no
 //     part of a plane is ever cleared and every cell of a block is rewritten with each block.
-// Division of a small non-negative number by a divisor fixed per launch: a multiply-high with
-// magic = ceil(2^32 / d), exact while n * d < 2^32 (the launcher checks the largest n of each use and passes
-// magic = 0, meaning "divide", where that does not hold or d is 1).  The generic 32-bit division costs some 30
-// instructions per use, and the kernel's first microsecond was mostly these.
-struct FastDiv {
-    unsigned d, magic;
-};
-static __device__ __forceinline__ int fdiv(int n, FastDiv f)
-{
-    return f.magic ? (int)__umulhi((unsigned)n, f.magic) : n / (int)f.d;
-}
-static FastDiv make_fastdiv(int d, int64_t n_max)
-{
-    FastDiv f;
-    f.d = (unsigned)d;
-    f.magic = (d > 1 && n_max * (int64_t)d < ((int64_t)1 << 32)) ? (unsigned)((((uint64_t)1 << 32) + d - 1) / (uint64_t)d) : 0u;
-    return f;
-}
-
 struct Lds2Args {
     const float *in;
     float *out;
@@ -263,7 +244,6 @@ struct Lds2Args {
     FastDiv d_units, d_splits, d_bands, d_nkt, d_cg, d_wl, d_strip; // the divisors of the index arithmetic below
 };
 
-typedef int int4v __attribute__((ext_vector_type(4)));
 
 #include "sconv_lds2_asm.inc"
 

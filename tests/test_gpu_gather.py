@@ -1,0 +1,125 @@
+"""The gather kernels (small launches, straight from global memory): the library picks them by itself, so the cases
+here are small enough that it does, at the sizes where their index arithmetic can go wrong.  Tolerance as in
+test_gpu_parity.py: |gpu - oracle| <= 1e-5 * sum|w*x| per output, exactly zero where that sum is zero."""
+import sys
+
+import numpy as np
+import pytest
+import torch
+
+from oracle import spmdm_oracle as so
+from paper_1608_01409_amd import binding as B
+from paper_1608_01409_amd import workloads as wl
+
+pytestmark = pytest.mark.gpu
+TOL = 1e-5
+
+
+def say(msg):
+    print(f"[gpu-case] {msg}", flush=True)
+    sys.stdout.flush()
+
+
+def conv_case(layer, N, density, seed):
+    rng = np.random.default_rng(seed)
+    x = rng.standard_normal((N, layer.C, layer.H, layer.W)).astype(np.float32)
+    w = (rng.standard_normal((layer.K, layer.Cg, layer.R, layer.S)) * 0.01).astype(np.float32)
+    w = np.where(rng.random(w.shape) < density, w, np.float32(0)).astype(np.float32)
+    return x, w
+
+
+def lay(C, H, W, K, R, S, stride=1, pad=0, groups=1):
+    return wl.Layer(f"c{C}h{H}w{W}k{K}r{R}s{S}t{stride}p{pad}g{groups}", C, H, W, K, R, S, stride, pad, groups)
+
+
+# positions around a wave's 64 and 128, rows that do not fill a workgroup, every stride / padding / group form, the most
+# taps the lane mask holds (31), filters taller than wide and the reverse, images smaller than the filter's padding
+CONVS = [
+    (lay(1, 1, 1, 1, 1, 1), 1), (lay(3, 1, 1, 5, 1, 1), 63), (lay(3, 1, 1, 5, 1, 1), 65), (lay(5, 8, 8, 7, 3, 3, pad=1), 1),
+    (lay(5, 8, 8, 7, 3, 3, pad=1), 2), (lay(4, 9, 15, 6, 5, 5, pad=2), 1), (lay(6, 7, 9, 3, 1, 31, pad=15), 1),
+    (lay(6, 9, 7, 9, 31, 1, pad=15), 2), (lay(8, 11, 6, 4, 6, 5, pad=1, groups=2), 3), (lay(6, 13, 13, 12, 3, 3, 2, 1, 3), 5),
+    (lay(2, 23, 10, 5, 5, 3, 3, 2), 4), (lay(9, 2, 3, 8, 3, 3, pad=2), 7), (lay(64, 5, 5, 33, 3, 3, pad=1), 1),
+    (lay(300, 7, 7, 24, 3, 3, pad=1), 1), (lay(128, 6, 6, 130, 1, 1), 2), (lay(40, 6, 6, 10, 3, 3, 2), 1),
+]
+
+
+@pytest.mark.parametrize("layer,N", CONVS, ids=[f"{l.name}n{n}" for l, n in CONVS])
+@pytest.mark.parametrize("density", [0.15, 1.0])
+def test_small_convolutions(oracle, layer, N, density):
+    x, w = conv_case(layer, N, density, seed=N + layer.C)
+    if layer.K > 2:
+        w[1] = 0
+    say(f"gather {layer.name} N={N} density={density}")
+    h = B.sconv_create_csr(layer, w)
+    xd = torch.from_numpy(x).cuda()
+    out = torch.full((N, layer.K, layer.OH, layer.OW), float("nan"), device="cuda")
+    B.sconv_forward(h, xd, out)
+    got = out.cpu().numpy()
+    ref, ab, _ = oracle.sparse_conv(layer, w, x)
+    assert np.all(np.abs(got.astype(np.float64) - ref) <= TOL * ab)
+    assert np.all(got[ab == 0] == 0)
+    # the entry point that allocates nothing: the same kernel, the same bits
+    # (layers without an LDS tiling run the direct kernel, which that entry point refuses)
+    if B.sconv_csr_info(h)["plan"]["kernel"] != 2:
+        out2 = torch.full_like(out, float("nan"))
+        B.sconv_forward_noalloc(h, xd, out2)
+        assert torch.equal(out, out2)
+    # bias and ReLU, and a handle that is told to use the direct kernel
+    bias = np.random.default_rng(5).standard_normal(layer.K).astype(np.float32) * 0.05
+    bd = torch.from_numpy(bias).cuda()
+    got = B.sconv_forward_fused(h, xd, bd, True).cpu().numpy().astype(np.float64)
+    ref2, scale = oracle.bias_relu(ref, ab, bias, True)
+    assert np.all(np.abs(got - ref2) <= TOL * scale)
+    hd = B.sconv_create_csr(layer, w, dict(kernel=2))
+    direct = B.sconv_forward(hd, xd).cpu().numpy().astype(np.float64)
+    assert np.all(np.abs(direct - out.cpu().numpy()) <= 2 * TOL * ab)
+
+
+def test_infinities_reach_only_the_outputs_whose_nonzeros_read_them():
+    """Zero padding stays zero beside an infinite neighbour, padding entries of a row multiply nothing, and a pruned
+    weight never touches a NaN: the set of non-finite outputs is exactly what the nonzeros say."""
+    layer = lay(5, 6, 6, 11, 3, 3, pad=1)
+    x, w = conv_case(layer, 2, 0.2, seed=3)
+    x[0, 2, 0, 0], x[0, 2, 5, 5], x[1, 4, 3, 0] = np.inf, np.nan, -np.inf
+    say("gather non-finite inputs")
+    h = B.sconv_create_csr(layer, w)
+    got = B.sconv_forward(h, torch.from_numpy(x).cuda()).cpu().numpy()
+    xp = np.pad(x, ((0, 0), (0, 0), (1, 1), (1, 1)))
+    ref = np.zeros_like(got, dtype=np.float64)
+    for k, c, r, s in np.argwhere(w != 0):
+        ref[:, k] += np.float64(w[k, c, r, s]) * xp[:, c, r:r + 6, s:s + 6].astype(np.float64)
+    assert np.array_equal(np.isnan(ref), np.isnan(got)) and np.array_equal(np.isinf(ref), np.isinf(got))
+    assert np.isnan(ref).any() and np.isinf(ref).any() and np.isfinite(ref).any()
+    ok = np.isfinite(ref)
+    assert np.allclose(got[ok], ref[ok], rtol=0, atol=1e-6)
+
+
+@pytest.mark.parametrize("N", [4, 8, 12, 16, 20, 32, 36, 64, 68, 124, 128, 132, 252, 256])
+@pytest.mark.parametrize("K,C,density", [(1, 3, 1.0), (37, 129, 0.3), (9, 2500, 0.2), (300, 70, 0.02)])
+def test_fully_connected_small_batches(N, K, C, density):
+    rng = np.random.default_rng(N + K)
+    w = np.where(rng.random((K, C)) < density, rng.standard_normal((K, C)) * 0.05, 0).astype(np.float32)
+    if K > 4:
+        w[2] = 0
+    x_t = rng.standard_normal((C, N)).astype(np.float32)
+    if K == 37:
+        # activations no stored weight reads: nothing of them may show
+        unread = np.flatnonzero((w != 0).sum(0) == 0)
+        w[:, 5] = 0
+        x_t[5] = np.nan
+        x_t[unread] = np.inf
+    bias = (rng.standard_normal(K) * 0.5).astype(np.float32)
+    say(f"fc gather K={K} C={C} N={N} density={density}")
+    h = B.sconv_create_csr(B.fc_layer(C, K), w.reshape(K, C, 1, 1))
+    ref, ab = so.spmdm(w, np.where(np.isfinite(x_t), x_t, 0))
+    # activations and outputs that are only 4-byte aligned as well
+    for shift in (0, 1):
+        xd = torch.empty(C * N + shift, device="cuda")[shift:].view(C, N)
+        xd.copy_(torch.from_numpy(x_t))
+        out = torch.full((K * N + shift,), float("nan"), device="cuda")[shift:].view(K, N)
+        got = B.sconv_fc_forward(h, xd, None, False, out).cpu().numpy().astype(np.float64)
+        assert np.all(np.abs(got - ref) <= TOL * ab)
+        assert np.all(got[ab == 0] == 0)
+        got = B.sconv_fc_forward(h, xd, torch.from_numpy(bias).cuda(), True, out).cpu().numpy().astype(np.float64)
+        ref2, scale = so.bias_relu_t(ref, ab, bias, True)
+        assert np.all(np.abs(got - ref2) <= TOL * scale)
