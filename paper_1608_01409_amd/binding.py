@@ -133,6 +133,7 @@ class Csr:
     def __init__(self, handle, layer):
         self._h = C.c_void_p(handle)
         self.layer = layer
+        self._dims = None
         self._destroy = lib().sconv_destroy_csr   # module globals may be gone when __del__ runs at exit
 
     def __del__(self):
@@ -146,6 +147,15 @@ class Csr:
     @property
     def handle(self):
         return self._h
+
+    def dims(self):
+        """((C, H, W), (K, OH, OW)) of one image: fixed when the handle was created, so asked for once."""
+        if self._dims is None:
+            oh, ow = C.c_int32(), C.c_int32()
+            _check(lib().sconv_csr_info(self._h, None, C.byref(oh), C.byref(ow), None), "sconv_csr_info")
+            L = self.layer
+            self._dims = (L.C, L.H, L.W), (L.K, oh.value, ow.value)
+        return self._dims
 
 
 def sconv_create_csr(layer, dense_w: np.ndarray, plan=None) -> Csr:
@@ -199,50 +209,77 @@ def sconv_csr_unpack(csr: Csr, which: int):
     return _export(lib().sconv_csr_unpack, csr, C.c_int32(which))
 
 
-def _conv_buffers(csr: Csr, x, out, stream):
-    """Checks the input tensor, allocates or checks the output, picks the stream: (N, out, stream)."""
-    import torch
+_torch = None
+_raw_stream = None
 
-    assert x.is_cuda and x.dtype == torch.float32 and x.is_contiguous()
-    L = csr.layer
-    assert tuple(x.shape[1:]) == (L.C, L.H, L.W), (tuple(x.shape), L)
-    N = x.shape[0]
-    info = sconv_csr_info(csr)
+
+def _use_torch():
+    """torch, imported on the first call that is handed tensors (the host-only calls do not need it)."""
+    global _torch, _raw_stream
+    if _torch is None:
+        import torch
+
+        _torch = torch
+        # the current stream's handle without building a Stream object around it, where this torch has the call
+        _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None) or (
+            lambda index: torch.cuda.current_stream(index).cuda_stream)
+    return _torch
+
+
+def _stream_of(x, stream):
+    return stream.cuda_stream if stream is not None else _raw_stream(x.get_device())
+
+
+def _launch(x, fn, *args):
+    """fn(*args) with x's device current (switching costs more than asking)."""
+    index = x.get_device()
+    if _torch.cuda.current_device() == index:
+        return fn(*args)
+    with _torch.cuda.device(index):
+        return fn(*args)
+
+
+def _is_f32(t):
+    return t.is_cuda and t.dtype is _torch.float32 and t.is_contiguous()
+
+
+def _conv_buffers(csr: Csr, x, out, stream):
+    """Checks the input tensor, allocates or checks the output, picks the stream: (N, out, stream handle)."""
+    torch = _use_torch()
+    assert _is_f32(x)
+    in_dims, out_dims = csr.dims()
+    shape = x.shape
+    assert shape[1:] == in_dims, (tuple(shape), csr.layer)
+    N = shape[0]
     if out is None:
-        out = torch.empty((N, L.K, info["OH"], info["OW"]), dtype=torch.float32, device=x.device)
-    assert out.is_cuda and out.dtype == torch.float32 and out.is_contiguous()
-    assert tuple(out.shape) == (N, L.K, info["OH"], info["OW"])
-    return N, out, stream if stream is not None else torch.cuda.current_stream(x.device)
+        out = torch.empty((N, *out_dims), dtype=torch.float32, device=x.device)
+    assert _is_f32(out)
+    assert out.shape == (N, *out_dims)
+    return N, out, _stream_of(x, stream)
 
 
 def _fc_buffers(csr: Csr, x_t, out_t, bias, stream):
-    import torch
-
+    torch = _use_torch()
     L = csr.layer
-    assert x_t.is_cuda and x_t.dtype == torch.float32 and x_t.is_contiguous() and x_t.dim() == 2 and x_t.shape[0] == L.C
+    assert _is_f32(x_t) and x_t.dim() == 2 and x_t.shape[0] == L.C
     N = x_t.shape[1]
     if out_t is None:
         out_t = torch.empty((L.K, N), dtype=torch.float32, device=x_t.device)
-    assert out_t.is_cuda and out_t.dtype == torch.float32 and out_t.is_contiguous() and tuple(out_t.shape) == (L.K, N)
+    assert _is_f32(out_t) and out_t.shape == (L.K, N)
     _check_bias(csr, bias)
-    return N, out_t, stream if stream is not None else torch.cuda.current_stream(x_t.device)
+    return N, out_t, _stream_of(x_t, stream)
 
 
 def _check_bias(csr: Csr, bias):
-    import torch
-
     if bias is not None:
-        assert bias.is_cuda and bias.dtype == torch.float32 and bias.is_contiguous() and tuple(bias.shape) == (csr.layer.K,)
+        _use_torch()
+        assert _is_f32(bias) and bias.shape == (csr.layer.K,)
 
 
 def sconv_forward(csr: Csr, x, out=None, stream=None):
     """x: contiguous fp32 CUDA tensor [N,C,H,W]; returns/overwrites out [N,K,OH,OW] on the same device."""
-    import torch
-
     N, out, s = _conv_buffers(csr, x, out, stream)
-    with torch.cuda.device(x.device):
-        rc = lib().sconv_forward(csr.handle, C.c_void_p(x.data_ptr()), C.c_void_p(out.data_ptr()), N,
-                                 C.c_void_p(s.cuda_stream))
+    rc = _launch(x, lib().sconv_forward, csr.handle, x.data_ptr(), out.data_ptr(), N, s)
     if rc != SCONV_OK:
         raise SconvError(rc, f"sconv_forward (hip error {lib().sconv_last_hip_error(csr.handle)})")
     return out
@@ -251,13 +288,9 @@ def sconv_forward(csr: Csr, x, out=None, stream=None):
 def sconv_forward_noalloc(csr: Csr, x, out, stream=None):
     """sconv_forward without any allocation: `out` must be given, and the handle prepared by an earlier
     sconv_forward call with the same batch size."""
-    import torch
-
     assert out is not None
     N, out, s = _conv_buffers(csr, x, out, stream)
-    with torch.cuda.device(x.device):
-        rc = lib().sconv_forward_noalloc(csr.handle, C.c_void_p(x.data_ptr()), C.c_void_p(out.data_ptr()), N,
-                                         C.c_void_p(s.cuda_stream))
+    rc = _launch(x, lib().sconv_forward_noalloc, csr.handle, x.data_ptr(), out.data_ptr(), N, s)
     if rc != SCONV_OK:
         raise SconvError(rc, f"sconv_forward_noalloc (hip error {lib().sconv_last_hip_error(csr.handle)})")
     return out
@@ -274,12 +307,8 @@ def sconv_rank_plans(csr: Csr, N: int, max_plans: int = 8) -> list:
 
 def sconv_tune(csr: Csr, x, out=None, max_plans=8, stream=None):
     """Times the best-ranked tilings for this batch size on x and keeps the fastest; returns the output."""
-    import torch
-
     N, out, s = _conv_buffers(csr, x, out, stream)
-    with torch.cuda.device(x.device):
-        rc = lib().sconv_tune(csr.handle, C.c_void_p(x.data_ptr()), C.c_void_p(out.data_ptr()), N, int(max_plans),
-                              C.c_void_p(s.cuda_stream))
+    rc = _launch(x, lib().sconv_tune, csr.handle, x.data_ptr(), out.data_ptr(), N, int(max_plans), s)
     if rc != SCONV_OK:
         raise SconvError(rc, f"sconv_tune (hip error {lib().sconv_last_hip_error(csr.handle)})")
     return out
@@ -288,14 +317,10 @@ def sconv_tune(csr: Csr, x, out=None, max_plans=8, stream=None):
 def sconv_forward_fused(csr: Csr, x, bias=None, relu=False, out=None, stream=None):
     """sconv_forward followed, inside the kernel where it can, by out = max(out + bias[k], 0); bias: fp32 CUDA
     tensor [K] or None."""
-    import torch
-
     N, out, s = _conv_buffers(csr, x, out, stream)
     _check_bias(csr, bias)
-    with torch.cuda.device(x.device):
-        rc = lib().sconv_forward_fused(csr.handle, C.c_void_p(x.data_ptr()), C.c_void_p(out.data_ptr()), N,
-                                       C.c_void_p(bias.data_ptr()) if bias is not None else None, int(bool(relu)),
-                                       C.c_void_p(s.cuda_stream))
+    rc = _launch(x, lib().sconv_forward_fused, csr.handle, x.data_ptr(), out.data_ptr(), N,
+                 bias.data_ptr() if bias is not None else None, int(bool(relu)), s)
     if rc != SCONV_OK:
         raise SconvError(rc, f"sconv_forward_fused (hip error {lib().sconv_last_hip_error(csr.handle)})")
     return out
@@ -315,13 +340,9 @@ def sconv_fc_plan(csr: Csr, N: int) -> dict:
 
 def sconv_fc_forward(csr: Csr, x_t, bias=None, relu=False, out_t=None, stream=None):
     """x_t: contiguous fp32 CUDA tensor [C][N] (feature-major); returns/overwrites out_t [K][N]."""
-    import torch
-
     N, out_t, s = _fc_buffers(csr, x_t, out_t, bias, stream)
-    with torch.cuda.device(x_t.device):
-        rc = lib().sconv_fc_forward(csr.handle, C.c_void_p(x_t.data_ptr()), C.c_void_p(out_t.data_ptr()), N,
-                                    C.c_void_p(bias.data_ptr()) if bias is not None else None, int(bool(relu)),
-                                    C.c_void_p(s.cuda_stream))
+    rc = _launch(x_t, lib().sconv_fc_forward, csr.handle, x_t.data_ptr(), out_t.data_ptr(), N,
+                 bias.data_ptr() if bias is not None else None, int(bool(relu)), s)
     if rc != SCONV_OK:
         raise SconvError(rc, f"sconv_fc_forward (hip error {lib().sconv_last_hip_error(csr.handle)})")
     return out_t
@@ -329,12 +350,8 @@ def sconv_fc_forward(csr: Csr, x_t, bias=None, relu=False, out_t=None, stream=No
 
 def sconv_fc_tune(csr: Csr, x_t, out_t=None, max_plans=8, stream=None):
     """Times the best-ranked tilings of the fully connected layer for this batch size; returns the output."""
-    import torch
-
     N, out_t, s = _fc_buffers(csr, x_t, out_t, None, stream)
-    with torch.cuda.device(x_t.device):
-        rc = lib().sconv_fc_tune(csr.handle, C.c_void_p(x_t.data_ptr()), C.c_void_p(out_t.data_ptr()), N, int(max_plans),
-                                 C.c_void_p(s.cuda_stream))
+    rc = _launch(x_t, lib().sconv_fc_tune, csr.handle, x_t.data_ptr(), out_t.data_ptr(), N, int(max_plans), s)
     if rc != SCONV_OK:
         raise SconvError(rc, f"sconv_fc_tune (hip error {lib().sconv_last_hip_error(csr.handle)})")
     return out_t
