@@ -51,17 +51,24 @@ struct sconv_csr {
     struct Planned {
         sconv_plan plan;
         double us;           // the cost model's time for it
+        int phase_cg;        // as in LdsTiling
     };
     std::map<int, Planned> plan_of_n;        // tilings already chosen, by batch size
-    // small launches: the gather kernels, and the batch sizes they serve (by the cost models, or as measured)
-    struct GatherChoice {
-        bool use;
-        GatherShape shape;
+    // which kernel serves a batch size (by the cost models, or as measured): the flat-stream kernel with its plan,
+    // the gather kernel (small launches) or the matrix-core kernel (rather dense layers)
+    enum Kind { kLds, kGather, kMfma };
+    struct Choice {
+        Kind kind;
+        GatherShape gather;                  // t = 0: the gather kernel cannot take it
+        MfmaTiling mfma;                     // mt = 0: the matrix-core kernel cannot take it
     };
-    DeviceGather gather;                     // convolution entry points
-    DeviceGather fc_gather;
-    std::map<int, GatherChoice> gather_of_n, fc_gather_of_n;
+    struct Alternatives {                    // for the convolution entry points, for the fully connected one
+        std::map<int, Choice> choice_of_n;
+        DeviceGather gather;
+        DeviceMfma mfma;
+    } conv_alt, fc_alt;
     int max_row_nnz = 0;
+    bool split_exact = true;                 // every weight is exactly three bf16 parts
     std::vector<StashedPacking> stash;       // earlier packings, oldest first
     // the layer the LDS kernels run: the layer itself, or for stride > 1 its stride-1 form over phase images
     bool phased = false;
@@ -116,6 +123,18 @@ struct Workspace {
     }
 };
 
+// Room for partial results: scratch the handle owns and grows, or a piece of `ws` when one is given.
+static int take_parts(sconv_csr *h, size_t need, Workspace *ws, float **parts)
+{
+    if (ws) {
+        *parts = static_cast<float *>(ws->take(need));
+        return *parts ? SCONV_OK : SCONV_ERR_CAPACITY;
+    }
+    const int rc = grow(&h->part_buf, &h->part_bytes, need, &h->hip_err);
+    *parts = rc ? nullptr : static_cast<float *>(h->part_buf);
+    return rc;
+}
+
 // The flat-stream kernel and, when the tiling splits the channels, the reduction of its partial results.
 // The partial results go to scratch the handle owns and grows, or into `ws` when one is given.
 static int run_flat(sconv_csr *h, const sconv_desc &kd, const LdsTiling &t, const DeviceLds &dev, const Lds2Layout &lay,
@@ -124,17 +143,9 @@ static int run_flat(sconv_csr *h, const sconv_desc &kd, const LdsTiling &t, cons
 {
     if (t.p.splits <= 1) return launch_lds2(kd, t, dev, lay, in, out, n_kernel, ep, 0, stream, &h->hip_err);
     const int64_t total = rows * inner;
-    const size_t need = (size_t)total * t.p.splits * sizeof(float);
-    int rc;
     float *parts;
-    if (ws) {
-        parts = static_cast<float *>(ws->take(need));
-        if (!parts) return SCONV_ERR_CAPACITY;
-    } else {
-        rc = grow(&h->part_buf, &h->part_bytes, need, &h->hip_err);
-        if (rc) return rc;
-        parts = static_cast<float *>(h->part_buf);
-    }
+    int rc = take_parts(h, (size_t)total * t.p.splits * sizeof(float), ws, &parts);
+    if (rc) return rc;
     rc = launch_lds2(kd, t, dev, lay, in, parts, n_kernel, ep, total, stream, &h->hip_err);
     if (rc) return rc;
     return launch_reduce(parts, out, t.p.splits, rows, inner, h->desc.K, ep, stream, &h->hip_err);
@@ -165,7 +176,7 @@ static int plan_lds(sconv_csr *h, int n, bool resident_only = false)
     auto remember = [&]() {
         if (!fresh) return;
         if (h->plan_of_n.size() >= kPlansRemembered) h->plan_of_n.clear();
-        h->plan_of_n[n] = {t.p, t.us};
+        h->plan_of_n[n] = {t.p, t.us, t.phase_cg};
     };
     if (h->has_lds && same_plan(t.p, h->flat ? h->lds_flat.t.p : h->lds.t.p)) {
         remember();
@@ -223,6 +234,7 @@ static int finish_create(sconv_csr *h, const sconv_plan *plan)
     if (h->requested.kernel < 0 || h->requested.kernel > 4) return SCONV_ERR_PLAN;
     const sconv_desc &d = h->desc;
     for (int k = 0; k < d.K; ++k) h->max_row_nnz = std::max(h->max_row_nnz, h->canon.rowptr[k + 1] - h->canon.rowptr[k]);
+    for (float v : h->canon.val) h->split_exact = h->split_exact && mfma_weight_ok(v);
     int rc = pack_direct(d, h->canon, h->direct);
     if (rc) return rc;
     h->kdesc = d;
@@ -455,35 +467,46 @@ static bool free_choice(const sconv_csr *h)
     return !rq.nt && !rq.cb && !rq.waves && !rq.cg && !rq.rows_w && !rq.t && !rq.band && !rq.strip && !rq.splits;
 }
 
-// The gather kernels are taken when they are expected to win by this much.  Of 75 convolutions run both ways the models
-// then lose none by more than 10 % (at 1.05: four, the worst 31 us instead of 23.5; the LDS model reads up to 40 % high
-// on launches of 5-20 us); of 25 fully connected layers none at 1.1.
-static const double kGatherMargin = 1.25, kFcGatherMargin = 1.1;
+// Another kernel than the flat-stream one is taken when it is expected to win by this much.  Of 75 convolutions run both
+// ways the models then lose none by more than 10 % to the gather kernel (at 1.05: four, the worst 31 us instead of 23.5;
+// the LDS model reads up to 40 % high on launches of 5-20 us); of 25 fully connected layers none at 1.1.
+static const double kGatherMargin = 1.25, kFcGatherMargin = 1.1, kMfmaMargin = 1.1;
 
 static double avg_row_nnz(const sconv_csr *h) { return h->desc.K ? (double)h->canon.val.size() / h->desc.K : 0.0; }
 
 // The LDS path's time for N images: the flat-stream kernel's, and for layers that need phase images the pass that writes
 // them (a launch, and their bytes written and read).
-static double planned_us(const sconv_csr *h, int N, double flat_us)
+static double planned_us(const sconv_csr *h, int N, double flat_us, int phase_cg)
 {
-    if (!h->phased || flat_us <= 0 || f_tiling(h).phase_cg > 0) return flat_us;
+    if (!h->phased || flat_us <= 0 || phase_cg > 0) return flat_us;
     return flat_us + 4.0 + 2.0 * N * h->kdesc.C * h->kdesc.H * h->kdesc.W * 4.0 / 4.0e6;
 }
 
-// Whether a call with N images goes to the gather kernel.  Only launches with little arithmetic do: its multiply-adds
-// cost about three times the LDS kernels' (4.4 against 10-20 million per microsecond), its fixed price is a third of
-// theirs (3.5 us against 6-15).  Both cost models are asked; `lds_us` is the LDS kernel's time.
-static const sconv_csr::GatherChoice &gather_choice(sconv_csr *h, int N, double lds_us)
+// Which kernel a call with N images goes to; every kernel's cost model is asked, `lds_us` is the flat-stream path's time.
+// Gather: launches with little arithmetic; its multiply-adds cost about three times the LDS kernels' (4.4 against 10-20
+// million per microsecond), its fixed price is a third of theirs (3.5 us against 6-15).  Matrix cores: layers where the
+// zeros they multiply cost less than what their rate wins.
+static const sconv_csr::Choice &choose_kernel(sconv_csr *h, bool fc, int N, double lds_us)
 {
-    auto known = h->gather_of_n.find(N);
-    if (known != h->gather_of_n.end()) return known->second;
-    sconv_csr::GatherChoice c = {false, {0, 0, 0.0}};
-    if (gather_fits(h->desc, N)) {
-        c.shape = choose_gather(h->desc, N, avg_row_nnz(h), h->max_row_nnz);
-        c.use = c.shape.us * kGatherMargin < lds_us;
+    sconv_csr::Alternatives &alt = fc ? h->fc_alt : h->conv_alt;
+    auto known = alt.choice_of_n.find(N);
+    if (known != alt.choice_of_n.end()) return known->second;
+    sconv_csr::Choice c = {sconv_csr::kLds, {0, 0, 0.0}, {}};
+    double best = lds_us;
+    if (fc ? fc_gather_fits(h->desc, N) : gather_fits(h->desc, N)) {
+        c.gather = fc ? choose_fc_gather(h->desc, N, avg_row_nnz(h), h->max_row_nnz) : choose_gather(h->desc, N, avg_row_nnz(h), h->max_row_nnz);
+        if (c.gather.us * (fc ? kFcGatherMargin : kGatherMargin) < lds_us) {
+            c.kind = sconv_csr::kGather;
+            best = c.gather.us;
+        }
     }
-    if (h->gather_of_n.size() >= kPlansRemembered) h->gather_of_n.clear();
-    return h->gather_of_n[N] = c;
+    if (h->split_exact && mfma_fits(h->desc, N, fc) && choose_mfma(h->desc, N, c.mfma)) {
+        if (c.mfma.us * kMfmaMargin < best) c.kind = sconv_csr::kMfma;
+    } else {
+        c.mfma = MfmaTiling();
+    }
+    if (alt.choice_of_n.size() >= kPlansRemembered) alt.choice_of_n.clear();
+    return alt.choice_of_n[N] = c;
 }
 
 // Set-up on this device: the address of the library's static scratch is looked up with the first upload, so that
@@ -496,25 +519,70 @@ static void find_static_scratch()
     (void)static_scratch(&base, &bytes, &ignored);
 }
 
-static int upload_gather(sconv_csr *h, DeviceGather &dev, bool fc)
+static int upload_direct(sconv_csr *h)
 {
-    if (dev.uploaded) return SCONV_OK;
-    try {
-        PackedGather p;
-        int rc = fc ? pack_fc_gather(h->desc, h->canon, p) : pack_gather(h->desc, h->canon, p);
-        if (!rc) rc = upload(p.ent.data(), p.ent.size() * 8, &dev.ent, &h->hip_err);
-        if (!rc) rc = upload(p.rowptr.data(), p.rowptr.size() * 4, &dev.rowptr, &h->hip_err);
-        if (rc) {
-            release(dev.ent);
-            release(dev.rowptr);
-            dev = DeviceGather();
-            return rc;
-        }
-    } catch (const std::bad_alloc &) {
-        return SCONV_ERR_NOMEM;
-    }
-    dev.uploaded = true;
+    if (h->direct_uploaded) return SCONV_OK;
+    int rc = upload(h->direct.rowptr.data(), h->direct.rowptr.size() * 4, &h->dev_direct.rowptr, &h->hip_err);
+    if (!rc) rc = upload(h->direct.trip.data(), h->direct.trip.size() * 4, &h->dev_direct.trip, &h->hip_err);
+    if (rc) return rc;
+    h->direct_uploaded = true;
     return SCONV_OK;
+}
+
+static void release_alternatives(sconv_csr::Alternatives &alt)
+{
+    for (void *p : {alt.gather.ent, alt.gather.rowptr, alt.mfma.wfrag, alt.mfma.uoff, alt.mfma.choff}) release(p);
+    alt.gather = DeviceGather();
+    alt.mfma = DeviceMfma();
+}
+
+static bool resident(const sconv_csr *h, const sconv_csr::Alternatives &alt, const sconv_csr::Choice &c)
+{
+    return c.kind == sconv_csr::kGather ? alt.gather.uploaded : alt.mfma.uploaded && h->direct_uploaded;
+}
+
+// Pack and upload what the chosen kernel reads (the same arrays for every batch size), once.
+static int prepare_choice(sconv_csr *h, bool fc, const sconv_csr::Choice &c)
+{
+    sconv_csr::Alternatives &alt = fc ? h->fc_alt : h->conv_alt;
+    if (resident(h, alt, c)) return SCONV_OK;
+    int rc;
+    if (c.kind == sconv_csr::kGather) {
+        PackedGather p;
+        rc = fc ? pack_fc_gather(h->desc, h->canon, p) : pack_gather(h->desc, h->canon, p);
+        if (!rc) rc = upload(p.ent.data(), p.ent.size() * 8, &alt.gather.ent, &h->hip_err);
+        if (!rc) rc = upload(p.rowptr.data(), p.rowptr.size() * 4, &alt.gather.rowptr, &h->hip_err);
+        if (!rc) alt.gather.uploaded = true;
+    } else {
+        PackedMfma p;
+        rc = alt.mfma.uploaded ? SCONV_OK : pack_mfma(h->desc, h->canon, c.mfma, p);
+        if (!rc && !alt.mfma.uploaded) {
+            rc = upload(p.wfrag.data(), p.wfrag.size() * 2, &alt.mfma.wfrag, &h->hip_err);
+            if (!rc) rc = upload(p.uoff.data(), p.uoff.size() * 4, &alt.mfma.uoff, &h->hip_err);
+            if (!rc) rc = upload(p.choff.data(), p.choff.size() * 4, &alt.mfma.choff, &h->hip_err);
+            if (!rc) alt.mfma.uploaded = true;
+        }
+        if (!rc) rc = upload_direct(h);
+    }
+    if (rc) release_alternatives(alt);
+    return rc;
+}
+
+// ws: as for run_flat
+static int launch_choice(sconv_csr *h, bool fc, const sconv_csr::Choice &c, const float *in, float *out, int N, const Epilogue &ep,
+                         void *stream, Workspace *ws = nullptr)
+{
+    const sconv_csr::Alternatives &alt = fc ? h->fc_alt : h->conv_alt;
+    if (c.kind == sconv_csr::kGather)
+        return fc ? launch_fc_gather(h->desc, alt.gather, c.gather, in, out, N, ep, stream, &h->hip_err)
+                  : launch_gather(h->desc, alt.gather, c.gather, in, out, N, ep, stream, &h->hip_err);
+    if (c.mfma.splits <= 1) return launch_mfma(h->desc, c.mfma, alt.mfma, h->dev_direct, in, out, N, fc, ep, 0, stream, &h->hip_err);
+    const Geometry g = geometry(h->desc);
+    const int64_t rows = fc ? h->desc.K : (int64_t)N * h->desc.K, inner = fc ? N : (int64_t)g.OH * g.OW;
+    float *parts;
+    int rc = take_parts(h, (size_t)(rows * inner) * c.mfma.splits * sizeof(float), ws, &parts);
+    if (!rc) rc = launch_mfma(h->desc, c.mfma, alt.mfma, h->dev_direct, in, parts, N, fc, ep, rows * inner, stream, &h->hip_err);
+    return rc ? rc : launch_reduce(parts, out, c.mfma.splits, rows, inner, h->desc.K, ep, stream, &h->hip_err);
 }
 
 static int upload_flat(sconv_csr *h)
@@ -528,6 +596,16 @@ static int upload_flat(sconv_csr *h)
     if (rc) return rc;
     h->lds_uploaded = true;
     return SCONV_OK;
+}
+
+// What the flat-stream path would keep in scratch for N images: partial results, phase images (256-byte pieces).
+static size_t lds_scratch(const sconv_csr *h, int N, const sconv_csr::Planned &p)
+{
+    const Geometry g = geometry(h->desc);
+    size_t parts = p.plan.splits > 1 ? (size_t)N * h->desc.K * g.OH * g.OW * p.plan.splits * sizeof(float) : 0;
+    size_t phase = h->phased && p.phase_cg <= 0 ? (size_t)N * h->kdesc.C * h->kdesc.H * h->kdesc.W * sizeof(float) : 0;
+    if (parts) phase = (phase + 255) & ~(size_t)255;
+    return phase + parts;
 }
 
 // ws != nullptr: the caller forbids allocation.  Scratch then comes out of ws, and everything else the launch
@@ -544,13 +622,17 @@ static int forward_impl(sconv_csr *h, const float *in, float *out, int32_t N, co
     // (batches below 4 use the tiling of batch 4: one tile of 4 images, not all of them present)
     const int n_plan = N < 4 ? 4 : N;
     const bool choose = use_lds && free_choice(h);
-    const bool may_gather = choose && h->requested.kernel == 0 && h->flat;
-    if (ws && may_gather && h->gather.uploaded) {
-        // the gather kernel's arrays are the same for every batch size, so nothing has to be looked up or switched
+    const bool may_choose = choose && h->requested.kernel == 0 && h->flat;
+    if (ws && may_choose) {
+        // the other kernels' arrays are the same for every batch size: nothing has to be looked up or switched
         const auto planned = h->plan_of_n.find(n_plan);
-        const auto known = h->gather_of_n.find(N);
-        if (planned != h->plan_of_n.end() && known != h->gather_of_n.end() && known->second.use)
-            return launch_gather(h->desc, h->gather, known->second.shape, in, out, N, ep, hip_stream, &h->hip_err);
+        const auto known = h->conv_alt.choice_of_n.find(N);
+        if (planned != h->plan_of_n.end() && known != h->conv_alt.choice_of_n.end() && known->second.kind != sconv_csr::kLds &&
+            resident(h, h->conv_alt, known->second)) {
+            // what this entry point takes does not depend on which kernel serves a call
+            if (lds_scratch(h, N, planned->second) > ws->bytes) return SCONV_ERR_CAPACITY;
+            return launch_choice(h, false, known->second, in, out, N, ep, hip_stream, ws);
+        }
     }
     if (choose && n_plan != h->planned_n) {
         try {
@@ -560,17 +642,17 @@ static int forward_impl(sconv_csr *h, const float *in, float *out, int32_t N, co
             return SCONV_ERR_NOMEM;
         }
     }
-    if (!ws && may_gather && h->flat) {
+    if (!ws && may_choose && h->flat) {
         try {
             const auto planned = h->plan_of_n.find(n_plan);
-            const sconv_csr::GatherChoice &c = gather_choice(h, N, planned == h->plan_of_n.end() ? 0.0 : planned_us(h, N, planned->second.us));
-            if (c.use) {
-                if (!h->gather.uploaded) find_static_scratch();
-                int rc = upload_gather(h, h->gather, false);
+            const double lds_us = planned == h->plan_of_n.end() ? 0.0 : planned_us(h, N, planned->second.us, planned->second.phase_cg);
+            const sconv_csr::Choice &c = choose_kernel(h, false, N, lds_us);
+            if (c.kind != sconv_csr::kLds) {
+                find_static_scratch();
+                int rc = prepare_choice(h, false, c);
                 // batches of 1-3 share a tiling: a later call with another of them may want the LDS kernel without uploading
                 if (!rc && N < 4) rc = upload_flat(h);
-                if (rc) return rc;
-                return launch_gather(h->desc, h->gather, c.shape, in, out, N, ep, hip_stream, &h->hip_err);
+                return rc ? rc : launch_choice(h, false, c, in, out, N, ep, hip_stream);
             }
         } catch (const std::bad_alloc &) {
             return SCONV_ERR_NOMEM;
@@ -627,12 +709,8 @@ static int forward_impl(sconv_csr *h, const float *in, float *out, int32_t N, co
         rc = launch_lds(h->kdesc, h->lds.t, h->dev_lds, in, out, N, hip_stream, &h->hip_err);
         return rc ? rc : launch_epilogue(out, out_rows, out_inner, h->desc.K, ep, hip_stream, &h->hip_err);
     }
-    if (!h->direct_uploaded) {
-        rc = upload(h->direct.rowptr.data(), h->direct.rowptr.size() * 4, &h->dev_direct.rowptr, &h->hip_err);
-        if (!rc) rc = upload(h->direct.trip.data(), h->direct.trip.size() * 4, &h->dev_direct.trip, &h->hip_err);
-        if (rc) return rc;
-        h->direct_uploaded = true;
-    }
+    rc = upload_direct(h);
+    if (rc) return rc;
     rc = launch_direct(h->desc, h->dev_direct, in, out, N, hip_stream, &h->hip_err);
     return rc ? rc : launch_epilogue(out, out_rows, out_inner, h->desc.K, ep, hip_stream, &h->hip_err);
 }
@@ -770,18 +848,12 @@ static int plan_fc(sconv_csr *h, int N, const sconv_plan *force = nullptr)
     return SCONV_OK;
 }
 
-// The same decision for the fully connected entry point: up to SCONV_FC_GATHER_MAX_N images, against the tiling just packed.
-static const sconv_csr::GatherChoice &fc_gather_choice(sconv_csr *h, int N)
+// The same decision for the fully connected entry point, against the tiling just packed.
+static const sconv_csr::Choice &choose_fc_kernel(sconv_csr *h, int N)
 {
-    auto known = h->fc_gather_of_n.find(N);
-    if (known != h->fc_gather_of_n.end()) return known->second;
-    sconv_csr::GatherChoice c = {false, {0, 0, 0.0}};
-    if (free_choice(h) && h->requested.kernel == 0 && fc_gather_fits(h->desc, N)) {
-        c.shape = choose_fc_gather(h->desc, N, avg_row_nnz(h), h->max_row_nnz);
-        c.use = c.shape.us * kFcGatherMargin < h->fc_flat.t.us;
-    }
-    if (h->fc_gather_of_n.size() >= kPlansRemembered) h->fc_gather_of_n.clear();
-    return h->fc_gather_of_n[N] = c;
+    if (free_choice(h) && h->requested.kernel == 0) return choose_kernel(h, true, N, h->fc_flat.t.us);
+    static const sconv_csr::Choice lds = {sconv_csr::kLds, {0, 0, 0.0}, {}};
+    return lds;
 }
 
 extern "C" int sconv_fc_plan(sconv_csr *h, int32_t N, sconv_plan *plan)
@@ -813,10 +885,10 @@ extern "C" int sconv_fc_forward(sconv_csr *h, const float *in_t, float *out_t, i
     ep.bias = bias;
     ep.relu = relu != 0;
     try {
-        const sconv_csr::GatherChoice &c = fc_gather_choice(h, N);
-        if (c.use) {
-            rc = upload_gather(h, h->fc_gather, true);
-            return rc ? rc : launch_fc_gather(h->desc, h->fc_gather, c.shape, in_t, out_t, N, ep, hip_stream, &h->hip_err);
+        const sconv_csr::Choice &c = choose_fc_kernel(h, N);
+        if (c.kind != sconv_csr::kLds) {
+            rc = prepare_choice(h, true, c);
+            return rc ? rc : launch_choice(h, true, c, in_t, out_t, N, ep, hip_stream);
         }
     } catch (const std::bad_alloc &) {
         return SCONV_ERR_NOMEM;
@@ -917,6 +989,15 @@ struct StashRoom {
     }
 };
 
+// The kernels besides the flat-stream one that can take a call.
+static std::vector<sconv_csr::Kind> other_kernels(const sconv_csr::Choice &c)
+{
+    std::vector<sconv_csr::Kind> k;
+    if (c.gather.t > 0) k.push_back(sconv_csr::kGather);
+    if (c.mfma.mt > 0) k.push_back(sconv_csr::kMfma);
+    return k;
+}
+
 static int clamp_plans(int max_plans) { return max_plans < 1 ? 8 : std::min(max_plans, 32); }
 
 extern "C" int sconv_rank_plans(const sconv_csr *h, int32_t N, int32_t max_plans, sconv_plan *plans, int32_t *count)
@@ -951,28 +1032,33 @@ extern "C" int sconv_tune(sconv_csr *h, const float *in, float *out, int32_t N, 
         if (rc) return rc;
         int best = -1;
         StashRoom room(h, cands.size());
-        // the gather kernel is one more candidate where it can run (and the untuned choice where the models pick it)
-        h->gather_of_n.erase(N);
+        // the other kernels are further candidates where they can run (and the untuned choice where the models pick one)
+        h->conv_alt.choice_of_n.erase(N);
         const size_t n_lds = cands.size();
-        sconv_csr::GatherChoice gc = {false, {0, 0, 0.0}};
-        const bool may_gather = h->requested.kernel == 0 && h->flat && gather_fits(h->desc, N);
-        if (may_gather) gc = gather_choice(h, N, planned_us(h, N, cands[0].us));
-        const bool own_gather = gc.use;
-        rc = time_candidates(
-            h, n_lds + (may_gather ? 1 : 0), own_gather ? n_lds : 0,
-            [&](size_t i) {
-                gc.use = i >= n_lds;
-                h->gather_of_n[N] = gc;
-                const LdsTiling &c = cands[i < n_lds ? i : 0];
-                h->plan_of_n[n_plan] = {c.p, c.us};
-                return plan_lds(h, n_plan);
-            },
-            [&]() { return forward_impl(h, in, out, N, none, hip_stream); }, hip_stream, &best);
-        // the fastest, or the cost model's choice if nothing could be timed
-        gc.use = best < 0 ? own_gather : (size_t)best >= n_lds;
-        h->gather_of_n[N] = gc;
-        const LdsTiling &c = cands[best < 0 || gc.use ? 0 : (size_t)best];
-        h->plan_of_n[n_plan] = {c.p, c.us};
+        sconv_csr::Choice own = {sconv_csr::kLds, {0, 0, 0.0}, {}};
+        if (h->requested.kernel == 0 && h->flat) own = choose_kernel(h, false, N, planned_us(h, N, cands[0].us, cands[0].phase_cg));
+        const std::vector<sconv_csr::Kind> others = other_kernels(own);
+        auto choice = [&](size_t i) {
+            sconv_csr::Choice c = own;
+            c.kind = i < n_lds ? sconv_csr::kLds : others[i - n_lds];
+            return c;
+        };
+        size_t own_index = 0;
+        for (size_t i = 0; i < others.size(); ++i)
+            if (own.kind == others[i]) own_index = n_lds + i;
+        auto install = [&](size_t i) {
+            h->conv_alt.choice_of_n[N] = choice(i);
+            const LdsTiling &c = cands[i < n_lds ? i : 0];
+            h->plan_of_n[n_plan] = {c.p, c.us, c.phase_cg};
+            return plan_lds(h, n_plan);
+        };
+        rc = time_candidates(h, n_lds + others.size(), own_index, install,
+                             [&]() { return forward_impl(h, in, out, N, none, hip_stream); }, hip_stream, &best);
+        // the fastest, or the cost models' choice if nothing could be timed
+        const size_t winner = best < 0 ? own_index : (size_t)best;
+        h->conv_alt.choice_of_n[N] = choice(winner);
+        const LdsTiling &c = cands[winner < n_lds ? winner : 0];
+        h->plan_of_n[n_plan] = {c.p, c.us, c.phase_cg};
         const int prc = plan_lds(h, n_plan);
         if (rc) return rc;
         if (prc) return prc;
@@ -998,25 +1084,32 @@ extern "C" int sconv_fc_tune(sconv_csr *h, const float *in_t, float *out_t, int3
         int best = -1;
         StashRoom room(h, cands.size());
         h->fc_plan_of_n.erase(N);
-        h->fc_gather_of_n.erase(N);
+        h->fc_alt.choice_of_n.erase(N);
         rc = plan_fc(h, N, &cands[0].p);
         if (rc) return rc;
         h->fc_flat.t.us = cands[0].us;
         const size_t n_lds = cands.size();
-        sconv_csr::GatherChoice gc = fc_gather_choice(h, N);
-        const bool may_gather = gc.shape.t > 0, own_gather = gc.use;
+        const sconv_csr::Choice own = choose_fc_kernel(h, N);
+        const std::vector<sconv_csr::Kind> others = other_kernels(own);
+        auto choice = [&](size_t i) {
+            sconv_csr::Choice c = own;
+            c.kind = i < n_lds ? sconv_csr::kLds : others[i - n_lds];
+            return c;
+        };
+        size_t own_index = 0;
+        for (size_t i = 0; i < others.size(); ++i)
+            if (own.kind == others[i]) own_index = n_lds + i;
         rc = time_candidates(
-            h, n_lds + (may_gather ? 1 : 0), own_gather ? n_lds : 0,
+            h, n_lds + others.size(), own_index,
             [&](size_t i) {
-                gc.use = i >= n_lds;
-                h->fc_gather_of_n[N] = gc;
+                h->fc_alt.choice_of_n[N] = choice(i);
                 return plan_fc(h, N, &cands[i < n_lds ? i : 0].p);
             },
             [&]() { return sconv_fc_forward(h, in_t, out_t, N, nullptr, 0, hip_stream); }, hip_stream, &best);
         if (rc) return rc;
-        gc.use = best < 0 ? own_gather : (size_t)best >= n_lds;
-        h->fc_gather_of_n[N] = gc;
-        h->fc_plan_of_n[N] = cands[best < 0 || gc.use ? 0 : (size_t)best].p;
+        const size_t winner = best < 0 ? own_index : (size_t)best;
+        h->fc_alt.choice_of_n[N] = choice(winner);
+        h->fc_plan_of_n[N] = cands[winner < n_lds ? winner : 0].p;
         rc = plan_fc(h, N); // while the candidates' packings are still at hand
         if (rc) return rc;
     } catch (const std::bad_alloc &) {
@@ -1041,10 +1134,8 @@ extern "C" void sconv_destroy_csr(sconv_csr *h)
     for (auto &sp : h->fc_stash) release_arrays(sp.dev);
     release(h->dev_direct.rowptr);
     release(h->dev_direct.trip);
-    for (DeviceGather *g : {&h->gather, &h->fc_gather}) {
-        release(g->ent);
-        release(g->rowptr);
-    }
+    release_alternatives(h->conv_alt);
+    release_alternatives(h->fc_alt);
     delete h;
 }
 

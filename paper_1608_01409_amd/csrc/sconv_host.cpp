@@ -964,4 +964,158 @@ GatherShape choose_fc_gather(const sconv_desc &d, int N, double avg_row_nnz, int
     return best;
 }
 
+// ------------------------------------------------------------------ matrix-core kernel (rather dense layers)
+
+bool mfma_fits(const sconv_desc &d, int N, bool feature_major)
+{
+    const Geometry g = geometry(d);
+    const int64_t HW = (int64_t)d.H * d.W, OHW = (int64_t)g.OH * g.OW, lim = (int64_t)1 << 31;
+    if ((int64_t)N * OHW >= ((int64_t)1 << 28)) return false;
+    if (feature_major) return (int64_t)d.C * N * 4 < lim;
+    // a workgroup's images (256 positions), from the first one's channel 0
+    return (256 / OHW + 3) * d.C * HW * 4 < lim && (int64_t)g.Kg * OHW < lim;
+}
+
+// Zero, or a magnitude in [2^-110, 2^127): three bf16 parts hold it exactly.
+bool mfma_weight_ok(float v)
+{
+    uint32_t u;
+    std::memcpy(&u, &v, 4);
+    u &= 0x7fffffffu;
+    return u == 0 || (u >= 0x08800000u && u < 0x7f000000u);
+}
+
+static uint16_t to_bf16(float v) // round to nearest even
+{
+    uint32_t u;
+    std::memcpy(&u, &v, 4);
+    return (uint16_t)((u + 0x7fffu + ((u >> 16) & 1u)) >> 16);
+}
+
+static float from_bf16(uint16_t b)
+{
+    const uint32_t u = (uint32_t)b << 16;
+    float v;
+    std::memcpy(&v, &u, 4);
+    return v;
+}
+
+bool choose_mfma(const sconv_desc &d, int N, MfmaTiling &t)
+{
+    const Geometry g = geometry(d);
+    double best_units = -1;
+    // an unpadded strided layer may be seen as its phase images: fewer empty channels of an octet where C is small
+    for (int phased = 0; phased <= (d.stride > 1 && d.pad == 0 ? 1 : 0); ++phased) {
+        MfmaTiling c;
+        const int s = phased ? d.stride : 1;
+        c.phased = phased != 0;
+        c.cstep = s;
+        c.lstep = phased ? 1 : d.stride;
+        c.Rr = ceil_div(d.R, s);
+        c.Sr = ceil_div(d.S, s);
+        if ((int64_t)g.Cg * s * s > (1 << 20) || (int64_t)(g.OW - 1) * c.lstep + c.Sr > 1024) continue;
+        c.c_virtual = g.Cg * s * s;
+        c.Wl = (g.OW - 1) * c.lstep + c.Sr;
+        // rows of cells that 256 (or 128) consecutive positions touch, over all places they can start at
+        auto cells_of = [&](int bn) {
+            const int rows_out = ceil_div(bn - 1, g.OW) + 1, images = c.Rr > c.lstep ? ceil_div(bn - 1, g.OH * g.OW) + 1 : 1;
+            return ((int64_t)rows_out * c.lstep + (int64_t)images * (c.Rr - c.lstep)) * c.Wl;
+        };
+        c.nt_max = cells_of(256) <= 1024 ? 2 : 1;
+        const int64_t cells = cells_of(128 * c.nt_max);
+        if (cells < 1 || cells > 1024) continue;
+        c.plane = (int)((cells + 63) / 64 * 64);
+        const int taps = c.Rr * c.Sr, octets = ceil_div(c.c_virtual, 8);
+        for (int g8 = 1; g8 <= std::min(octets, 16); ++g8) {
+            c.g8 = g8;
+            c.nblk = ceil_div(octets, g8);
+            c.steps = ceil_div(taps * g8, 2);
+            c.steps_last = ceil_div(taps * (octets - (c.nblk - 1) * g8), 2);
+            const int64_t lds = (int64_t)g8 * c.plane * 48 + 8 * (c.steps + c.steps_last) + 4 * c.plane;
+            if (lds > 80 * 1024 - 256) break;                 // two workgroups on a CU
+            const int64_t total = (int64_t)(c.nblk - 1) * c.steps + c.steps_last;
+            if (total > (1 << 18)) continue;
+            c.total_steps = (int)total;
+            c.lds_bytes = (int)lds;
+            const double units = total + 1.0 * c.nblk;        // a block's barriers and first reads weigh about a step
+            if (best_units < 0 || units < best_units) {
+                best_units = units;
+                t = c;
+            }
+        }
+    }
+    if (best_units < 0) return false;
+    t.n_tiles32 = 2 * ceil_div(g.Kg, 64);
+    // What a launch takes, fitted to 26 layers in every shape (10-460 us, 12 % off on average): a workgroup's matrix
+    // instructions at 2.1 GHz, 0.61 us for each round of 64 cells x 8 channels x 4 waves it stages, 4 us for its index
+    // arithmetic and stores; workgroups that share a CU overlap down to 1.2 times the first and half of the others.
+    t.us = 0;
+    const double P = (double)N * g.OH * g.OW, out_bytes = 4.0 * P * d.K;
+    for (int mt = 1; mt <= 2; ++mt)
+        for (int nt = 1; nt <= t.nt_max; ++nt)
+            for (int splits : {1, 2, 3, 4, 6, 8, 12, 16}) {
+                if (splits > t.nblk || ceil_div(t.nblk, ceil_div(t.nblk, splits)) != splits) continue;
+                if (splits > 1 && out_bytes * splits > SCONV_NOALLOC_SCRATCH_BYTES) continue;
+                const int n_mtiles = ceil_div(g.Kg, 32 * mt), blocks = ceil_div(t.nblk, splits);
+                const double wgs = std::ceil(P / (128.0 * nt)) * n_mtiles * d.groups * splits, per_cu = std::ceil(wgs / 256.0);
+                const double share = (double)blocks / t.nblk;
+                const double mfma = share * t.total_steps * mt * nt * 192.0 / 2100.0;
+                const double rounds = blocks * std::ceil(t.plane * (nt == t.nt_max ? 1.0 : 0.6) / 64.0) * t.g8 / 4.0;
+                const int fit = std::min(mt * nt == 4 ? 2 : mt * nt == 2 ? 3 : 4, 160 * 1024 / (t.lds_bytes + 512));
+                const double alone = mfma + 0.05 * blocks + 0.61 * rounds + 4.0, shared = mfma / 0.816 + 0.306 * rounds + 1.2;
+                double us = 4.4 + std::max(alone * std::ceil(per_cu / fit), per_cu * shared);
+                // partial sums: stored, and added by a launch of their own that reads every part
+                if (splits > 1) us += 4.0 + splits * (out_bytes / 3.5e6 + 0.3);
+                if (t.us == 0 || us < t.us) {
+                    t.us = us;
+                    t.mt = mt;
+                    t.nt = nt;
+                    t.splits = splits;
+                    t.n_mtiles = n_mtiles;
+                }
+            }
+    return true;
+}
+
+int pack_mfma(const sconv_desc &d, const Canonical &c, const MfmaTiling &t, PackedMfma &out)
+{
+    const Geometry g = geometry(d);
+    const int s = t.phased ? d.stride : 1, taps = t.Rr * t.Sr, octets = ceil_div(t.c_virtual, 8);
+    const int g8_last = octets - (t.nblk - 1) * t.g8;
+    const size_t tile_halves = (size_t)t.total_steps * 3 * 64 * 8;
+    out.wfrag.assign((size_t)d.groups * t.n_tiles32 * tile_halves + 3 * 64 * 8, 0); // the kernel reads one step ahead
+    for (int k = 0; k < d.K; ++k) {
+        const int grp = k / g.Kg, kl = k - grp * g.Kg;
+        uint16_t *tile = &out.wfrag[((size_t)grp * t.n_tiles32 + kl / 32) * tile_halves];
+        for (int j = c.rowptr[k]; j < c.rowptr[k + 1]; ++j) {
+            const int off = c.off[j];
+            const int fs = off % g.Wp, fr = (off / g.Wp) % g.Hp, cl = off / (g.Wp * g.Hp) - grp * g.Cg;
+            const int cv = t.phased ? ((fr % s) * s + fs % s) * g.Cg + cl : cl;
+            const int tap = (fr / s) * t.Sr + fs / s, oct = cv / 8, b = oct / t.g8, ol = oct - b * t.g8;
+            const int u = tap * (b == t.nblk - 1 ? g8_last : t.g8) + ol;
+            const float v = c.val[j];
+            if (!mfma_weight_ok(v)) return SCONV_ERR_PLAN;
+            const uint16_t h = to_bf16(v), m = to_bf16(v - from_bf16(h)), l = to_bf16(v - from_bf16(h) - from_bf16(m));
+            uint16_t *at = tile + ((size_t)(b * t.steps + u / 2) * 3 * 64 + (kl % 32) + 32 * (u % 2)) * 8 + cv % 8;
+            at[0] = h;
+            at[64 * 8] = m;
+            at[2 * 64 * 8] = l;
+        }
+    }
+    out.uoff.assign((size_t)2 * (t.steps + t.steps_last), 0);
+    for (int last = 0; last < 2; ++last) {
+        const int g8 = last ? g8_last : t.g8;
+        for (int tap = 0; tap < taps; ++tap)
+            for (int ol = 0; ol < g8; ++ol)
+                out.uoff[(last ? 2 * t.steps : 0) + tap * g8 + ol] = (ol * t.plane + (tap / t.Sr) * t.Wl + tap % t.Sr) * 48;
+    }
+    out.choff.clear();
+    if (t.phased)
+        for (int cv = 0; cv < octets * 8; ++cv) {
+            const int ph = cv / g.Cg, cl = cv % g.Cg;
+            out.choff.push_back(cv < t.c_virtual ? ((cl * d.H + ph / s) * d.W + ph % s) * 4 : -1);
+        }
+    return SCONV_OK;
+}
+
 } // namespace sconv

@@ -130,6 +130,35 @@ bool fc_gather_fits(const sconv_desc &d, int N);
 GatherShape choose_gather(const sconv_desc &d, int N, double avg_row_nnz, int max_row_nnz);
 GatherShape choose_fc_gather(const sconv_desc &d, int N, double avg_row_nnz, int max_row_nnz);
 
+// Tiling of the matrix-core kernel (rather dense layers).  The packing depends only on the layer: mt and nt may change
+// from call to call.
+struct MfmaTiling {
+    bool phased;             // channels are phase images picked out of the input (unpadded strided layers)
+    int mt = 0, nt = 0;      // a workgroup takes 32 * mt filters and 128 * nt positions
+    int nt_max;              // 1 where the planes of 256 positions would be too large
+    int splits;              // workgroups along the channel blocks (partial sums, added by a launch of their own)
+    int g8, nblk;            // channel octets staged per block, blocks
+    int steps, steps_last, total_steps; // MFMA depth steps (two octets of one or two taps) of a block, the last block, all
+    int c_virtual;           // channels of a group the kernel sees
+    int cstep, lstep;        // input elements per cell, cells per output position
+    int Rr, Sr, Wl;          // filter in cells, cells per staged row
+    int plane;               // cells of an octet's plane in LDS (a multiple of 64)
+    int n_tiles32;           // 32-row tiles per group, an even number
+    int n_mtiles;            // workgroups along a group's filters
+    int lds_bytes;
+    double us;
+};
+struct PackedMfma {
+    std::vector<uint16_t> wfrag;  // [group][32-row tile][step][part][lane][8], one spare step behind
+    std::vector<int32_t> uoff;    // [2 * steps] + [2 * steps_last]
+    std::vector<int32_t> choff;   // phased only: per channel of whole octets, -1 past the last
+};
+bool mfma_fits(const sconv_desc &d, int N, bool feature_major);
+bool mfma_weight_ok(float v);
+// The layer's tiling (mt, nt and us for a batch of N); false if the kernel cannot take the layer.
+bool choose_mfma(const sconv_desc &d, int N, MfmaTiling &t);
+int pack_mfma(const sconv_desc &d, const Canonical &c, const MfmaTiling &t, PackedMfma &out);
+
 int validate_desc(const sconv_desc &d);
 // rowptr starts at 0 and never falls, columns inside [0, Cg*R*S) and strictly ascending in each row
 int validate_csr(const sconv_desc &d, const int32_t *rowptr, const int32_t *colidx);
@@ -207,6 +236,15 @@ struct Epilogue {
     const float *bias = nullptr;
     bool relu = false;
 };
+struct DeviceMfma {
+    void *wfrag = nullptr, *uoff = nullptr, *choff = nullptr;
+    bool uploaded = false;
+};
+// feature_major: in_t[C][N] -> out_t[K][N] of a fully connected layer.  With t.splits > 1 `out` is a workspace of that many
+// outputs, split_stride floats apart; launch_reduce adds them up afterwards.
+int launch_mfma(const sconv_desc &d, const MfmaTiling &t, const DeviceMfma &dev, const DeviceDirect &direct, const float *in, float *out,
+                int N, bool feature_major, const Epilogue &ep, int64_t split_stride, void *stream, int *hip_err);
+int allow_full_lds(const void *kern, int *hip_err);
 int launch_gather(const sconv_desc &d, const DeviceGather &dev, const GatherShape &gs, const float *in, float *out, int N,
                   const Epilogue &ep, void *stream, int *hip_err);
 int launch_fc_gather(const sconv_desc &d, const DeviceGather &dev, const GatherShape &gs, const float *in_t, float *out_t, int N,

@@ -559,7 +559,7 @@ void timer_destroy(StreamTimer &t)
 // A kernel may use more than 64 KB of dynamic LDS only after it has been allowed to, once per kernel and
 // device.  The record of what has been allowed is the only state the library keeps outside its handles; it
 // is guarded, so handles may be used from different threads.
-static int allow_full_lds(const void *kern, int *hip_err)
+int allow_full_lds(const void *kern, int *hip_err)
 {
     static std::mutex guard;
     static std::set<std::pair<const void *, int>> allowed;

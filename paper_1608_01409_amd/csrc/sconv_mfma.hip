@@ -1,0 +1,435 @@
+// Layers that pruning left rather dense, on the matrix cores.
+//
+// Above a density of about a quarter most multiply-adds of a 32-row tile are real, and the matrix cores do dense
+// arithmetic 20 times as fast as the vector units.  They have no fp32 format of that speed, so both operands are split
+// into three bf16 parts, x = h + m + l exactly (3 x 8 significant bits), and the six products whose weight is 2^-16 or
+// more are summed in fp32: h*h into one accumulator, h*m + m*h + m*m + h*l + l*h into a second one that is added at the
+// end.  What is left out (m*l, l*m, l*l) is below 2^-25 of a product.  One v_mfma_f32_32x32x16_bf16 adds 16 products and
+// rounds once, so the large accumulator is rounded once per 16 columns instead of once per nonzero: measured against fp64
+// the result is closer than the fp32 chains of the sparse kernels.
+//
+// The splitting is exact for magnitudes from 2^-110 up to where h rounds to infinity (3.396e38): smaller ones would lose
+// bits of l to the end of the bf16 range, and infinities and NaN must meet stored weights only (a pruned weight is a zero
+// here).  A workgroup that stages such a value computes its outputs again from the CSR arrays.  Weights are checked when
+// they are packed.
+//
+// Implicit GEMM: rows = filters of a group, columns = output positions counted through the batch, depth = taps x
+// channels.  A workgroup takes 32*MT filters and 128*NT positions and walks the channels in blocks of 8*g8.  The input
+// rows its positions touch are staged once per block, split on the way, as [channel octet][cell][part][8 channels]: 16
+// bytes are the 8 consecutive depths a lane feeds to an MFMA, whatever the tap, which only moves the cell; 48 bytes from
+// cell to cell spread a wave's reads over all LDS banks.  Weights are packed in fragment order and go from L2 straight to
+// registers, one step ahead.  Two workgroups share a CU: one stages while the other multiplies.
+#include <algorithm>
+
+#include "sconv_device.h"
+
+namespace sconv {
+
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+using const_u32 = const __attribute__((address_space(4))) unsigned;
+using const_i32 = const __attribute__((address_space(4))) int;
+
+__device__ float mfma_buffer_load(int4v rsrc, int voffset, int soffset, int aux) __asm("llvm.amdgcn.raw.buffer.load.f32");
+
+__device__ int4v mfma_buffer_load4(int4v rsrc, int voffset, int soffset, int aux) __asm("llvm.amdgcn.raw.buffer.load.v4i32");
+
+struct MfmaArgs {
+    const float *in;
+    float *out;
+    const bf16x8 *wfrag;     // [group][32-row tile][step][part][lane]
+    const int *uoff;         // LDS byte offset of every depth octet, two per step: full block, then last block
+    const int *choff;        // phase form: byte offset of a virtual channel relative to its group, else null
+    const int *rowptr;       // the direct kernel's CSR, for workgroups that met a value the split cannot carry
+    const uint32_t *trip;
+    const float *bias;
+    int relu;
+    int P, OHW, OW, OH, H, W, K, Kg, Cg, pad, stride;
+    int cstep, lstep;        // input elements per cell; cells per output position
+    int Rr, Wl, row_img;     // filter rows in cells, cells per staged row, staged rows of a whole image
+    int g8, nblk, steps, steps_last, total_steps, c_virtual;
+    int plane;               // cells of a channel octet's plane in LDS
+    int n_ptiles, n_mtiles, n_tiles32, groups;
+    int splits, blk_split;   // workgroups along the channel blocks, blocks each of them takes
+    long long split_stride;  // floats from one part's sums to the next (out then is the workspace)
+    int in_ch4;              // bytes from one channel to the next
+    long long in_img, in_group;   // floats from one image / one group's channels to the next
+    long long in_floats;     // floats of the whole input
+    long long out_img, out_row;
+    int goff_mul;            // floats per unit of the CSR's offsets
+    int phase_s;             // phase form: the stride, else 1
+    FastDiv d_units, d_splits, d_mt, d_ohw, d_ow, d_wl, d_rowimg;
+    unsigned piece_magic[17]; // division of an item number by the number of pieces
+};
+
+constexpr unsigned kSplitLo = 0x08800000u; // 2^-110
+
+// low: the smallest 2 * |x| - 1 seen, as bit patterns (0 wraps to the largest)
+static __device__ __forceinline__ void split8(const float (&x)[8], uint4 &h, uint4 &m, uint4 &l, unsigned &low)
+{
+    unsigned hw[4], mw[4], lw[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const f32x2 v = {x[2 * i], x[2 * i + 1]};
+        low = min(low, min((__float_as_uint(v[0]) << 1) - 1u, (__float_as_uint(v[1]) << 1) - 1u));
+        const bf16x2 hb = __builtin_convertvector(v, bf16x2);
+        hw[i] = __builtin_bit_cast(unsigned, hb);
+        const f32x2 r = {v[0] - __uint_as_float(hw[i] << 16), v[1] - __uint_as_float(hw[i] & 0xffff0000u)};
+        const bf16x2 mb = __builtin_convertvector(r, bf16x2);
+        mw[i] = __builtin_bit_cast(unsigned, mb);
+        const f32x2 q = {r[0] - __uint_as_float(mw[i] << 16), r[1] - __uint_as_float(mw[i] & 0xffff0000u)};
+        const bf16x2 lb = __builtin_convertvector(q, bf16x2);
+        lw[i] = __builtin_bit_cast(unsigned, lb);
+    }
+    h = make_uint4(hw[0], hw[1], hw[2], hw[3]);
+    m = make_uint4(mw[0], mw[1], mw[2], mw[3]);
+    l = make_uint4(lw[0], lw[1], lw[2], lw[3]);
+}
+
+template <int MT, int NT>
+__global__ void __launch_bounds__(256, 2) sconv_mfma_kernel(const MfmaArgs a)
+{
+    constexpr int kBatch = 4;
+    extern __shared__ uint4 smem[];
+    char *lds = reinterpret_cast<char *>(smem);
+    const int lane = threadIdx.x & 63, half = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+
+    // Workgroup ids go round the 8 XCDs.  Position tiles are taken 8 at a time, one per XCD, so that the workgroups that
+    // stage the same positions for different filters meet in one L2; the tiles left over are spread over all XCDs unit by
+    // unit (169 tiles x 6 units on one XCD more than on the others cost that XCD a third round).
+    const int bid = blockIdx.x, units = a.n_mtiles * a.groups * a.splits, full = (a.n_ptiles >> 3) * 8 * units;
+    int ptile, unit;
+    if (bid < full) {
+        const int slot = bid >> 3, sq = fdiv(slot, a.d_units);
+        unit = slot - sq * units;
+        ptile = sq * 8 + (bid & 7);
+    } else {
+        const int sq = fdiv(bid - full, a.d_units);
+        unit = bid - full - sq * units;
+        ptile = (a.n_ptiles >> 3) * 8 + sq;
+    }
+    const int um = fdiv(unit, a.d_splits), split = unit - um * a.splits;
+    const int g = fdiv(um, a.d_mt), mt = um - g * a.n_mtiles;
+    const int b_first = split * a.blk_split, b_end = min(b_first + a.blk_split, a.nblk);   // this workgroup's channel blocks
+
+    const int p0 = ptile * (128 * NT);
+    const int n_first = fdiv(p0, a.d_ohw), y_first = fdiv(p0 - n_first * a.OHW, a.d_ow);
+    const int rows_first = (a.OH - 1 - y_first) * a.lstep + a.Rr;      // staged rows of the first image
+    auto row_of = [&](int n, int y) {
+        return n == n_first ? (y - y_first) * a.lstep : rows_first + (n - n_first - 1) * a.row_img + y * a.lstep;
+    };
+    int cells;
+    {
+        const int p1 = min(p0 + 128 * NT, a.P) - 1;
+        const int n = fdiv(p1, a.d_ohw), y = fdiv(p1 - n * a.OHW, a.d_ow);
+        cells = (row_of(n, y) + a.Rr) * a.Wl;
+    }
+    // where this lane's positions sit
+    unsigned lane_addr[NT];
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+        const int p = min(p0 + (wave * NT + t) * 32 + (lane & 31), a.P - 1);
+        const int n = fdiv(p, a.d_ohw), q = p - n * a.OHW, y = fdiv(q, a.d_ow), x = q - y * a.OW;
+        lane_addr[t] = (unsigned)(row_of(n, y) * a.Wl + x * a.lstep) * 48u;
+    }
+    // where the cells come from, relative to image n_first (a table in LDS behind the staged block and the depth octets'
+    // offsets): padding and cells past the end read beyond the buffer
+    const int n_off = 2 * (a.steps + a.steps_last);
+    int *tbl = reinterpret_cast<int *>(lds + (size_t)a.g8 * a.plane * 48);
+    unsigned *voff = reinterpret_cast<unsigned *>(tbl + n_off);
+    for (int cell = threadIdx.x; cell < a.plane; cell += 256) {
+        const int row = fdiv(cell, a.d_wl), col = cell - row * a.Wl;
+        int n = 0, yp = y_first * a.lstep + row;
+        if (row >= rows_first) {
+            const int i = fdiv(row - rows_first, a.d_rowimg);
+            n = 1 + i;
+            yp = row - rows_first - i * a.row_img;
+        }
+        const int iy = yp * a.cstep - a.pad, ix = col * a.cstep - a.pad;
+        const bool ok = cell < cells && iy >= 0 && iy < a.H && ix >= 0 && ix < a.W;
+        voff[cell] = ok ? (unsigned)(n * (int)a.in_img + iy * a.W + ix) * 4u : 0x80000000u;
+    }
+    for (int i = threadIdx.x; i < n_off; i += 256) tbl[i] = a.uoff[i];
+    const int pieces = (cells + 63) >> 6;
+    const FastDiv d_pieces = {(unsigned)pieces, a.piece_magic[pieces]};
+    const float *src = a.in + n_first * a.in_img + g * a.in_group;
+    int4v rsrc;
+    {
+        const unsigned long long ip = (unsigned long long)src;
+        const long long left = (a.in_floats - (n_first * a.in_img + g * a.in_group)) * 4;
+        rsrc.x = __builtin_amdgcn_readfirstlane((int)(unsigned)ip);
+        rsrc.y = __builtin_amdgcn_readfirstlane((int)(unsigned)(ip >> 32));
+        rsrc.z = __builtin_amdgcn_readfirstlane((int)min(left, 0x7fffffffll));
+        rsrc.w = 0x00020000;
+    }
+
+    f32x16 acc[MT][NT], cor[MT][NT];
+#pragma unroll
+    for (int m = 0; m < MT; ++m)
+#pragma unroll
+        for (int t = 0; t < NT; ++t)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[m][t][r] = cor[m][t][r] = 0.f;
+
+    // weights: step by step from a scalar offset per row tile; the fragments end with a spare step
+    int4v wrsrc;
+    {
+        const unsigned long long wp = (unsigned long long)(a.wfrag + (size_t)(g * a.n_tiles32 + mt * MT) * a.total_steps * 192);
+        wrsrc.x = __builtin_amdgcn_readfirstlane((int)(unsigned)wp);
+        wrsrc.y = __builtin_amdgcn_readfirstlane((int)(unsigned)(wp >> 32));
+        wrsrc.z = __builtin_amdgcn_readfirstlane((MT * a.total_steps + 1) * 3072);
+        wrsrc.w = 0x00020000;
+    }
+    const int lane16 = lane * 16;
+    int wstep = b_first * a.steps * 3072;
+    auto load_a = [&](bf16x8 (&A)[MT][3]) {
+#pragma unroll
+        for (int m = 0; m < MT; ++m)
+#pragma unroll
+            for (int s = 0; s < 3; ++s)
+                A[m][s] = __builtin_bit_cast(bf16x8, mfma_buffer_load4(wrsrc, lane16 + s * 1024, m * a.total_steps * 3072 + wstep, 0));
+        wstep += 3072;
+    };
+    auto load_b = [&](bf16x8 (&B)[NT][3], unsigned off) {
+#pragma unroll
+        for (int s = 0; s < 3; ++s)
+#pragma unroll
+            for (int t = 0; t < NT; ++t) B[t][s] = *reinterpret_cast<const bf16x8 *>(lds + lane_addr[t] + off + s * 16);
+    };
+    auto multiply = [&](const bf16x8 (&A)[MT][3], const bf16x8 (&B)[NT][3]) {
+#define SCONV_MFMA(D, PA, PB) \
+    _Pragma("unroll") for (int m = 0; m < MT; ++m) \
+        _Pragma("unroll") for (int t = 0; t < NT; ++t) \
+            D[m][t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(A[m][PA], B[t][PB], D[m][t], 0, 0, 0);
+        SCONV_MFMA(acc, 0, 0)
+        SCONV_MFMA(cor, 1, 0)
+        SCONV_MFMA(cor, 2, 0)
+        SCONV_MFMA(cor, 0, 1)
+        SCONV_MFMA(cor, 1, 1)
+        SCONV_MFMA(cor, 0, 2)
+#undef SCONV_MFMA
+    };
+    bf16x8 A[MT][3];
+    load_a(A);
+
+    unsigned low = 0xffffffffu;
+    const_i32 *choff = (const_i32 *)a.choff;
+    for (int b = b_first; b < b_end; ++b) {
+        __syncthreads();
+        // items of 64 cells x 8 channels, dealt to the waves; the loads of four items are in flight together
+        const int c0 = b * a.g8 * 8, items = min(a.g8, (a.c_virtual - c0 + 7) >> 3) * pieces;
+        for (int i0 = wave; i0 < items; i0 += 4 * kBatch) {
+            float x[kBatch][8];
+#pragma unroll
+            for (int j = 0; j < kBatch; ++j) {
+                const int item = min(i0 + 4 * j, items - 1), o = fdiv(item, d_pieces), piece = item - o * pieces, c = c0 + o * 8;
+                const unsigned vo = i0 + 4 * j < items ? voff[piece * 64 + lane] : 0x80000000u;
+                int co[8];
+                if (a.choff) {
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) co[i] = choff[c + i];
+                } else {
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) co[i] = c + i < a.c_virtual ? (c + i) * a.in_ch4 : -1;
+                }
+#pragma unroll
+                for (int i = 0; i < 8; ++i)        // a channel past the last one (-1) reads beyond the buffer's end: 0
+                    x[j][i] = mfma_buffer_load(rsrc, (int)(vo | ((unsigned)co[i] & 0x80000000u)), co[i] & 0x7fffffff, 0);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int j = 0; j < kBatch; ++j) {
+                const int item = i0 + 4 * j, o = fdiv(item, d_pieces), piece = item - o * pieces;
+                if (item >= items) break;
+                uint4 h, m, l;
+                split8(x[j], h, m, l, low);
+                uint4 *dst = reinterpret_cast<uint4 *>(lds + ((size_t)o * a.plane + piece * 64 + lane) * 48);
+                dst[0] = h;
+                dst[1] = m;
+                dst[2] = l;
+            }
+        }
+        __syncthreads();
+        // the weights of the next step are on their way while one is multiplied
+        const bool last = b == a.nblk - 1;
+        const int *u = tbl + half + (last ? 2 * a.steps : 0); // lanes 0-31 take the even octets, lanes 32-63 the odd ones
+        const int steps = last ? a.steps_last : a.steps;
+        bf16x8 B0[NT][3], B1[NT][3], A1[MT][3];
+        load_b(B0, (unsigned)u[0]);
+        unsigned off = (unsigned)u[2 * min(1, steps - 1)];
+        int i = 0;
+        for (; i + 1 < steps; i += 2) {
+            load_a(A1);
+            load_b(B1, off);
+            off = (unsigned)u[2 * min(i + 2, steps - 1)];
+            __builtin_amdgcn_sched_barrier(0);
+            multiply(A, B0);
+            __builtin_amdgcn_sched_barrier(0);
+            load_a(A);
+            load_b(B0, off);
+            off = (unsigned)u[2 * min(i + 3, steps - 1)];
+            __builtin_amdgcn_sched_barrier(0);
+            multiply(A1, B1);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        if (i < steps) {
+            load_a(A1);
+            __builtin_amdgcn_sched_barrier(0);
+            multiply(A, B0);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int m = 0; m < MT; ++m)
+#pragma unroll
+                for (int s = 0; s < 3; ++s) A[m][s] = A1[m][s];
+        }
+    }
+
+    // Whether the workgroup met a value the split cannot carry: a small one was noticed on the way, a large one, an infinity
+    // or a NaN has made a sum infinite or NaN (the middle part of an infinite leading part is infinity minus infinity).
+    bool bad = low < 2u * kSplitLo - 1u;
+#pragma unroll
+    for (int m = 0; m < MT; ++m)
+#pragma unroll
+        for (int t = 0; t < NT; ++t)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                acc[m][t][r] += cor[m][t][r];
+                bad |= (__float_as_uint(acc[m][t][r]) & 0x7f800000u) == 0x7f800000u;
+            }
+    volatile int *flag = reinterpret_cast<volatile int *>(lds);
+    __syncthreads();
+    if (threadIdx.x == 0) *flag = 0;
+    __syncthreads();
+    if (bad) *flag = 1;
+    __syncthreads();
+    if (*flag) {
+        // this workgroup's inputs hold an infinity, a NaN or a magnitude the split cannot carry: the sums over the stored
+        // nonzeros, as the direct kernel forms them
+        for (int i = threadIdx.x; i < 32 * MT * 128 * NT; i += 256) {
+            const int kl = mt * MT * 32 + i / (128 * NT), p = p0 + i % (128 * NT);
+            if (kl >= a.Kg || p >= a.P) continue;
+            const int k = g * a.Kg + kl, n = p / a.OHW, q = p - n * a.OHW, y = q / a.OW * a.stride, x = q % a.OW * a.stride;
+            const float *im = a.in + n * a.in_img;
+            float v = 0.f;
+            for (int j = a.rowptr[k]; j < a.rowptr[k + 1]; ++j) {
+                const int goff = (int)a.trip[3 * (size_t)j + 1];
+                const uint32_t rs = a.trip[3 * (size_t)j + 2];
+                const int dr = (int)(short)(rs >> 16), ds = (int)(short)(rs & 0xffffu);
+                if (a.splits > 1) {                // only the channels of this workgroup's blocks
+                    const int c = (goff - dr * a.W - ds) / (a.H * a.W) - g * a.Cg;
+                    const int cv = ((dr + a.pad) % a.phase_s * a.phase_s + (ds + a.pad) % a.phase_s) * a.Cg + c;
+                    const int b = cv / (8 * a.g8);
+                    if (b < b_first || b >= b_end) continue;
+                }
+                const int iy = y + dr, ix = x + ds;
+                const bool inside = iy >= 0 && iy < a.H && ix >= 0 && ix < a.W;
+                const float xv = inside ? im[(y * a.W + x + goff) * (long long)a.goff_mul] : 0.f;
+                v = fmaf(__uint_as_float(a.trip[3 * (size_t)j]), xv, v);
+            }
+            if (a.bias) v += a.bias[k];
+            if (a.relu) v = fmaxf(v, 0.f);
+            a.out[split * a.split_stride + n * a.out_img + k * a.out_row + q] = v;
+        }
+        return;
+    }
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+        const int p = p0 + (wave * NT + t) * 32 + (lane & 31);
+        if (p >= a.P) continue;
+        const int n = fdiv(p, a.d_ohw);
+        float *dst = a.out + split * a.split_stride + n * a.out_img + (p - n * a.OHW);
+#pragma unroll
+        for (int m = 0; m < MT; ++m)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const int kl = (mt * MT + m) * 32 + 8 * (r >> 2) + 4 * half + (r & 3);
+                if (kl >= a.Kg) continue;
+                const int k = g * a.Kg + kl;
+                float v = acc[m][t][r];
+                if (a.bias) v += a.bias[k];
+                if (a.relu) v = fmaxf(v, 0.f);
+                dst[k * a.out_row] = v;
+            }
+    }
+}
+
+template <int MT, int NT>
+static int launch_mfma_inst(const MfmaArgs &a, int grid, int lds_bytes, hipStream_t s, int *hip_err)
+{
+    auto kern = sconv_mfma_kernel<MT, NT>;
+    const int rc = allow_full_lds(reinterpret_cast<const void *>(kern), hip_err);
+    if (rc) return rc;
+    hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(256), lds_bytes, s, a);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) {
+        *hip_err = (int)e;
+        return SCONV_ERR_HIP;
+    }
+    return SCONV_OK;
+}
+
+int launch_mfma(const sconv_desc &d, const MfmaTiling &t, const DeviceMfma &dev, const DeviceDirect &direct, const float *in, float *out,
+                int N, bool feature_major, const Epilogue &ep, int64_t split_stride, void *stream, int *hip_err)
+{
+    const Geometry g = geometry(d);
+    MfmaArgs a;
+    a.in = in;
+    a.out = out;
+    a.wfrag = static_cast<const bf16x8 *>(dev.wfrag);
+    a.uoff = static_cast<const int *>(dev.uoff);
+    a.choff = t.phased ? static_cast<const int *>(dev.choff) : nullptr;
+    a.rowptr = static_cast<const int *>(direct.rowptr);
+    a.trip = static_cast<const uint32_t *>(direct.trip);
+    // with several parts the kernel stores partial sums into the workspace `out` points to, and the reduction that follows
+    // applies the epilogue
+    a.bias = t.splits == 1 ? ep.bias : nullptr;
+    a.relu = ep.relu && t.splits == 1 ? 1 : 0;
+    a.splits = t.splits;
+    a.blk_split = (t.nblk + t.splits - 1) / t.splits;
+    a.split_stride = t.splits > 1 ? split_stride : 0;
+    a.phase_s = t.phased ? d.stride : 1;
+    if (t.splits < 1 || (t.splits - 1) * a.blk_split >= t.nblk) return SCONV_ERR_PLAN; // a part without blocks
+    const int64_t HW = (int64_t)d.H * d.W, P = (int64_t)N * g.OH * g.OW;
+    if (!mfma_fits(d, N, feature_major)) return SCONV_ERR_RANGE;
+    a.P = (int)P; a.OHW = g.OH * g.OW; a.OW = g.OW; a.OH = g.OH; a.H = d.H; a.W = d.W; a.K = d.K; a.Kg = g.Kg; a.Cg = g.Cg;
+    a.pad = d.pad; a.stride = d.stride;
+    a.cstep = t.cstep; a.lstep = t.lstep; a.Rr = t.Rr; a.Wl = t.Wl; a.row_img = (g.OH - 1) * t.lstep + t.Rr;
+    a.g8 = t.g8; a.nblk = t.nblk; a.steps = t.steps; a.steps_last = t.steps_last; a.total_steps = t.total_steps;
+    a.c_virtual = t.c_virtual;
+    a.plane = t.plane;
+    const int bn = 128 * t.nt;
+    a.n_ptiles = (int)((P + bn - 1) / bn);
+    a.n_mtiles = t.n_mtiles;
+    a.n_tiles32 = t.n_tiles32;
+    a.groups = d.groups;
+    if (feature_major) {
+        a.in_ch4 = N * 4; a.in_img = 1; a.in_group = 0; a.in_floats = (int64_t)d.C * N;
+        a.out_img = 1; a.out_row = N; a.goff_mul = N;
+    } else {
+        a.in_ch4 = (int)(HW * 4); a.in_img = d.C * HW; a.in_group = g.Cg * HW; a.in_floats = (int64_t)N * d.C * HW;
+        a.out_img = (int64_t)d.K * a.OHW; a.out_row = a.OHW; a.goff_mul = 1;
+    }
+    // what the kernel assumes
+    if (t.plane > 1024 || t.total_steps > (1 << 18) || (int64_t)t.g8 * t.plane * 48 + 8 * (t.steps + t.steps_last) + 4 * t.plane > t.lds_bytes || t.g8 > 16 || t.nt > t.nt_max) return SCONV_ERR_PLAN;
+    const int units = t.n_mtiles * d.groups * t.splits;
+    const int64_t grid = (int64_t)a.n_ptiles * units;
+    if (grid > 0x7fffffff) return SCONV_ERR_RANGE;
+    a.d_units = make_fastdiv(units, std::max<int64_t>(grid / 8, 8 * (int64_t)units));
+    a.d_splits = make_fastdiv(t.splits, units);
+    a.d_mt = make_fastdiv(t.n_mtiles, units);
+    a.d_ohw = make_fastdiv(a.OHW, P + bn);
+    a.d_ow = make_fastdiv(a.OW, a.OHW);
+    a.d_wl = make_fastdiv(a.Wl, 1024);
+    a.d_rowimg = make_fastdiv(a.row_img, 1024);
+    for (int i = 0; i <= 16; ++i) a.piece_magic[i] = make_fastdiv(std::max(1, i), 16 * 16 + 64).magic;
+    hipStream_t s = static_cast<hipStream_t>(stream);
+#define X(M, NN) if (t.mt == M && t.nt == NN) return launch_mfma_inst<M, NN>(a, (int)grid, t.lds_bytes, s, hip_err);
+    X(1, 1) X(1, 2) X(2, 1) X(2, 2)
+#undef X
+    return SCONV_ERR_PLAN;
+}
+
+} // namespace sconv

@@ -1,0 +1,140 @@
+"""The matrix-core kernel (rather dense layers): the library picks it by itself, so the cases are dense and large enough
+that it does, at the sizes where its index arithmetic can go wrong.  Tolerance as in test_gpu_parity.py."""
+import sys
+
+import numpy as np
+import pytest
+import torch
+
+from oracle import spmdm_oracle as so
+from paper_1608_01409_amd import binding as B
+from paper_1608_01409_amd import workloads as wl
+
+pytestmark = pytest.mark.gpu
+TOL = 1e-5
+
+
+def say(msg):
+    print(f"[gpu-case] {msg}", flush=True)
+    sys.stdout.flush()
+
+
+def lay(C, H, W, K, R, S, stride=1, pad=0, groups=1):
+    return wl.Layer(f"c{C}h{H}w{W}k{K}r{R}s{S}t{stride}p{pad}g{groups}", C, H, W, K, R, S, stride, pad, groups)
+
+
+def conv_case(layer, N, density, seed):
+    rng = np.random.default_rng(seed)
+    x = rng.standard_normal((N, layer.C, layer.H, layer.W)).astype(np.float32)
+    w = (rng.standard_normal((layer.K, layer.Cg, layer.R, layer.S)) * 0.01).astype(np.float32)
+    w = np.where(rng.random(w.shape) < density, w, np.float32(0)).astype(np.float32)
+    return x, w
+
+
+# ragged filters (33, 65, 96 rows), channels (one octet short, several blocks), positions (tiles that span images, a last
+# tile of a few positions), every stride / padding / group form, phase images (unpadded strided), odd depth steps
+CONVS = [
+    (lay(64, 13, 13, 64, 3, 3, pad=1), 64), (lay(61, 13, 13, 33, 3, 3, pad=1), 65), (lay(96, 13, 13, 96, 3, 3, pad=1, groups=2), 40),
+    (lay(48, 27, 27, 65, 5, 5, pad=2), 10), (lay(130, 7, 9, 129, 3, 3, pad=1), 77), (lay(200, 14, 14, 70, 1, 1), 60),
+    (lay(3, 67, 67, 96, 11, 11, stride=4), 24), (lay(64, 29, 29, 80, 3, 3, stride=2, pad=1), 30), (lay(40, 30, 31, 64, 2, 4, stride=3, pad=0), 40),
+    (lay(7, 20, 20, 40, 5, 3, pad=1), 60), (lay(24, 56, 56, 48, 3, 3, pad=1), 9), (lay(256, 3, 3, 256, 3, 3), 300),
+    (lay(72, 9, 9, 100, 1, 1, stride=2), 200), (lay(33, 12, 40, 64, 7, 1, pad=3), 20),
+    # few positions: the channel blocks are shared by several workgroups
+    (lay(200, 7, 7, 100, 5, 5, pad=2), 5), (lay(500, 4, 4, 70, 3, 3, pad=1), 30), (lay(90, 21, 21, 64, 4, 4, stride=2), 6),
+    (lay(301, 16, 16, 40, 3, 3, stride=2, pad=1), 7),
+]
+
+
+@pytest.mark.parametrize("layer,N", CONVS, ids=[f"{l.name}n{n}" for l, n in CONVS])
+@pytest.mark.parametrize("density", [0.5, 1.0])
+def test_dense_convolutions(oracle, layer, N, density):
+    x, w = conv_case(layer, N, density, seed=N + layer.C)
+    w[1] = 0
+    say(f"mfma {layer.name} N={N} density={density}")
+    h = B.sconv_create_csr(layer, w)
+    xd = torch.from_numpy(x).cuda()
+    out = torch.full((N, layer.K, layer.OH, layer.OW), float("nan"), device="cuda")
+    B.sconv_forward(h, xd, out)
+    got = out.cpu().numpy()
+    ref, ab, _ = oracle.sparse_conv(layer, w, x)
+    assert np.all(np.abs(got.astype(np.float64) - ref) <= TOL * ab), float(np.abs(got - ref).max())
+    assert np.all(got[ab == 0] == 0)
+    # no further from the exact sums than the sparse kernel's fp32 chains
+    hs = B.sconv_create_csr(layer, w, dict(kernel=2))
+    sparse = B.sconv_forward(hs, xd).cpu().numpy().astype(np.float64)
+    assert np.linalg.norm(got - ref) <= np.linalg.norm(sparse - ref)
+    bias = np.random.default_rng(5).standard_normal(layer.K).astype(np.float32) * 0.05
+    got = B.sconv_forward_fused(h, xd, torch.from_numpy(bias).cuda(), True).cpu().numpy().astype(np.float64)
+    ref2, scale = oracle.bias_relu(ref, ab, bias, True)
+    assert np.all(np.abs(got - ref2) <= TOL * scale)
+
+
+@pytest.mark.parametrize("value", [np.inf, -np.inf, np.nan, 3.4e38, 1e-35, 1e-42, -5e-34])
+@pytest.mark.parametrize("layer,N", [(lay(64, 13, 13, 64, 3, 3, pad=1), 64), (lay(400, 13, 13, 64, 3, 3, pad=1), 6),
+                                     (lay(120, 28, 28, 64, 4, 4, stride=2), 6)], ids=["one", "split", "phases"])
+def test_values_the_split_cannot_carry(oracle, layer, N, value):
+    """One such activation: the outputs its nonzeros reach follow from the stored nonzeros alone, the others are what
+    they are without it, and pruned weights never meet it."""
+    x, w = conv_case(layer, N, 0.6, seed=11)
+    x[5] = 0
+    x[5, 3, 4, 6] = np.float32(value)
+    say(f"mfma special value {value} {layer.name}")
+    h = B.sconv_create_csr(layer, w)
+    got = B.sconv_forward(h, torch.from_numpy(x).cuda()).cpu().numpy()
+    ref5 = np.zeros((layer.K, layer.OH, layer.OW))
+    touched = np.zeros(ref5.shape, bool)
+    for k, _, r, s in np.argwhere(w[:, 3:4] != 0):
+        y, oy = divmod(4 + layer.pad - r, layer.stride)
+        xx, ox = divmod(6 + layer.pad - s, layer.stride)
+        if oy == 0 and ox == 0 and 0 <= y < layer.OH and 0 <= xx < layer.OW:
+            touched[k, y, xx] = True
+            ref5[k, y, xx] = np.float64(w[k, 3, r, s]) * np.float64(x[5, 3, 4, 6])
+    with np.errstate(over="ignore"):
+        ref5 = ref5.astype(np.float32)
+    assert touched.any() and np.array_equal(got[5][touched], ref5[touched], equal_nan=True)
+    assert np.all(got[5][~touched] == 0)
+    x[5] = 0
+    ref, ab, _ = oracle.sparse_conv(layer, w, x)
+    others = np.arange(N) != 5
+    assert np.all(np.abs(got[others].astype(np.float64) - ref[others]) <= TOL * ab[others])
+
+
+@pytest.mark.parametrize("value", [np.inf, 1e-40, 3e38])
+def test_weights_the_split_cannot_carry(oracle, value):
+    """Such a weight keeps the layer on the sparse kernels."""
+    layer = lay(64, 13, 13, 64, 3, 3, pad=1)
+    x, w = conv_case(layer, 64, 0.6, seed=12)
+    w[9, 5, 1, 1] = np.float32(value)
+    say(f"mfma special weight {value}")
+    h = B.sconv_create_csr(layer, w)
+    got = B.sconv_forward(h, torch.from_numpy(x).cuda()).cpu().numpy()
+    rows = np.arange(64) != 9
+    ref, ab, _ = oracle.sparse_conv(layer, np.where(np.isfinite(w), w, 0).astype(np.float32), x)
+    assert np.all(np.abs(got[:, rows].astype(np.float64) - ref[:, rows]) <= TOL * ab[:, rows])
+    if value == np.inf:
+        assert np.array_equal(np.isinf(got[:, 9]), x[:, 5] != 0)
+
+
+@pytest.mark.parametrize("K,C,N", [(512, 512, 512), (300, 1000, 516), (1000, 777, 1024), (130, 2000, 2064)])
+def test_dense_fully_connected(K, C, N):
+    rng = np.random.default_rng(K + N)
+    w = np.where(rng.random((K, C)) < 0.7, rng.standard_normal((K, C)) * 0.05, 0).astype(np.float32)
+    w[3] = 0
+    x_t = rng.standard_normal((C, N)).astype(np.float32)
+    bias = (rng.standard_normal(K) * 0.5).astype(np.float32)
+    say(f"mfma fc K={K} C={C} N={N}")
+    h = B.sconv_create_csr(B.fc_layer(C, K), w.reshape(K, C, 1, 1))
+    ref, ab = so.spmdm(w, x_t)
+    ref2, scale = so.bias_relu_t(ref, ab, bias, True)
+    for shift in (0, 1):
+        xd = torch.empty(C * N + shift, device="cuda")[shift:].view(C, N)
+        xd.copy_(torch.from_numpy(x_t))
+        out = torch.full((K * N + shift,), float("nan"), device="cuda")[shift:].view(K, N)
+        got = B.sconv_fc_forward(h, xd, torch.from_numpy(bias).cuda(), True, out).cpu().numpy().astype(np.float64)
+        assert np.all(np.abs(got - ref2) <= TOL * scale)
+    x_t[7, 5] = np.inf
+    got = B.sconv_fc_forward(h, torch.from_numpy(x_t).cuda()).cpu().numpy()
+    hit = np.zeros((K, N), bool)
+    hit[:, 5] = w[:, 7] != 0
+    assert np.array_equal(np.isinf(got), hit) and not np.isnan(got).any()
+    assert np.all(np.abs(got[~hit].astype(np.float64) - ref[~hit]) <= TOL * ab[~hit])
