@@ -17,6 +17,22 @@ using const_u32 = const __attribute__((address_space(4))) unsigned;
 
 __device__ float raw_buffer_load(int4v rsrc, int voffset, int soffset, int aux) __asm("llvm.amdgcn.raw.buffer.load.f32");
 
+// Workgroup -> (tile of positions, group of rows).  Workgroup ids go round the 8 XCDs: tiles are taken 8 at a time, one per
+// XCD, so that a tile's inputs come into one L2 only; the tiles left over are spread over all of them.
+static __device__ __forceinline__ void tile_of_block(int n_tiles, int n_rowgroups, FastDiv d_rg, int &tile, int &rg)
+{
+    const int bid = blockIdx.x, whole = n_tiles & ~7, full = whole * n_rowgroups;
+    if (bid < full) {
+        const int slot = bid >> 3, q = fdiv(slot, d_rg);
+        rg = slot - q * n_rowgroups;
+        tile = q * 8 + (bid & 7);
+    } else {
+        const int q = fdiv(bid - full, d_rg);
+        rg = bid - full - q * n_rowgroups;
+        tile = whole + q;
+    }
+}
+
 // ---------------------------------------------------------------- convolutions
 //
 // A wave owns one CSR row and T x 64 output positions, counted through the images (position p = image * OHW + y * OW
@@ -38,7 +54,7 @@ struct GatherArgs {
     int P;                   // output positions of the call: N * OHW
     int shift_bytes;         // (pad * W + pad) * 4: lane offsets are relative to that many bytes before `in`
     int rec_bytes;           // bytes of the input + shift_bytes
-    int n_rowgroups;         // workgroups along K
+    int n_tiles, n_rowgroups;    // workgroups along the positions, along K
     FastDiv d_rg, d_ohw, d_ow;
 };
 
@@ -50,7 +66,8 @@ __global__ void __launch_bounds__(SPLIT > 4 ? SPLIT * 64 : 256) sconv_gather_ker
     __shared__ double part[SPLIT > 1 ? kRows * SPLIT * T * 64 : 1];
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-    const int tile = fdiv((int)blockIdx.x, a.d_rg), rg = (int)blockIdx.x - tile * a.n_rowgroups;
+    int tile, rg;
+    tile_of_block(a.n_tiles, a.n_rowgroups, a.d_rg, tile, rg);
     const int row_l = wave / SPLIT, part_i = wave - row_l * SPLIT;
     const int k = rg * kRows + row_l;
     const bool live = k < a.K;
@@ -155,11 +172,15 @@ static int launch_gather_inst(const GatherArgs &a, int tiles, hipStream_t s, int
     return SCONV_OK;
 }
 
+static int launch_gather4(const sconv_desc &d, const DeviceGather &dev, const GatherShape &gs, const float *in, float *out, int N,
+                          const Epilogue &ep, void *stream, int *hip_err);
+
 int launch_gather(const sconv_desc &d, const DeviceGather &dev, const GatherShape &gs, const float *in, float *out, int N,
                   const Epilogue &ep, void *stream, int *hip_err)
 {
     const Geometry g = geometry(d);
     if (!gather_fits(d, N)) return SCONV_ERR_RANGE;
+    if (gather4_fits(d)) return launch_gather4(d, dev, gs, in, out, N, ep, stream, hip_err);
     GatherArgs a;
     a.ent = static_cast<const unsigned *>(dev.ent);
     a.rowptr = static_cast<const int *>(dev.rowptr);
@@ -175,6 +196,7 @@ int launch_gather(const sconv_desc &d, const DeviceGather &dev, const GatherShap
     const int rows = gs.split >= 4 ? 1 : 4 / gs.split;
     a.n_rowgroups = (d.K + rows - 1) / rows;
     const int tiles = (a.P + gs.t * 64 - 1) / (gs.t * 64);
+    a.n_tiles = tiles;
     const int64_t grid = (int64_t)tiles * a.n_rowgroups;
     if (grid > 0x7fffffff) return SCONV_ERR_RANGE;
     a.d_rg = make_fastdiv(a.n_rowgroups, grid);
@@ -184,6 +206,186 @@ int launch_gather(const sconv_desc &d, const DeviceGather &dev, const GatherShap
     hipStream_t s = static_cast<hipStream_t>(stream);
 #define X(TT, SP) if (gs.t == TT && gs.split == SP) return launch_gather_inst<TT, SP>(a, tiles, s, hip_err);
     X(1, 1) X(1, 2) X(1, 4) X(1, 8) X(2, 1) X(2, 2) X(2, 4) X(2, 8)
+#undef X
+    return SCONV_ERR_PLAN;
+}
+
+// The same with four neighbouring positions of an output row per lane, for stride 1.  A load instruction occupies the
+// address unit for 16 clocks whether its lanes fetch 4 or 16 bytes (measured: 4.4 million multiply-adds per microsecond
+// with a dword per lane, all of them in L1 or not), so a lane fetches 16.  The four words may leave the row: what a tap
+// must not see is masked per word by the tap's bit of that position's mask.  They must not leave the tensor, so the
+// nonzeros of its first and its last channel (the "edge" entries) take the dword loads above, word by word.
+struct Gather4Args {
+    const unsigned *ent;     // like GatherArgs::ent, the low five bits being the tap itself
+    const int *rows;         // per row: first entry, chunks of eight, edge entries behind them
+    const float *in;
+    float *out;
+    const float *bias;
+    int relu;
+    int K, OHW, OW, H, W, R, S, pad;
+    int in_img, Q, OW4, Q_img;   // lanes' units: Q = N * OH * OW4, OW4 = ceil(OW / 4), Q_img = OH * OW4
+    int shift_bytes, rec_bytes, n_tiles, n_rowgroups;
+    FastDiv d_rg, d_qimg, d_ow4;
+};
+
+typedef float float4v __attribute__((ext_vector_type(4)));
+__device__ float4v raw_buffer_load4(int4v rsrc, int voffset, int soffset, int aux) __asm("llvm.amdgcn.raw.buffer.load.v4f32");
+
+template <int SPLIT>
+__global__ void __launch_bounds__(SPLIT > 4 ? SPLIT * 64 : 256) sconv_gather4_kernel(const Gather4Args a)
+{
+    constexpr int kRows = SPLIT >= 4 ? 1 : 4 / SPLIT;
+    constexpr int U = SCONV_GATHER_CHUNK;
+    __shared__ double part[SPLIT > 1 ? kRows * SPLIT * 256 : 1];
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    int tile, rg;
+    tile_of_block(a.n_tiles, a.n_rowgroups, a.d_rg, tile, rg);
+    const int row_l = wave / SPLIT, part_i = wave - row_l * SPLIT;
+    const int k = rg * kRows + row_l;
+    const bool live = k < a.K;
+
+    const int q = tile * 64 + lane;
+    const int n = fdiv(q, a.d_qimg), rem = q - n * a.Q_img, y = fdiv(rem, a.d_ow4), x0 = (rem - y * a.OW4) * 4;
+    const bool on = q < a.Q;
+    unsigned valid[4] = {0u, 0u, 0u, 0u};                     // bit `tap`: this tap lies inside the image; bit 31 is clear
+    {
+        const int iy = y - a.pad, ix = x0 - a.pad;
+        unsigned cols[4] = {0u, 0u, 0u, 0u};
+        for (int s = 0; s < a.S; ++s)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) cols[e] |= (ix + e + s >= 0 && ix + e + s < a.W) ? 1u << s : 0u;
+        for (int r = 0; r < a.R; ++r)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) valid[e] |= (iy + r >= 0 && iy + r < a.H && on && x0 + e < a.OW) ? cols[e] << (r * a.S) : 0u;
+    }
+    const unsigned base = on ? (unsigned)(n * a.in_img + y * a.W + x0) * 4u : 0u;
+    double acc[4] = {0.0, 0.0, 0.0, 0.0};
+
+    if (live) {
+        const unsigned long long ip = (unsigned long long)a.in - (unsigned long long)a.shift_bytes;
+        int4v rsrc;
+        rsrc.x = __builtin_amdgcn_readfirstlane((int)(unsigned)ip);
+        rsrc.y = __builtin_amdgcn_readfirstlane((int)(unsigned)(ip >> 32));
+        rsrc.z = __builtin_amdgcn_readfirstlane(a.rec_bytes);
+        rsrc.w = 0x00020000;
+        const __attribute__((address_space(4))) int *row = (const __attribute__((address_space(4))) int *)a.rows + 3 * k;
+        const int j0 = row[0], chunks = row[1], edges = row[2];
+        const int mine = (chunks + SPLIT - 1) / SPLIT;
+        const int c0 = part_i * mine, c1 = min(chunks, c0 + mine);
+        const_u32 *e = (const_u32 *)a.ent + 2 * ((size_t)j0 + (size_t)c0 * U);
+        unsigned cur[2 * U], nxt[2 * U];
+        if (c0 < c1) {
+#pragma unroll
+            for (int i = 0; i < 2 * U; ++i) cur[i] = e[i];
+        }
+        for (int c = c0; c < c1; ++c) {
+            e += 2 * U;                                       // the stream ends with a spare chunk
+#pragma unroll
+            for (int i = 0; i < 2 * U; ++i) nxt[i] = e[i];
+            float4v v[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) v[u] = raw_buffer_load4(rsrc, (int)base, (int)(cur[2 * u + 1] >> 3 & ~3u), 0);
+            __builtin_amdgcn_sched_barrier(0);                // all eight loads in flight
+            // eight products in fp32, their sum to the fp64 one: the conversions are too slow for every product
+            float s4[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const int m = __builtin_amdgcn_sbfe((int)valid[i], cur[2 * u + 1] & 31u, 1);
+                    s4[i] = fmaf(__uint_as_float(cur[2 * u]), __uint_as_float(__float_as_uint(v[u][i]) & (unsigned)m), s4[i]);
+                }
+#pragma unroll
+            for (int i = 0; i < 4; ++i) acc[i] += (double)s4[i];
+#pragma unroll
+            for (int i = 0; i < 2 * U; ++i) cur[i] = nxt[i];
+        }
+        // edge entries, shared by the waves of the row
+        const_u32 *ee = (const_u32 *)a.ent + 2 * ((size_t)j0 + (size_t)chunks * U);
+        for (int j = part_i; j < edges; j += SPLIT) {
+            const unsigned w = ee[2 * j], ctl = ee[2 * j + 1];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const unsigned off = (valid[i] >> (ctl & 31u) & 1u) ? base + 4u * i : 0x80000000u;
+                acc[i] = fma((double)__uint_as_float(w), (double)raw_buffer_load(rsrc, (int)off, (int)(ctl >> 3 & ~3u), 0), acc[i]);
+            }
+        }
+    }
+    if constexpr (SPLIT > 1) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) part[((row_l * SPLIT + part_i) * 4 + i) * 64 + lane] = acc[i];
+        __syncthreads();
+        if (part_i != 0) return;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            double v = 0.0;
+#pragma unroll
+            for (int p = 0; p < SPLIT; ++p) v += part[((row_l * SPLIT + p) * 4 + i) * 64 + lane];
+            acc[i] = v;
+        }
+    }
+    if (!live || !on) return;
+    const double b = a.bias ? (double)a.bias[k] : 0.0;
+    float *dst = a.out + ((size_t)n * a.K + k) * a.OHW + y * a.OW + x0;
+    float o[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        o[i] = (float)(a.bias ? acc[i] + b : acc[i]);
+        if (a.relu) o[i] = fmaxf(o[i], 0.f);
+    }
+    if (x0 + 4 <= a.OW) {
+        *(float4u *)dst = float4u{o[0], o[1], o[2], o[3]};
+    } else {
+#pragma unroll
+        for (int i = 0; i < 3; ++i)
+            if (x0 + i < a.OW) dst[i] = o[i];
+    }
+}
+
+template <int SPLIT>
+static int launch_gather4_inst(const Gather4Args &a, int tiles, hipStream_t s, int *hip_err)
+{
+    hipLaunchKernelGGL((sconv_gather4_kernel<SPLIT>), dim3((unsigned)(tiles * a.n_rowgroups)), dim3(SPLIT > 4 ? SPLIT * 64 : 256), 0, s, a);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) {
+        *hip_err = (int)e;
+        return SCONV_ERR_HIP;
+    }
+    return SCONV_OK;
+}
+
+static int launch_gather4(const sconv_desc &d, const DeviceGather &dev, const GatherShape &gs, const float *in, float *out, int N,
+                          const Epilogue &ep, void *stream, int *hip_err)
+{
+    const Geometry g = geometry(d);
+    if (!gather4_fits(d)) return SCONV_ERR_PLAN;
+    Gather4Args a;
+    a.ent = static_cast<const unsigned *>(dev.ent);
+    a.rows = static_cast<const int *>(dev.rowptr);
+    a.in = in;
+    a.out = out;
+    a.bias = ep.bias;
+    a.relu = ep.relu ? 1 : 0;
+    a.K = d.K; a.OHW = g.OH * g.OW; a.OW = g.OW; a.H = d.H; a.W = d.W; a.R = d.R; a.S = d.S; a.pad = d.pad;
+    a.in_img = d.C * d.H * d.W;
+    a.OW4 = (g.OW + 3) / 4;
+    a.Q_img = g.OH * a.OW4;
+    a.Q = N * a.Q_img;
+    a.shift_bytes = (d.pad * d.W + d.pad) * 4;
+    a.rec_bytes = N * a.in_img * 4 + a.shift_bytes;
+    const int rows = gs.split >= 4 ? 1 : 4 / gs.split;
+    a.n_rowgroups = (d.K + rows - 1) / rows;
+    const int tiles = (a.Q + 63) / 64;
+    a.n_tiles = tiles;
+    const int64_t grid = (int64_t)tiles * a.n_rowgroups;
+    if (grid > 0x7fffffff) return SCONV_ERR_RANGE;
+    a.d_rg = make_fastdiv(a.n_rowgroups, grid);
+    a.d_qimg = make_fastdiv(a.Q_img, (int64_t)tiles * 64);
+    a.d_ow4 = make_fastdiv(a.OW4, a.Q_img);
+    hipStream_t s = static_cast<hipStream_t>(stream);
+#define X(SP) if (gs.split == SP) return launch_gather4_inst<SP>(a, tiles, s, hip_err);
+    X(1) X(2) X(4) X(8)
 #undef X
     return SCONV_ERR_PLAN;
 }

@@ -871,24 +871,55 @@ int unpack_direct(const sconv_desc &d, const PackedDirect &p, Canonical &out)
 
 // ------------------------------------------------------------------ gather kernels (small launches)
 
+// The four-position kernel: neighbours in a row are neighbours in memory, and the four words of a lane stay inside the
+// tensor for every tap of every channel but the first and the last.
+bool gather4_fits(const sconv_desc &d)
+{
+    return d.stride == 1 && d.C >= 3 && (int64_t)d.H * d.W > (int64_t)d.pad * d.W + d.pad + 2;
+}
+
 int pack_gather(const sconv_desc &d, const Canonical &c, PackedGather &out)
 {
     const Geometry g = geometry(d);
+    const bool four = gather4_fits(d);
     out.ent.clear();
     out.ent.reserve(c.val.size() + (size_t)d.K * SCONV_GATHER_CHUNK);
-    out.rowptr.assign(d.K + 1, 0);
+    out.rowptr.assign(four ? (size_t)3 * d.K : (size_t)d.K + 1, 0);
+    // control word of every column of group 0; a group further on adds its channels' bytes
+    std::vector<uint32_t> ctl((size_t)g.Cg * d.R * d.S);
+    for (size_t col = 0; col < ctl.size(); ++col) {
+        const int s = (int)(col % d.S), r = (int)(col / d.S % d.R), cl = (int)(col / ((size_t)d.R * d.S)), tap = r * d.S + s;
+        ctl[col] = (uint32_t)((cl * d.H + r) * d.W + s) * 4u << 3 | (uint32_t)(four ? tap : 31 - tap);
+    }
+    // padding: weight 0 on a tap no position has (the four-position kernel reads there: channel 1, inside the tensor)
+    const uint64_t pad_entry = four ? (uint64_t)((uint32_t)(d.H * d.W) * 4u << 3 | 31u) << 32 : 0;
+    const int last = (g.Cg - 1) * d.R * d.S;       // first column of a group's last channel
+    std::vector<uint64_t> edge;
     for (int k = 0; k < d.K; ++k) {
+        const int grp = k / g.Kg;
+        const uint32_t add = (uint32_t)(grp * g.Cg * d.H * d.W) * 4u << 3;
+        const size_t start = out.ent.size();
+        edge.clear();
         for (int j = c.rowptr[k]; j < c.rowptr[k + 1]; ++j) {
-            const int off = c.off[j];
-            const int s = off % g.Wp, r = (off / g.Wp) % g.Hp, ca = off / (g.Wp * g.Hp);
-            const uint32_t byte_off = (uint32_t)((ca * d.H + r) * d.W + s) * 4u;
+            const int col = c.colidx[j];
             uint32_t vb;
             std::memcpy(&vb, &c.val[j], 4);
-            out.ent.push_back((uint64_t)vb | ((uint64_t)(byte_off << 3 | (uint32_t)(31 - (r * d.S + s))) << 32));
+            const uint64_t e = (uint64_t)vb | (uint64_t)(ctl[col] + add) << 32;
+            if (four && ((grp == 0 && col < d.R * d.S) || (grp == d.groups - 1 && col >= last)))
+                edge.push_back(e);
+            else
+                out.ent.push_back(e);
         }
-        while (out.ent.size() % SCONV_GATHER_CHUNK) out.ent.push_back(0);
-        if (out.ent.size() >= ((size_t)1 << 31)) return SCONV_ERR_RANGE;
-        out.rowptr[k + 1] = (int32_t)out.ent.size();
+        while ((out.ent.size() - start) % SCONV_GATHER_CHUNK) out.ent.push_back(pad_entry);
+        if (four) {
+            out.rowptr[3 * (size_t)k] = (int32_t)start;
+            out.rowptr[3 * (size_t)k + 1] = (int32_t)((out.ent.size() - start) / SCONV_GATHER_CHUNK);
+            out.rowptr[3 * (size_t)k + 2] = (int32_t)edge.size();
+            out.ent.insert(out.ent.end(), edge.begin(), edge.end());
+        } else {
+            out.rowptr[k + 1] = (int32_t)out.ent.size();
+        }
+        if (out.ent.size() >= ((size_t)1 << 30)) return SCONV_ERR_RANGE;
     }
     out.ent.resize(out.ent.size() + SCONV_GATHER_CHUNK, 0); // the kernel reads one chunk ahead
     return SCONV_OK;
@@ -922,22 +953,31 @@ bool fc_gather_fits(const sconv_desc &d, int N)
     return N >= 4 && N % 4 == 0 && N <= SCONV_FC_GATHER_MAX_N && (int64_t)d.C * N * 4 < ((int64_t)1 << 32);
 }
 
-// What a gather launch takes, in microseconds, fitted to 37 convolutions and 11 fully connected layers (0.1-480 million
-// multiply-adds) run in every shape: 3 us for a launch whatever it does, then the longer of two terms and a third of the
-// shorter one.  Throughput: a wave costs 0.12 us per thousand (index arithmetic, 30 % more for a second chunk of
-// positions), a 64-lane load 18 us per million (25 % more when the lanes are a stride apart).  Latency: a wave's
-// chunks of 8 nonzeros follow each other at 0.28 us; the longest row counts.
+// What a gather launch takes, in microseconds: 3 us whatever it does, then the longer of two terms and a third of the
+// shorter one.  Throughput: a wave's index arithmetic and a 64-lane load have a price each; latency: a wave's chunks of 8
+// nonzeros follow each other, the longest row counts.  Fitted for the four-position kernel to 60 random layers (3-85 us,
+// 14 % off on average): 0.25 us per thousand waves, 29 us per million loads (of 256 positions), 0.35 us per chunk; for the
+// other one to 37 (0.1-480 million multiply-adds): 0.12 us (30 % more for a second chunk of positions), 18 us per million
+// loads of 64 positions (25 % more when the lanes are a stride apart), 0.28 us.
 GatherShape choose_gather(const sconv_desc &d, int N, double avg_row_nnz, int max_row_nnz)
 {
     const Geometry g = geometry(d);
-    const double P = (double)N * g.OH * g.OW;
+    const bool four = gather4_fits(d);
+    const double P = four ? (double)N * g.OH * ceil_div(g.OW, 4) : (double)N * g.OH * g.OW;
     GatherShape best = {0, 0, 0.0};
-    for (int t = 1; t <= 2; ++t)
+    for (int t = 1; t <= (four ? 1 : 2); ++t)
         for (int split = 1; split <= 8; split *= 2) {
             const double tiles = std::ceil(P / (64.0 * t)), chunks = std::max(1.0, std::ceil(avg_row_nnz / SCONV_GATHER_CHUNK + 0.4));
-            const double waves = d.K * tiles * split, loads = d.K * tiles * t * chunks * SCONV_GATHER_CHUNK;
-            const double thr = 0.12e-3 * waves * (1.0 + 0.3 * (t - 1)) + 0.018e-3 * loads * (d.stride > 1 ? 1.25 : 1.0);
-            const double lat = 0.28 * std::ceil((double)max_row_nnz / (SCONV_GATHER_CHUNK * split)) * std::sqrt((double)t);
+            const double waves = d.K * tiles * split, chunks_wave = std::ceil((double)max_row_nnz / (SCONV_GATHER_CHUNK * split));
+            double loads = d.K * tiles * t * chunks * SCONV_GATHER_CHUNK, thr, lat;
+            if (four) {
+                loads += d.K * tiles * 8.0 * avg_row_nnz / d.C;          // entries of the two outer channels: four loads each
+                thr = 0.25e-3 * waves + 0.029e-3 * loads;
+                lat = 0.35 * chunks_wave;
+            } else {
+                thr = 0.12e-3 * waves * (1.0 + 0.3 * (t - 1)) + 0.018e-3 * loads * (d.stride > 1 ? 1.25 : 1.0);
+                lat = 0.28 * chunks_wave * std::sqrt((double)t);
+            }
             const double us = 3.0 + std::max(thr, lat) + 0.35 * std::min(thr, lat);
             if (best.t == 0 || us < best.us) best = GatherShape{t, split, us};
         }
@@ -1084,22 +1124,28 @@ int pack_mfma(const sconv_desc &d, const Canonical &c, const MfmaTiling &t, Pack
     const int g8_last = octets - (t.nblk - 1) * t.g8;
     const size_t tile_halves = (size_t)t.total_steps * 3 * 64 * 8;
     out.wfrag.assign((size_t)d.groups * t.n_tiles32 * tile_halves + 3 * 64 * 8, 0); // the kernel reads one step ahead
+    // where a column's weight of row 0 goes inside a 32-row tile
+    std::vector<uint32_t> at_col((size_t)g.Cg * d.R * d.S);
+    for (size_t col = 0; col < at_col.size(); ++col) {
+        const int fs = (int)(col % d.S), fr = (int)(col / d.S % d.R), cl = (int)(col / ((size_t)d.R * d.S));
+        const int cv = t.phased ? ((fr % s) * s + fs % s) * g.Cg + cl : cl;
+        const int tap = (fr / s) * t.Sr + fs / s, oct = cv / 8, b = oct / t.g8, ol = oct - b * t.g8;
+        const int u = tap * (b == t.nblk - 1 ? g8_last : t.g8) + ol;
+        at_col[col] = (uint32_t)(((size_t)(b * t.steps + u / 2) * 3 * 64 + 32 * (u % 2)) * 8 + cv % 8);
+    }
     for (int k = 0; k < d.K; ++k) {
         const int grp = k / g.Kg, kl = k - grp * g.Kg;
-        uint16_t *tile = &out.wfrag[((size_t)grp * t.n_tiles32 + kl / 32) * tile_halves];
+        uint16_t *tile = &out.wfrag[((size_t)grp * t.n_tiles32 + kl / 32) * tile_halves + (size_t)(kl % 32) * 8];
         for (int j = c.rowptr[k]; j < c.rowptr[k + 1]; ++j) {
-            const int off = c.off[j];
-            const int fs = off % g.Wp, fr = (off / g.Wp) % g.Hp, cl = off / (g.Wp * g.Hp) - grp * g.Cg;
-            const int cv = t.phased ? ((fr % s) * s + fs % s) * g.Cg + cl : cl;
-            const int tap = (fr / s) * t.Sr + fs / s, oct = cv / 8, b = oct / t.g8, ol = oct - b * t.g8;
-            const int u = tap * (b == t.nblk - 1 ? g8_last : t.g8) + ol;
             const float v = c.val[j];
             if (!mfma_weight_ok(v)) return SCONV_ERR_PLAN;
-            const uint16_t h = to_bf16(v), m = to_bf16(v - from_bf16(h)), l = to_bf16(v - from_bf16(h) - from_bf16(m));
-            uint16_t *at = tile + ((size_t)(b * t.steps + u / 2) * 3 * 64 + (kl % 32) + 32 * (u % 2)) * 8 + cv % 8;
+            const uint16_t h = to_bf16(v);
+            const float r1 = v - from_bf16(h);
+            const uint16_t m = to_bf16(r1);
+            uint16_t *at = tile + at_col[c.colidx[j]];
             at[0] = h;
             at[64 * 8] = m;
-            at[2 * 64 * 8] = l;
+            at[2 * 64 * 8] = to_bf16(r1 - from_bf16(m));
         }
     }
     out.uoff.assign((size_t)2 * (t.steps + t.steps_last), 0);

@@ -109,13 +109,15 @@ struct Canonical {
 
 // Packing for the gather kernels (small launches), the same for every batch size.  Convolutions: rows padded to whole
 // chunks, entry = (value bits, byte offset of (c, r, s) in the unpadded image << 3 | (31 - tap)); padding entries are
-// (0, 0).  Fully connected layers (taps = 0): entry = (value bits, feature), rows not padded.
+// (0, 0).  Layers the four-position kernel takes (gather4_fits): the entries between the first and the last channel of the
+// tensor in whole chunks, low bits = tap, then the others one by one; per row (first entry, chunks, other entries).
+// Fully connected layers (taps = 0): entry = (value bits, feature), rows not padded.
 #define SCONV_GATHER_CHUNK 8
 #define SCONV_GATHER_MAX_TAPS 31
 #define SCONV_FC_GATHER_MAX_N 256
 struct PackedGather {
     std::vector<uint64_t> ent;
-    std::vector<int32_t> rowptr;   // [K + 1], in entries
+    std::vector<int32_t> rowptr;   // [K + 1], in entries (gather4_fits: [K][3])
 };
 // What one wave of a gather kernel covers: t x 64 output positions (fully connected: t pieces of 4 images); split waves
 // share a row.
@@ -126,6 +128,7 @@ struct GatherShape {
 int pack_gather(const sconv_desc &d, const Canonical &c, PackedGather &out);
 int pack_fc_gather(const sconv_desc &d, const Canonical &c, PackedGather &out);
 bool gather_fits(const sconv_desc &d, int N);
+bool gather4_fits(const sconv_desc &d);
 bool fc_gather_fits(const sconv_desc &d, int N);
 GatherShape choose_gather(const sconv_desc &d, int N, double avg_row_nnz, int max_row_nnz);
 GatherShape choose_fc_gather(const sconv_desc &d, int N, double avg_row_nnz, int max_row_nnz);

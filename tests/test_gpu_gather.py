@@ -39,6 +39,9 @@ CONVS = [
     (lay(5, 8, 8, 7, 3, 3, pad=1), 2), (lay(4, 9, 15, 6, 5, 5, pad=2), 1), (lay(6, 7, 9, 3, 1, 31, pad=15), 1),
     (lay(6, 9, 7, 9, 31, 1, pad=15), 2), (lay(8, 11, 6, 4, 6, 5, pad=1, groups=2), 3), (lay(6, 13, 13, 12, 3, 3, 2, 1, 3), 5),
     (lay(2, 23, 10, 5, 5, 3, 3, 2), 4), (lay(9, 2, 3, 8, 3, 3, pad=2), 7), (lay(64, 5, 5, 33, 3, 3, pad=1), 1),
+    # four positions per lane: rows of 4k .. 4k+3 positions, planes just large enough, two groups, tiles on all eight XCDs
+    (lay(3, 3, 5, 6, 3, 3, pad=1), 2), (lay(4, 4, 9, 5, 3, 3, pad=1), 3), (lay(5, 6, 10, 5, 2, 3), 3), (lay(6, 5, 15, 8, 1, 4, groups=2), 2),
+    (lay(3, 4, 4, 4, 5, 5, pad=2), 1), (lay(20, 30, 31, 6, 3, 3, pad=1), 12), (lay(2, 9, 9, 3, 3, 3, pad=1), 2),
     (lay(300, 7, 7, 24, 3, 3, pad=1), 1), (lay(128, 6, 6, 130, 1, 1), 2), (lay(40, 6, 6, 10, 3, 3, 2), 1),
 ]
 
