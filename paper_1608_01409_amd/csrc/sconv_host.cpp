@@ -1040,8 +1040,20 @@ static float from_bf16(uint16_t b)
     return v;
 }
 
-bool choose_mfma(const sconv_desc &d, int N, MfmaTiling &t)
+// A 1x1 layer sees its image as one column: the cells a workgroup stages are then exactly its positions, not whole rows.
+sconv_desc mfma_desc(const sconv_desc &d)
 {
+    sconv_desc f = d;
+    if (d.R == 1 && d.S == 1 && d.stride == 1 && d.pad == 0) {
+        f.H = d.H * d.W;
+        f.W = 1;
+    }
+    return f;
+}
+
+bool choose_mfma(const sconv_desc &layer, int N, MfmaTiling &t)
+{
+    const sconv_desc d = mfma_desc(layer);
     const Geometry g = geometry(d);
     double best_units = -1;
     // an unpadded strided layer may be seen as its phase images: fewer empty channels of an octet where C is small
@@ -1061,7 +1073,9 @@ bool choose_mfma(const sconv_desc &d, int N, MfmaTiling &t)
             const int rows_out = ceil_div(bn - 1, g.OW) + 1, images = c.Rr > c.lstep ? ceil_div(bn - 1, g.OH * g.OW) + 1 : 1;
             return ((int64_t)rows_out * c.lstep + (int64_t)images * (c.Rr - c.lstep)) * c.Wl;
         };
-        c.nt_max = cells_of(256) <= 1024 ? 2 : 1;
+        // (layers of one tap are a few matrix steps per staged channel: they want deep blocks, and 128 positions leave LDS
+        // for twice the octets; 192 -> 64 on 28x28, batch 64: 6 blocks of 4 octets 25 us, 2 of 12 22 us)
+        c.nt_max = cells_of(256) <= 1024 && c.Rr * c.Sr > 1 ? 2 : 1;
         const int64_t cells = cells_of(128 * c.nt_max);
         if (cells < 1 || cells > 1024) continue;
         c.plane = (int)((cells + 63) / 64 * 64);

@@ -114,7 +114,7 @@ struct Canonical {
 // Fully connected layers (taps = 0): entry = (value bits, feature), rows not padded.
 #define SCONV_GATHER_CHUNK 8
 #define SCONV_GATHER_MAX_TAPS 31
-#define SCONV_FC_GATHER_MAX_N 256
+#define SCONV_FC_GATHER_MAX_N 16384  // images: the grid's second dimension counts pieces of them
 struct PackedGather {
     std::vector<uint64_t> ent;
     std::vector<int32_t> rowptr;   // [K + 1], in entries (gather4_fits: [K][3])
@@ -138,7 +138,7 @@ GatherShape choose_fc_gather(const sconv_desc &d, int N, double avg_row_nnz, int
 struct MfmaTiling {
     bool phased;             // channels are phase images picked out of the input (unpadded strided layers)
     int mt = 0, nt = 0;      // a workgroup takes 32 * mt filters and 128 * nt positions
-    int nt_max;              // 1 where the planes of 256 positions would be too large
+    int nt_max;              // 1 where 256 positions are too many for LDS, or 128 serve better
     int splits;              // workgroups along the channel blocks (partial sums, added by a launch of their own)
     int g8, nblk;            // channel octets staged per block, blocks
     int steps, steps_last, total_steps; // MFMA depth steps (two octets of one or two taps) of a block, the last block, all
@@ -158,6 +158,7 @@ struct PackedMfma {
 };
 bool mfma_fits(const sconv_desc &d, int N, bool feature_major);
 bool mfma_weight_ok(float v);
+sconv_desc mfma_desc(const sconv_desc &d);
 // The layer's tiling (mt, nt and us for a batch of N); false if the kernel cannot take the layer.
 bool choose_mfma(const sconv_desc &d, int N, MfmaTiling &t);
 int pack_mfma(const sconv_desc &d, const Canonical &c, const MfmaTiling &t, PackedMfma &out);

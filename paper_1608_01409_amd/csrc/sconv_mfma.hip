@@ -371,9 +371,10 @@ static int launch_mfma_inst(const MfmaArgs &a, int grid, int lds_bytes, hipStrea
     return SCONV_OK;
 }
 
-int launch_mfma(const sconv_desc &d, const MfmaTiling &t, const DeviceMfma &dev, const DeviceDirect &direct, const float *in, float *out,
+int launch_mfma(const sconv_desc &layer, const MfmaTiling &t, const DeviceMfma &dev, const DeviceDirect &direct, const float *in, float *out,
                 int N, bool feature_major, const Epilogue &ep, int64_t split_stride, void *stream, int *hip_err)
 {
+    const sconv_desc d = mfma_desc(layer);
     const Geometry g = geometry(d);
     MfmaArgs a;
     a.in = in;
