@@ -467,10 +467,11 @@ static bool free_choice(const sconv_csr *h)
     return !rq.nt && !rq.cb && !rq.waves && !rq.cg && !rq.rows_w && !rq.t && !rq.band && !rq.strip && !rq.splits;
 }
 
-// Another kernel than the flat-stream one is taken when it is expected to win by this much.  Of 75 convolutions run both
-// ways the models then lose none by more than 10 % to the gather kernel (at 1.05: four, the worst 31 us instead of 23.5;
-// the LDS model reads up to 40 % high on launches of 5-20 us); of 25 fully connected layers none at 1.1.
-static const double kGatherMargin = 1.25, kFcGatherMargin = 1.1, kMfmaMargin = 1.1;
+// How far the other kernels' models are trusted against the flat-stream kernel's and each other's: their times count with
+// these factors.  Of 75 convolutions run both ways the models then lose none by more than 10 % to the gather kernel (at
+// 1.05: four, the worst 31 us instead of 23.5; the LDS model reads up to 40 % high on launches of 5-20 us); of 110 layers
+// of density 0.1-1 one (fully connected, at 1.1: 33 us instead of 31) to it and none to the matrix-core kernel.
+static const double kGatherMargin = 1.25, kFcGatherMargin = 1.2, kMfmaMargin = 1.15;
 
 static double avg_row_nnz(const sconv_csr *h) { return h->desc.K ? (double)h->canon.val.size() / h->desc.K : 0.0; }
 
@@ -495,9 +496,10 @@ static const sconv_csr::Choice &choose_kernel(sconv_csr *h, bool fc, int N, doub
     double best = lds_us;
     if (fc ? fc_gather_fits(h->desc, N) : gather_fits(h->desc, N)) {
         c.gather = fc ? choose_fc_gather(h->desc, N, avg_row_nnz(h), h->max_row_nnz) : choose_gather(h->desc, N, avg_row_nnz(h), h->max_row_nnz);
-        if (c.gather.us * (fc ? kFcGatherMargin : kGatherMargin) < lds_us) {
+        const double us = c.gather.us * (fc ? kFcGatherMargin : kGatherMargin);
+        if (us < best) {
             c.kind = sconv_csr::kGather;
-            best = c.gather.us;
+            best = us;
         }
     }
     if (h->split_exact && mfma_fits(h->desc, N, fc) && choose_mfma(h->desc, N, c.mfma)) {

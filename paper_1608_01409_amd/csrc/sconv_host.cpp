@@ -1100,9 +1100,10 @@ bool choose_mfma(const sconv_desc &layer, int N, MfmaTiling &t)
     }
     if (best_units < 0) return false;
     t.n_tiles32 = 2 * ceil_div(g.Kg, 64);
-    // What a launch takes, fitted to 26 layers in every shape (10-460 us, 12 % off on average): a workgroup's matrix
-    // instructions at 2.1 GHz, 0.61 us for each round of 64 cells x 8 channels x 4 waves it stages, 4 us for its index
-    // arithmetic and stores; workgroups that share a CU overlap down to 1.2 times the first and half of the others.
+    // What a launch takes, fitted to 26 layers in every shape and checked on 50 more (10-460 us, 12 % off on average): a
+    // workgroup's matrix instructions at 2.1 GHz, 0.61 us for each round of 64 cells x 8 channels x 4 waves it stages, 4 us
+    // for its index arithmetic; workgroups that share a CU overlap down to 1.3 times the first and half of the others; the
+    // output at 6 TB/s, stored when a workgroup is done.
     t.us = 0;
     const double P = (double)N * g.OH * g.OW, out_bytes = 4.0 * P * d.K;
     for (int mt = 1; mt <= 2; ++mt)
@@ -1116,8 +1117,8 @@ bool choose_mfma(const sconv_desc &layer, int N, MfmaTiling &t)
                 const double mfma = share * t.total_steps * mt * nt * 192.0 / 2100.0;
                 const double rounds = blocks * std::ceil(t.plane * (nt == t.nt_max ? 1.0 : 0.6) / 64.0) * t.g8 / 4.0;
                 const int fit = std::min(mt * nt == 4 ? 2 : mt * nt == 2 ? 3 : 4, 160 * 1024 / (t.lds_bytes + 512));
-                const double alone = mfma + 0.05 * blocks + 0.61 * rounds + 4.0, shared = mfma / 0.816 + 0.306 * rounds + 1.2;
-                double us = 4.4 + std::max(alone * std::ceil(per_cu / fit), per_cu * shared);
+                const double alone = mfma + 0.05 * blocks + 0.61 * rounds + 4.0, shared = mfma / 0.78 + 0.306 * rounds + 1.2;
+                double us = 4.4 + std::max(alone * std::ceil(per_cu / fit), per_cu * shared) + out_bytes / 6.0e6;
                 // partial sums: stored, and added by a launch of their own that reads every part
                 if (splits > 1) us += 4.0 + splits * (out_bytes / 3.5e6 + 0.3);
                 if (t.us == 0 || us < t.us) {
