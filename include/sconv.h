@@ -150,6 +150,11 @@ int sconv_csr_unpack(const sconv_csr *h, int32_t which, int32_t *rowptr, int32_t
  * it (host work, milliseconds, then a device allocation and a blocking upload:
  * that call synchronises with the device); the packings of the last four
  * tilings stay on the device, so alternating batch sizes cost nothing more.
+ * A handle created without a tiling may also run a call on another kernel than
+ * the LDS-tiled one its plan describes: launches with little arithmetic gather
+ * straight from global memory, rather dense layers run on the matrix cores.
+ * The library decides by the layer, its density and N (sconv_tune by measuring);
+ * either kernel reads arrays of its own, uploaded with the first call it serves.
  * If packing for a new N fails the handle keeps the packing it had.
  * Calls on one handle must not overlap in time (the handle owns scratch);
  * different handles are independent.
