@@ -468,9 +468,13 @@ static bool free_choice(const sconv_csr *h)
 }
 
 // How far the other kernels' models are trusted against the flat-stream kernel's and each other's: their times count with
-// these factors.  Of 75 convolutions run both ways the models then lose none by more than 10 % to the gather kernel (at
-// 1.05: four, the worst 31 us instead of 23.5; the LDS model reads up to 40 % high on launches of 5-20 us); of 110 layers
-// of density 0.1-1 one (fully connected, at 1.1: 33 us instead of 31) to it and none to the matrix-core kernel.
+// these factors.  260 random convolutions of 0.02-1.2 GFLOP, flat-stream and gather timed in turn: at 1.25 two go to the
+// gather kernel wrongly by more than 2 % (213 -> 26 3x3 on 36x36, batch 58, density 0.03: 39.8 us instead of 33.0;
+// 216 -> 35 3x3 on 18x18, batch 5, density 0.73: 27.0 instead of 24.6) and 16 stay away from it wrongly by more than 5 %
+// (up to 32 %); at 1.15 five and nine.  1.25 costs 1.2 % on average over the better kernel, 1.15 0.6 %, but it is the one
+// that makes fewer calls slower.  A term for the input's bytes (at the copy rate) takes the first of the two away and
+// makes the average worse (2.0 %).  Of 110 layers of density 0.1-1 one goes wrongly to the fully connected gather (at
+// 1.1: 33 us instead of 31) and none to the matrix-core kernel.
 static const double kGatherMargin = 1.25, kFcGatherMargin = 1.2, kMfmaMargin = 1.15;
 
 static double avg_row_nnz(const sconv_csr *h) { return h->desc.K ? (double)h->canon.val.size() / h->desc.K : 0.0; }
