@@ -9,7 +9,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libsconv.so")
-SOURCES = ["sconv_api.cpp", "sconv_host.cpp", "sconv_kernels.hip", "sconv_gather.hip", "sconv_mfma.hip"]
+SOURCES = ["sconv_api.cpp", "sconv_host.cpp", "sconv_kernels.hip", "sconv_gather.hip", "sconv_mfma.hip", "sconv_flat_mc.hip"]
 # -packed-fp32-ops is switched off: the packed FP32 forms are not to be generated for this machine.
 DEVICE_FLAGS = ["--offload-arch=gfx950", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
 

@@ -57,20 +57,26 @@ struct sconv_csr {
     };
     std::map<int, Planned> plan_of_n;        // tilings already chosen, by batch size
     // which kernel serves a batch size (by the cost models, or as measured): the flat-stream kernel with its plan,
-    // the gather kernel (small launches) or the matrix-core kernel (rather dense layers)
-    enum Kind { kLds, kGather, kMfma };
+    // the gather kernel (small launches), the matrix-core kernel (rather dense layers) or the flat streams on the matrix cores
+    enum Kind { kLds, kGather, kMfma, kFlatMc };
     struct Choice {
         Kind kind;
         GatherShape gather;                  // t = 0: the gather kernel cannot take it
         MfmaTiling mfma;                     // mt = 0: the matrix-core kernel cannot take it
+        FlatMcTiling mc;                     // mt = 0: the flat streams stay on the vector units
         bool tuned;                          // as in Planned
     };
     struct Alternatives {                    // for the convolution entry points, for the fully connected one
         std::map<int, Choice> choice_of_n;
         DeviceGather gather;
         DeviceMfma mfma;
+        DeviceLds mc;
+        bool mc_uploaded = false;
+        int mc_wexp = 0;
+        int64_t mc_bytes = 0;
     } conv_alt, fc_alt;
     int max_row_nnz = 0;
+    bool mc_ok = false;                      // rows and weights are such that the flat streams may run on the matrix cores
     bool split_exact = true;                 // every weight is exactly three bf16 parts
     int short_rows = 0;                      // rows of 1 to SCONV_MFMA_SHORT_ROW - 1 nonzeros
     std::vector<StashedPacking> stash;       // earlier packings, oldest first
@@ -300,6 +306,7 @@ static int finish_create(sconv_csr *h, const sconv_plan *plan)
         h->short_rows += nnz > 0 && nnz < SCONV_MFMA_SHORT_ROW;
     }
     for (float v : h->canon.val) h->split_exact = h->split_exact && mfma_weight_ok(v);
+    h->mc_ok = flat_mc_weights_ok(d, h->canon);
     int rc = pack_direct(d, h->canon, h->direct);
     if (rc) return rc;
     h->kdesc = d;
@@ -550,6 +557,10 @@ static bool free_choice(const sconv_csr *h)
 // kernels).  Of 4100 random calls it was chosen for, 7 take more than 2 % longer than on the flat-stream kernel (at most 14 %).
 static const double kMfmaMargin = 1.15;
 
+// The flat streams on the matrix cores against the same on the vector units and against the three-part kernel.  Of 60 random calls
+// 22 go there, none of them slower than before; with 1.1 and 1.0 it was 20, one of them 14 % slower.
+static const double kFlatMcMargin = 1.0, kFlatMcMfmaMargin = 1.15;
+
 // The LDS path's time for N images: the flat-stream kernel's, and for layers that need phase images the pass that writes
 // them (a launch, and their bytes written and read).
 static double planned_us(const sconv_csr *h, int N, double flat_us, int phase_cg)
@@ -562,12 +573,12 @@ static double planned_us(const sconv_csr *h, int N, double flat_us, int phase_cg
 // Gather: launches with little arithmetic; its multiply-adds cost about three times the LDS kernels' (4.4 against 10-20
 // million per microsecond), its fixed price is a third of theirs (3.5 us against 6-15).  Matrix cores: layers where the
 // zeros they multiply cost less than what their rate wins.
-static const sconv_csr::Choice &choose_kernel(sconv_csr *h, bool fc, int N, double lds_us)
+static const sconv_csr::Choice &choose_kernel(sconv_csr *h, bool fc, int N, double lds_us, int lds_splits)
 {
     sconv_csr::Alternatives &alt = fc ? h->fc_alt : h->conv_alt;
     auto known = alt.choice_of_n.find(N);
     if (known != alt.choice_of_n.end()) return known->second;
-    sconv_csr::Choice c = {sconv_csr::kLds, {0, 0, 0.0, 0.0}, {}, false};
+    sconv_csr::Choice c = {sconv_csr::kLds, {0, 0, 0.0, 0.0}, {}, {}, false};
     double best = lds_us; // (a tiling the cost model gave no time keeps the call)
     if (fc ? fc_gather_fits(h->desc, N) : gather_fits(h->desc, N)) {
         c.gather = fc ? choose_fc_gather(h->desc, N, avg_row_nnz(h), h->max_row_nnz) : choose_gather(h->desc, N, avg_row_nnz(h), h->max_row_nnz);
@@ -581,6 +592,18 @@ static const sconv_csr::Choice &choose_kernel(sconv_csr *h, bool fc, int N, doub
         if (c.mfma.us * kMfmaMargin < best) c.kind = sconv_csr::kMfma;
     } else {
         c.mfma = MfmaTiling();
+    }
+    // The flat streams on the matrix cores, where their sums are no further from the exact ones than those they replace: what
+    // counts is the length of the chains there, which parts make shorter.
+    const double row = avg_row_nnz(h);
+    const bool three_parts = c.kind == sconv_csr::kMfma, flushed = three_parts || lds_splits > 1;
+    const bool exact = three_parts ? row >= (c.mfma.splits <= 1 ? SCONV_MC_LONG_ROW : c.mfma.splits * SCONV_MC_LONG_ROW_SPLIT)
+                                   : c.kind == sconv_csr::kLds && (lds_splits <= 1 || row >= lds_splits * SCONV_MC_ROW_SPLIT);
+    if (!fc && exact && h->mc_ok && mfma_fits(h->desc, N, false) && choose_flat_mc(h->desc, h->canon, N, flushed, c.mc)) {
+        c.mc.for_dense = three_parts;
+        if (three_parts ? c.mc.us * kFlatMcMfmaMargin < c.mfma.us : c.mc.us * kFlatMcMargin < lds_us) c.kind = sconv_csr::kFlatMc;
+    } else {
+        c.mc = FlatMcTiling();
     }
     if (fc) make_room(alt.choice_of_n); // (a convolution's choices make room with its tilings, in plan_lds)
     return alt.choice_of_n[N] = c;
@@ -624,6 +647,7 @@ static void release_mfma(DeviceMfma &dev)
 
 static bool resident(const sconv_csr *h, const sconv_csr::Alternatives &alt, const sconv_csr::Choice &c)
 {
+    if (c.kind == sconv_csr::kFlatMc) return alt.mc_uploaded;
     return c.kind == sconv_csr::kGather ? alt.gather.uploaded : alt.mfma.uploaded && (!h->short_rows || h->direct_uploaded);
 }
 
@@ -640,6 +664,18 @@ static int prepare_choice(sconv_csr *h, bool fc, const sconv_csr::Choice &c)
         if (!rc) rc = upload(p.rowptr.data(), p.rowptr.size() * 4, &alt.gather.rowptr, &h->hip_err);
         if (!rc) alt.gather.uploaded = true;
         else release_gather(alt.gather);
+    } else if (c.kind == sconv_csr::kFlatMc) {
+        PackedFlatMc p;
+        FlatMcTiling t = c.mc;
+        rc = pack_flat_mc(mfma_desc(h->desc), h->canon, t, p);
+        if (!rc) rc = upload(p.stream.data(), p.stream.size(), &alt.mc.pairs, &h->hip_err);
+        if (!rc) rc = upload(p.seg.data(), p.seg.size() * 4, &alt.mc.seg_ptr, &h->hip_err);
+        if (!rc) rc = upload(p.row_of.data(), p.row_of.size() * 4, &alt.mc.row_of, &h->hip_err);
+        if (!rc) rc = upload(p.choff.data(), p.choff.size() * 4, &alt.mc.store_tbl, &h->hip_err);
+        alt.mc_wexp = t.wexp;
+        alt.mc_bytes = t.stream_bytes;
+        if (!rc) alt.mc_uploaded = true;
+        else release_arrays(alt.mc);
     } else {
         PackedMfma p;
         rc = alt.mfma.uploaded ? SCONV_OK : pack_mfma(h->desc, h->canon, c.mfma, p);
@@ -678,6 +714,17 @@ static int launch_choice(sconv_csr *h, bool fc, const sconv_csr::Choice &c, cons
     if (c.kind == sconv_csr::kGather)
         return fc ? launch_fc_gather(h->desc, alt.gather, c.gather, in, out, N, ep, stream, &h->hip_err)
                   : launch_gather(h->desc, alt.gather, c.gather, in, out, N, ep, stream, &h->hip_err);
+    if (c.kind == sconv_csr::kFlatMc) {
+        FlatMcTiling mc = c.mc;
+        mc.wexp = alt.mc_wexp;
+        mc.stream_bytes = alt.mc_bytes;
+        LdsTiling t = {};
+        t.p.splits = mc.splits;
+        t.mc = &mc;
+        const Geometry g = geometry(h->desc);
+        const int64_t rows = fc ? h->desc.K : (int64_t)N * h->desc.K, inner = fc ? N : (int64_t)g.OH * g.OW;
+        return run_flat(h, h->desc, t, alt.mc, Lds2Layout(), in, out, N, rows, inner, ep, stream, ws);
+    }
     if (c.mfma.splits <= 1) return launch_mfma(h->desc, c.mfma, alt.mfma, h->dev_direct, in, out, N, fc, ep, 0, stream, &h->hip_err);
     const Geometry g = geometry(h->desc);
     const int64_t rows = fc ? h->desc.K : (int64_t)N * h->desc.K, inner = fc ? N : (int64_t)g.OH * g.OW;
@@ -735,7 +782,7 @@ static int decide(sconv_csr *h, int N, const sconv_csr::Choice **c)
             planned = h->plan_of_n.find(n_plan);
         }
         const sconv_csr::Planned &p = planned->second;
-        auto choice_for = [&](int n) -> const sconv_csr::Choice & { return choose_kernel(h, false, n, planned_us(h, n, p.us, p.phase_cg)); };
+        auto choice_for = [&](int n) -> const sconv_csr::Choice & { return choose_kernel(h, false, n, planned_us(h, n, p.us, p.phase_cg), p.plan.splits); };
         // batches of 1-4 share a tiling: sconv_forward_noalloc takes all of them once one has run, so their kernels are chosen
         // together and the LDS kernel's arrays go up as well
         if (N <= 4 && !h->conv_alt.choice_of_n.count(N))
@@ -865,6 +912,7 @@ static int forward_impl(sconv_csr *h, const float *in, float *out, int32_t N, co
 static sconv_route route_of_choice(const sconv_desc &d, bool fc, const sconv_csr::Choice &c)
 {
     if (c.kind == sconv_csr::kMfma) return {SCONV_KERNEL_MFMA, c.mfma.splits > 1 ? 2 : 1, c.mfma.mt, c.mfma.nt, c.mfma.splits};
+    if (c.kind == sconv_csr::kFlatMc) return {c.mc.for_dense ? SCONV_KERNEL_MFMA : SCONV_KERNEL_FLAT, c.mc.splits > 1 ? 2 : 1, c.mc.mt, c.mc.nt, c.mc.splits};
     const int kernel = fc ? SCONV_KERNEL_FC_GATHER : gather4_fits(d) ? SCONV_KERNEL_GATHER4 : SCONV_KERNEL_GATHER;
     return {kernel, 1, c.gather.t, 1, c.gather.split};
 }
@@ -1037,8 +1085,8 @@ static int plan_fc(sconv_csr *h, int N, const sconv_csr::Planned *force = nullpt
 // The same decision for the fully connected entry point, against the tiling just planned.
 static const sconv_csr::Choice &choose_fc_kernel(sconv_csr *h, int N)
 {
-    if (free_choice(h) && h->requested.kernel == 0) return choose_kernel(h, true, N, h->fc_flat.t.us);
-    static const sconv_csr::Choice lds = {sconv_csr::kLds, {0, 0, 0.0, 0.0}, {}, false};
+    if (free_choice(h) && h->requested.kernel == 0) return choose_kernel(h, true, N, h->fc_flat.t.us, 1);
+    static const sconv_csr::Choice lds = {sconv_csr::kLds, {0, 0, 0.0, 0.0}, {}, {}, false};
     return lds;
 }
 
@@ -1190,6 +1238,7 @@ static std::vector<sconv_csr::Kind> other_kernels(const sconv_csr::Choice &c)
     std::vector<sconv_csr::Kind> k;
     if (c.gather.t > 0) k.push_back(sconv_csr::kGather);
     if (c.mfma.mt > 0) k.push_back(sconv_csr::kMfma);
+    if (c.mc.mt > 0) k.push_back(sconv_csr::kFlatMc);
     return k;
 }
 
@@ -1230,8 +1279,8 @@ extern "C" int sconv_tune(sconv_csr *h, const float *in, float *out, int32_t N, 
         // the other kernels are further candidates where they can run (and the untuned choice where the models pick one)
         h->conv_alt.choice_of_n.erase(N);
         const size_t n_lds = cands.size();
-        sconv_csr::Choice own = {sconv_csr::kLds, {0, 0, 0.0, 0.0}, {}, false};
-        if (h->requested.kernel == 0 && h->flat) own = choose_kernel(h, false, N, planned_us(h, N, cands[0].us, cands[0].phase_cg));
+        sconv_csr::Choice own = {sconv_csr::kLds, {0, 0, 0.0, 0.0}, {}, {}, false};
+        if (h->requested.kernel == 0 && h->flat) own = choose_kernel(h, false, N, planned_us(h, N, cands[0].us, cands[0].phase_cg), cands[0].p.splits);
         const std::vector<sconv_csr::Kind> others = other_kernels(own);
         auto choice = [&](size_t i) {
             sconv_csr::Choice c = own;
@@ -1340,6 +1389,7 @@ extern "C" void sconv_destroy_csr(sconv_csr *h)
     for (sconv_csr::Alternatives *alt : {&h->conv_alt, &h->fc_alt}) {
         release_gather(alt->gather);
         release_mfma(alt->mfma);
+        release_arrays(alt->mc);
     }
     delete h;
 }

@@ -2,9 +2,12 @@
 // (Figure 2's colidx -> f(c,r,s)), choice of a tiling, and packing of the nonzeros
 // into the order and units the kernels read.  No device work happens here.
 #include <algorithm>
+#include <atomic>
 #include <cmath>
 #include <cstring>
+#include <functional>
 #include <numeric>
+#include <thread>
 
 #include "sconv_internal.h"
 
@@ -1207,6 +1210,447 @@ int pack_mfma(const sconv_desc &d, const Canonical &c, const MfmaTiling &t, Pack
             const bool there = cv < t.c_virtual && ph / s < d.R && ph % s < d.S;
             out.choff.push_back(there ? ((cl * d.H + ph / s) * d.W + ph % s) * 4 : SCONV_MFMA_NO_CHANNEL);
         }
+    return SCONV_OK;
+}
+
+// ------------------------------------------------------------------ flat streams on the matrix cores
+
+// How often a step's octet is needed, on average over the workgroups (the waves of one wait for each other): once where one of a wave's row tiles has weights in it, twice
+// where a row has more than two of four channels.  The second time of a few tiles goes to steps of their own (an octet per tile),
+// of many tiles to the shared steps.  Rows as pack_flat_mc orders them, their weights taken as evenly spread.
+static double mc_slots_per_octet(const sconv_desc &d, const Canonical &c, int mt, int wr)
+{
+    const Geometry g = geometry(d);
+    const double cols = (double)g.Cg * d.R * d.S;
+    std::vector<int> nnz(g.Kg);
+    double sum = 0;
+    int units = 0;
+    for (int grp = 0; grp < d.groups; ++grp) {
+        for (int k = 0; k < g.Kg; ++k) nnz[k] = c.rowptr[grp * g.Kg + k + 1] - c.rowptr[grp * g.Kg + k];
+        std::sort(nnz.begin(), nnz.end(), std::greater<int>());
+        double most = 0;
+        for (int r0 = 0, u = 0; r0 < g.Kg; r0 += 16 * mt, ++u) {
+            double none = 1, once = 1, tiles = 0;       // no row has weights in an octet, no row needs it twice, tiles that do
+            for (int t0 = r0; t0 < std::min(g.Kg, r0 + 16 * mt); t0 += 16) {
+                double tile = 1;
+                for (int r = t0; r < std::min(g.Kg, t0 + 16); ++r) {
+                    const double x = std::min(1.0, nnz[r] / cols), q = 4 * x * x * x * (1 - x) + x * x * x * x;
+                    none *= std::pow(1 - x, 8);
+                    tile *= (1 - q) * (1 - q);
+                }
+                once *= tile;
+                tiles += 1 - tile;
+            }
+            most = std::max(most, 1 - none + std::min(1 - once, 1.5 * tiles / mt));
+            if (u % wr == wr - 1 || r0 + 16 * mt >= g.Kg) {
+                sum += most;
+                most = 0;
+                ++units;
+            }
+        }
+    }
+    return sum / std::max(1, units);
+}
+
+bool flat_mc_weights_ok(const sconv_desc &d, const Canonical &c)
+{
+    if ((double)c.val.size() < (double)SCONV_MC_FLUSHED_ROW * d.K) return false;
+    for (int k = 0; k < d.K; ++k) {
+        const int nnz = c.rowptr[k + 1] - c.rowptr[k];
+        if (nnz > 0 && nnz < 16) return false;
+    }
+    float most = 0, least = INFINITY;
+    for (float v : c.val) {
+        const float m = std::fabs(v);
+        most = std::max(most, m);
+        if (!(m <= 3.4028235e38f)) return false;
+        if (m > 0) least = std::min(least, m);
+    }
+    return most == 0 || (most >= 0x1p-100f && most <= 0x1p100f && least >= most * 0x1p-26f);
+}
+
+bool choose_flat_mc(const sconv_desc &layer, const Canonical &csr, int N, bool flushed, FlatMcTiling &t)
+{
+    const double avg_row_nnz = (double)csr.val.size() / std::max(1, layer.K);
+    if (avg_row_nnz < SCONV_MC_FLUSHED_ROW) return false;
+    const sconv_desc d = mfma_desc(layer);
+    const Geometry g = geometry(d);
+    const double density = std::min(1.0, avg_row_nnz / ((double)g.Cg * d.R * d.S));
+    if (d.H * d.W > 1 && (256 / ((int64_t)g.OH * g.OW) + 3) * d.K * g.OH * g.OW * 4 >= ((int64_t)1 << 31)) return false; // 32-bit store offsets
+    // Rather dense layers (most octets twice): 64 filters x 128 positions, the sums flushed every few steps.  The others: up to
+    // 128 x 128.  As few padded filters as possible, rather more than fewer.
+    const bool dense = density >= SCONV_MC_DENSE;
+    int mt = 0, wr = 0;
+    double best_rows = 0;
+    const int shapes[][2] = {{4, 2}, {3, 2}, {4, 1}, {3, 1}, {2, 1}};
+    for (const auto &sh : shapes) {
+        if (dense && sh[1] == 2) continue;
+        const int rows = 16 * sh[0] * sh[1];
+        const double cost = (double)ceil_div(g.Kg, rows) * rows * (sh[0] == 4 ? 1.0 : sh[0] == 3 ? 1.06 : 1.2) * (sh[1] == 2 ? 1.0 : 1.1);
+        if (mt == 0 || cost < best_rows) {
+            best_rows = cost;
+            mt = sh[0];
+            wr = sh[1];
+        }
+    }
+    const int pos_waves = wr == 2 ? 2 : 4;
+    const double slots = mc_slots_per_octet(d, csr, mt, wr);
+    double best_units = -1, steps_total = 0, rows_at[2] = {0, 0};
+    for (int phased = 0; phased <= (d.stride > 1 && d.pad == 0 ? 1 : 0); ++phased) {
+        FlatMcTiling c;
+        const int s = phased ? d.stride : 1;
+        c.phased = phased != 0;
+        c.cstep = s;
+        c.lstep = phased ? 1 : d.stride;
+        c.Rr = ceil_div(d.R, s);
+        c.Sr = ceil_div(d.S, s);
+        if ((int64_t)g.Cg * s * s > (1 << 20) || (int64_t)(g.OW - 1) * c.lstep + c.Sr > 1024) continue;
+        c.c_virtual = g.Cg * s * s;
+        c.Wl = (g.OW - 1) * c.lstep + c.Sr;
+        // the right padding of a row is the left padding of what follows it
+        int over = 0;
+        if (d.stride == 1 && d.W + d.pad >= g.OW && c.Wl > d.W + d.pad) {
+            over = c.Wl - (d.W + d.pad);
+            c.Wl = d.W + d.pad;
+        }
+        if (over > d.pad) continue;
+        // rows that a workgroup's consecutive positions touch, over all places they can start at
+        auto rows_of = [&](int bn) {
+            const int rows_out = ceil_div(bn - 1, g.OW) + 1, images = c.Rr > c.lstep ? ceil_div(bn - 1, g.OH * g.OW) + 1 : 1;
+            return (int64_t)rows_out * c.lstep + (int64_t)images * (c.Rr - c.lstep);
+        };
+        c.nt_max = !dense && rows_of(64 * pos_waves) * c.Wl <= 1024 ? 4 : 2;
+        const int64_t n_rows = rows_of(16 * pos_waves * c.nt_max), cells = n_rows * c.Wl;
+        if (cells < 1 || cells > 1024) continue;
+        c.plane = (int)((cells + 63) / 64 * 64);
+        // Sixteen lanes read sixteen consecutive positions: without bank conflicts also across the end of a row if the pitch is
+        // as many units as there are positions in a row, modulo 16.  High and low parts of a row side by side leave little room
+        // unused then; where they would leave much, they go to planes of their own.
+        c.pitch = 2 * c.Wl + ((g.OW * c.lstep - 2 * c.Wl) % 16 + 16) % 16;
+        c.part = c.Wl;
+        c.octet = (int)(n_rows * c.pitch + over);
+        if (g.OW == 1 || c.pitch * 8 > c.Wl * 19) {
+            c.pitch = c.Wl;
+            c.part = (int)(n_rows * c.pitch + over);
+            c.octet = 2 * c.part;
+        }
+        const int taps = c.Rr * c.Sr, octets = ceil_div(c.c_virtual, 8);
+        for (int g8 = 1; g8 <= std::min(octets, 32); ++g8) {
+            c.g8 = g8;
+            c.nblk = ceil_div(octets, g8);
+            const int64_t lds = std::max<int64_t>((int64_t)g8 * c.octet * 16 + 8 * c.plane, 4 * SCONV_MC_STORE_BYTES(mt, c.nt_max)) + 16;
+            if (lds > 80 * 1024 - 256 || (int64_t)g8 * taps * 2 > 0xffff) break; // two workgroups on a CU
+            c.lds_bytes = (int)lds;
+            auto steps_of = [&](int o) { return std::max<double>(ceil_div(taps * o, 8), taps * o * slots / 8 + 0.5); };
+            const double steps = (c.nblk - 1) * steps_of(g8) + steps_of(octets - (c.nblk - 1) * g8);
+            const double units = steps + 1.0 * c.nblk;        // a block's barriers and first reads weigh about a step
+            if (best_units < 0 || units < best_units) {
+                best_units = units;
+                steps_total = steps;
+                rows_at[0] = (double)rows_of(32 * pos_waves);
+                rows_at[1] = (double)rows_of(64 * pos_waves);
+                t = c;
+            }
+        }
+    }
+    if (best_units < 0) return false;
+    t.mt = mt;
+    t.wr = wr;
+    t.n_units = ceil_div(g.Kg, 16 * mt * wr) * wr;
+    t.wexp = 0;
+    t.stream_bytes = 0;
+    t.us = 0;
+    const double P = (double)N * g.OH * g.OW, out_bytes = 4.0 * P * d.K;
+    // (fitted to 60 layers of all shapes, 11-500 us: 9 % off)
+    const bool wide = t.cstep == 1 && (d.W >= 4 ? t.Wl >= d.W + d.pad : t.Wl == 1 && g.OH % 4 == 0);
+    const int nt_most = flushed || avg_row_nnz < SCONV_MC_ROW ? 2 : t.nt_max;
+    for (int nt = 2; nt <= nt_most; nt += 2)
+        for (int splits : {1, 2, 3, 4, 6, 8, 12, 16}) {
+            if (splits > t.nblk || ceil_div(t.nblk, ceil_div(t.nblk, splits)) != splits) continue;
+            if (splits > 1 && out_bytes * splits > SCONV_NOALLOC_SCRATCH_BYTES) continue;
+            const int blocks = ceil_div(t.nblk, splits), positions = 16 * nt * pos_waves;
+            const double wgs = std::ceil(P / positions) * (t.n_units / wr) * d.groups * splits, per_cu = wgs / 256.0;
+            const double steps = (double)blocks / t.nblk * steps_total * mt * nt, stored = 16.0 * mt * wr * positions * 4 / 6900.0;
+            const double cells = blocks * rows_at[nt / 2 - 1] * t.Wl * std::min(t.g8, ceil_div(t.c_virtual, 8));
+            const double stage = 0.66 * blocks + cells * (wide ? 0.00086 : 0.0018);
+            const double two = 3.3 + stage + steps * (nt == 4 ? 0.080 : 0.092) + stored;     // workgroups on a CU
+            const double one = 3.3 + 1.4 * stage + steps * 0.056 + 0.3 * stored;
+            double us = 3.8;
+            if (per_cu <= 1) us += one;
+            else if (per_cu <= 2) us += two;
+            else us += two * (per_cu > 4 ? 1 + 0.98 * (per_cu / 2 - 1) : 1 + 1.07 * (std::ceil(per_cu) / 2 - 1));
+            if (splits > 1) us += 2.0 + splits * (out_bytes / 1.7e6);
+            if (t.us == 0 || us < t.us) {
+                t.us = us;
+                t.nt = nt;
+                t.splits = splits;
+            }
+        }
+    return true;
+}
+
+static uint16_t to_f16(float v) // round to nearest even; |v| below 65520, denormals carried
+{
+    uint32_t u;
+    std::memcpy(&u, &v, 4);
+    const uint16_t sign = (uint16_t)(u >> 16 & 0x8000u);
+    u &= 0x7fffffffu;
+    if (u < 0x38800000u) { // below 2^-14: adding 2^-1 leaves the value's multiple of 2^-24 in the low bits
+        float m;
+        std::memcpy(&m, &u, 4);
+        m += 0.5f;
+        std::memcpy(&u, &m, 4);
+        return (uint16_t)(sign | (uint16_t)(u - 0x3f000000u));
+    }
+    u += 0xfffu + (u >> 13 & 1u);
+    return (uint16_t)(sign | (uint16_t)((u >> 13) - (112u << 10)));
+}
+
+static float from_f16(uint16_t b)
+{
+    uint32_t u = (uint32_t)(b & 0x7fffu) << 13;
+    float v;
+    std::memcpy(&v, &u, 4);
+    v *= 0x1p112f;
+    return b & 0x8000u ? -v : v;
+}
+
+// Which of four channels a row's nth use of them takes (two at most, in order; the places of what is not real only differ).
+struct Pick {
+    uint8_t at[2], real[2], places;
+};
+static const struct Picks {
+    Pick pick[2][16];
+    uint8_t uses[256]; // of an octet by a row that has these of its channels
+    Picks()
+    {
+        for (int both = 0; both < 256; ++both) {
+            const int most = std::max(__builtin_popcount(both & 15), __builtin_popcount(both >> 4));
+            uses[both] = (uint8_t)((most + 1) / 2);
+        }
+        for (int nth = 0; nth < 2; ++nth)
+            for (int four = 0; four < 16; ++four) {
+                Pick &p = pick[nth][four];
+                int ch[4], n = 0;
+                for (int z = 0; z < 4; ++z)
+                    if (four >> z & 1) ch[n++] = z;
+                p = {{0, 1}, {0, 0}, 0};
+                const int left = std::min(2, n - 2 * nth);
+                if (left == 2) {
+                    p = {{(uint8_t)ch[2 * nth], (uint8_t)ch[2 * nth + 1]}, {1, 1}, 0};
+                } else if (left == 1) {
+                    const int z = ch[2 * nth];
+                    p = z == 3 ? Pick{{0, 3}, {0, 1}, 0} : Pick{{(uint8_t)z, 3}, {1, 0}, 0};
+                }
+                p.places = (uint8_t)(p.at[0] | p.at[1] << 2);
+            }
+    }
+} kPicks;
+
+int pack_flat_mc(const sconv_desc &layer, const Canonical &c, FlatMcTiling &t, PackedFlatMc &out)
+{
+    const sconv_desc &d = layer;
+    const Geometry g = geometry(d);
+    const int s = t.phased ? d.stride : 1, taps = t.Rr * t.Sr, octets = ceil_div(t.c_virtual, 8), rows = 16 * t.mt;
+    const int slots = octets * taps; // block after block, tap after tap, octet after octet
+    const size_t rec = SCONV_MC_RECORD(t.mt);
+    const int meta = (t.mt + 1) / 2 * 2 + 2; // 16-bit words a lane has behind the weights
+    float most = 0;
+    for (float v : c.val) most = std::max(most, std::fabs(v));
+    int e = 0;
+    std::frexp(most, &e);
+    t.wexp = most > 0 ? 14 - e : 0;
+    const float scale = std::ldexp(1.f, t.wexp);
+    std::vector<int32_t> col_slot((size_t)g.Cg * d.R * d.S); // slot * 8 + channel of the octet
+    std::vector<int32_t> slot_off(slots), block_first(t.nblk + 1);
+    for (int b = 0; b <= t.nblk; ++b) block_first[b] = std::min(b * t.g8, octets) * taps;
+    for (int b = 0; b < t.nblk; ++b) {
+        const int o8 = std::min(t.g8, octets - b * t.g8);
+        for (int tap = 0; tap < taps; ++tap)
+            for (int ol = 0; ol < o8; ++ol)
+                slot_off[block_first[b] + tap * o8 + ol] = ol * t.octet + (tap / t.Sr) * t.pitch + tap % t.Sr;
+    }
+    for (size_t col = 0; col < col_slot.size(); ++col) {
+        const int fs = (int)(col % d.S), fr = (int)(col / d.S % d.R), cl = (int)(col / ((size_t)d.R * d.S));
+        const int cv = t.phased ? ((fr % s) * s + fs % s) * g.Cg + cl : cl;
+        const int oct = cv / 8, b = oct / t.g8, o8 = std::min(t.g8, octets - b * t.g8);
+        const int tap = (fr / s) * t.Sr + fs / s;
+        col_slot[col] = (block_first[b] + tap * o8 + oct - b * t.g8) * 8 + cv % 8;
+    }
+    out = PackedFlatMc();
+    out.seg.assign((size_t)d.groups * t.n_units * t.nblk * 2, 0);
+    out.row_of.assign((size_t)d.groups * t.n_units * rows, -1);
+    // rows of like length together: tiles of short rows need fewer octets twice, or at all
+    std::vector<int32_t> order(d.K);
+    std::iota(order.begin(), order.end(), 0);
+    for (int grp = 0; grp < d.groups; ++grp)
+        std::stable_sort(order.begin() + grp * g.Kg, order.begin() + (grp + 1) * g.Kg,
+                         [&](int a, int b) { return c.rowptr[a + 1] - c.rowptr[a] > c.rowptr[b + 1] - c.rowptr[b]; });
+    struct Item {
+        int32_t slot;
+        int tiles, nth;
+    };
+    // one wave's filters: its records, numbered from 0 until all are there
+    auto pack_unit = [&](int unit, std::vector<uint8_t> &stream) -> int {
+        std::vector<uint8_t> mask((size_t)rows * slots);   // channels of an octet that a row has
+        std::vector<float> val((size_t)slots * 8);         // one row's weights
+        std::vector<uint8_t> need((size_t)t.mt * slots);   // how often a tile needs an octet: 0, 1, 2
+        std::vector<uint8_t> shared(slots);
+        std::vector<int32_t> where((size_t)(t.mt + 1) * slots * 2); // record * 8 + octet of an octet's nth use: shared, then by tile
+        std::vector<Item> items[5];                        // by the number of tiles
+        stream.reserve((size_t)(slots / 8 + t.nblk) * rec * 5 / 4);
+        int64_t n_rec = 0;
+        const int grp = unit / t.n_units, r0 = (unit - grp * t.n_units) * rows, n_rows = std::max(0, std::min(rows, g.Kg - r0));
+        int32_t *row_of = &out.row_of[(size_t)unit * rows];
+        for (int r = 0; r < n_rows; ++r) {
+            const int k = row_of[r] = order[grp * g.Kg + r0 + r];
+            uint8_t *m = &mask[(size_t)r * slots], *n = &need[(size_t)(r / 16) * slots];
+            for (int j = c.rowptr[k]; j < c.rowptr[k + 1]; ++j) {
+                const int at = col_slot[c.colidx[j]];
+                m[at / 8] |= (uint8_t)(1u << (at & 7));
+            }
+            for (int i = 0; i < slots; ++i) n[i] = std::max(n[i], kPicks.uses[m[i]]);
+        }
+        for (int b = 0; b < t.nblk; ++b) {
+            const int lo = block_first[b], hi = block_first[b + 1];
+            for (auto &v : items) v.clear();
+            int n_items = 0;
+            for (int i = lo; i < hi; ++i) {
+                shared[i] = 0;
+                for (int nth = 1; nth >= 0; --nth) {
+                    int tiles = 0;
+                    for (int m = 0; m < t.mt; ++m) tiles += need[(size_t)m * slots + i] > nth;
+                    if (tiles) items[tiles].push_back({i, tiles, nth});
+                    n_items += tiles > 0;
+                    shared[i] += tiles > 0;
+                }
+            }
+            // what single tiles need goes to steps that every tile has its own octets of, as much as these hold
+            auto nth_item = [&](int i) -> const Item & {
+                int z = 1;
+                while (i >= (int)items[z].size()) i -= (int)items[z++].size();
+                return items[z][i];
+            };
+            int best_p = 0, best_take = 0;
+            double best = ceil_div(n_items, 8);
+            for (int p = 1; p <= 4 && p < best; ++p) {
+                int load[4] = {0, 0, 0, 0}, take = 0;
+                for (; take < n_items; ++take) {
+                    const Item &it = nth_item(take);
+                    bool room = it.tiles < t.mt;
+                    for (int m = 0; m < t.mt; ++m) room = room && (need[(size_t)m * slots + it.slot] <= it.nth || load[m] < 8 * p);
+                    if (!room) break;
+                    for (int m = 0; m < t.mt; ++m) load[m] += need[(size_t)m * slots + it.slot] > it.nth;
+                }
+                const double cost = ceil_div(n_items - take, 8) + SCONV_MC_PRIVATE_COST * p;
+                if (cost < best) {
+                    best = cost;
+                    best_p = p;
+                    best_take = take;
+                }
+            }
+            for (int i = 0; i < best_take; ++i) --shared[nth_item(i).slot];
+            const int n_shared = ceil_div(n_items - best_take, 8);
+            int32_t *seg = &out.seg[((size_t)unit * t.nblk + b) * 2];
+            seg[0] = (int32_t)n_rec;
+            seg[1] = n_shared | best_p << 16;
+            int pos = 0, load[4] = {0, 0, 0, 0};
+            for (int i = lo; i < hi; ++i) {
+                for (int nth = 0; nth < shared[i]; ++nth) where[(size_t)i * 2 + nth] = (int32_t)(n_rec * 8 + pos++);
+                for (int m = 0; m < t.mt; ++m)
+                    for (int nth = shared[i]; nth < need[(size_t)m * slots + i]; ++nth)
+                        where[((size_t)(m + 1) * slots + i) * 2 + nth] = (int32_t)((n_rec + n_shared) * 8 + load[m]++);
+            }
+            bool fits = pos <= 8 * n_shared;
+            for (int m = 0; m < t.mt; ++m) fits = fits && load[m] <= 8 * best_p;
+            if (!fits) return SCONV_ERR_PLAN;
+            n_rec += n_shared + best_p;
+            if (n_rec >= 0x7fffffff / 8) return SCONV_ERR_RANGE;
+            // rows without weights: places 0 and 1.  Which lanes read an octet: the first four of a step are a quarter's first
+            // ones, the others its second ones
+            stream.resize((size_t)n_rec * rec);
+            for (int i = seg[0]; i < (int)n_rec; ++i) {
+                uint16_t *lanes = reinterpret_cast<uint16_t *>(&stream[(size_t)i * rec] + t.mt * 2048);
+                for (int z = 0; z < 64; ++z)
+                    for (int q = 0; q < meta - 2; ++q) lanes[z * meta + q] = 0x4444;
+            }
+            for (int i = lo; i < hi; ++i)
+                for (int m = -1; m < t.mt; ++m)
+                    for (int nth = m < 0 ? 0 : shared[i]; nth < (m < 0 ? shared[i] : need[(size_t)m * slots + i]); ++nth) {
+                        const int at = where[((size_t)(m + 1) * slots + i) * 2 + nth], o = at % 8;
+                        uint16_t *lanes = reinterpret_cast<uint16_t *>(&stream[(size_t)(at / 8) * rec] + t.mt * 2048);
+                        for (int l = m < 0 ? 0 : m; l < 16; l += m < 0 ? 1 : 4) lanes[((o & 3) * 16 + l) * meta + meta - 2 + (o >> 2)] = (uint16_t)slot_off[i];
+                    }
+        }
+        for (int r = 0; r < n_rows; ++r) {
+            const int k = row_of[r], m = r / 16, row = r % 16;
+            for (int j = c.rowptr[k]; j < c.rowptr[k + 1]; ++j) val[col_slot[c.colidx[j]]] = c.val[j];
+            for (int i = 0; i < slots; ++i) {
+                const unsigned both = mask[(size_t)r * slots + i];
+                if (!both) continue;
+                const float *v = &val[(size_t)i * 8];
+                for (int nth = 0; nth < kPicks.uses[both]; ++nth) {
+                    // (nth uses of a row are nth uses of its tile: the shared ones come first)
+                    const int at = where[((size_t)(nth < shared[i] ? 0 : m + 1) * slots + i) * 2 + nth], o = at % 8;
+                    uint8_t *rp = &stream[(size_t)(at / 8) * rec];
+                    uint16_t *w = reinterpret_cast<uint16_t *>(rp + m * 2048) + ((o / 2) * 16 + row) * 8 + (o % 2) * 4;
+                    const Pick &p0 = kPicks.pick[nth][both & 15], &p1 = kPicks.pick[nth][both >> 4];
+                    rp[t.mt * 2048 + (((o / 2) * 16 + row) * meta + m) * 2 + o % 2] = (uint8_t)(p0.places | p1.places << 4);
+                    auto put = [&](int e, int channel) {
+                        const float x = v[channel] * scale;
+                        const uint16_t h = x == 0.f ? 0x8000 : to_f16(x);
+                        w[e] = h;
+                        w[512 + e] = to_f16((x - from_f16(h)) * 2048.f);
+                    };
+                    for (int e = 0; e < 2; ++e) {
+                        if (p0.real[e]) put(e, p0.at[e]);
+                        if (p1.real[e]) put(2 + e, 4 + p1.at[e]);
+                    }
+                }
+            }
+        }
+        return SCONV_OK;
+    };
+    // (the units are independent; small layers are not worth a thread)
+    const int n_all = d.groups * t.n_units;
+    std::vector<std::vector<uint8_t>> streams(n_all);
+    std::vector<int> status(n_all, SCONV_OK);
+    std::atomic<int> next(0);
+    auto work = [&]() {
+        for (int u = next++; u < n_all; u = next++) {
+            try {
+                status[u] = pack_unit(u, streams[u]);
+            } catch (const std::bad_alloc &) {
+                status[u] = SCONV_ERR_NOMEM;
+            }
+        }
+    };
+    std::vector<std::thread> threads;
+    try {
+        for (int i = 1; c.val.size() > 16384 && i < std::min(n_all, 8); ++i) threads.emplace_back(work);
+    } catch (const std::exception &) { // (no more threads: the ones there are do the work)
+    }
+    work();
+    for (std::thread &th : threads) th.join();
+    int64_t n_rec = 0;
+    for (int u = 0; u < n_all; ++u) {
+        if (status[u]) return status[u];
+        for (int b = 0; b < t.nblk; ++b) out.seg[((size_t)u * t.nblk + b) * 2] += (int32_t)n_rec;
+        n_rec += (int64_t)(streams[u].size() / rec);
+        if (n_rec >= 0x7fffffff / 8) return SCONV_ERR_RANGE;
+    }
+    out.stream.reserve((size_t)(n_rec + 1) * rec);
+    for (const auto &v : streams) out.stream.insert(out.stream.end(), v.begin(), v.end());
+    out.stream.resize(out.stream.size() + rec); // the kernel reads one record ahead
+    t.stream_bytes = (int64_t)out.stream.size();
+    if (t.phased)
+        for (int cv = 0; cv < octets * 8; ++cv) {
+            const int ph = cv / g.Cg, cl = cv % g.Cg;
+            const bool there = cv < t.c_virtual && ph / s < d.R && ph % s < d.S;
+            out.choff.push_back(there ? ((cl * d.H + ph / s) * d.W + ph % s) * 4 : SCONV_MFMA_NO_CHANNEL);
+        }
+    else
+        out.choff.push_back(0);
     return SCONV_OK;
 }
 

@@ -67,6 +67,7 @@ struct LdsTiling {
     int strip_rows;     // strip layout: rows of the block of positions one chunk covers (64 / strip), else 0
     int out_pos;        // floats from one output position to the next in the caller's layout (1 for NCHW)
     double us;          // what the cost model expects a launch to take (flat-stream tilings the search chose, else 0)
+    const struct FlatMcTiling *mc = nullptr; // set: the launch runs on the matrix cores, with this tiling and p.splits
 };
 
 struct PackedLds {
@@ -173,6 +174,53 @@ sconv_desc mfma_desc(const sconv_desc &d);
 bool choose_mfma(const sconv_desc &d, int N, MfmaTiling &t);
 int pack_mfma(const sconv_desc &d, const Canonical &c, const MfmaTiling &t, PackedMfma &out);
 
+// Flat streams on the matrix cores (sconv_flat_mc.hip).  The packing depends only on the layer: nt and splits may change from
+// call to call.
+struct FlatMcTiling {
+    bool phased;             // as in MfmaTiling
+    int mt = 0, nt = 0;      // a wave takes 16 * mt filters and 16 * nt positions
+    int wr;                  // waves along the filters: 2 (then 2 along the positions) or 1 (then 4)
+    int nt_max;              // 2 where 64 positions a wave are too many for LDS
+    int splits;              // workgroups along the channel blocks (partial sums, added by a launch of their own)
+    int g8, nblk;            // channel octets staged per block, blocks
+    int c_virtual;           // channels of a group the kernel sees
+    int cstep, lstep;        // input elements per cell, cells per output position
+    int Rr, Sr, Wl;          // filter in cells, cells per staged row
+    int plane;               // cells that are staged at most, a multiple of 64
+    int pitch, part, octet;  // 16-byte units of LDS from one row of cells, high to low part, one channel octet to the next
+    int n_units;             // waves' worth of filters per group, a multiple of wr
+    int lds_bytes;
+    int wexp;                // weights are packed times 2^wexp
+    int64_t stream_bytes;
+    bool for_dense;          // the call would be the three-part kernel's
+    double us;
+};
+// A record of a wave's stream: one matrix step.  [tile][high, low part][lane] 8 fp16 weights (the two a row keeps of each four
+// channels of two octets), then per lane the weights' places (2 bits each, 16 bits a tile, 32 a pair of tiles) and the LDS
+// address / 16 of the two octets it reads, 16 bits each (lane i of four those of tile i in steps that every tile has its own of).
+#define SCONV_MC_RECORD(MT) ((MT) * 2048 + 64 * (((MT) + 1) / 2 * 4 + 4))
+// What a wave's results take in LDS on their way out.
+#define SCONV_MC_STORE_BYTES(MT, NT) (16 * (MT) * (16 * (NT) + 4) * 4)
+struct PackedFlatMc {
+    std::vector<uint8_t> stream;
+    std::vector<int32_t> seg;     // [group][unit][block]: first record, shared steps | private steps << 16
+    std::vector<int32_t> row_of;  // [group][unit][16 * mt]
+    std::vector<int32_t> choff;   // phased only: per channel of whole octets
+};
+// A step that every tile has its own octets of against one that all share: four times the LDS reads.
+#define SCONV_MC_PRIVATE_COST 1.5
+#define SCONV_MC_ROW 108         // nonzeros a row has on average for sums that are not flushed, for sums that are
+#define SCONV_MC_FLUSHED_ROW 72
+#define SCONV_MC_ROW_SPLIT 80     // ... per part of a flat-stream tiling that splits the channels (flushed sums then)
+#define SCONV_MC_LONG_ROW 800    // ... for flushed sums in place of the three-part kernel's
+#define SCONV_MC_LONG_ROW_SPLIT 1100 // ... per part where that kernel splits the channels
+// From this density on most octets are needed twice.
+#define SCONV_MC_DENSE 0.35
+bool flat_mc_weights_ok(const sconv_desc &d, const Canonical &c);
+// Tiling and time of the layer on the matrix cores; flushed: sums as exact as the three-part kernel's.  False if it cannot take it.
+bool choose_flat_mc(const sconv_desc &d, const Canonical &c, int N, bool flushed, FlatMcTiling &t);
+int pack_flat_mc(const sconv_desc &d, const Canonical &c, FlatMcTiling &t, PackedFlatMc &out);
+
 int validate_desc(const sconv_desc &d);
 // rowptr starts at 0 and never falls, columns inside [0, Cg*R*S) and strictly ascending in each row
 int validate_csr(const sconv_desc &d, const int32_t *rowptr, const int32_t *colidx);
@@ -278,6 +326,8 @@ struct Lds2Layout {
     int64_t out_tile, out_band, out_row, out_img, out_pos;
 };
 Lds2Layout nchw_layout(const sconv_desc &d, const LdsTiling &t);
+int launch_flat_mc(const sconv_desc &d, const FlatMcTiling &t, const DeviceLds &dev, const float *in, float *out, int N, const Epilogue &ep,
+                   int64_t split_stride, void *stream, int *hip_err);
 // With t.p.splits > 1 `out` is a workspace of splits * split_stride floats that receives each part's partial
 // results in the output's layout, and launch_reduce adds them up (and applies the epilogue) afterwards.
 int launch_lds2(const sconv_desc &d, const LdsTiling &t, const DeviceLds &dev, const Lds2Layout &lay, const float *in,

@@ -1,0 +1,194 @@
+"""The flat streams on the matrix cores: convolutions and fully connected layers against the fp64 oracles."""
+import numpy as np
+import pytest
+import torch
+
+from paper_1608_01409_amd import binding as B
+from paper_1608_01409_amd import workloads as wl
+
+pytestmark = pytest.mark.gpu
+TOL = 1e-5     # of sum|w*x| per output, as in test_gpu_parity.py
+
+
+def make(layer, N, density, seed=1, signed=False):
+    rng = np.random.default_rng(seed)
+    x = rng.standard_normal((N, layer.C, layer.H, layer.W)).astype(np.float32)
+    if not signed:
+        x = np.maximum(x, 0)
+    w = (rng.standard_normal((layer.K, layer.Cg, layer.R, layer.S)) * 0.01).astype(np.float32)
+    w[rng.random(w.shape) >= density] = 0
+    return x, w
+
+
+def on_matrix_cores(route):
+    """As flat streams, or in place of the three-part kernel, whose shapes end at (2, 2)."""
+    return route["kernel"] == "flat" and route["nt"] > 1 or route["kernel"] == "mfma" and route["mt"] > 2
+
+
+def check(oracle, layer, N, x, w, bias=None, relu=False):
+    h = B.sconv_create_csr(layer, w)
+    route = B.sconv_route_of(h, N)
+    assert on_matrix_cores(route), route
+    print(f"[gpu-case] {layer.name} C{layer.C} {layer.H}x{layer.W} K{layer.K} N={N} {route}", flush=True)
+    out = torch.full((N, layer.K, layer.OH, layer.OW), float("nan"), device="cuda")
+    xd = torch.from_numpy(x).cuda()
+    if bias is None:
+        B.sconv_forward(h, xd, out)
+    else:
+        B.sconv_forward_fused(h, xd, torch.from_numpy(bias).cuda(), relu, out)
+    got = out.cpu().numpy()
+    ref, ab, _ = oracle.sparse_conv(layer, w, x)
+    if bias is not None:
+        ref, ab = oracle.bias_relu(ref, ab, bias, relu)
+    err = np.abs(got.astype(np.float64) - ref)
+    bad = ~(err <= TOL * ab + 2.0 ** -149)     # (2^-149: the spacing of the smallest results)
+    assert not bad.any(), (route, int(bad.sum()), float(np.nanmax(err / np.maximum(ab, 1e-300))), np.argwhere(bad)[:4])
+    return got, ref, route
+
+
+FIELDS = ("C", "H", "W", "K", "R", "S", "stride", "pad", "groups")
+
+
+def layer_of(dims):
+    return wl.small_layer("mc", **dict(zip(FIELDS, dims)))
+
+
+# C, H, W, K, R, S, stride, pad, groups, N, density
+SHAPES = [
+    (256, 13, 13, 384, 3, 3, 1, 1, 1, 70, 0.10),    # several blocks, filters and positions of whole and part workgroups
+    (96, 27, 27, 256, 5, 5, 1, 2, 2, 41, 0.10),
+    (384, 13, 13, 384, 3, 3, 1, 1, 2, 70, 0.15),
+    (192, 28, 28, 128, 3, 3, 1, 1, 1, 33, 0.12),
+    (3, 99, 99, 96, 11, 11, 4, 0, 1, 100, 0.30),    # phases of a strided layer, a cell per lane
+    (160, 27, 27, 80, 3, 3, 2, 1, 1, 160, 0.10),    # stride on the cells, odd width
+    (96, 28, 28, 80, 3, 3, 2, 1, 1, 64, 0.10),
+    (99, 30, 30, 40, 3, 3, 1, 1, 1, 64, 0.20),      # channels that do not fill an octet, 40 filters
+    (60, 20, 20, 250, 3, 3, 1, 1, 1, 32, 0.20),
+    (99, 20, 20, 150, 3, 3, 1, 1, 1, 32, 0.13),
+    (130, 21, 5, 96, 3, 3, 1, 1, 1, 256, 0.15),     # a row of five, the last four of it shifted back
+    (300, 7, 7, 150, 3, 3, 1, 1, 1, 256, 0.10),
+    (64, 18, 18, 96, 3, 3, 1, 3, 1, 64, 0.20),      # padding as wide as the filter
+    (400, 28, 28, 64, 1, 1, 1, 0, 1, 100, 0.30),    # 1x1: positions in fours
+    (500, 27, 27, 128, 1, 1, 1, 0, 1, 64, 0.22),    # 1x1: images that no four divides
+    (384, 13, 13, 384, 3, 3, 1, 1, 2, 64, 0.50),    # in place of the three-part kernel
+    (180, 20, 20, 90, 3, 3, 1, 1, 1, 64, 0.60),
+    (472, 12, 12, 356, 3, 3, 1, 1, 1, 34, 0.94),    # channels split over workgroups
+]
+
+
+@pytest.mark.parametrize("shape", SHAPES)
+def test_layers_against_the_oracle(oracle, shape):
+    *dims, N, density = shape
+    layer = layer_of(dims)
+    x, w = make(layer, N, density)
+    bias = (np.random.default_rng(5).standard_normal(layer.K) * 0.05).astype(np.float32)
+    w[1] = 0                                        # an empty row
+    check(oracle, layer, N, x, w)
+    check(oracle, layer, N, x, w, bias, True)
+    check(oracle, layer, N, x, w, bias, False)
+
+
+MIXED = [(99, 20, 20, 150, 3, 3, 1, 1, 1, 32, 0.13), (256, 13, 13, 384, 3, 3, 1, 1, 1, 70, 0.10), (472, 12, 12, 356, 3, 3, 1, 1, 1, 34, 0.94)]
+
+
+@pytest.mark.parametrize("shape", MIXED)
+@pytest.mark.parametrize("what", ["tiny", "huge", "images", "one", "spread", "late", "zero", "denormal"])
+def test_activations_of_every_magnitude(oracle, shape, what):
+    """Every output within the tolerance of its own sum of magnitudes, whatever else is in the batch."""
+    *dims, N, density = shape
+    layer = layer_of(dims)
+    x, w = make(layer, N, density)
+    rng = np.random.default_rng(7)
+    if what == "tiny":
+        x *= np.float32(1e-33)
+    elif what == "huge":
+        x *= np.float32(1e30)
+    elif what == "images":                          # image by image 1e-30 ... 1e+30
+        x *= (10.0 ** np.linspace(-30, 30, N)).astype(np.float32)[:, None, None, None]
+    elif what == "one":                             # one value far above the others, and one below
+        x[N // 2, 3, 5, 5] = 1e25
+        x[0, 0, 0, 0] = 1e-25
+    elif what == "spread":
+        x *= (10.0 ** rng.uniform(-20, 20, x.shape)).astype(np.float32)
+    elif what == "late":                            # nothing in the channels that the scale is taken from
+        x[:, :layer.C - 4] = 0
+        x[:, layer.C - 2:] *= np.float32(1e15)
+    elif what == "zero":
+        x[:] = 0
+    else:
+        x *= np.float32(1e-39)
+    check(oracle, layer, N, x, w)
+
+
+@pytest.mark.parametrize("shape", MIXED)
+def test_infinities_meet_stored_weights_only(shape):
+    """Infinities, NaN and values near the largest: the outputs the direct kernel gives, stored zeros included."""
+    *dims, N, density = shape
+    layer = layer_of(dims)
+    x, w = make(layer, N, density, signed=True)
+    rng = np.random.default_rng(9)
+    for v in (np.inf, -np.inf, np.nan, 3e38, -3e38):
+        for _ in range(3):
+            x[rng.integers(N), rng.integers(layer.C), rng.integers(layer.H), rng.integers(layer.W)] = v
+    cols = layer.Cg * layer.R * layer.S
+    rowptr, colidx, values = [0], [], []
+    for k in range(layer.K):
+        (j,) = np.nonzero(w.reshape(layer.K, cols)[k])
+        v = w.reshape(layer.K, cols)[k][j].copy()
+        v[::50] = 0
+        colidx.extend(j), values.extend(v), rowptr.append(len(colidx))
+    bias = torch.from_numpy((rng.standard_normal(layer.K) * 0.05).astype(np.float32)).cuda()
+    xd = torch.from_numpy(x).cuda()
+    h = B.sconv_create_csr_from_arrays(layer, rowptr, colidx, values)
+    direct = B.sconv_create_csr_from_arrays(layer, rowptr, colidx, values, dict(kernel=2))
+    assert on_matrix_cores(B.sconv_route_of(h, N))
+    for b, relu in ((None, False), (bias, False), (bias, True)):
+        got = B.sconv_forward_fused(h, xd, b, relu).cpu().numpy()
+        want = B.sconv_forward_fused(direct, xd, b, relu).cpu().numpy()
+        assert np.array_equal(np.isnan(got), np.isnan(want)) and np.array_equal(np.isinf(got), np.isinf(want))
+        assert np.array_equal(np.sign(got[np.isinf(got)]), np.sign(want[np.isinf(want)]))
+        finite = np.isfinite(want)
+        largest = np.where(np.isfinite(x), np.abs(x), 0).max(axis=(1, 2, 3)).astype(np.float64)   # of an image
+        scale = np.abs(w).reshape(layer.K, -1).sum(1)[None, :, None, None] * largest[:, None, None, None]
+        assert np.all(np.abs(got[finite].astype(np.float64) - want[finite]) <= (np.broadcast_to(scale, want.shape)[finite] + 1) * TOL)
+
+
+def test_without_allocation_and_under_capture():
+    """sconv_forward_noalloc gives sconv_forward's bits, also replayed from a graph between other calls."""
+    *dims, N, density = MIXED[0]
+    layer = layer_of(dims)
+    x, w = make(layer, N, density)
+    h = B.sconv_create_csr(layer, w)
+    assert on_matrix_cores(B.sconv_route_of(h, N))
+    xd = torch.from_numpy(x).cuda()
+    want = B.sconv_forward(h, xd)
+    out = torch.full_like(want, float("nan"))
+    B.sconv_forward_noalloc(h, xd, out)
+    assert torch.equal(out, want)
+    s = torch.cuda.Stream()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=s):
+        B.sconv_forward_noalloc(h, xd, out, stream=torch.cuda.current_stream())
+    for i in range(3):
+        xd.mul_(1.0 + i)
+        want = B.sconv_forward(h, xd)
+        out.fill_(float("nan"))
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, want), i
+
+
+def test_short_rows_and_unfit_weights_stay_on_the_vector_units():
+    """Layers with rows of fewer than 16 nonzeros, or weights that lie too far apart, keep the chains."""
+    *dims, N, density = MIXED[0]
+    layer = layer_of(dims)
+    _, w = make(layer, 1, density)
+    assert on_matrix_cores(B.sconv_route_of(B.sconv_create_csr(layer, w), N))
+    for change in ("short", "small", "inf"):
+        v = w.copy()
+        if change == "short":
+            v[3] = 0
+            v[3, :15, 0, 0] = 1
+        else:
+            v[3, 0, 0, 0] = 1e-12 if change == "small" else np.inf
+        assert B.sconv_route_of(B.sconv_create_csr(layer, v), N)["nt"] == 1, change
