@@ -209,7 +209,7 @@ struct PackedFlatMc {
 };
 // A step that every tile has its own octets of against one that all share: four times the LDS reads.
 #define SCONV_MC_PRIVATE_COST 1.5
-#define SCONV_MC_ROW 108         // nonzeros a row has on average for sums that are not flushed, for sums that are
+#define SCONV_MC_ROW 105         // nonzeros a row has on average for sums that are not flushed, for sums that are
 #define SCONV_MC_FLUSHED_ROW 72
 #define SCONV_MC_ROW_SPLIT 80     // ... per part of a flat-stream tiling that splits the channels (flushed sums then)
 #define SCONV_MC_LONG_ROW 800    // ... for flushed sums in place of the three-part kernel's

@@ -26,7 +26,10 @@
 // channels.  A workgroup takes 32*MT filters and 128*NT positions and walks the channels in blocks of 8*g8.  The input
 // rows its positions touch are staged once per block, split on the way, as [channel octet][cell][part][8 channels]: 16
 // bytes are the 8 consecutive depths a lane feeds to an MFMA, whatever the tap, which only moves the cell; 48 bytes from
-// cell to cell spread a wave's reads over all LDS banks.  Weights are packed in fragment order and go from L2 straight to
+// cell to cell spread a wave's reads over all LDS banks.  Where four neighbouring cells are 16 consecutive bytes of the input a lane
+// loads four cells x 8 channels in 8 loads: the address unit takes 16 clocks a load instruction whatever its width (45 random
+// layers, 8-140 us: 1.064x, none slower by more than 1 %; two of them in flight at once cost the shapes with one accumulator
+// tile a third of their waves and were 5-7 % slower there).  Weights are packed in fragment order and go from L2 straight to
 // registers, one step ahead.  Two workgroups share a CU: one stages while the other multiplies.
 //
 // Measured: 13x13, 384 -> 384 in two groups, 3x3, batch 256, density 0.5: flat-stream kernel 530 us, here 250-264 us as the
@@ -44,6 +47,7 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef short s16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 using const_u32 = const __attribute__((address_space(4))) unsigned;
 using const_i32 = const __attribute__((address_space(4))) int;
@@ -78,7 +82,9 @@ struct MfmaArgs {
     long long out_img, out_row;
     int goff_mul;            // floats per unit of the CSR's offsets
     int short_rows;          // there are rows of 1 to SCONV_MFMA_SHORT_ROW - 1 nonzeros
-    FastDiv d_units, d_splits, d_mt, d_ohw, d_ow, d_wl, d_rowimg;
+    int wide;                // four neighbouring cells are 16 consecutive bytes of the input: 1 along rows, 2 along the positions
+    int quads;               // wide = 1: fours of cells per row, the last one back by what it would pass the row's end
+    FastDiv d_units, d_splits, d_mt, d_ohw, d_ow, d_wl, d_rowimg, d_quads;
 };
 
 // Division of an item number (below 320) by the number of pieces, at most 16: ceil(2^32 / pieces), 0 for 1.  (A table among the
@@ -176,6 +182,12 @@ static __device__ __forceinline__ Tile tile_of(const MfmaArgs &a, int bid)
 
 // again = false: a workgroup's sums, stored with the epilogue, or without it and true if some are not finite.
 // again = true: those sums once more (see above).
+// Four neighbouring cells x 8 channels on their way into LDS, and where they go (all ones: nowhere).
+struct Four {
+    f32x4 x[8];
+    unsigned at;
+};
+
 template <int MT, int NT, bool again>
 static __device__ __forceinline__ bool multiply_tile(const MfmaArgs &a, int bid, char *lds)
 {
@@ -211,18 +223,35 @@ static __device__ __forceinline__ bool multiply_tile(const MfmaArgs &a, int bid,
     const int n_off = 2 * (a.steps + a.steps_last);
     int *tbl = reinterpret_cast<int *>(lds + (size_t)a.g8 * a.plane * 48);
     unsigned *voff = reinterpret_cast<unsigned *>(tbl + n_off);
-    for (int cell = threadIdx.x; cell < a.plane; cell += 256) {
-        const int row = fdiv(cell, a.d_wl), col = cell - row * a.Wl;
+    // wide: per four of cells also where they go in LDS; what no four covers is padding and stays zero
+    uint2 *four = reinterpret_cast<uint2 *>(voff);
+    const bool wide = !again && a.wide;
+    const int n_fours = !wide ? 0 : a.wide == 1 ? fdiv(cells, a.d_wl) * a.quads : cells >> 2;
+    if (wide && a.wide == 1)
+        for (int i = threadIdx.x; i < a.g8 * a.plane * 3; i += 256) reinterpret_cast<uint4 *>(lds)[i] = make_uint4(0, 0, 0, 0);
+    for (int i = threadIdx.x; i < (wide ? n_fours : a.plane); i += 256) {
+        int row, col;            // of the cell, or of the first of four
+        if (wide && a.wide == 1) {
+            row = fdiv(i, a.d_quads);
+            col = a.pad + min((i - row * a.quads) * 4, a.W - 4);
+        } else {
+            const int cell = wide ? i * 4 : i;
+            row = fdiv(cell, a.d_wl);
+            col = cell - row * a.Wl;
+        }
         int n = 0, yp = y_first * a.lstep + row;
         if (row >= rows_first) {
-            const int i = fdiv(row - rows_first, a.d_rowimg);
-            n = 1 + i;
-            yp = row - rows_first - i * a.row_img;
+            const int img = fdiv(row - rows_first, a.d_rowimg);
+            n = 1 + img;
+            yp = row - rows_first - img * a.row_img;
         }
         const int iy = yp * a.cstep - a.pad, ix = col * a.cstep - a.pad;
-        const bool ok = cell < cells && iy >= 0 && iy < a.H && ix >= 0 && ix < a.W;
-        voff[cell] = ok ? (unsigned)(n * (int)a.in_img + iy * a.W + ix) * 4u : 0x80000000u;
+        const bool ok = (wide || i < cells) && iy >= 0 && iy < a.H && ix >= 0 && ix < a.W;
+        const unsigned from = ok ? (unsigned)(n * (int)a.in_img + iy * a.W + ix) * 4u : 0x80000000u;
+        if (wide) four[i] = make_uint2(from, ok ? (unsigned)(row * a.Wl + col) * 48u : 0xffffffffu);
+        else voff[i] = from;
     }
+    const FastDiv d_fours = {(unsigned)n_fours, n_fours > 1 ? 0xffffffffu / (unsigned)n_fours + 1u : 0u};
     for (int i = threadIdx.x; i < n_off; i += 256) tbl[i] = a.uoff[i];
     const int pieces = (cells + 63) >> 6;
     const FastDiv d_pieces = {(unsigned)pieces, ((const_u32 *)kPieceMagic)[pieces]};
@@ -320,52 +349,91 @@ static __device__ __forceinline__ bool multiply_tile(const MfmaArgs &a, int bid,
             else
                 multiply(A, B);
         };
-        for (int b = b_first; b < b_end; ++b) {
-            __syncthreads();
-            // items of 64 cells x 8 channels, dealt to the waves; the loads of four items are in flight together
-            const int c0 = b * a.g8 * 8, items = min(a.g8, (a.c_virtual - c0 + 7) >> 3) * pieces;
-            for (int i0 = wave; i0 < items; i0 += 4 * kBatch) {
-                float x[kBatch][8];
+        auto load_four = [&](Four &v, int b, int i0, int fours) INLINE {
+            const int i = min(i0 + lane, fours - 1), o = fdiv(i, d_fours);
+            const uint2 e = four[i - o * n_fours];
+            const int c = (b * a.g8 + o) * 8;
+            v.at = i0 + lane < fours && e.y != 0xffffffffu ? e.y + (unsigned)(o * a.plane) * 48u : 0xffffffffu;
+            const unsigned vo = i0 + lane < fours ? e.x + (unsigned)(c * a.in_ch4) : 0x80000000u;
 #pragma unroll
-                for (int j = 0; j < kBatch; ++j) {
-                    const int item = min(i0 + 4 * j, items - 1), o = fdiv(item, d_pieces), piece = item - o * pieces, c = c0 + o * 8;
-                    const unsigned vo = i0 + 4 * j < items ? voff[piece * 64 + lane] : 0x80000000u;
-                    int co[8];
-                    if (a.choff) {
+            for (int q = 0; q < 8; ++q)
+                v.x[q] = __builtin_bit_cast(f32x4, mfma_buffer_load4(rsrc, (int)(c + q < a.c_virtual ? vo + (unsigned)(q * a.in_ch4) : 0x80000000u), 0, 0));
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        auto store_four = [&](const Four &v) INLINE {
+            if (v.at != 0xffffffffu) {
 #pragma unroll
-                        for (int i = 0; i < 8; ++i) co[i] = choff[c + i];
-                    } else {
-#pragma unroll
-                        for (int i = 0; i < 8; ++i) co[i] = c + i < a.c_virtual ? (c + i) * a.in_ch4 : SCONV_MFMA_NO_CHANNEL;
-                    }
-#pragma unroll
-                    for (int i = 0; i < 8; ++i)        // a channel past the last one reads beyond the buffer's end: 0
-                        x[j][i] = mfma_buffer_load(rsrc, (int)(vo | ((unsigned)co[i] & 0x80000000u)), co[i] & 0x7fffffff, 0);
-                }
-                __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-                for (int j = 0; j < kBatch; ++j) {
-                    const int item = i0 + 4 * j, o = fdiv(item, d_pieces), piece = item - o * pieces;
-                    if (item >= items) break;
+                for (int e = 0; e < 4; ++e) {
+                    const float x[8] = {v.x[0][e], v.x[1][e], v.x[2][e], v.x[3][e], v.x[4][e], v.x[5][e], v.x[6][e], v.x[7][e]};
                     uint4 h, m, l;
-                    if constexpr (mode == kCount) {
-                        marks8(x[j], h, m);
-                        l = make_uint4(0, 0, 0, 0);
-                    } else {
-#pragma unroll
-                        for (int i = 0; mode != kAll && i < 8; ++i) {
-                            const float v = x[j][i];
-                            const bool inf = not_finite(v), large = too_large(v) && !inf;
-                            seen_inf |= inf;
-                            seen_large |= large;
-                            x[j][i] = mode == kLarge ? (large ? v * 0x1p-32f : 0.f) : (inf || large ? 0.f : v);
-                        }
-                        split8(x[j], h, m, l);
-                    }
-                    uint4 *dst = reinterpret_cast<uint4 *>(lds + ((size_t)o * a.plane + piece * 64 + lane) * 48);
+                    split8(x, h, m, l);
+                    uint4 *dst = reinterpret_cast<uint4 *>(lds + v.at + e * 48);
                     dst[0] = h;
                     dst[1] = m;
                     dst[2] = l;
+                }
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        if (wide) __syncthreads();           // the table is there
+        for (int b = b_first; b < b_end; ++b) {
+            if (mode == kAll && wide) {
+                // items of 64 lanes, four cells x 8 channels each, counted through the block's octets
+                const int fours = min(a.g8, (a.c_virtual - b * a.g8 * 8 + 7) >> 3) * n_fours;
+                Four v;
+                load_four(v, b, wave * 64, fours);
+                __syncthreads();             // the block before is used up
+                for (int i0 = wave * 64; i0 < fours; i0 += 256) {
+                    if (i0 >= 256) load_four(v, b, i0, fours);
+                    store_four(v);
+                }
+            } else {
+                __syncthreads();
+                // items of 64 cells x 8 channels, dealt to the waves; the loads of four items are in flight together
+                const int c0 = b * a.g8 * 8, items = min(a.g8, (a.c_virtual - c0 + 7) >> 3) * pieces;
+                for (int i0 = wave; i0 < items; i0 += 4 * kBatch) {
+                    float x[kBatch][8];
+#pragma unroll
+                    for (int j = 0; j < kBatch; ++j) {
+                        const int item = min(i0 + 4 * j, items - 1), o = fdiv(item, d_pieces), piece = item - o * pieces, c = c0 + o * 8;
+                        const unsigned vo = i0 + 4 * j < items ? voff[piece * 64 + lane] : 0x80000000u;
+                        int co[8];
+                        if (a.choff) {
+#pragma unroll
+                            for (int i = 0; i < 8; ++i) co[i] = choff[c + i];
+                        } else {
+#pragma unroll
+                            for (int i = 0; i < 8; ++i) co[i] = c + i < a.c_virtual ? (c + i) * a.in_ch4 : SCONV_MFMA_NO_CHANNEL;
+                        }
+#pragma unroll
+                        for (int i = 0; i < 8; ++i)        // a channel past the last one reads beyond the buffer's end: 0
+                            x[j][i] = mfma_buffer_load(rsrc, (int)(vo | ((unsigned)co[i] & 0x80000000u)), co[i] & 0x7fffffff, 0);
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                    for (int j = 0; j < kBatch; ++j) {
+                        const int item = i0 + 4 * j, o = fdiv(item, d_pieces), piece = item - o * pieces;
+                        if (item >= items) break;
+                        uint4 h, m, l;
+                        if constexpr (mode == kCount) {
+                            marks8(x[j], h, m);
+                            l = make_uint4(0, 0, 0, 0);
+                        } else {
+#pragma unroll
+                            for (int i = 0; mode != kAll && i < 8; ++i) {
+                                const float v = x[j][i];
+                                const bool inf = not_finite(v), large = too_large(v) && !inf;
+                                seen_inf |= inf;
+                                seen_large |= large;
+                                x[j][i] = mode == kLarge ? (large ? v * 0x1p-32f : 0.f) : (inf || large ? 0.f : v);
+                            }
+                            split8(x[j], h, m, l);
+                        }
+                        uint4 *dst = reinterpret_cast<uint4 *>(lds + ((size_t)o * a.plane + piece * 64 + lane) * 48);
+                        dst[0] = h;
+                        dst[1] = m;
+                        dst[2] = l;
+                    }
                 }
             }
             __syncthreads();
@@ -575,6 +643,11 @@ int launch_mfma(const sconv_desc &layer, const MfmaTiling &t, const DeviceMfma &
         a.in_ch4 = (int)(HW * 4); a.in_img = d.C * HW; a.in_group = g.Cg * HW; a.in_floats = (int64_t)N * d.C * HW;
         a.out_img = (int64_t)d.K * a.OHW; a.out_row = a.OHW; a.goff_mul = 1;
     }
+    a.quads = (d.W + 3) / 4;
+    // (a four's table entry has 8 bytes, a cell's 4: a row's fours need no more room)
+    a.wide = t.cstep == 1 && d.W >= 4 && t.Wl >= d.W + d.pad && 2 * a.quads <= t.Wl ? 1
+             : t.cstep == 1 && t.Wl == 1 && t.Rr == 1 && t.lstep == 1 && d.pad == 0 && (feature_major ? N : a.OHW) % 4 == 0 ? 2 : 0;
+    a.d_quads = make_fastdiv(a.quads, 1024);
     // what the kernel assumes
     if (t.plane > 1024 || t.total_steps > (1 << 18) || (int64_t)t.g8 * t.plane * 48 + 8 * (t.steps + t.steps_last) + 4 * t.plane > t.lds_bytes || t.g8 > 16 || t.nt > t.nt_max) return SCONV_ERR_PLAN;
     const int units = t.n_mtiles * d.groups * t.splits;
@@ -585,7 +658,7 @@ int launch_mfma(const sconv_desc &layer, const MfmaTiling &t, const DeviceMfma &
     a.d_mt = make_fastdiv(t.n_mtiles, units);
     a.d_ohw = make_fastdiv(a.OHW, P + bn);
     a.d_ow = make_fastdiv(a.OW, a.OHW);
-    a.d_wl = make_fastdiv(a.Wl, 1024);
+    a.d_wl = make_fastdiv(a.Wl, 1025);
     a.d_rowimg = make_fastdiv(a.row_img, 1024);
     hipStream_t s = static_cast<hipStream_t>(stream);
 #define X(M, NN) if (t.mt == M && t.nt == NN) return launch_mfma_inst<M, NN>(a, (int)grid, t.lds_bytes, s, hip_err);
