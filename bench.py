@@ -127,7 +127,7 @@ def main() -> int:
         tf = L["flops"] / (ms * 1e-3) / 1e12
         per_layer.append(dict(layer=L["name"], kernel_us=round(ms * 1e3, 2), tflops=round(tf, 3),
                               effective_tflops=round(L["dense_flops"] / (ms * 1e-3) / 1e12, 2),
-                              frac_of_fma_peak=round(tf / PEAK_FMA_TFLOPS, 4), nnz=L["nnz"], plan=L["plan"]))
+                              frac_of_fma_peak=round(tf / PEAK_FMA_TFLOPS, 4), nnz=L["nnz"], plan=L["plan"], route=L["route"]))
     # The target is per layer, so the headline fraction is the LOWEST of the four layers, not the one of the
     # longest-running (and most efficient) kernel; that one is listed beside it.
     low = min(range(len(layers)), key=lambda i: per_layer[i]["tflops"])
@@ -144,8 +144,11 @@ def main() -> int:
             traffic = None
 
     def kname(i):
+        r = layers[i]["route"]
+        if (r["kernel"] == "flat" and r["nt"] > 1) or (r["kernel"] == "mfma" and r["mt"] > 2):
+            return f"sconv_flat_mc_kernel on {layers[i]['name']}"    # on the matrix cores
         return dict(rows="sconv_lds_kernel", flat="sconv_lds2_kernel", flow="sconv_lds2_kernel").get(
-            layers[i]["route"]["kernel"], f"sconv_{layers[i]['route']['kernel']}_kernel") + f" on {layers[i]['name']}"
+            r["kernel"], f"sconv_{r['kernel']}_kernel") + f" on {layers[i]['name']}"
 
     roofline = dict(bound="alu", achieved=achieved, peak=PEAK_FMA_TFLOPS, unit="TFLOP/s",
                     frac=round(achieved / PEAK_FMA_TFLOPS, 4), traffic=traffic, traffic_source=traffic_source,

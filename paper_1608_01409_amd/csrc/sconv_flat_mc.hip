@@ -21,15 +21,16 @@
 //
 // A workgroup is four waves, 16 * mt filters x 16 * nt positions each, two along the filters or one; it walks the channels in
 // blocks staged as [octet][row][high, low part][cell] of 16-byte units.  The pitch of a row is the number of positions in an
-// output row modulo 16: sixteen lanes that run over the end of a row then still hit all banks (46 % of the LDS cycles were
-// conflicts with rows back to back).  Activations are loaded four neighbouring cells x 8 channels a lane: the address unit takes
+// output row modulo 16: sixteen lanes that run over the end of a row then still hit all banks; an octet is a multiple of 16 units,
+// since lanes of two quarters are served together (conflicts 46 % of the LDS cycles with rows back to back, 25 % now: what is
+// left are steps whose octets lie at different taps).  Activations are loaded four neighbouring cells x 8 channels a lane: the address unit takes
 // 16 clocks an instruction, and one cell a lane kept it busy for 5 of the 8 us that staging a block took.  Weights go from L2 to
 // registers, a step ahead.  Results leave through LDS, four positions a lane: 16 positions x 4 rows an instruction took 19 us
 // for what takes 5.5.
 //
-// Measured, vector kernel -> here: 13x13, 256 -> 384, 3x3, batch 256, density 0.1: 160 -> 149 us; 28x28, 192 -> 128, 3x3, batch
-// 64, density 0.2: 120 -> 74; 227x227, 3 -> 96, 11x11 stride 4, batch 64, density 0.3: 111 -> 96; three-part kernel -> here: 13x13,
-// 384 -> 384 in two groups, batch 256, density 0.5: 256 -> 206.  60 random layers: 0.7-1.85x, 1.11x as the model chooses.
+// Measured, vector kernel -> here: 13x13, 256 -> 384, 3x3, batch 256, density 0.1: 162 -> 148 us; 28x28, 192 -> 128, 3x3, batch
+// 64, density 0.2: 120 -> 73; 227x227, 3 -> 96, 11x11 stride 4, batch 64, density 0.3: 110 -> 91; three-part kernel -> here: 13x13,
+// 384 -> 384 in two groups, batch 256, density 0.5: 258 -> 208.  60 random layers: 0.7-1.85x, 1.11x as the model chooses.
 // The first: of a workgroup's 78 us 47 are shared steps (13 of them, 1.1 us for two workgroups on a CU: 1960 clocks for 1536 of
 // matrix instructions at 1.65 GHz), 9 private steps, 16 staging, 4 before the first load, 6 the stores.  Without activations'
 // bits (all zero) it takes 133 us.  Two workgroups out of step by half a block: no faster; one workgroup of 512 registers a lane

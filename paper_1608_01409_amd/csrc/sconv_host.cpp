@@ -1334,10 +1334,12 @@ bool choose_flat_mc(const sconv_desc &layer, const Canonical &csr, int N, bool f
             c.part = (int)(n_rows * c.pitch + over);
             c.octet = 2 * c.part;
         }
+        c.octet = (c.octet + 15) / 16 * 16; // lanes of two quarters are served together: their octets at one tap must not collide
         const int taps = c.Rr * c.Sr, octets = ceil_div(c.c_virtual, 8);
         for (int g8 = 1; g8 <= std::min(octets, 32); ++g8) {
             c.g8 = g8;
             c.nblk = ceil_div(octets, g8);
+            if (g8 != ceil_div(octets, c.nblk)) continue;     // blocks alike
             const int64_t lds = std::max<int64_t>((int64_t)g8 * c.octet * 16 + 8 * c.plane, 4 * SCONV_MC_STORE_BYTES(mt, c.nt_max)) + 16;
             if (lds > 80 * 1024 - 256 || (int64_t)g8 * taps * 2 > 0xffff) break; // two workgroups on a CU
             c.lds_bytes = (int)lds;
