@@ -3,6 +3,12 @@ import os
 import shutil
 import subprocess
 
+import numpy as np
+import pytest
+
+from paper_1608_01409_amd import binding as B
+from paper_1608_01409_amd import workloads as wl
+
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 PKG = os.path.join(ROOT, "paper_1608_01409_amd")
 
@@ -18,3 +24,15 @@ def test_records_as_the_kernel_reads_them(tmp_path):
                            "-Wl,-rpath-link,/opt/rocm/lib", "-o", str(exe)])
     res = subprocess.run([str(exe)], capture_output=True, text=True, timeout=300)
     assert res.returncode == 0, res.stdout[-4000:] + res.stderr[-2000:]
+
+
+@pytest.mark.parametrize("per_group,tiles_of_16", [(15, True), (97, False)])
+def test_few_filters_of_a_tile_stay_on_the_three_part_kernel(per_group, tiles_of_16):
+    """A group's 15 filters would fill half of the flat streams' smallest tile (18 % slower); 97 of 128 are enough."""
+    c, hw, n, density = (114, 54, 87, 0.72) if tiles_of_16 else (246, 23, 45, 0.45)
+    layer = wl.Layer("few", C=c, H=hw, W=hw, K=2 * per_group, R=5, S=5, stride=1, pad=2, groups=2)
+    rng = np.random.default_rng(3)
+    w = rng.standard_normal((layer.K, c // 2, 5, 5), dtype=np.float32)
+    w[rng.random(w.shape) >= density] = 0
+    route = B.sconv_route_of(B.sconv_create_csr(layer, w), n)
+    assert route["kernel"] == "mfma" and (route["mt"] == 1 if tiles_of_16 else route["mt"] > 2), route
