@@ -557,8 +557,8 @@ static bool free_choice(const sconv_csr *h)
 // kernels).  Of 4100 random calls it was chosen for, 7 take more than 2 % longer than on the flat-stream kernel (at most 14 %).
 static const double kMfmaMargin = 1.15;
 
-// The flat streams on the matrix cores against the same on the vector units and against the three-part kernel.  Of 60 random calls
-// (before the lines on precision) 22 went there, one of them slower; with 1.1 and 1.0 it was 20, one of them 14 % slower.
+// The flat streams on the matrix cores against the same on the vector units and against the three-part kernel.  With 1.1
+// and 1.0 one of 20 random calls that went there was 14 % slower; as they are, 16 of 17 gain 11-84 %, the other is below.
 static const double kFlatMcMargin = 1.0, kFlatMcMfmaMargin = 1.15;
 
 // A group's filters fill at least this share of the units' rows for a call to leave the three-part kernel, whose tiles are 16
