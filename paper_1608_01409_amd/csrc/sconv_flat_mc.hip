@@ -39,6 +39,7 @@
 #include <type_traits>
 
 #include "sconv_device.h"
+#include "sconv_mc_walk.h"
 
 namespace sconv {
 
@@ -274,6 +275,11 @@ static __device__ __forceinline__ bool mc_tile(const FlatMcArgs &a, int bid, cha
         }
         wpos += kRec;
     };
+    // the record that stands at the beginning of block b
+    auto first_record = [&](Record &r, int b) INLINE {
+        wpos = mc_block_at(seg, b, b_first, kRec);
+        load_record(r);
+    };
     auto offset_of = [&](int off, int m) INLINE {   // tile m's of a private step
         return m == 0 ? __builtin_amdgcn_mov_dpp(off, 0x00, 0xf, 0xf, true) : m == 1 ? __builtin_amdgcn_mov_dpp(off, 0x55, 0xf, 0xf, true) :
                m == 2 ? __builtin_amdgcn_mov_dpp(off, 0xaa, 0xf, 0xf, true) : __builtin_amdgcn_mov_dpp(off, 0xff, 0xf, 0xf, true);
@@ -472,7 +478,7 @@ static __device__ __forceinline__ bool mc_tile(const FlatMcArgs &a, int bid, cha
                     split_fours(v1);
                     i0 += 256;
                 }
-                load_record(r0);
+                first_record(r0, b);
                 split_fours(v0);
             } else {
                 const int items = items_of(b);
@@ -515,17 +521,14 @@ static __device__ __forceinline__ bool mc_tile(const FlatMcArgs &a, int bid, cha
                     split_items(y1, i0);
                     i0 += 4 * kBatch;
                 }
-                load_record(r0);
+                first_record(r0, b);
                 split_items(y0, i0);
             }
             __syncthreads();
             const unsigned steps = (unsigned)seg[2 * b + 1];
             const int n_shared = (int)(steps & 0xffffu), n_private = (int)(steps >> 16);
-            Record r1;
             Cols c0, c1;
-            int left = n_shared + n_private;     // steps of this block still to come, this one included
-            auto shared_step = [&](const Record &cur, Record &next) INLINE {
-                if (--left) load_record(next);
+            auto shared_step = [&](const Record &cur, const Record &next) INLINE {
 #pragma unroll
                 for (int t = 0; t < NT; t += 2) {
                     load_cols(c1, t + 1, cur.off);
@@ -539,8 +542,7 @@ static __device__ __forceinline__ bool mc_tile(const FlatMcArgs &a, int bid, cha
                     __builtin_amdgcn_sched_barrier(0);
                 }
             };
-            auto private_step = [&](const Record &cur, Record &next) INLINE {
-                if (--left) load_record(next);
+            auto private_step = [&](const Record &cur, const Record &) INLINE {
 #pragma unroll
                 for (int m = 0; m < MT; ++m) {
                     const int off = offset_of(cur.off, m);
@@ -558,21 +560,8 @@ static __device__ __forceinline__ bool mc_tile(const FlatMcArgs &a, int bid, cha
                     }
                 }
             };
-            auto run = [&](int n, auto step) INLINE {
-                int i = 0;
-                for (; i + 1 < n; i += 2) {
-                    step(r0, r1);
-                    step(r1, r0);
-                    if (kTotals && (i & 2)) flush();
-                }
-                if (i < n) {
-                    step(r0, r1);
-                    r0 = r1;
-                }
-            };
             load_cols(c0, 0, r0.off);
-            run(n_shared, shared_step);
-            run(n_private, private_step);
+            mc_walk_block(r0, n_shared, n_private, load_record, shared_step, private_step, flush);
         }
         if constexpr (kTotals) {
             flush();

@@ -1,6 +1,6 @@
 // Host check of the flat streams packed for the matrix cores: records decoded the way sconv_flat_mc_kernel feeds them to
 // v_smfmac_f32_16x16x64_f16, every weight of the layer found once and within the split's precision, every LDS address inside
-// the staged block.  Built by test_host_flat_mc.py and linked to libsconv.so; no GPU.
+// the staged block; the streams walked by the kernel's own lines, every step on its record.  Built by test_host_flat_mc.py and linked to libsconv.so; no GPU.
 #include <algorithm>
 #include <cmath>
 #include <cstdio>
@@ -9,10 +9,11 @@
 #include <vector>
 
 #include "sconv_internal.h"
+#include "sconv_mc_walk.h"
 
 using namespace sconv;
 
-static long failures = 0, layers = 0, private_steps = 0, twice = 0;
+static long failures = 0, layers = 0, private_steps = 0, twice = 0, empty_blocks = 0;
 
 #define CHECK(cond, ...) \
     do { \
@@ -35,7 +36,49 @@ static double f16(uint16_t b)
     return b & 0x8000 ? -v : v;
 }
 
-static void check(const sconv_desc &layer, int N, double density, bool skewed, bool explicit_zeros)
+// A wave's way through its part of the stream, for every way to split the channel blocks over workgroups.
+static void walk(const PackedFlatMc &p, const FlatMcTiling &t, int units, const char *what)
+{
+    const int rec = SCONV_MC_RECORD(t.mt);
+    struct Record {
+        int at = -1;         // in the stream, -1 where nothing was loaded
+    };
+    for (int u = 0; u < units; ++u)
+        for (int splits = 1; splits <= t.nblk; ++splits) {
+            const int per = (t.nblk + splits - 1) / splits;
+            const int32_t *seg = &p.seg[(size_t)u * t.nblk * 2];
+            for (int b_first = 0; b_first < t.nblk; b_first += per) {
+                int64_t pos = 0;
+                Record r0;
+                auto load = [&](Record &r) {
+                    r.at = seg[2 * b_first] + (int)(pos / rec);
+                    pos += rec;
+                    CHECK((int64_t)(r.at + 1) * rec <= t.stream_bytes, "a record past the end: %s", what);
+                };
+                for (int b = b_first; b < std::min(b_first + per, t.nblk); ++b) {
+                    const int n_shared = seg[2 * b + 1] & 0xffff, n_private = seg[2 * b + 1] >> 16;
+                    int steps = 0;
+                    bool own = false;
+                    pos = mc_block_at(seg, b, b_first, rec);
+                    load(r0);
+                    auto step = [&](const Record &cur, const Record &) {
+                        CHECK(cur.at == seg[2 * b] + steps, "unit %d block %d step %d on record %d: %s", u, b, steps, cur.at - seg[2 * b], what);
+                        CHECK(own == (steps >= n_shared), "%s", what);
+                        ++steps;
+                        own = steps >= n_shared;
+                    };
+                    own = n_shared == 0;
+                    mc_walk_block(r0, n_shared, n_private, load, step, step, [] {});
+                    CHECK(steps == n_shared + n_private, "%s", what);
+                    empty_blocks += splits == 1 && steps == 0 && b + 1 < t.nblk;
+                }
+            }
+        }
+}
+
+// no_first .. no_last: input channels of a group that no filter has weights on; short_row: a filter of 16 nonzeros in one channel
+static void check(const sconv_desc &layer, int N, double density, bool skewed, bool explicit_zeros, int no_first = 0, int no_last = -1,
+                  bool short_row = false)
 {
     const Geometry lg = geometry(layer);
     const int cols = lg.Cg * layer.R * layer.S;
@@ -44,7 +87,8 @@ static void check(const sconv_desc &layer, int N, double density, bool skewed, b
     for (int k = 0; k < layer.K; ++k) {
         const double dk = skewed ? (k % 5 == 0 ? 0.0 : density * (0.3 + 1.7 * uniform())) : density;
         for (int j = 0; j < cols; ++j)
-            if (uniform() < dk) {
+            if (short_row && k == layer.K - 1 ? j >= cols / 2 && j < cols / 2 + 16
+                                              : uniform() < dk && !(j / (layer.R * layer.S) >= no_first && j / (layer.R * layer.S) <= no_last)) {
                 col.push_back(j);
                 val.push_back(explicit_zeros && j % 7 == 0 ? 0.f : (float)((uniform() + 0.001) * (uniform() < 0.5 ? -1 : 1)));
             }
@@ -144,6 +188,7 @@ static void check(const sconv_desc &layer, int N, double density, bool skewed, b
         }
     }
     for (size_t i = 0; i < p.seg.size(); i += 2) twice += p.seg[i + 1] & 0xffff;
+    walk(p, t, d.groups * t.n_units, what);
     // Staged as the kernel stages (cell numbers for values), then every position reads every tap: the input element or the zero
     // of the padding, from both parts.
     const int pos_waves = t.wr == 2 ? 2 : 4, bn = 16 * t.nt * pos_waves, OHW = g.OH * g.OW, row_img = (g.OH - 1) * t.lstep + t.Rr;
@@ -202,7 +247,21 @@ int main()
     check({3, 227, 227, 96, 11, 11, 4, 0, 1}, 1, 0.3, false, false);
     check({600, 1, 1, 300, 1, 1, 1, 0, 1}, 64, 0.2, false, false);
     check({384, 13, 13, 192, 3, 3, 1, 1, 1}, 2, 0.1, true, false);
-    CHECK(layers > 200 && private_steps > 100 && twice > 1000, "%ld layers, %ld private steps", layers, private_steps);
-    std::printf("%ld layers, %ld private steps of %ld, %ld failures\n", layers, private_steps, twice, failures);
+    // channels that pruning took from every filter: first, middle and last blocks of the stream without records
+    for (int lo : {0, 32, 96})
+        for (int groups : {1, 2})
+            for (int hi : {lo + 31, lo + 40, lo + 90}) {
+                check({128 * groups, 28, 28, 96 * groups, 3, 3, 1, 1, groups}, 3, 0.3, false, false, lo, std::min(hi, 127));
+                check({128 * groups, 14, 14, 40 * groups, 3, 3, 1, 1, groups}, 2, 0.8, false, false, lo, std::min(hi, 127));
+                check({128 * groups, 28, 28, 40 * groups, 3, 3, 2, 0, groups}, 3, 0.4, false, false, lo, std::min(hi, 127));
+            }
+    check({256, 13, 13, 384, 3, 3, 1, 1, 1}, 256, 0.2, false, false, 0, 95);
+    check({256, 13, 13, 384, 3, 3, 1, 1, 1}, 256, 0.2, false, false, 88, 175);
+    check({128, 28, 28, 65, 3, 3, 1, 1, 1}, 3, 0.3, false, false, 0, -1, true);   // a wave of one short row
+    check({40, 40, 40, 64, 3, 3, 4, 0, 1}, 3, 0.7, false, false);                 // phases that no tap of the filter has
+    CHECK(layers > 200 && private_steps > 100 && twice > 1000 && empty_blocks > 50, "%ld layers, %ld private steps, %ld empty blocks", layers,
+          private_steps, empty_blocks);
+    std::printf("%ld layers, %ld private steps of %ld, %ld empty blocks before others, %ld failures\n", layers, private_steps, twice, empty_blocks,
+                failures);
     return failures ? 1 : 0;
 }

@@ -88,6 +88,33 @@ def test_layers_against_the_oracle(oracle, shape):
     check(oracle, layer, N, x, w, bias, False)
 
 
+# ... and the input channels of a group that pruning took from every filter; -1: the last filter has 14 channels only
+PRUNED = [
+    (256, 13, 13, 384, 3, 3, 1, 1, 1, 256, 0.20, 0, 96),      # the first channel block without weights
+    (256, 13, 13, 384, 3, 3, 1, 1, 1, 70, 0.20, 88, 176),     # one in the middle
+    (256, 13, 13, 384, 3, 3, 1, 1, 1, 70, 0.20, 160, 256),    # the last one
+    (384, 13, 13, 384, 3, 3, 1, 1, 2, 70, 0.30, 60, 130),
+    (400, 28, 28, 64, 1, 1, 1, 0, 1, 100, 0.50, 96, 200),
+    (160, 27, 27, 80, 3, 3, 2, 1, 1, 160, 0.15, 30, 90),      # staged a cell per lane
+    (472, 12, 12, 356, 3, 3, 1, 1, 1, 34, 0.94, 0, 100),      # channels split over workgroups
+    (472, 12, 12, 356, 3, 3, 1, 1, 1, 34, 0.94, 300, 400),
+    (256, 13, 13, 385, 3, 3, 1, 1, 1, 70, 0.14, -1, 0),
+]
+
+
+@pytest.mark.parametrize("shape", PRUNED)
+def test_channels_without_weights(oracle, shape):
+    *dims, N, density, lo, hi = shape
+    layer = layer_of(dims)
+    x, w = make(layer, N, density)
+    if lo < 0:
+        w[-1] = 0
+        w[-1, :14] = 0.01
+    else:
+        w[:, lo:hi] = 0
+    check(oracle, layer, N, x, w)
+
+
 MIXED = [(99, 20, 20, 150, 3, 3, 1, 1, 1, 32, 0.13), (256, 13, 13, 384, 3, 3, 1, 1, 1, 70, 0.10), (472, 12, 12, 356, 3, 3, 1, 1, 1, 34, 0.94)]
 
 
