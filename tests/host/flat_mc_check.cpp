@@ -42,6 +42,7 @@ static void walk(const PackedFlatMc &p, const FlatMcTiling &t, int units, const 
     const int rec = SCONV_MC_RECORD(t.mt);
     struct Record {
         int at = -1;         // in the stream, -1 where nothing was loaded
+        int off = -1;        // the record that its LDS addresses are from
     };
     for (int u = 0; u < units; ++u)
         for (int splits = 1; splits <= t.nblk; ++splits) {
@@ -51,7 +52,7 @@ static void walk(const PackedFlatMc &p, const FlatMcTiling &t, int units, const 
                 int64_t pos = 0;
                 Record r0;
                 auto load = [&](Record &r) {
-                    r.at = seg[2 * b_first] + (int)(pos / rec);
+                    r.at = r.off = seg[2 * b_first] + (int)(pos / rec);
                     pos += rec;
                     CHECK((int64_t)(r.at + 1) * rec <= t.stream_bytes, "a record past the end: %s", what);
                 };
@@ -61,7 +62,9 @@ static void walk(const PackedFlatMc &p, const FlatMcTiling &t, int units, const 
                     bool own = false;
                     pos = mc_block_at(seg, b, b_first, rec);
                     load(r0);
-                    auto step = [&](const Record &cur, const Record &) {
+                    auto step = [&](const Record &cur, const Record &next) {
+                        CHECK(cur.off >= 0 && next.off >= 0, "unit %d block %d step %d of %d: LDS read at an address that no record gave: %s", u, b,
+                              steps, n_shared + n_private, what);
                         CHECK(cur.at == seg[2 * b] + steps, "unit %d block %d step %d on record %d: %s", u, b, steps, cur.at - seg[2 * b], what);
                         CHECK(own == (steps >= n_shared), "%s", what);
                         ++steps;
