@@ -73,6 +73,7 @@ struct sconv_csr {
         DeviceLds mc;
         bool mc_uploaded = false;
         int mc_wexp = 0;
+        float mc_small = 0;
         int64_t mc_bytes = 0;
     } conv_alt, fc_alt;
     int max_row_nnz = 0;
@@ -679,6 +680,7 @@ static int prepare_choice(sconv_csr *h, bool fc, const sconv_csr::Choice &c)
         if (!rc) rc = upload(p.row_of.data(), p.row_of.size() * 4, &alt.mc.row_of, &h->hip_err);
         if (!rc) rc = upload(p.choff.data(), p.choff.size() * 4, &alt.mc.store_tbl, &h->hip_err);
         alt.mc_wexp = t.wexp;
+        alt.mc_small = t.small_sum;
         alt.mc_bytes = t.stream_bytes;
         if (!rc) alt.mc_uploaded = true;
         else release_arrays(alt.mc);
@@ -723,6 +725,7 @@ static int launch_choice(sconv_csr *h, bool fc, const sconv_csr::Choice &c, cons
     if (c.kind == sconv_csr::kFlatMc) {
         FlatMcTiling mc = c.mc;
         mc.wexp = alt.mc_wexp;
+        mc.small_sum = alt.mc_small;
         mc.stream_bytes = alt.mc_bytes;
         LdsTiling t = {};
         t.p.splits = mc.splits;

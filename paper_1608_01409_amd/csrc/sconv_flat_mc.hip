@@ -79,7 +79,7 @@ struct FlatMcArgs {
     int wide;                // four neighbouring cells are 16 consecutive bytes of the input: 1 along rows, 2 along the positions
     int quads;               // wide = 1: fours of cells per row, the last one back by what it would pass the row's end
     int pitch, part, octet;  // 16-byte units of LDS from one row of cells, high to low part, one channel octet to the next
-    int words_at;            // two words of LDS behind the staged block, its table and the results
+    int words_at;            // four words of LDS behind the staged block, its table and the results
     int n_ptiles, n_mtiles, groups, n_units;
     int wr;                  // waves along the filters: 2 (then 2 along the positions) or 1 (then 4)
     int splits, blk_split;   // workgroups along the channel blocks, blocks each of them takes
@@ -90,6 +90,7 @@ struct FlatMcArgs {
     long long stream_bytes;
     long long out_img, out_row;
     int wexp;                // weights are packed times 2^wexp
+    float small_sum;         // sums below it may be of activations that all have lost bits
     FastDiv d_units, d_splits, d_mt, d_ohw, d_ow, d_wl, d_rowimg, d_quads;
 };
 
@@ -200,7 +201,7 @@ static __device__ __forceinline__ bool mc_tile(const FlatMcArgs &a, int bid, cha
     // cells past the end read beyond the buffer.  What no cell is written to stays zero: the right padding of a row.
     const int block16 = a.g8 * a.octet;
     uint2 *table = reinterpret_cast<uint2 *>(lds + (size_t)block16 * 16);
-    // the largest of the first activations; a flag, read while other waves already store their results
+    // the largest of the first activations; flags, read while other waves already store their results
     unsigned *word = reinterpret_cast<unsigned *>(lds + a.words_at);
     for (int i = threadIdx.x; i < block16; i += 256) reinterpret_cast<uint4 *>(lds)[i] = make_uint4(0, 0, 0, 0);
     const bool wide = !again && a.wide;
@@ -228,7 +229,7 @@ static __device__ __forceinline__ bool mc_tile(const FlatMcArgs &a, int bid, cha
                               there && (ok || !wide) ? (unsigned)(row * a.pitch + col) * 16u : 0xffffffffu);
     }
     const FastDiv d_nquads = {(unsigned)n_quads, n_quads > 1 ? 0xffffffffu / (unsigned)n_quads + 1u : 0u};
-    if (threadIdx.x == 0) word[0] = word[1] = 0;
+    if (threadIdx.x == 0) word[0] = word[1] = word[2] = word[3] = 0;
     const int pieces = (cells + 63) >> 6;
     const FastDiv d_pieces = {(unsigned)pieces, ((const_u32 *)kMcPieceMagic)[pieces]};
     int4v rsrc;
@@ -570,9 +571,14 @@ static __device__ __forceinline__ bool mc_tile(const FlatMcArgs &a, int bid, cha
 #pragma unroll
                 for (int t = 0; t < NT; ++t) acc[m][t] = tot[m][t];
         }
-        // what the split did not carry: sums that are not finite, or activations 2^30 below the scale's (there the low part's
-        // last bit is 2^-18 of the value)
-        bool bad = least < ((unsigned)(109 - expo) << 24) - 1u;
+        // What the split did not carry: sums that are not finite, and sums that only small activations went into.  Scaled below
+        // 2^-13 an activation has lost more than the two parts of a larger one lose (2^-23 of it), below 2^-18 it may be gone.
+        // That counts where the sum is not much larger than what is lost, 2^-36.8 a product on average: a value in 3e7 of a normal
+        // distribution is that small, and a workgroup stages 5e4 to 2e5 of them.
+        volatile unsigned *const flag = word + 1;      // again; activations: byte 0 small, byte 1 gone; sums: byte 0 small, byte 1 small or 0
+        volatile unsigned char *const lost = reinterpret_cast<volatile unsigned char *>(flag + 1), *const low = lost + 4;
+        if (least < ((unsigned)(114 - expo) << 24) - 1u) lost[least < ((unsigned)(109 - expo) << 24) - 1u] = 1;
+        bool bad = false;
 #pragma unroll
         for (int m = 0; m < MT; ++m)
 #pragma unroll
@@ -582,9 +588,26 @@ static __device__ __forceinline__ bool mc_tile(const FlatMcArgs &a, int bid, cha
                     acc[m][t][r] = __builtin_ldexpf(__builtin_fmaf(cor[m][t][r], 0x1p-11f, acc[m][t][r]), -(expo + a.wexp));
                     bad |= mc_not_finite(acc[m][t][r]);
                 }
-        if (bad) *(volatile unsigned *)(word + 1) = 1;
+        if (bad) flag[0] = 1;
         __syncthreads();
-        if (*(volatile unsigned *)(word + 1)) return true;
+        if (__builtin_amdgcn_readfirstlane(flag[1])) {
+            unsigned smallest = 0xffffffffu;               // of the sums that are not zero, as `least`
+            float smallest_or_0 = __builtin_inff();
+#pragma unroll
+            for (int m = 0; m < MT; ++m)
+#pragma unroll
+                for (int t = 0; t < NT; ++t)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        smallest = min(smallest, (__float_as_uint(acc[m][t][r]) << 1) - 1u);
+                        smallest_or_0 = fminf(smallest_or_0, fabsf(acc[m][t][r]));
+                    }
+            const float limit = __builtin_ldexpf(a.small_sum, -(expo + a.wexp));
+            if (smallest < (__float_as_uint(limit) << 1)) low[0] = 1;
+            if (smallest_or_0 < limit) low[1] = 1;
+            __syncthreads();
+        }
+        if (flag[0] | (flag[1] & flag[2])) return true;
         // Through LDS, a wave's rows of 16 * NT positions each for itself: every store is whole rows of positions instead of 16.
         // (a pitch of 4 modulo 16 words: the 16 positions x 4 rows of a write fall into different banks)
         constexpr int kPos = 16 * NT, kPitch = kPos + 4, kRows = 64 / kPos;
@@ -787,6 +810,7 @@ int launch_flat_mc(const sconv_desc &layer, const FlatMcTiling &t, const DeviceL
     a.n_units = t.n_units;
     a.groups = d.groups;
     a.wexp = t.wexp;
+    a.small_sum = t.small_sum;
     a.stream_bytes = t.stream_bytes;
     a.in_ch4 = (int)(HW * 4); a.in_img = d.C * HW; a.in_group = g.Cg * HW; a.in_floats = (int64_t)N * d.C * HW;
     a.out_img = (int64_t)d.K * a.OHW; a.out_row = a.OHW;

@@ -1360,6 +1360,7 @@ bool choose_flat_mc(const sconv_desc &layer, const Canonical &csr, int N, bool f
     t.wr = wr;
     t.n_units = ceil_div(g.Kg, 16 * mt * wr) * wr;
     t.wexp = 0;
+    t.small_sum = 0;
     t.stream_bytes = 0;
     t.us = 0;
     const double P = (double)N * g.OH * g.OW, out_bytes = 4.0 * P * d.K;
@@ -1463,6 +1464,14 @@ int pack_flat_mc(const sconv_desc &layer, const Canonical &c, FlatMcTiling &t, P
     std::frexp(most, &e);
     t.wexp = most > 0 ? 14 - e : 0;
     const float scale = std::ldexp(1.f, t.wexp);
+    // A row's sum of small activations is off by 2^-36.8 times the row's norm: 2^-25 of a sum from here on.
+    double norm = 0;
+    for (int k = 0; k < d.K; ++k) {
+        double sum = 0;
+        for (int j = c.rowptr[k]; j < c.rowptr[k + 1]; ++j) sum += (double)c.val[j] * c.val[j];
+        norm = std::max(norm, sum);
+    }
+    t.small_sum = (float)std::ldexp(std::sqrt(norm) * 0.574, t.wexp - 11);
     std::vector<int32_t> col_slot((size_t)g.Cg * d.R * d.S); // slot * 8 + channel of the octet
     std::vector<int32_t> slot_off(slots), block_first(t.nblk + 1);
     for (int b = 0; b <= t.nblk; ++b) block_first[b] = std::min(b * t.g8, octets) * taps;

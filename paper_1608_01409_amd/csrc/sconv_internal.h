@@ -191,6 +191,7 @@ struct FlatMcTiling {
     int n_units;             // waves' worth of filters per group, a multiple of wr
     int lds_bytes;
     int wexp;                // weights are packed times 2^wexp
+    float small_sum;         // packed: sums below it are taken again where there are activations that have lost bits
     int64_t stream_bytes;
     bool for_dense;          // the call would be the three-part kernel's
     double us;

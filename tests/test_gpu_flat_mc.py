@@ -148,6 +148,25 @@ def test_activations_of_every_magnitude(oracle, shape, what):
 
 
 @pytest.mark.parametrize("shape", MIXED)
+def test_small_images_lose_no_bits_beside_large_ones(shape):
+    """Image by image as close to 64 bits as the direct kernel's chains, whatever the magnitudes in the batch: where a workgroup
+    meets activations that its scale leaves fewer bits of, its sums are taken again."""
+    *dims, N, density = shape
+    layer = layer_of(dims)
+    x, w = make(layer, N, density)
+    x *= np.ldexp(np.float32(1), -np.array([0, 22, 0, 25, 0, 28, 0, 29, 0, 31, 18, 0, 27, 0, 20, 0, 34])[np.arange(N) % 17]).astype(np.float32)[:, None, None, None]
+    xd = torch.from_numpy(x).cuda()
+    h = B.sconv_create_csr(layer, w)
+    assert on_matrix_cores(B.sconv_route_of(h, N))
+    print(f"[gpu-case] small images {layer.name} C{layer.C} K{layer.K} N={N}", flush=True)
+    exact = torch.nn.functional.conv2d(xd.cpu().double(), torch.from_numpy(w).double(), padding=layer.pad)
+    err, chain = ((B.sconv_forward(g, xd).cpu().double() - exact).flatten(1).norm(dim=1) / exact.flatten(1).norm(dim=1)
+                  for g in (h, B.sconv_create_csr(layer, w, dict(kernel=2))))
+    print(f"[gpu-case] largest ratio {float((err / chain).max()):.3f}", flush=True)
+    assert bool((err <= chain).all()), (err / chain).tolist()
+
+
+@pytest.mark.parametrize("shape", MIXED)
 def test_infinities_meet_stored_weights_only(shape):
     """Infinities, NaN and values near the largest: the outputs the direct kernel gives, stored zeros included."""
     *dims, N, density = shape
