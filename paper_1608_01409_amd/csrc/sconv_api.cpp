@@ -77,6 +77,7 @@ struct sconv_csr {
         int64_t mc_bytes = 0;
     } conv_alt, fc_alt;
     int max_row_nnz = 0;
+    int shortest_row = 0;                    // of the rows that are not empty
     bool mc_ok = false;                      // rows and weights are such that the flat streams may run on the matrix cores
     bool split_exact = true;                 // every weight is exactly three bf16 parts
     int short_rows = 0;                      // rows of 1 to SCONV_MFMA_SHORT_ROW - 1 nonzeros
@@ -307,6 +308,7 @@ static int finish_create(sconv_csr *h, const sconv_plan *plan)
         h->short_rows += nnz > 0 && nnz < SCONV_MFMA_SHORT_ROW;
     }
     for (float v : h->canon.val) h->split_exact = h->split_exact && mfma_weight_ok(v);
+    h->shortest_row = shortest_row(h->canon);
     h->mc_ok = flat_mc_weights_ok(d, h->canon);
     int rc = pack_direct(d, h->canon, h->direct);
     if (rc) return rc;
@@ -599,9 +601,9 @@ static const sconv_csr::Choice &choose_kernel(sconv_csr *h, bool fc, int N, doub
     } else {
         c.mfma = MfmaTiling();
     }
-    // The flat streams on the matrix cores, where their sums are no further from the exact ones than those they replace: what
+    // The flat streams on the matrix cores, where the sums of no row are further from the exact ones than those they replace: what
     // counts is the length of the chains there, which parts make shorter.
-    const double row = avg_row_nnz(h);
+    const int row = h->shortest_row;
     const bool three_parts = c.kind == sconv_csr::kMfma, flushed = three_parts || lds_splits > 1;
     const bool exact = three_parts ? row >= (c.mfma.splits <= 1 ? SCONV_MC_LONG_ROW : c.mfma.splits * SCONV_MC_LONG_ROW_SPLIT)
                                    : c.kind == sconv_csr::kLds && (lds_splits <= 1 || row >= lds_splits * SCONV_MC_ROW_SPLIT);

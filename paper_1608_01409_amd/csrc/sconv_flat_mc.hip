@@ -9,15 +9,18 @@
 // it, in a step in which every tile has octets of its own (four times the LDS reads: 2 us where a shared step takes 1.1).
 //
 // Numbers: an fp32 value is h + l / 2^11, both fp16, at one power of two for a workgroup's activations and one for the weights;
-// of 24 significant bits 23 or 24 remain.  h*h goes to one accumulator, l*h + h*l to a second one, l*l (2^-24) is left out.
-// l is kept 2^11 larger than its value: at a value 2^27 below the largest fp16 the split still loses nothing, and 2^-18 of the
-// value at 2^33 below.  Smaller ones, larger ones, infinities and NaN send the workgroup back (`again`): one pass for every
-// window of 26 binades that occurs, each at its own scale, and a pass that counts which stored weights meet an infinity.  The
-// scale is taken from the first activations a workgroup stages: their largest goes to 2^12.
-// Error against 64 bits, relative 2-norm, row of n nonzeros, here / here with flushed sums (nt = 2: every four steps the large
-// accumulator is added to a total by the vector units; the matrix instruction truncates small products against a large sum) /
-// fp32 chain: n = 58 1.1e-7, 1.0e-7, 1.0e-7; 120 1.38, 1.06, 1.40; 230 1.71, 1.12, 1.91; 346 1.94, 1.17, 2.29; 864 2.58, 1.30,
-// 3.63.  The three-part kernel (sconv_mfma.hip) has 1.1 at 350 and 1.33 at 864: the lines in sconv_internal.h follow from these.
+// of 24 significant bits 23 or 24 remain.  h*h goes to one accumulator, l*h + h*l to a second one, l*l is left out: up to 2^-22
+// of a product, 2^-24.6 as the mean square goes.  l is kept 2^11 larger than its value: at a value 2^27 below the largest fp16 the
+// split still loses nothing, and 2^-18 of the value at 2^33 below.  Smaller ones that matter (`small_sum`), larger ones, infinities
+// and NaN send the workgroup back (`again`): one pass for every window of 26 binades that occurs, each at its own scale, and a pass
+// that counts which stored weights meet an infinity.  The scale is taken from the first activations a workgroup stages: their
+// largest goes to 2^12.
+// Sums: the matrix instruction truncates small products against a large sum.  Up to 48 x 64 or 64 x 32 a wave there are registers for totals: every six
+// steps the large accumulator is added to one, and keeps what that addition rounds off.  (Every four: 11.0 instead of 11.8 e-8 at 800
+// nonzeros, 3.6 % slower at 384 -> 384, density 0.5, than plain additions every four; every six 1.9 %, every eight 0.7 % and 12.9.)
+// Error against 64 bits, relative 2-norm in 1e-8, of a row of n nonzeros on rectified normals, totals / none / fp32 chain / three-part
+// kernel (sconv_mfma.hip): n = 60 9.2 / 11.9 / 9.8 / -, 120 9.8 / 14.3 / 13.7 / 5.5, 346 11 / 21 / 23 / 8.6, 800 11.8 / 27 / 35 / 12.8,
+// 2304 13 / 32 / 62 / 23.  A call comes here where no row is off by more than on the kernel it leaves: the lines in sconv_internal.h.
 //
 // A workgroup is four waves, 16 * mt filters x 16 * nt positions each, two along the filters or one; it walks the channels in
 // blocks staged as [octet][row][high, low part][cell] of 16-byte units.  The pitch of a row is the number of positions in an
@@ -296,7 +299,7 @@ static __device__ __forceinline__ bool mc_tile(const FlatMcArgs &a, int bid, cha
         b.l = __builtin_shufflevector(l0, l1, 0, 1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11, 12, 13, 14, 15);
     };
 
-    constexpr bool kTotals = NT == 2 && !again;
+    constexpr bool kTotals = SCONV_MC_TOTALS(MT, NT);
     f32x4 acc[MT][NT], cor[MT][NT], tot[kTotals ? MT : 1][kTotals ? NT : 1];
     auto clear = [&]() INLINE {
 #pragma unroll
@@ -307,15 +310,23 @@ static __device__ __forceinline__ bool mc_tile(const FlatMcArgs &a, int bid, cha
                 if constexpr (kTotals) tot[m][t] = f32x4{0.f, 0.f, 0.f, 0.f};
             }
     };
+    // (What the total's rounding leaves out stays in the accumulator.  In this order both are changed in place: with the sum in a
+    // variable of its own a second set of totals is live, 117 spilled registers with 48 x 64 a wave.)
     auto flush = [&]() INLINE {
         if constexpr (kTotals)
 #pragma unroll
             for (int m = 0; m < MT; ++m)
 #pragma unroll
                 for (int t = 0; t < NT; ++t) {
-                    tot[m][t] += acc[m][t];
-                    acc[m][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+                    const f32x4 grown = (tot[m][t] + acc[m][t]) - tot[m][t];
+                    acc[m][t] -= grown;
+                    tot[m][t] += grown;
                 }
+    };
+    auto sum_of = [&](int m, int t, int r) INLINE {
+        const float v = __builtin_fmaf(cor[m][t][r], 0x1p-11f, acc[m][t][r]);
+        if constexpr (kTotals) return tot[m][t][r] + v;
+        else return v;
     };
 #define SCONV_SMFMAC(D, M, T, A, B, I) \
     D[M][T] = (M) & 1 ? __builtin_amdgcn_smfmac_f32_16x16x64_f16(A, B, D[M][T], I, 0, 1) : __builtin_amdgcn_smfmac_f32_16x16x64_f16(A, B, D[M][T], I, 0, 0)
@@ -377,7 +388,7 @@ static __device__ __forceinline__ bool mc_tile(const FlatMcArgs &a, int bid, cha
     };
     auto items_of = [&](int b) { return min(a.g8, (a.c_virtual - b * a.g8 * 8 + 7) >> 3) * pieces; };
 
-    // f(output, row, sums) for every output of this lane
+    // f(output, row, the sum, its two accumulators) for every output of this lane
     auto outputs = [&](auto f) INLINE {
 #pragma unroll
         for (int t = 0; t < NT; ++t) {
@@ -392,7 +403,7 @@ static __device__ __forceinline__ bool mc_tile(const FlatMcArgs &a, int bid, cha
                 for (int r = 0; r < 4; ++r) {
                     const int k = r == 0 ? rows.x : r == 1 ? rows.y : r == 2 ? rows.z : rows.w;
                     if (k < 0) continue;
-                    f(dst[k * a.out_row], k, acc[m][t][r], cor[m][t][r]);
+                    f(dst[k * a.out_row], k, sum_of(m, t, r), acc[m][t][r], cor[m][t][r]);
                 }
             }
         }
@@ -564,13 +575,6 @@ static __device__ __forceinline__ bool mc_tile(const FlatMcArgs &a, int bid, cha
             load_cols(c0, 0, r0.off);
             mc_walk_block(r0, n_shared, n_private, load_record, shared_step, private_step, flush);
         }
-        if constexpr (kTotals) {
-            flush();
-#pragma unroll
-            for (int m = 0; m < MT; ++m)
-#pragma unroll
-                for (int t = 0; t < NT; ++t) acc[m][t] = tot[m][t];
-        }
         // What the split did not carry: sums that are not finite, and sums that only small activations went into.  Scaled below
         // 2^-13 an activation has lost more than the two parts of a larger one lose (2^-23 of it), below 2^-18 it may be gone.
         // That counts where the sum is not much larger than what is lost, 2^-36.8 a product on average: a value in 3e7 of a normal
@@ -585,7 +589,7 @@ static __device__ __forceinline__ bool mc_tile(const FlatMcArgs &a, int bid, cha
             for (int t = 0; t < NT; ++t)
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
-                    acc[m][t][r] = __builtin_ldexpf(__builtin_fmaf(cor[m][t][r], 0x1p-11f, acc[m][t][r]), -(expo + a.wexp));
+                    acc[m][t][r] = __builtin_ldexpf(sum_of(m, t, r), -(expo + a.wexp));
                     bad |= mc_not_finite(acc[m][t][r]);
                 }
         if (bad) flag[0] = 1;
@@ -717,25 +721,26 @@ static __device__ __forceinline__ bool mc_tile(const FlatMcArgs &a, int bid, cha
                             else multiply(r, c, t, m, m + 1);
                         }
                     }
+                    if (window != 31 && i % 6 == 5) flush();
                 }
             }
         };
         // (through the output: there is no room for a second set of accumulators)
-        outputs([&](float &out, int, float, float) INLINE { out = 0.f; });
+        outputs([&](float &out, int, float, float, float) INLINE { out = 0.f; });
         for (int w = 0; w < 10; ++w) {
             if (!(there >> w & 1)) continue;
             pass(w);
-            outputs([&](float &out, int, float v, float c) INLINE { out += __builtin_ldexpf(__builtin_fmaf(c, 0x1p-11f, v), 26 * w - 115 - a.wexp); });
+            outputs([&](float &out, int, float v, float, float) INLINE { out += __builtin_ldexpf(v, 26 * w - 115 - a.wexp); });
         }
         if (there >> 31) {
             pass(31);
-            outputs([&](float &out, int, float up, float down) INLINE {
+            outputs([&](float &out, int, float, float up, float down) INLINE {
                 if (up > 0.f) out += __builtin_inff();
                 if (down > 0.f) out -= __builtin_inff();
             });
         }
         if (a.bias || a.relu)
-            outputs([&](float &out, int k, float, float) INLINE {
+            outputs([&](float &out, int k, float, float, float) INLINE {
                 const float v = a.bias ? out + a.bias[k] : out;
                 out = a.relu ? fmaxf(v, 0.f) : v;
             });

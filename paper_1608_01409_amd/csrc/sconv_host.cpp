@@ -1252,13 +1252,19 @@ static double mc_slots_per_octet(const sconv_desc &d, const Canonical &c, int mt
     return sum / std::max(1, units);
 }
 
+int shortest_row(const Canonical &c)
+{
+    int shortest = 0;
+    for (size_t k = 1; k < c.rowptr.size(); ++k) {
+        const int nnz = c.rowptr[k] - c.rowptr[k - 1];
+        if (nnz > 0 && (shortest == 0 || nnz < shortest)) shortest = nnz;
+    }
+    return shortest;
+}
+
 bool flat_mc_weights_ok(const sconv_desc &d, const Canonical &c)
 {
-    if ((double)c.val.size() < (double)SCONV_MC_FLUSHED_ROW * d.K) return false;
-    for (int k = 0; k < d.K; ++k) {
-        const int nnz = c.rowptr[k + 1] - c.rowptr[k];
-        if (nnz > 0 && nnz < 16) return false;
-    }
+    if ((double)c.val.size() < (double)SCONV_MC_FLUSHED_ROW * d.K || shortest_row(c) < SCONV_MC_FLUSHED_ROW) return false;
     float most = 0, least = INFINITY;
     for (float v : c.val) {
         const float m = std::fabs(v);
@@ -1366,9 +1372,10 @@ bool choose_flat_mc(const sconv_desc &layer, const Canonical &csr, int N, bool f
     const double P = (double)N * g.OH * g.OW, out_bytes = 4.0 * P * d.K;
     // (fitted to 60 layers of all shapes, 11-500 us: 9 % off)
     const bool wide = t.cstep == 1 && (d.W >= 4 ? t.Wl >= d.W + d.pad : t.Wl == 1 && g.OH % 4 == 0);
-    const int nt_most = flushed || avg_row_nnz < SCONV_MC_ROW ? 2 : t.nt_max;
-    for (int nt = 2; nt <= nt_most; nt += 2)
+    const bool totals = flushed || shortest_row(csr) < SCONV_MC_ROW;
+    for (int nt = 2; nt <= t.nt_max; nt += 2)
         for (int splits : {1, 2, 3, 4, 6, 8, 12, 16}) {
+            if (totals && !SCONV_MC_TOTALS(mt, nt)) continue;
             if (splits > t.nblk || ceil_div(t.nblk, ceil_div(t.nblk, splits)) != splits) continue;
             if (splits > 1 && out_bytes * splits > SCONV_NOALLOC_SCRATCH_BYTES) continue;
             const int blocks = ceil_div(t.nblk, splits), positions = 16 * nt * pos_waves;

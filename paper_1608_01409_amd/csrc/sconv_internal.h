@@ -202,6 +202,8 @@ struct FlatMcTiling {
 #define SCONV_MC_RECORD(MT) ((MT) * 2048 + 64 * (((MT) + 1) / 2 * 4 + 4))
 // What a wave's results take in LDS on their way out.
 #define SCONV_MC_STORE_BYTES(MT, NT) (16 * (MT) * (16 * (NT) + 4) * 4)
+// Where a wave has registers for totals, to which its accumulators are added every few steps.
+#define SCONV_MC_TOTALS(MT, NT) ((MT) * (NT) <= 12)
 struct PackedFlatMc {
     std::vector<uint8_t> stream;
     std::vector<int32_t> seg;     // [group][unit][block]: first record, shared steps | private steps << 16
@@ -210,15 +212,26 @@ struct PackedFlatMc {
 };
 // A step that every tile has its own octets of against one that all share: four times the LDS reads.
 #define SCONV_MC_PRIVATE_COST 1.5
-#define SCONV_MC_ROW 105         // nonzeros a row has on average for sums that are not flushed, for sums that are
+// Nonzeros that the shortest row has, empty ones apart, for sums that are no further from 64 bits than those of the kernel they
+// replace.  Relative error of a row in 1e-8, here / there, rectified normal inputs, the mean of 100 and more rows a length:
+//   sums without totals (64 x 64 a wave) against the vector units' chains: 120 nonzeros 14.3 / 13.7, 150 15.4 / 15.3, 160 15.6 / 15.8
+#define SCONV_MC_ROW 160
+//   with totals against the chains: 50 9.1 / 9.0, 60 9.2 / 9.8, 75 9.3 / 10.8
 #define SCONV_MC_FLUSHED_ROW 72
-#define SCONV_MC_ROW_SPLIT 80     // ... per part of a flat-stream tiling that splits the channels (flushed sums then)
-#define SCONV_MC_LONG_ROW 800    // ... for flushed sums in place of the three-part kernel's
-#define SCONV_MC_LONG_ROW_SPLIT 1100 // ... per part where that kernel splits the channels
+//   totals in up to three parts against chains in two parts: 100 10.2 / 9.6, 120 10.4 / 10.5; in four: 210 10.6 / 10.4, 240
+//   10.6 / 10.9; so many per part of a flat-stream tiling that splits the channels
+#define SCONV_MC_ROW_SPLIT 80
+//   totals against the three-part kernel: 650 11.7 / 11.6, 700 11.8 / 11.8, 750 11.9 / 12.6
+#define SCONV_MC_LONG_ROW 740
+//   ... where that kernel splits the channels, per part: in two 1200 12.1 / 11.8, 1400 12.3 / 12.7; three 1800 12.0 / 11.8, 2000
+//   12.4 / 12.6; four 2600 12.5 / 12.3, 2800 12.6 / 12.8
+#define SCONV_MC_LONG_ROW_SPLIT 1100
 // From this density on most octets are needed twice.
 #define SCONV_MC_DENSE 0.35
 bool flat_mc_weights_ok(const sconv_desc &d, const Canonical &c);
-// Tiling and time of the layer on the matrix cores; flushed: sums as exact as the three-part kernel's.  False if it cannot take it.
+// The shortest row that is not empty; 0 if all are.
+int shortest_row(const Canonical &c);
+// Tiling and time of the layer on the matrix cores; flushed: with totals, whatever the rows' length.  False if it cannot take it.
 bool choose_flat_mc(const sconv_desc &d, const Canonical &c, int N, bool flushed, FlatMcTiling &t);
 int pack_flat_mc(const sconv_desc &d, const Canonical &c, FlatMcTiling &t, PackedFlatMc &out);
 

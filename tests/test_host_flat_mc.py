@@ -36,3 +36,26 @@ def test_few_filters_of_a_tile_stay_on_the_three_part_kernel(per_group, tiles_of
     w[rng.random(w.shape) >= density] = 0
     route = B.sconv_route_of(B.sconv_create_csr(layer, w), n)
     assert route["kernel"] == "mfma" and (route["mt"] == 1 if tiles_of_16 else route["mt"] > 2), route
+
+
+def test_the_shortest_row_decides():
+    """A layer whose rows are long on average and whose shortest one is not keeps the sums that are good enough for that one."""
+    def route(c, groups, n, density, length):
+        layer = wl.Layer("rows", C=c, H=13, W=13, K=384, R=3, S=3, stride=1, pad=1, groups=groups)
+        rng = np.random.default_rng(5)
+        w = rng.standard_normal((layer.K, layer.Cg, 3, 3), dtype=np.float32)
+        w[rng.random(w.shape) >= density] = 0
+        if length:
+            w[7].reshape(-1)[np.flatnonzero(w[7])[length:]] = 0
+        if length == 0:
+            w[7] = 0
+        return B.sconv_route_of(B.sconv_create_csr(layer, w), n)
+
+    full = route(256, 1, 256, 0.12, None)
+    assert full["kernel"] == "flat" and full["nt"] == 4, full
+    for length, nt in ((0, 4), (160, 4), (159, 2), (72, 2), (71, 1), (16, 1)):
+        r = route(256, 1, 256, 0.12, length)
+        assert r["kernel"] in ("flat", "flow") and r["nt"] == nt, (length, r)
+    for length, there in ((None, True), (0, True), (740, True), (739, False), (100, False)):
+        r = route(384, 2, 256, 0.5, length)
+        assert r["kernel"] == "mfma" and (r["mt"] > 2) == there, (length, r)
