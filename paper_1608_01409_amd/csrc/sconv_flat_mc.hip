@@ -11,10 +11,13 @@
 // Numbers: an fp32 value is h + l / 2^11, both fp16, at one power of two for a workgroup's activations and one for the weights;
 // of 24 significant bits 23 or 24 remain.  h*h goes to one accumulator, l*h + h*l to a second one, l*l is left out: up to 2^-22
 // of a product, 2^-24.6 as the mean square goes.  l is kept 2^11 larger than its value: at a value 2^27 below the largest fp16 the
-// split still loses nothing, and 2^-18 of the value at 2^33 below.  Smaller ones that matter (`small_sum`), larger ones, infinities
-// and NaN send the workgroup back (`again`): one pass for every window of 26 binades that occurs, each at its own scale, and a pass
-// that counts which stored weights meet an infinity.  The scale is taken from the first activations a workgroup stages: their
-// largest goes to 2^12.
+// split still loses nothing, and 2^-18 of the value at 2^33 below.  The scale is taken from the first activations a workgroup
+// stages: their largest goes to 2^12.  Where a later block holds one from 2^15 on, the scale and the sums shrink and the block is
+// staged again.  Smaller ones that matter (`small_sum`), infinities and NaN send the workgroup back (`again`): one pass for every
+// window of 26 binades that occurs, each at its own scale, and a pass that counts which stored weights meet an infinity.
+// What that costs, 13x13, 256 -> 384, batch 256 (133 us; the vector kernel 160): channels that differ by a factor e^2 (one sigma) 143,
+// later channels 100 times the first ones 150-165, an outlier of 60 sigma an image 139; every other image 2^-28 700, an outlier of
+// 1e4 sigma or an infinity an image 720, a single infinity 294, magnitudes 1e-20 to 1e20 1840.
 // Sums: the matrix instruction truncates small products against a large sum.  Up to 48 x 64 or 64 x 32 a wave there are registers for totals: every six
 // steps the large accumulator is added to one, and keeps what that addition rounds off.  (Every four: 11.0 instead of 11.8 e-8 at 800
 // nonzeros, 3.6 % slower at 384 -> 384, density 0.5, than plain additions every four; every six 1.9 %, every eight 0.7 % and 12.9.)
@@ -415,10 +418,9 @@ static __device__ __forceinline__ bool mc_tile(const FlatMcArgs &a, int bid, cha
         float scale = 1.f;
         int expo = 0;                        // activations are staged times 2^expo
         unsigned least = 0xffffffffu;        // smallest nonzero magnitude, twice its bits less one
-        auto set_scale = [&](unsigned most) INLINE {   // the largest of the first activations goes to [2^12, 2^13)
-            if (most) atomicMax(word, most);
-            __syncthreads();
-            const int e = (int)(__builtin_amdgcn_readfirstlane(*(volatile unsigned *)word) >> 23);
+        // (the largest so far goes to [2^12, 2^13))
+        auto largest = [&]() INLINE { return (int)(__builtin_amdgcn_readfirstlane(*(volatile unsigned *)word) >> 23); };
+        auto set_scale = [&](int e) INLINE {
             expo = 139 - (e == 0 ? 129 : max(e, 40));
             scale = __uint_as_float((unsigned)(127 + expo) << 23);
         };
@@ -426,7 +428,11 @@ static __device__ __forceinline__ bool mc_tile(const FlatMcArgs &a, int bid, cha
             const unsigned u = __float_as_uint(v) & 0x7fffffffu;
             return u < 0x7f800000u ? u : 0u;
         };
-        auto note = [&](float v0, float v1) INLINE { least = min(least, min((__float_as_uint(v0) << 1) - 1u, (__float_as_uint(v1) << 1) - 1u)); };
+        float most = 0.f;                    // largest magnitude of a block, infinities among them
+        auto note = [&](float v0, float v1) INLINE {
+            least = min(least, min((__float_as_uint(v0) << 1) - 1u, (__float_as_uint(v1) << 1) - 1u));
+            asm("v_max3_f32 %0, |%1|, |%2|, %0" : "+v"(most) : "v"(v0), "v"(v1));   // (fmaxf would quiet every loaded value first)
+        };
         // wide: items of 64 lanes, four cells x 8 channels each, counted through a block's octets
         struct Four {
             f32x4 x[8];
@@ -461,19 +467,23 @@ static __device__ __forceinline__ bool mc_tile(const FlatMcArgs &a, int bid, cha
             __builtin_amdgcn_sched_barrier(0);
         };
         __syncthreads();                     // the table is there
-        for (int b = b_first; b < b_end; ++b) {
+        bool unscaled = true;
+        for (int b = b_first; b < b_end;) {
+            most = 0.f;
             if (wide) {
                 const int fours = fours_of(b);
                 int i0 = wave * 64;
                 Four v0, v1;
                 load_fours(v0, b, i0);
-                if (b == b_first) {
-                    unsigned most = 0;
+                if (unscaled) {
+                    unsigned first = 0;
 #pragma unroll
                     for (int q = 0; q < 8; ++q)
 #pragma unroll
-                        for (int e = 0; e < 4; ++e) most = max(most, magnitude(v0.x[q][e]));
-                    set_scale(most);
+                        for (int e = 0; e < 4; ++e) first = max(first, magnitude(v0.x[q][e]));
+                    if (first) atomicMax(word, first);
+                    __syncthreads();
+                    set_scale(largest());
                 } else {
                     __syncthreads();         // the block before is used up
                 }
@@ -510,13 +520,15 @@ static __device__ __forceinline__ bool mc_tile(const FlatMcArgs &a, int bid, cha
                 };
                 int i0 = wave;
                 load_items(y0, b, i0, items);
-                if (b == b_first) {
-                    unsigned most = 0;
+                if (unscaled) {
+                    unsigned first = 0;
 #pragma unroll
                     for (int j = 0; j < kBatch; ++j)
 #pragma unroll
-                        for (int i = 0; i < 8; ++i) most = max(most, magnitude(y0.x[j][i]));
-                    set_scale(most);
+                        for (int i = 0; i < 8; ++i) first = max(first, magnitude(y0.x[j][i]));
+                    if (first) atomicMax(word, first);
+                    __syncthreads();
+                    set_scale(largest());
                 } else {
                     __syncthreads();
                 }
@@ -536,8 +548,27 @@ static __device__ __forceinline__ bool mc_tile(const FlatMcArgs &a, int bid, cha
                 first_record(r0, b);
                 split_items(y0, i0);
             }
+            // From 2^15 on a value is too large for the scale: it shrinks, with what is summed, and the block is staged again.
+            // (A loop that runs once: with a branch the compiler keeps a second set of accumulators, 200 spilled registers.)
+            if (most >= __uint_as_float((unsigned)min(142 - expo, 255) << 23) && most < __builtin_inff()) atomicMax(word, __float_as_uint(most));
             __syncthreads();
-            const unsigned steps = (unsigned)seg[2 * b + 1];
+            unscaled = false;
+            const bool over = largest() > 141 - expo;
+            for (int k = over; k; --k) {
+                const int before = expo;
+                set_scale(largest());
+                const float down = __builtin_ldexpf(1.f, expo - before);
+#pragma unroll
+                for (int m = 0; m < MT; ++m)
+#pragma unroll
+                    for (int t = 0; t < NT; ++t)
+                    {
+                        acc[m][t] *= down;
+                        cor[m][t] *= down;
+                        if constexpr (kTotals) tot[m][t] *= down;
+                    }
+            }
+            const unsigned steps = over ? 0u : (unsigned)seg[2 * b + 1];
             const int n_shared = (int)(steps & 0xffffu), n_private = (int)(steps >> 16);
             Cols c0, c1;
             auto shared_step = [&](const Record &cur, const Record &next) INLINE {
@@ -574,11 +605,13 @@ static __device__ __forceinline__ bool mc_tile(const FlatMcArgs &a, int bid, cha
             };
             load_cols(c0, 0, r0.off);
             mc_walk_block(r0, n_shared, n_private, load_record, shared_step, private_step, flush);
+            b += !over;
         }
         // What the split did not carry: sums that are not finite, and sums that only small activations went into.  Scaled below
         // 2^-13 an activation has lost more than the two parts of a larger one lose (2^-23 of it), below 2^-18 it may be gone.
-        // That counts where the sum is not much larger than what is lost, 2^-36.8 a product on average: a value in 3e7 of a normal
-        // distribution is that small, and a workgroup stages 5e4 to 2e5 of them.
+        // That counts where what goes into a sum is not much larger than what is lost, 2^-36.8 a product on average.  A sum may
+        // be small by itself; the second accumulator, of the same size and no relation to it, is small as well only where all is.
+        // (Ordinary inputs: one value in 3e7 of a normal distribution is lost, a workgroup stages 5e4 to 2e5 of them.)
         volatile unsigned *const flag = word + 1;      // again; activations: byte 0 small, byte 1 gone; sums: byte 0 small, byte 1 small or 0
         volatile unsigned char *const lost = reinterpret_cast<volatile unsigned char *>(flag + 1), *const low = lost + 4;
         if (least < ((unsigned)(114 - expo) << 24) - 1u) lost[least < ((unsigned)(109 - expo) << 24) - 1u] = 1;
@@ -603,8 +636,9 @@ static __device__ __forceinline__ bool mc_tile(const FlatMcArgs &a, int bid, cha
                 for (int t = 0; t < NT; ++t)
 #pragma unroll
                     for (int r = 0; r < 4; ++r) {
-                        smallest = min(smallest, (__float_as_uint(acc[m][t][r]) << 1) - 1u);
-                        smallest_or_0 = fminf(smallest_or_0, fabsf(acc[m][t][r]));
+                        const float v = fmaxf(fabsf(acc[m][t][r]), fabsf(__builtin_ldexpf(cor[m][t][r], -(expo + a.wexp))));
+                        smallest = min(smallest, (__float_as_uint(v) << 1) - 1u);
+                        smallest_or_0 = fminf(smallest_or_0, v);
                     }
             const float limit = __builtin_ldexpf(a.small_sum, -(expo + a.wexp));
             if (smallest < (__float_as_uint(limit) << 1)) low[0] = 1;

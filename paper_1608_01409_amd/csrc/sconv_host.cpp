@@ -1471,14 +1471,15 @@ int pack_flat_mc(const sconv_desc &layer, const Canonical &c, FlatMcTiling &t, P
     std::frexp(most, &e);
     t.wexp = most > 0 ? 14 - e : 0;
     const float scale = std::ldexp(1.f, t.wexp);
-    // A row's sum of small activations is off by 2^-36.8 times the row's norm: 2^-25 of a sum from here on.
+    // What is lost of small activations (below 2^-13, see the kernel) takes 2^-36.8 times a row's norm from its sum: 2^-25 of one of
+    // 2^-11.8 times the norm.  2^-8, for rows and activations of one sign, whose errors add up.
     double norm = 0;
     for (int k = 0; k < d.K; ++k) {
         double sum = 0;
         for (int j = c.rowptr[k]; j < c.rowptr[k + 1]; ++j) sum += (double)c.val[j] * c.val[j];
         norm = std::max(norm, sum);
     }
-    t.small_sum = (float)std::ldexp(std::sqrt(norm) * 0.574, t.wexp - 11);
+    t.small_sum = (float)std::ldexp(std::sqrt(norm), t.wexp - 8);
     std::vector<int32_t> col_slot((size_t)g.Cg * d.R * d.S); // slot * 8 + channel of the octet
     std::vector<int32_t> slot_off(slots), block_first(t.nblk + 1);
     for (int b = 0; b <= t.nblk; ++b) block_first[b] = std::min(b * t.g8, octets) * taps;

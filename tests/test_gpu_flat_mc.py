@@ -121,7 +121,7 @@ MIXED = [(150, 17, 17, 256, 3, 3, 1, 1, 1, 100, 0.18), (99, 20, 20, 150, 3, 3, 1
 
 
 @pytest.mark.parametrize("shape", MIXED)
-@pytest.mark.parametrize("what", ["tiny", "huge", "images", "one", "spread", "late", "zero", "denormal"])
+@pytest.mark.parametrize("what", ["tiny", "huge", "images", "one", "spread", "late", "growing", "zero", "denormal"])
 def test_activations_of_every_magnitude(oracle, shape, what):
     """Every output within the tolerance of its own sum of magnitudes, whatever else is in the batch."""
     *dims, N, density = shape
@@ -139,6 +139,8 @@ def test_activations_of_every_magnitude(oracle, shape, what):
         x[0, 0, 0, 0] = 1e-25
     elif what == "spread":
         x *= (10.0 ** rng.uniform(-20, 20, x.shape)).astype(np.float32)
+    elif what == "growing":                         # every few channels sixteen times larger: the scale shrinks with every block
+        x *= np.float32(16) ** (np.arange(layer.C) * 20 // layer.C)[None, :, None, None].astype(np.float32)
     elif what == "late":                            # nothing in the channels that the scale is taken from
         x[:, :layer.C - 4] = 0
         x[:, layer.C - 2:] *= np.float32(1e15)
@@ -151,13 +153,17 @@ def test_activations_of_every_magnitude(oracle, shape, what):
 
 @pytest.mark.parametrize("shape", MIXED)
 @pytest.mark.parametrize("binades", [12, 20, 24, 26, 27, 28, 29, 30, 33])
-def test_small_images_lose_no_bits_beside_large_ones(shape, binades):
+@pytest.mark.parametrize("alike", [False, True])
+def test_small_images_lose_no_bits_beside_large_ones(shape, binades, alike):
     """Image by image as close to 64 bits as the direct kernel's chains where every other image is 2^binades smaller, its
-    activations all of about one size: a workgroup's scale leaves them fewer bits, and their sums are taken again."""
+    activations all of about one size: a workgroup's scale leaves them fewer bits, and their sums are taken again.  alike: the
+    weights have one sign, so that what is lost adds up."""
     *dims, N, density = shape
     layer = layer_of(dims)
     x, w = make(layer, N, density)
-    x = np.where(x > 0, 0.5 + 0.5 * np.random.default_rng(3).random(x.shape), 0).astype(np.float32)
+    if alike:
+        w = np.abs(w)
+    x = np.where(alike | (x > 0), 0.5 + 0.5 * np.random.default_rng(3).random(x.shape), 0).astype(np.float32)
     x[1::2] *= np.float32(2.0 ** -binades)
     xd = torch.from_numpy(x).cuda()
     h = B.sconv_create_csr(layer, w)
