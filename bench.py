@@ -144,11 +144,8 @@ def main() -> int:
             traffic = None
 
     def kname(i):
-        r = layers[i]["route"]
-        if (r["kernel"] == "flat" and r["nt"] > 1) or (r["kernel"] == "mfma" and r["mt"] > 2):
-            return f"sconv_flat_mc_kernel on {layers[i]['name']}"    # on the matrix cores
         return dict(rows="sconv_lds_kernel", flat="sconv_lds2_kernel", flow="sconv_lds2_kernel").get(
-            r["kernel"], f"sconv_{r['kernel']}_kernel") + f" on {layers[i]['name']}"
+            layers[i]["route"]["kernel"], f"sconv_{layers[i]['route']['kernel']}_kernel") + f" on {layers[i]['name']}"
 
     roofline = dict(bound="alu", achieved=achieved, peak=PEAK_FMA_TFLOPS, unit="TFLOP/s",
                     frac=round(achieved / PEAK_FMA_TFLOPS, 4), traffic=traffic, traffic_source=traffic_source,

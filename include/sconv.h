@@ -221,19 +221,20 @@ int sconv_forward_fused(sconv_csr *h, const float *in, float *out, int32_t N, co
 enum {
     SCONV_KERNEL_ROWS = 1,      /* LDS tiles, a stream per row (plan.kernel 1) */
     SCONV_KERNEL_DIRECT = 2,    /* a thread per output */
-    SCONV_KERNEL_FLAT = 3,      /* LDS tiles, flat streams, a barrier per block; nt > 1: on the matrix cores */
+    SCONV_KERNEL_FLAT = 3,      /* LDS tiles, flat streams, a barrier per block */
     SCONV_KERNEL_FLOW = 4,      /* ... landing counters instead of barriers */
     SCONV_KERNEL_GATHER = 5,    /* straight from global memory, one position per lane */
     SCONV_KERNEL_GATHER4 = 6,   /* ... four positions per lane */
     SCONV_KERNEL_FC_GATHER = 7, /* ... fully connected layers */
-    SCONV_KERNEL_MFMA = 8       /* matrix cores, rather dense layers */
+    SCONV_KERNEL_MFMA = 8,      /* matrix cores, rather dense layers: three bf16 parts */
+    SCONV_KERNEL_FLAT_MC = 9    /* matrix cores, long rows: flat streams, two fp16 parts */
 };
 typedef struct {
     int32_t kernel;
     int32_t launches; /* of a call without bias and ReLU: phase images, the kernel, the reduction of partial sums */
-    int32_t mt, nt;   /* matrix cores: a workgroup takes 32 * mt filters and 128 * nt positions (mt, nt up to 2), or a wave
-                         takes 16 * mt filters and 16 * nt positions (flat streams, and mt > 2); gather: a wave takes 64 * mt
-                         positions; fully connected gather: mt lanes share a nonzero; LDS tiles: plan.t (nt 1); direct: 0, 0 */
+    int32_t mt, nt;   /* three bf16 parts: a workgroup takes 32 * mt filters and 128 * nt positions; flat streams on the matrix
+                         cores: a wave takes 16 * mt filters and 16 * nt positions; gather: a wave takes 64 * mt positions; fully
+                         connected gather: mt lanes share a nonzero; LDS tiles: plan.t (nt 1); direct: 0, 0 */
     int32_t splits;   /* workgroups (gather kernels: waves) that share a row's nonzeros */
 } sconv_route;
 int sconv_route_of(sconv_csr *h, int32_t N, sconv_route *route);

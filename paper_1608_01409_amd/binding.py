@@ -31,7 +31,7 @@ class sconv_route(C.Structure):
     _fields_ = [(n, C.c_int32) for n in ("kernel", "launches", "mt", "nt", "splits")]
 
 
-KERNELS = {1: "rows", 2: "direct", 3: "flat", 4: "flow", 5: "gather", 6: "gather4", 7: "fc_gather", 8: "mfma"}
+KERNELS = {1: "rows", 2: "direct", 3: "flat", 4: "flow", 5: "gather", 6: "gather4", 7: "fc_gather", 8: "mfma", 9: "flat_mc"}
 
 
 class sconv_machine(C.Structure):

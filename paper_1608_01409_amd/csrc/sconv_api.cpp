@@ -70,12 +70,12 @@ struct sconv_csr {
         std::map<int, Choice> choice_of_n;
         DeviceGather gather;
         DeviceMfma mfma;
-        DeviceLds mc;
-        bool mc_uploaded = false;
-        int mc_wexp = 0;
-        float mc_small = 0;
-        int64_t mc_bytes = 0;
     } conv_alt, fc_alt;
+    struct {                                 // convolutions on kFlatMc
+        DeviceLds dev;
+        FlatMcTiling packed;                 // as packed; nt and splits follow the batch size
+        bool uploaded = false;
+    } flat_mc;
     int max_row_nnz = 0;
     int shortest_row = 0;                    // of the rows that are not empty
     bool mc_ok = false;                      // rows and weights are such that the flat streams may run on the matrix cores
@@ -608,7 +608,6 @@ static const sconv_csr::Choice &choose_kernel(sconv_csr *h, bool fc, int N, doub
     const bool exact = three_parts ? row >= (c.mfma.splits <= 1 ? SCONV_MC_LONG_ROW : c.mfma.splits * SCONV_MC_LONG_ROW_SPLIT)
                                    : c.kind == sconv_csr::kLds && (lds_splits <= 1 || row >= lds_splits * SCONV_MC_ROW_SPLIT);
     if (!fc && exact && h->mc_ok && mfma_fits(h->desc, N, false) && choose_flat_mc(h->desc, h->canon, N, flushed, c.mc)) {
-        c.mc.for_dense = three_parts;
         const bool filled = h->desc.K / h->desc.groups >= kFlatMcFilled * c.mc.n_units * 16 * c.mc.mt;
         if (three_parts ? filled && c.mc.us * kFlatMcMfmaMargin < c.mfma.us : c.mc.us * kFlatMcMargin < lds_us) c.kind = sconv_csr::kFlatMc;
     } else {
@@ -656,7 +655,7 @@ static void release_mfma(DeviceMfma &dev)
 
 static bool resident(const sconv_csr *h, const sconv_csr::Alternatives &alt, const sconv_csr::Choice &c)
 {
-    if (c.kind == sconv_csr::kFlatMc) return alt.mc_uploaded;
+    if (c.kind == sconv_csr::kFlatMc) return h->flat_mc.uploaded;
     return c.kind == sconv_csr::kGather ? alt.gather.uploaded : alt.mfma.uploaded && (!h->short_rows || h->direct_uploaded);
 }
 
@@ -675,17 +674,15 @@ static int prepare_choice(sconv_csr *h, bool fc, const sconv_csr::Choice &c)
         else release_gather(alt.gather);
     } else if (c.kind == sconv_csr::kFlatMc) {
         PackedFlatMc p;
-        FlatMcTiling t = c.mc;
-        rc = pack_flat_mc(mfma_desc(h->desc), h->canon, t, p);
-        if (!rc) rc = upload(p.stream.data(), p.stream.size(), &alt.mc.pairs, &h->hip_err);
-        if (!rc) rc = upload(p.seg.data(), p.seg.size() * 4, &alt.mc.seg_ptr, &h->hip_err);
-        if (!rc) rc = upload(p.row_of.data(), p.row_of.size() * 4, &alt.mc.row_of, &h->hip_err);
-        if (!rc) rc = upload(p.choff.data(), p.choff.size() * 4, &alt.mc.store_tbl, &h->hip_err);
-        alt.mc_wexp = t.wexp;
-        alt.mc_small = t.small_sum;
-        alt.mc_bytes = t.stream_bytes;
-        if (!rc) alt.mc_uploaded = true;
-        else release_arrays(alt.mc);
+        DeviceLds &dev = h->flat_mc.dev;
+        h->flat_mc.packed = c.mc;
+        rc = pack_flat_mc(mfma_desc(h->desc), h->canon, h->flat_mc.packed, p);
+        if (!rc) rc = upload(p.stream.data(), p.stream.size(), &dev.pairs, &h->hip_err);
+        if (!rc) rc = upload(p.seg.data(), p.seg.size() * 4, &dev.seg_ptr, &h->hip_err);
+        if (!rc) rc = upload(p.row_of.data(), p.row_of.size() * 4, &dev.row_of, &h->hip_err);
+        if (!rc) rc = upload(p.choff.data(), p.choff.size() * 4, &dev.store_tbl, &h->hip_err);
+        if (!rc) h->flat_mc.uploaded = true;
+        else release_arrays(dev);
     } else {
         PackedMfma p;
         rc = alt.mfma.uploaded ? SCONV_OK : pack_mfma(h->desc, h->canon, c.mfma, p);
@@ -724,25 +721,21 @@ static int launch_choice(sconv_csr *h, bool fc, const sconv_csr::Choice &c, cons
     if (c.kind == sconv_csr::kGather)
         return fc ? launch_fc_gather(h->desc, alt.gather, c.gather, in, out, N, ep, stream, &h->hip_err)
                   : launch_gather(h->desc, alt.gather, c.gather, in, out, N, ep, stream, &h->hip_err);
-    if (c.kind == sconv_csr::kFlatMc) {
-        FlatMcTiling mc = c.mc;
-        mc.wexp = alt.mc_wexp;
-        mc.small_sum = alt.mc_small;
-        mc.stream_bytes = alt.mc_bytes;
-        LdsTiling t = {};
-        t.p.splits = mc.splits;
-        t.mc = &mc;
-        const Geometry g = geometry(h->desc);
-        const int64_t rows = fc ? h->desc.K : (int64_t)N * h->desc.K, inner = fc ? N : (int64_t)g.OH * g.OW;
-        return run_flat(h, h->desc, t, alt.mc, Lds2Layout(), in, out, N, rows, inner, ep, stream, ws);
-    }
-    if (c.mfma.splits <= 1) return launch_mfma(h->desc, c.mfma, alt.mfma, h->dev_direct, in, out, N, fc, ep, 0, stream, &h->hip_err);
+    FlatMcTiling mc = h->flat_mc.packed;
+    mc.nt = c.mc.nt;
+    mc.splits = c.mc.splits;
+    auto launch = [&](float *to, int64_t split_stride) {
+        return c.kind == sconv_csr::kFlatMc ? launch_flat_mc(h->desc, mc, h->flat_mc.dev, in, to, N, ep, split_stride, stream, &h->hip_err)
+                                            : launch_mfma(h->desc, c.mfma, alt.mfma, h->dev_direct, in, to, N, fc, ep, split_stride, stream, &h->hip_err);
+    };
+    const int splits = c.kind == sconv_csr::kFlatMc ? mc.splits : c.mfma.splits;
+    if (splits <= 1) return launch(out, 0);
     const Geometry g = geometry(h->desc);
     const int64_t rows = fc ? h->desc.K : (int64_t)N * h->desc.K, inner = fc ? N : (int64_t)g.OH * g.OW;
     float *parts;
-    int rc = take_parts(h, (size_t)(rows * inner) * c.mfma.splits * sizeof(float), ws, &parts);
-    if (!rc) rc = launch_mfma(h->desc, c.mfma, alt.mfma, h->dev_direct, in, parts, N, fc, ep, rows * inner, stream, &h->hip_err);
-    return rc ? rc : launch_reduce(parts, out, c.mfma.splits, rows, inner, h->desc.K, ep, stream, &h->hip_err);
+    int rc = take_parts(h, (size_t)(rows * inner) * splits * sizeof(float), ws, &parts);
+    if (!rc) rc = launch(parts, rows * inner);
+    return rc ? rc : launch_reduce(parts, out, splits, rows, inner, h->desc.K, ep, stream, &h->hip_err);
 }
 
 static int upload_flat(sconv_csr *h)
@@ -923,7 +916,7 @@ static int forward_impl(sconv_csr *h, const float *in, float *out, int32_t N, co
 static sconv_route route_of_choice(const sconv_desc &d, bool fc, const sconv_csr::Choice &c)
 {
     if (c.kind == sconv_csr::kMfma) return {SCONV_KERNEL_MFMA, c.mfma.splits > 1 ? 2 : 1, c.mfma.mt, c.mfma.nt, c.mfma.splits};
-    if (c.kind == sconv_csr::kFlatMc) return {c.mc.for_dense ? SCONV_KERNEL_MFMA : SCONV_KERNEL_FLAT, c.mc.splits > 1 ? 2 : 1, c.mc.mt, c.mc.nt, c.mc.splits};
+    if (c.kind == sconv_csr::kFlatMc) return {SCONV_KERNEL_FLAT_MC, c.mc.splits > 1 ? 2 : 1, c.mc.mt, c.mc.nt, c.mc.splits};
     const int kernel = fc ? SCONV_KERNEL_FC_GATHER : gather4_fits(d) ? SCONV_KERNEL_GATHER4 : SCONV_KERNEL_GATHER;
     return {kernel, 1, c.gather.t, 1, c.gather.split};
 }
@@ -1400,8 +1393,8 @@ extern "C" void sconv_destroy_csr(sconv_csr *h)
     for (sconv_csr::Alternatives *alt : {&h->conv_alt, &h->fc_alt}) {
         release_gather(alt->gather);
         release_mfma(alt->mfma);
-        release_arrays(alt->mc);
     }
+    release_arrays(h->flat_mc.dev);
     delete h;
 }
 

@@ -67,7 +67,6 @@ struct LdsTiling {
     int strip_rows;     // strip layout: rows of the block of positions one chunk covers (64 / strip), else 0
     int out_pos;        // floats from one output position to the next in the caller's layout (1 for NCHW)
     double us;          // what the cost model expects a launch to take (flat-stream tilings the search chose, else 0)
-    const struct FlatMcTiling *mc = nullptr; // set: the launch runs on the matrix cores, with this tiling and p.splits
 };
 
 struct PackedLds {
@@ -193,7 +192,6 @@ struct FlatMcTiling {
     int wexp;                // weights are packed times 2^wexp
     float small_sum;         // packed: sums below it are taken again where there are activations that have lost bits
     int64_t stream_bytes;
-    bool for_dense;          // the call would be the three-part kernel's
     double us;
 };
 // A record of a wave's stream: one matrix step.  [tile][high, low part][lane] 8 fp16 weights (the two a row keeps of each four

@@ -766,7 +766,6 @@ Lds2Layout nchw_layout(const sconv_desc &d, const LdsTiling &t)
 int launch_lds2(const sconv_desc &d, const LdsTiling &t, const DeviceLds &dev, const Lds2Layout &lay, const float *in,
                 float *out, int N, const Epilogue &ep, int64_t split_stride, void *stream, int *hip_err)
 {
-    if (t.mc) return launch_flat_mc(d, *t.mc, dev, in, out, N, ep, split_stride, stream, hip_err);
     const Geometry g = geometry(d);
     Lds2Args a;
     a.in = in;

@@ -65,6 +65,11 @@ int launch_mfma(const sconv_desc &, const MfmaTiling &, const DeviceMfma &dev, c
     if (!dev.wfrag || (dev.short_rows && !direct.trip)) std::abort();
     return ran("mfma");
 }
+int launch_flat_mc(const sconv_desc &, const FlatMcTiling &t, const DeviceLds &dev, const float *, float *, int, const Epilogue &, int64_t, void *, int *)
+{
+    if (!dev.pairs || !dev.seg_ptr || !dev.row_of || !dev.store_tbl || t.stream_bytes < 1 || t.nt < 2) std::abort();
+    return ran("flat_mc");
+}
 int upload(const void *, size_t bytes, void **dev, int *hip_err)
 {
     *dev = nullptr;
@@ -151,6 +156,8 @@ static std::string fc(sconv_csr *h, int N)
 }
 
 static const sconv_desc MID = {32, 13, 13, 50, 3, 3, 1, 1, 2}, FC = {600, 1, 1, 300, 1, 1, 1, 0, 1};
+// long rows: flat streams on the matrix cores at large batches
+static const sconv_desc LONG = {128, 13, 13, 256, 3, 3, 1, 1, 1}, LONG2 = {64, 27, 27, 96, 3, 3, 2, 0, 1}, LONGER = {472, 12, 12, 356, 3, 3, 1, 1, 1};
 static const char *const FLAT = "flat", *const FLAT2 = "flat+reduce";
 
 // What a tuning call measured holds for its batch size however many others follow.
@@ -370,13 +377,13 @@ static void first_call()
 // What sconv_route_of says is what the call launches.
 static void routes()
 {
-    const char *const names[] = {"", "rows", "direct", "flat", "flat", "gather", "gather", "fc_gather", "mfma"};
-    bool seen[9] = {};
+    const char *const names[] = {"", "rows", "direct", "flat", "flat", "gather", "gather", "fc_gather", "mfma", "flat_mc"};
+    bool seen[10] = {};
     auto check = [&](const sconv_route &r, const std::string &got, const sconv_desc &d, int N) {
-        std::string want = r.kernel >= 1 && r.kernel <= 8 ? names[r.kernel] : "?";
+        std::string want = r.kernel >= 1 && r.kernel <= 9 ? names[r.kernel] : "?";
         seen[r.kernel] = true;
         const bool lds = r.kernel == SCONV_KERNEL_ROWS || r.kernel == SCONV_KERNEL_FLAT || r.kernel == SCONV_KERNEL_FLOW;
-        const bool parts = r.splits > 1 && (lds || r.kernel == SCONV_KERNEL_MFMA);
+        const bool parts = r.splits > 1 && (lds || r.kernel == SCONV_KERNEL_MFMA || r.kernel == SCONV_KERNEL_FLAT_MC);
         if (lds && r.launches > 1 + parts) want = "phase+" + want;
         if (parts) want += "+reduce";
         CHECK(got == want, "C%d %dx%d K%d %dx%d stride %d pad %d N=%d: %s, by the route %s", d.C, d.H, d.W, d.K, d.R, d.S, d.stride, d.pad, N,
@@ -403,6 +410,19 @@ static void routes()
                             }
                             sconv_destroy_csr(h);
                         }
+    bool mc_parts = false;
+    for (const sconv_desc &d : {LONG, LONG2, LONGER})
+        for (double density : {0.12, 0.2, 0.95}) {
+            sconv_csr *h = make(d, density);
+            for (int N : {1, 8, 16, 34, 64, 100, 256}) {
+                sconv_route route;
+                if (sconv_route_of(h, N, &route)) std::abort();
+                check(route, forward(h, N), d, N);
+                mc_parts |= route.kernel == SCONV_KERNEL_FLAT_MC && route.splits > 1;
+            }
+            sconv_destroy_csr(h);
+        }
+    CHECK(mc_parts, "no call of the flat streams on the matrix cores splits the channels");
     for (double density : {0.02, 0.2, 0.9}) {
         sconv_csr *h = make(FC, density);
         for (int N : {4, 12, 64, 256, 1024, 2048, 5, 1028}) {
@@ -414,7 +434,47 @@ static void routes()
         }
         sconv_destroy_csr(h);
     }
-    for (int k = 1; k <= 8; ++k) CHECK(seen[k], "kernel %d takes none of the calls", k);
+    for (int k = 1; k <= 9; ++k) CHECK(seen[k], "kernel %d takes none of the calls", k);
+}
+
+// The flat streams on the matrix cores: kept as measured, prepared for the call without allocation, left when their arrays find
+// no room, uploaded once for all batch sizes.
+static void flat_mc()
+{
+    const std::string MC = "flat_mc";
+    sconv_csr *h = make(LONG, 0.2);
+    CHECK(noalloc(h, 256) == sconv_strerror(SCONV_ERR_PLAN), "never run: %s", launched.c_str());
+    CHECK(forward(h, 256) == MC && noalloc(h, 256) == MC, "%s", launched.c_str());
+    uploaded = 0;
+    CHECK(forward(h, 200) == MC && forward(h, 256) == MC && uploaded == 0, "%s, %zu bytes once more", launched.c_str(), uploaded);
+    cost = {{MC, 50.f}, {"mfma", 50.f}};
+    CHECK(sconv_tune(h, in, out, 256, 4, nullptr) == SCONV_OK && (forward(h, 256) == FLAT || launched == FLAT2), "measured against the model: %s", launched.c_str());
+    CHECK(noalloc(h, 256) == FLAT || launched == FLAT2, "%s", launched.c_str());
+    CHECK(forward(h, 200) == MC, "another batch size: %s", launched.c_str());
+    cost = {{"flat", 50.f}, {"mfma", 50.f}};
+    CHECK(sconv_tune(h, in, out, 256, 4, nullptr) == SCONV_OK && forward(h, 256) == MC, "measured: %s", launched.c_str());
+    for (int n = 10; n < 80; ++n) forward(h, n);
+    CHECK(forward(h, 256) == MC && noalloc(h, 256) == MC, "70 batch sizes later: %s", launched.c_str());
+    cost.clear();
+    sconv_destroy_csr(h);
+    for (int ok = 0; ok < 4; ++ok) { // (its arrays go up in order)
+        h = make(LONG, 0.2);
+        uploads_ok = ok;
+        uploads_fail = 1;
+        CHECK(forward(h, 256) == FLAT || launched == FLAT2, "%d uploads, then none: %s", ok, launched.c_str());
+        CHECK(forward(h, 256) == FLAT || launched == FLAT2, "again: %s", launched.c_str());
+        CHECK(forward(h, 200) == MC, "another batch size, room again: %s", launched.c_str());
+        sconv_destroy_csr(h);
+        uploads_ok = uploads_fail = 0;
+    }
+    // parts come out of the handle's scratch, or the caller's
+    h = make(LONGER, 0.95);
+    CHECK(forward(h, 34) == "flat_mc+reduce" && noalloc(h, 34) == "flat_mc+reduce", "%s", launched.c_str());
+    sconv_destroy_csr(h);
+    const sconv_plan plan = {3};
+    h = make(LONG, 0.2, &plan);
+    CHECK(forward(h, 256) == FLAT || launched == FLAT2, "a kernel was asked for: %s", launched.c_str());
+    sconv_destroy_csr(h);
 }
 
 static sconv_csr *rows_of(const sconv_desc &d, const std::vector<int> &nnz)
@@ -474,6 +534,7 @@ int main(int argc, char **argv)
     else if (what == "short_rows") short_rows();
     else if (what == "first_call") first_call();
     else if (what == "routes") routes();
+    else if (what == "flat_mc") flat_mc();
     else if (what == "gather_limits") gather_limits();
     else if (what == "unpacked_tilings") unpacked_tilings();
     else return 2;

@@ -25,12 +25,13 @@ def say(msg):
 
 
 def full_check(layer, w, x, oracle, what, plan=None, kernel=None):
-    """kernel: which one must serve the call ("lds": either variant of the flat-stream kernel)."""
+    """kernel: which one, or one of which, must serve the call ("lds": either variant of the flat-stream kernel)."""
     N = x.shape[0]
     say(f"{what} layer={layer.name} N={N} nnz={int(np.count_nonzero(w))}")
     h = B.sconv_create_csr(layer, w, plan)
     route = B.sconv_route_of(h, N)["kernel"]
-    assert kernel is None or (route in ("flat", "flow") if kernel == "lds" else route == kernel), route
+    kernels = () if kernel is None else (kernel,) if isinstance(kernel, str) else kernel
+    assert not kernels or route in kernels or ("lds" in kernels and route in ("flat", "flow")), route
     if plan is None and route not in ("flat", "flow"):
         full_check(layer, w, x, oracle, what + "-flat", B.sconv_rank_plans(h, N, 1)[0], "lds")
     xd = torch.from_numpy(x).cuda()
@@ -67,7 +68,7 @@ def test_config2_alexnet_batch256_every_image(oracle, li):
     name, N, dens = wl.CONFIGS[1][li]
     layer = wl.LAYERS[name]
     x, w = wl.make_case(1, li, layer, N, dens)
-    full_check(layer, w, x, oracle, f"config2-{name}", kernel="lds")
+    full_check(layer, w, x, oracle, f"config2-{name}", kernel="flat_mc" if name in ("conv3", "conv4") else "lds")
 
 
 @pytest.mark.parametrize("li", range(4))
@@ -87,7 +88,7 @@ def test_config3_density_sweep_batch256_every_image(oracle, li, dens):
     name, N, _ = wl.CONFIGS[1][li]
     layer = wl.LAYERS[name]
     x, w = wl.make_case(2, li, layer, N, dens)
-    full_check(layer, w, x, oracle, f"config3-{name}-x{dens}", kernel="mfma" if dens >= 0.3 else "lds")
+    full_check(layer, w, x, oracle, f"config3-{name}-x{dens}", kernel=("mfma", "flat_mc") if dens >= 0.3 else ("lds", "flat_mc"))
 
 
 @pytest.mark.parametrize("cluster", ["channels", "positions"])
@@ -107,7 +108,7 @@ def test_config5_googlenet_like_and_strided_batch64_every_image(oracle, li):
     name, N, dens = wl.CONFIGS[4][li]
     layer = wl.LAYERS[name]
     x, w = wl.make_case(4, li, layer, N, dens)
-    full_check(layer, w, x, oracle, f"config5-{name}", kernel="mfma" if name == "goog5x5" else "lds")
+    full_check(layer, w, x, oracle, f"config5-{name}", kernel="mfma" if name == "goog5x5" else "flat_mc")
 
 
 @pytest.mark.parametrize("li", range(2))

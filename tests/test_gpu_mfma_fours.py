@@ -31,7 +31,7 @@ def test_layers_against_the_oracle(oracle, shape):
     w[rng.random(w.shape) >= 0.7] = 0
     h = B.sconv_create_csr(layer, w)
     route = B.sconv_route_of(h, N)
-    assert route["kernel"] == "mfma" and route["mt"] <= 2, route
+    assert route["kernel"] == "mfma", route
     print(f"[gpu-case] {shape} {route}", flush=True)
     out = torch.full((N, layer.K, layer.OH, layer.OW), float("nan"), device="cuda")
     got = B.sconv_forward(h, torch.from_numpy(x).cuda(), out).cpu().numpy()

@@ -63,3 +63,7 @@ def test_calls_that_measured_slower_on_a_gather_kernel_do_not_go_there(program):
 
 def test_a_tiling_that_no_call_runs_is_not_packed(program):
     run(program, "unpacked_tilings")
+
+
+def test_the_flat_streams_on_the_matrix_cores(program):
+    run(program, "flat_mc")

@@ -35,7 +35,7 @@ def test_few_filters_of_a_tile_stay_on_the_three_part_kernel(per_group, tiles_of
     w = rng.standard_normal((layer.K, c // 2, 5, 5), dtype=np.float32)
     w[rng.random(w.shape) >= density] = 0
     route = B.sconv_route_of(B.sconv_create_csr(layer, w), n)
-    assert route["kernel"] == "mfma" and (route["mt"] == 1 if tiles_of_16 else route["mt"] > 2), route
+    assert route["kernel"] == ("mfma" if tiles_of_16 else "flat_mc"), route
 
 
 def test_the_shortest_row_decides():
@@ -52,10 +52,10 @@ def test_the_shortest_row_decides():
         return B.sconv_route_of(B.sconv_create_csr(layer, w), n)
 
     full = route(256, 1, 256, 0.12, None)
-    assert full["kernel"] == "flat" and full["nt"] == 4, full
+    assert full["kernel"] == "flat_mc" and full["nt"] == 4, full
     for length, nt in ((0, 4), (160, 4), (159, 2), (72, 2), (71, 1), (16, 1)):
         r = route(256, 1, 256, 0.12, length)
-        assert r["kernel"] in ("flat", "flow") and r["nt"] == nt, (length, r)
+        assert r["kernel"] in (("flat_mc",) if nt > 1 else ("flat", "flow")) and r["nt"] == nt, (length, r)
     for length, there in ((None, True), (0, True), (740, True), (739, False), (100, False)):
         r = route(384, 2, 256, 0.5, length)
-        assert r["kernel"] == "mfma" and (r["mt"] > 2) == there, (length, r)
+        assert r["kernel"] == ("flat_mc" if there else "mfma"), (length, r)
