@@ -1471,15 +1471,6 @@ int pack_flat_mc(const sconv_desc &layer, const Canonical &c, FlatMcTiling &t, P
     std::frexp(most, &e);
     t.wexp = most > 0 ? 14 - e : 0;
     const float scale = std::ldexp(1.f, t.wexp);
-    // What is lost of small activations (below 2^-13, see the kernel) takes 2^-36.8 times a row's norm from its sum: 2^-25 of one of
-    // 2^-11.8 times the norm.  2^-8, for rows and activations of one sign, whose errors add up.
-    double norm = 0;
-    for (int k = 0; k < d.K; ++k) {
-        double sum = 0;
-        for (int j = c.rowptr[k]; j < c.rowptr[k + 1]; ++j) sum += (double)c.val[j] * c.val[j];
-        norm = std::max(norm, sum);
-    }
-    t.small_sum = (float)std::ldexp(std::sqrt(norm), t.wexp - 8);
     std::vector<int32_t> col_slot((size_t)g.Cg * d.R * d.S); // slot * 8 + channel of the octet
     std::vector<int32_t> slot_off(slots), block_first(t.nblk + 1);
     for (int b = 0; b <= t.nblk; ++b) block_first[b] = std::min(b * t.g8, octets) * taps;
@@ -1510,7 +1501,7 @@ int pack_flat_mc(const sconv_desc &layer, const Canonical &c, FlatMcTiling &t, P
         int tiles, nth;
     };
     // one wave's filters: its records, numbered from 0 until all are there
-    auto pack_unit = [&](int unit, std::vector<uint8_t> &stream) -> int {
+    auto pack_unit = [&](int unit, std::vector<uint8_t> &stream, double &norm) -> int {
         std::vector<uint8_t> mask((size_t)rows * slots);   // channels of an octet that a row has
         std::vector<float> val((size_t)slots * 8);         // one row's weights
         std::vector<uint8_t> need((size_t)t.mt * slots);   // how often a tile needs an octet: 0, 1, 2
@@ -1603,7 +1594,12 @@ int pack_flat_mc(const sconv_desc &layer, const Canonical &c, FlatMcTiling &t, P
         }
         for (int r = 0; r < n_rows; ++r) {
             const int k = row_of[r], m = r / 16, row = r % 16;
-            for (int j = c.rowptr[k]; j < c.rowptr[k + 1]; ++j) val[col_slot[c.colidx[j]]] = c.val[j];
+            double sum = 0;
+            for (int j = c.rowptr[k]; j < c.rowptr[k + 1]; ++j) {
+                val[col_slot[c.colidx[j]]] = c.val[j];
+                sum += (double)c.val[j] * c.val[j];
+            }
+            norm = std::max(norm, sum);
             for (int i = 0; i < slots; ++i) {
                 const unsigned both = mask[(size_t)r * slots + i];
                 if (!both) continue;
@@ -1634,12 +1630,13 @@ int pack_flat_mc(const sconv_desc &layer, const Canonical &c, FlatMcTiling &t, P
     const int n_all = d.groups * t.n_units;
     std::vector<std::vector<uint8_t>> streams(n_all);
     std::vector<int> status(n_all, SCONV_OK);
+    std::vector<double> norm(n_all, 0.0);    // squared, of a unit's largest row
     std::atomic<int> next(0);
     auto work = [&]() {
         for (int u = next++; u < n_all; u = next++) {
             try {
-                status[u] = pack_unit(u, streams[u]);
-            } catch (const std::bad_alloc &) {
+                status[u] = pack_unit(u, streams[u], norm[u]);
+            } catch (...) { // (out of a thread it would end the process)
                 status[u] = SCONV_ERR_NOMEM;
             }
         }
@@ -1647,7 +1644,7 @@ int pack_flat_mc(const sconv_desc &layer, const Canonical &c, FlatMcTiling &t, P
     std::vector<std::thread> threads;
     try {
         for (int i = 1; c.val.size() > 16384 && i < std::min(n_all, 8); ++i) threads.emplace_back(work);
-    } catch (const std::exception &) { // (no more threads: the ones there are do the work)
+    } catch (...) { // (no more threads: the ones there are do the work)
     }
     work();
     for (std::thread &th : threads) th.join();
@@ -1662,6 +1659,9 @@ int pack_flat_mc(const sconv_desc &layer, const Canonical &c, FlatMcTiling &t, P
     for (const auto &v : streams) out.stream.insert(out.stream.end(), v.begin(), v.end());
     out.stream.resize(out.stream.size() + rec); // the kernel reads one record ahead
     t.stream_bytes = (int64_t)out.stream.size();
+    // What is lost of small activations (below 2^-13, see the kernel) takes 2^-36.8 times a row's norm from its sum: 2^-25 of one of
+    // 2^-11.8 times the norm.  2^-8, for rows and activations of one sign, whose errors add up.
+    t.small_sum = (float)std::ldexp(std::sqrt(*std::max_element(norm.begin(), norm.end())), t.wexp - 8);
     if (t.phased)
         for (int cv = 0; cv < octets * 8; ++cv) {
             const int ph = cv / g.Cg, cl = cv % g.Cg;
