@@ -608,13 +608,15 @@ static __device__ __forceinline__ bool mc_tile(const FlatMcArgs &a, int bid, cha
             b += !over;
         }
         // What the split did not carry: sums that are not finite, and sums that only small activations went into.  Scaled below
-        // 2^-13 an activation has lost more than the two parts of a larger one lose (2^-23 of it), below 2^-18 it may be gone.
+        // 2^-13 an activation has lost more than the two parts of a larger one lose (2^-23 of it), below 2^-35 it may be gone.
         // That counts where what goes into a sum is not much larger than what is lost, 2^-36.8 a product on average.  A sum may
         // be small by itself; the second accumulator, of the same size and no relation to it, is small as well only where all is.
-        // (Ordinary inputs: one value in 3e7 of a normal distribution is lost, a workgroup stages 5e4 to 2e5 of them.)
+        // (Ordinary inputs: one value in 3e7 of a normal distribution is below 2^-13, a workgroup stages 5e4 to 2e5 of them.  Sums
+        // of 0, empty filters among them, count only where activations may be gone: with 2^-18 for that, 3 % of such calls took twice
+        // as long.)
         volatile unsigned *const flag = word + 1;      // again; activations: byte 0 small, byte 1 gone; sums: byte 0 small, byte 1 small or 0
         volatile unsigned char *const lost = reinterpret_cast<volatile unsigned char *>(flag + 1), *const low = lost + 4;
-        if (least < ((unsigned)(114 - expo) << 24) - 1u) lost[least < ((unsigned)(109 - expo) << 24) - 1u] = 1;
+        if (least < ((unsigned)(114 - expo) << 24) - 1u) lost[least < ((unsigned)max(92 - expo, 0) << 24) - 1u] = 1;
         bool bad = false;
 #pragma unroll
         for (int m = 0; m < MT; ++m)
