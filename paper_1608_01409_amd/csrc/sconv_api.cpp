@@ -564,11 +564,6 @@ static const double kMfmaMargin = 1.15;
 // and 1.0 one of 20 random calls that went there was 14 % slower; as they are, 16 of 17 gain 11-84 %, the other is below.
 static const double kFlatMcMargin = 1.0, kFlatMcMfmaMargin = 1.15;
 
-// A group's filters fill at least this share of the units' rows for a call to leave the three-part kernel, whose tiles are 16
-// filters high where these are 32 and more: 15 of 32 filters 225 -> 266 us, 17 of 32 89 -> 97, 20 of 32 52 -> 60, but 42 of 48
-// 107 -> 82, 86 of 96 177 -> 159, 97 of 128 179 -> 147.
-static const double kFlatMcFilled = 0.7;
-
 // The LDS path's time for N images: the flat-stream kernel's, and for layers that need phase images the pass that writes
 // them (a launch, and their bytes written and read).
 static double planned_us(const sconv_csr *h, int N, double flat_us, int phase_cg)
@@ -608,8 +603,7 @@ static const sconv_csr::Choice &choose_kernel(sconv_csr *h, bool fc, int N, doub
     const bool exact = three_parts ? row >= (c.mfma.splits <= 1 ? SCONV_MC_LONG_ROW : c.mfma.splits * SCONV_MC_LONG_ROW_SPLIT)
                                    : c.kind == sconv_csr::kLds && (lds_splits <= 1 || row >= lds_splits * SCONV_MC_ROW_SPLIT);
     if (!fc && exact && h->mc_ok && mfma_fits(h->desc, N, false) && choose_flat_mc(h->desc, h->canon, N, flushed, c.mc)) {
-        const bool filled = h->desc.K / h->desc.groups >= kFlatMcFilled * c.mc.n_units * 16 * c.mc.mt;
-        if (three_parts ? filled && c.mc.us * kFlatMcMfmaMargin < c.mfma.us : c.mc.us * kFlatMcMargin < lds_us) c.kind = sconv_csr::kFlatMc;
+        if (three_parts ? c.mc.us * kFlatMcMfmaMargin < c.mfma.us : c.mc.us * kFlatMcMargin < lds_us) c.kind = sconv_csr::kFlatMc;
     } else {
         c.mc = FlatMcTiling();
     }

@@ -1380,7 +1380,9 @@ bool choose_flat_mc(const sconv_desc &layer, const Canonical &csr, int N, bool f
             if (splits > 1 && out_bytes * splits > SCONV_NOALLOC_SCRATCH_BYTES) continue;
             const int blocks = ceil_div(t.nblk, splits), positions = 16 * nt * pos_waves;
             const double wgs = std::ceil(P / positions) * (t.n_units / wr) * d.groups * splits, per_cu = wgs / 256.0;
-            const double steps = (double)blocks / t.nblk * steps_total * mt * nt, stored = 16.0 * mt * wr * positions * 4 / 6900.0;
+            // (a column that is read feeds half as many products with two row tiles as with four; with two of columns as well that is
+            // not hidden: 12 layers took 1.07-1.5 times what they were read as, the longer the more, the other shapes 0.8-1.2)
+            const double steps = (double)blocks / t.nblk * steps_total * mt * nt * (mt == 2 && nt == 2 ? 1.45 : 1.0), stored = 16.0 * mt * wr * positions * 4 / 6900.0;
             const double cells = blocks * rows_at[nt / 2 - 1] * t.Wl * std::min(t.g8, ceil_div(t.c_virtual, 8));
             const double stage = 0.66 * blocks + cells * (wide ? 0.00086 : 0.0018);
             const double two = 3.3 + stage + steps * (nt == 4 ? 0.080 : 0.092) + stored;     // workgroups on a CU

@@ -26,16 +26,24 @@ def test_records_as_the_kernel_reads_them(tmp_path):
     assert res.returncode == 0, res.stdout[-4000:] + res.stderr[-2000:]
 
 
-@pytest.mark.parametrize("per_group,tiles_of_16", [(15, True), (97, False)])
-def test_few_filters_of_a_tile_stay_on_the_three_part_kernel(per_group, tiles_of_16):
-    """A group's 15 filters would fill half of the flat streams' smallest tile (18 % slower); 97 of 128 are enough."""
-    c, hw, n, density = (114, 54, 87, 0.72) if tiles_of_16 else (246, 23, 45, 0.45)
-    layer = wl.Layer("few", C=c, H=hw, W=hw, K=2 * per_group, R=5, S=5, stride=1, pad=2, groups=2)
+# channels, height and width, batch, density, filters of a group, groups; what they took on the three-part kernel and here, us
+@pytest.mark.parametrize("c,hw,n,density,per_group,groups,there", [
+    (114, 54, 87, 0.72, 15, 2, False),   # 225 266
+    (131, 41, 89, 0.65, 24, 1, False),   # 165 190
+    (278, 53, 25, 0.74, 18, 2, False),   # 163 204
+    (164, 26, 108, 0.88, 12, 1, False),  # 99 126
+    (204, 15, 88, 0.48, 17, 2, False),   # 47 58
+    (246, 23, 45, 0.45, 97, 2, True),    # 179 147
+    (472, 21, 106, 0.454, 39, 2, True),  # 300 195
+])
+def test_few_filters_stay_on_the_three_part_kernel(c, hw, n, density, per_group, groups, there):
+    """Filters that fill two row tiles at most keep a wave waiting for columns: slower than the three-part kernel."""
+    layer = wl.Layer("few", C=c, H=hw, W=hw, K=groups * per_group, R=5, S=5, stride=1, pad=2, groups=groups)
     rng = np.random.default_rng(3)
-    w = rng.standard_normal((layer.K, c // 2, 5, 5), dtype=np.float32)
+    w = rng.standard_normal((layer.K, layer.Cg, 5, 5), dtype=np.float32)
     w[rng.random(w.shape) >= density] = 0
     route = B.sconv_route_of(B.sconv_create_csr(layer, w), n)
-    assert route["kernel"] == ("mfma" if tiles_of_16 else "flat_mc"), route
+    assert route["kernel"] == ("flat_mc" if there else "mfma"), route
 
 
 def test_the_shortest_row_decides():
