@@ -604,7 +604,9 @@ static __device__ __forceinline__ bool mc_tile(const FlatMcArgs &a, int bid, cha
                 }
             };
             load_cols(c0, 0, r0.off);
-            mc_walk_block(r0, n_shared, n_private, load_record, shared_step, private_step, flush);
+            mc_walk_block(r0, n_shared, n_private, load_record, shared_step, private_step, [&](int left) INLINE {
+                if (left || b + 1 < b_end) flush();          // (the last ones are added in sum_of)
+            });
             b += !over;
         }
         // What the split did not carry: sums that are not finite, and sums that only small activations went into.  Scaled below

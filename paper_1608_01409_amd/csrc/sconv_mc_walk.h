@@ -16,7 +16,8 @@ template <class Seg>
 SCONV_MC_WALK int mc_block_at(const Seg &seg, int b, int b_first, int record_bytes) { return (seg[2 * b] - seg[2 * b_first]) * record_bytes; }
 
 // The steps of one block; r0 holds the record that stands at the block's beginning.  load(r) takes the stream's next record;
-// the steps take their own record and the `off` of the one that follows (some record's, if none follows), shared ones first; flush() follows every sixth step.
+// the steps take their own record and the `off` of the one that follows (some record's, if none follows), shared ones first; flush(steps left) follows
+// every sixth step.
 template <class Record, class Load, class Shared, class Private, class Flush>
 SCONV_MC_WALK void mc_walk_block(Record &r0, int n_shared, int n_private, Load load, Shared shared, Private own, Flush flush)
 {
@@ -33,7 +34,7 @@ SCONV_MC_WALK void mc_walk_block(Record &r0, int n_shared, int n_private, Load l
             one(r0, r1);
             one(r1, r0);
             if (++pairs == 3) {
-                flush();
+                flush(left);
                 pairs = 0;
             }
         }

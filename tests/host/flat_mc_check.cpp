@@ -71,7 +71,7 @@ static void walk(const PackedFlatMc &p, const FlatMcTiling &t, int units, const 
                         own = steps >= n_shared;
                     };
                     own = n_shared == 0;
-                    mc_walk_block(r0, n_shared, n_private, load, step, step, [] {});
+                    mc_walk_block(r0, n_shared, n_private, load, step, step, [&](int left) { CHECK(left == n_shared + n_private - steps, "%s", what); });
                     CHECK(steps == n_shared + n_private, "%s", what);
                     empty_blocks += splits == 1 && steps == 0 && b + 1 < t.nblk;
                 }
