@@ -180,14 +180,14 @@ static __device__ __forceinline__ Tile tile_of(const MfmaArgs &a, int bid)
     return t;
 }
 
-// again = false: a workgroup's sums, stored with the epilogue, or without it and true if some are not finite.
-// again = true: those sums once more (see above).
 // Four neighbouring cells x 8 channels on their way into LDS, and where they go (all ones: nowhere).
 struct Four {
     f32x4 x[8];
     unsigned at;
 };
 
+// again = false: a workgroup's sums, stored with the epilogue, or without it and true if some are not finite.
+// again = true: those sums once more (see above).
 template <int MT, int NT, bool again>
 static __device__ __forceinline__ bool multiply_tile(const MfmaArgs &a, int bid, char *lds)
 {

@@ -187,7 +187,7 @@ static void check(const sconv_desc &layer, int N, double density, bool skewed, b
             const double want = there ? c.val[j] : 0.0;
             j += there;
             CHECK(seen[(size_t)k * cols + i] == (there ? 1 : 0), "row %d column %d packed %d times: %s", k, i, seen[(size_t)k * cols + i], what);
-            CHECK(std::fabs(got[(size_t)k * cols + i] - want) <= std::fabs(want) * 0x1p-22, "row %d column %d: %s", k, i, what);
+            CHECK(std::fabs(got[(size_t)k * cols + i] - want) <= std::fabs(want) * 0x1p-23, "row %d column %d: %s", k, i, what);
         }
     }
     for (size_t i = 0; i < p.seg.size(); i += 2) twice += p.seg[i + 1] & 0xffff;
