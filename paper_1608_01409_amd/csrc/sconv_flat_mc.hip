@@ -468,6 +468,7 @@ static __device__ __forceinline__ bool mc_tile(const FlatMcArgs &a, int bid, cha
         };
         __syncthreads();                     // the table is there
         bool unscaled = true;
+        int since = 0;                       // steps since the totals were added to
         for (int b = b_first; b < b_end;) {
             most = 0.f;
             if (wide) {
@@ -604,7 +605,7 @@ static __device__ __forceinline__ bool mc_tile(const FlatMcArgs &a, int bid, cha
                 }
             };
             load_cols(c0, 0, r0.off);
-            mc_walk_block(r0, n_shared, n_private, load_record, shared_step, private_step, [&](int left) INLINE {
+            mc_walk_block(r0, n_shared, n_private, since, load_record, shared_step, private_step, [&](int left) INLINE {
                 if (left || b + 1 < b_end) flush();          // (the last ones are added in sum_of)
             });
             b += !over;
@@ -717,6 +718,7 @@ static __device__ __forceinline__ bool mc_tile(const FlatMcArgs &a, int bid, cha
         auto pass = [&](int window) INLINE {
             clear();
             wpos = 0;
+            int since = 0;
             const float scale = __uint_as_float((unsigned)(242 - 26 * min(window, 9)) << 23);
             for (int b = b_first; b < b_end; ++b) {
                 __syncthreads();
@@ -759,7 +761,10 @@ static __device__ __forceinline__ bool mc_tile(const FlatMcArgs &a, int bid, cha
                             else multiply(r, c, t, m, m + 1);
                         }
                     }
-                    if (window != 31 && i % 6 == 5) flush();
+                    if (window != 31 && ++since == 6) {
+                        flush();
+                        since = 0;
+                    }
                 }
             }
         };

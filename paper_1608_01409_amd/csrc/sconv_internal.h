@@ -214,14 +214,14 @@ struct PackedFlatMc {
 // replace.  Relative error of a row in 1e-8, here / there, rectified normal inputs, the mean of 100 and more rows a length:
 //   sums without totals (64 x 64 a wave) against the vector units' chains: 120 nonzeros 14.3 / 13.7, 150 15.4 / 15.3, 160 15.6 / 15.8
 #define SCONV_MC_ROW 160
-//   with totals against the chains: 50 9.1 / 9.0, 60 9.2 / 9.8, 75 9.3 / 10.8
+//   with totals against the chains: 50 9.3 / 9.0, 60 9.4 / 9.9, 70 9.7 / 10.8
 #define SCONV_MC_FLUSHED_ROW 72
-//   totals in up to three parts against chains in two parts: 100 10.2 / 9.6, 120 10.4 / 10.5; in four: 210 10.6 / 10.4, 240
-//   10.6 / 10.9; so many per part of a flat-stream tiling that splits the channels
+//   totals in up to three parts against chains in two parts: 120 10.4 / 10.3, 150 10.6 / 11.4; in four: 180 10.5 / 10.3,
+//   210 10.5 / 10.8; so many per part of a flat-stream tiling that splits the channels
 #define SCONV_MC_ROW_SPLIT 80
-//   totals against the three-part kernel: 650 11.7 / 11.6, 700 11.8 / 11.8, 750 11.9 / 12.6
+//   totals against the three-part kernel: 650 11.7 / 11.4, 700 11.8 / 12.0, 750 11.9 / 12.4
 #define SCONV_MC_LONG_ROW 740
-//   ... where that kernel splits the channels, per part: in two 1200 12.1 / 11.8, 1400 12.3 / 12.7; three 1800 12.0 / 11.8, 2000
+//   ... where that kernel splits the channels, per part: in two 1000 11.4 / 10.9, 1200 11.6 / 11.8; three 1800 12.0 / 11.8, 2000
 //   12.4 / 12.6; four 2600 12.5 / 12.3, 2800 12.6 / 12.8
 #define SCONV_MC_LONG_ROW_SPLIT 1100
 // From this density on most octets are needed twice.

@@ -50,6 +50,7 @@ static void walk(const PackedFlatMc &p, const FlatMcTiling &t, int units, const 
             const int32_t *seg = &p.seg[(size_t)u * t.nblk * 2];
             for (int b_first = 0; b_first < t.nblk; b_first += per) {
                 int64_t pos = 0;
+                int since = 0, added = 0, done = 0;   // steps that the totals had when they were last added to, all steps
                 Record r0;
                 auto load = [&](Record &r) {
                     r.at = r.off = seg[2 * b_first] + (int)(pos / rec);
@@ -71,7 +72,13 @@ static void walk(const PackedFlatMc &p, const FlatMcTiling &t, int units, const 
                         own = steps >= n_shared;
                     };
                     own = n_shared == 0;
-                    mc_walk_block(r0, n_shared, n_private, load, step, step, [&](int left) { CHECK(left == n_shared + n_private - steps, "%s", what); });
+                    mc_walk_block(r0, n_shared, n_private, since, load, step, step, [&](int left) {
+                        CHECK(left == n_shared + n_private - steps, "%s", what);
+                        CHECK(done + steps - added <= 7, "%d steps in the accumulators: %s", done + steps - added, what);
+                        added = done + steps;
+                    });
+                    done += steps;
+                    CHECK(done - added <= 6, "%d steps in the accumulators after block %d: %s", done - added, b, what);
                     CHECK(steps == n_shared + n_private, "%s", what);
                     empty_blocks += splits == 1 && steps == 0 && b + 1 < t.nblk;
                 }

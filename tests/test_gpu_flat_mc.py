@@ -175,16 +175,20 @@ def test_small_images_lose_no_bits_beside_large_ones(shape, binades, alike):
     assert bool((err <= chain).all()), (err / chain).tolist()
 
 
-# the shortest rows that go there, by what their layer would run on otherwise: C, K, groups, N, nonzeros, the plan or kernel left
-SHORTEST = [(40, 256, 1, 256, 72, dict(kernel=2)), (256, 384, 1, 256, 160, dict(kernel=2)), (384, 384, 2, 96, 740, "mfma")]
+# the shortest rows that go there, by what their layer would run on otherwise: C, H = W, stride, K, groups, N, nonzeros, the kernel
+# left
+SHORTEST = [
+    (40, 13, 1, 256, 1, 256, 72, "lds"), (256, 13, 1, 384, 1, 256, 160, "lds"), (384, 13, 1, 384, 2, 96, 740, "mfma"),
+    (408, 53, 2, 128, 1, 34, 330, "lds"), (197, 51, 2, 384, 1, 20, 800, "mfma"),     # channel blocks of few steps
+]
 
 
 @pytest.mark.parametrize("case", SHORTEST)
 def test_no_row_is_further_off_than_on_the_kernel_that_it_leaves(case):
-    """Rows of the least length and others: by length, no further from 64 bits than fp32 chains (the direct kernel), or than the
-    three-part kernel, which serves the same layer with one of its rows shortened."""
-    C, K, groups, N, least, left = case
-    layer = layer_of((C, 13, 13, K, 3, 3, 1, 1, groups))
+    """Rows of the least length and others: by length, no further from 64 bits than on the flat-stream kernel with the tiling ranked
+    first, or than on the three-part kernel, which serves the same layer with one of its rows shortened."""
+    C, hw, stride, K, groups, N, least, left = case
+    layer = layer_of((C, hw, hw, K, 3, 3, stride, 1, groups))
     cols = layer.Cg * 9
     rng = np.random.default_rng(21)
     lengths = np.array([least, least + least // 8, 2 * least])[np.arange(K) % 3]
@@ -192,7 +196,7 @@ def test_no_row_is_further_off_than_on_the_kernel_that_it_leaves(case):
     for k in range(K):
         w[k, rng.permutation(cols)[:lengths[k]]] = rng.standard_normal(lengths[k]) * 0.01
     w = w.reshape(K, layer.Cg, 3, 3)
-    xd = torch.from_numpy(np.maximum(rng.standard_normal((N, C, 13, 13)), 0).astype(np.float32)).cuda()
+    xd = torch.from_numpy(np.maximum(rng.standard_normal((N, C, hw, hw)), 0).astype(np.float32)).cuda()
     h = B.sconv_create_csr(layer, w)
     route = B.sconv_route_of(h, N)
     assert on_matrix_cores(route), route
@@ -200,12 +204,12 @@ def test_no_row_is_further_off_than_on_the_kernel_that_it_leaves(case):
     v = w.copy()
     if left == "mfma":
         v[0].reshape(-1)[np.flatnonzero(v[0].reshape(-1))[300:]] = 0
-    other = B.sconv_create_csr(layer, v, None if left == "mfma" else left)
+    other = B.sconv_create_csr(layer, v, None if left == "mfma" else B.sconv_rank_plans(h, N, 1)[0])
     if left == "mfma":
         assert B.sconv_route_of(other, N)["kernel"] == "mfma"
     x64, kg = xd.double(), K // groups
     exact = torch.cat([torch.cat([torch.from_numpy(w[g * kg:(g + 1) * kg]).cuda().double().reshape(kg, -1) @ torch.nn.functional.unfold(
-        x64[i:i + 1, g * layer.Cg:(g + 1) * layer.Cg], (3, 3), padding=1)[0] for g in range(groups)])[None] for i in range(N)])
+        x64[i:i + 1, g * layer.Cg:(g + 1) * layer.Cg], (3, 3), padding=1, stride=stride)[0] for g in range(groups)])[None] for i in range(N)])
     err, was = (((B.sconv_forward(g, xd).double().flatten(2) - exact).transpose(0, 1).flatten(1).norm(dim=1) /
                  exact.transpose(0, 1).flatten(1).norm(dim=1)).cpu().numpy() for g in (h, other))
     for n in np.unique(lengths):
