@@ -68,7 +68,7 @@ def test_config2_alexnet_batch256_every_image(oracle, li):
     name, N, dens = wl.CONFIGS[1][li]
     layer = wl.LAYERS[name]
     x, w = wl.make_case(1, li, layer, N, dens)
-    full_check(layer, w, x, oracle, f"config2-{name}", kernel="flat_mc" if name in ("conv3", "conv4") else "lds")
+    full_check(layer, w, x, oracle, f"config2-{name}", kernel="flat_mc" if name == "conv3" else "lds")
 
 
 @pytest.mark.parametrize("li", range(4))

@@ -54,8 +54,8 @@ def layer_of(dims):
 
 # C, H, W, K, R, S, stride, pad, groups, N, density
 SHAPES = [
-    (256, 13, 13, 384, 3, 3, 1, 1, 1, 70, 0.10),    # several blocks, filters and positions of whole and part workgroups
-    (96, 27, 27, 256, 5, 5, 1, 2, 2, 41, 0.10),
+    (256, 13, 13, 384, 3, 3, 1, 1, 1, 70, 0.13),    # several blocks, filters and positions of whole and part workgroups
+    (96, 27, 27, 256, 5, 5, 1, 2, 2, 41, 0.13),
     (384, 13, 13, 384, 3, 3, 1, 1, 2, 70, 0.15),
     (192, 28, 28, 128, 3, 3, 1, 1, 1, 33, 0.12),
     (3, 99, 99, 96, 11, 11, 4, 0, 1, 100, 0.30),    # phases of a strided layer, a cell per lane
@@ -65,7 +65,7 @@ SHAPES = [
     (60, 20, 20, 250, 3, 3, 1, 1, 1, 32, 0.20),
     (99, 20, 20, 150, 3, 3, 1, 1, 1, 32, 0.13),
     (130, 21, 5, 96, 3, 3, 1, 1, 1, 256, 0.19),     # a row of five, the last four of it shifted back
-    (300, 7, 7, 150, 3, 3, 1, 1, 1, 256, 0.10),
+    (300, 7, 7, 150, 3, 3, 1, 1, 1, 256, 0.13),
     (64, 18, 18, 96, 3, 3, 1, 3, 1, 64, 0.20),      # padding as wide as the filter
     (400, 28, 28, 64, 1, 1, 1, 0, 1, 100, 0.30),    # 1x1: positions in fours
     (500, 27, 27, 128, 1, 1, 1, 0, 1, 64, 0.22),    # 1x1: images that no four divides
@@ -99,7 +99,7 @@ PRUNED = [
     (160, 27, 27, 80, 3, 3, 2, 1, 1, 160, 0.15, 30, 90),      # staged a cell per lane
     (472, 12, 12, 356, 3, 3, 1, 1, 1, 34, 0.94, 0, 100),      # channels split over workgroups
     (472, 12, 12, 356, 3, 3, 1, 1, 1, 34, 0.94, 300, 400),
-    (256, 13, 13, 385, 3, 3, 1, 1, 1, 70, 0.14, -1, 0),
+    (256, 13, 13, 385, 3, 3, 1, 1, 1, 70, 0.17, -1, 0),
 ]
 
 
@@ -116,7 +116,7 @@ def test_channels_without_weights(oracle, shape):
     check(oracle, layer, N, x, w)
 
 
-MIXED = [(150, 17, 17, 256, 3, 3, 1, 1, 1, 100, 0.18), (99, 20, 20, 150, 3, 3, 1, 1, 1, 32, 0.13), (256, 13, 13, 384, 3, 3, 1, 1, 1, 70, 0.10), (472, 12, 12, 356, 3, 3, 1, 1, 1, 34, 0.94)]
+MIXED = [(150, 17, 17, 256, 3, 3, 1, 1, 1, 100, 0.18), (99, 20, 20, 150, 3, 3, 1, 1, 1, 32, 0.13), (256, 13, 13, 384, 3, 3, 1, 1, 1, 70, 0.13), (472, 12, 12, 356, 3, 3, 1, 1, 1, 34, 0.94)]
 
 
 @pytest.mark.parametrize("shape", MIXED)
