@@ -564,6 +564,8 @@ static const double kMfmaMargin = 1.15;
 // calls that went there from the former at 1.0, 12 took more than 2 % longer, two of them more than 10 %; at 1.01 it is 6 of 341,
 // none more than 10 %, and at 1.03 one less, while 27 more stay that would gain 1.12x.  None of 47 from the latter was slower.
 static const double kFlatMcMargin = 1.01, kFlatMcMfmaMargin = 1.15;
+// Strided layers take longer on the vector units than their model says: 32 of them 1.09-2.2 times (stride 1: 1.06 on average).
+static const double kFlatPhasedReadsLow = 1.09;
 
 // The LDS path's time for N images: the flat-stream kernel's, and for layers that need phase images the pass that writes
 // them (a launch, and their bytes written and read).
@@ -604,7 +606,7 @@ static const sconv_csr::Choice &choose_kernel(sconv_csr *h, bool fc, int N, doub
     const bool exact = three_parts ? row >= (c.mfma.splits <= 1 ? SCONV_MC_LONG_ROW : c.mfma.splits * SCONV_MC_LONG_ROW_SPLIT)
                                    : c.kind == sconv_csr::kLds && (lds_splits <= 1 || row >= lds_splits * SCONV_MC_ROW_SPLIT);
     if (!fc && exact && h->mc_ok && mfma_fits(h->desc, N, false) && choose_flat_mc(h->desc, h->canon, N, flushed, c.mc)) {
-        if (three_parts ? c.mc.us * kFlatMcMfmaMargin < c.mfma.us : c.mc.us * kFlatMcMargin < lds_us) c.kind = sconv_csr::kFlatMc;
+        if (three_parts ? c.mc.us * kFlatMcMfmaMargin < c.mfma.us : c.mc.us * kFlatMcMargin < lds_us * (h->phased ? kFlatPhasedReadsLow : 1.0)) c.kind = sconv_csr::kFlatMc;
     } else {
         c.mc = FlatMcTiling();
     }
