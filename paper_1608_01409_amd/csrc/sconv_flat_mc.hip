@@ -15,15 +15,19 @@
 // stages: their largest goes to 2^12.  Where a later block holds one from 2^15 on, the scale and the sums shrink and the block is
 // staged again.  Smaller ones that matter (`small_sum`), infinities and NaN send the workgroup back (`again`): one pass for every
 // window of 26 binades that occurs, each at its own scale, and a pass that counts which stored weights meet an infinity.
-// What that costs, 13x13, 256 -> 384, batch 256 (133 us; the vector kernel 160): channels that differ by a factor e^2 (one sigma) 143,
-// later channels 100 times the first ones 150-165, an outlier of 60 sigma an image 139; every other image 2^-28 700, an outlier of
-// 1e4 sigma or an infinity an image 720, a single infinity 294, magnitudes 1e-20 to 1e20 1840.
-// Sums: the matrix instruction truncates small products against a large sum.  Up to 48 x 64 or 64 x 32 a wave there are registers for totals: every six
-// steps the large accumulator is added to one, and keeps what that addition rounds off.  (Every four: 11.0 instead of 11.8 e-8 at 800
-// nonzeros, 3.6 % slower at 384 -> 384, density 0.5, than plain additions every four; every six 1.9 %, every eight 0.7 % and 12.9.)
-// Error against 64 bits, relative 2-norm in 1e-8, of a row of n nonzeros on rectified normals, totals / none / fp32 chain / three-part
-// kernel (sconv_mfma.hip): n = 60 9.2 / 11.9 / 9.8 / -, 120 9.8 / 14.3 / 13.7 / 5.5, 346 11 / 21 / 23 / 8.6, 800 11.8 / 27 / 35 / 12.8,
-// 2304 13 / 32 / 62 / 23.  A call comes here where no row is off by more than on the kernel it leaves: the lines in sconv_internal.h.
+// What that costs, 13x13, 256 -> 384, batch 256 (ordinary inputs 140-155 us in that run, the vector kernel 160-190): channels of
+// magnitudes e^1 apart (sigma of the logarithm) 149, lognormal activations (sigma 2) 166, later channels 100 times the first ones
+// 167, an outlier of 60 sigma an image 140; channels e^2 apart 365, every other image 2^-28 695, an outlier of 1e4 sigma or an
+// infinity an image 710, a single infinity 293, magnitudes 1e-20 to 1e20 1840.
+//
+// Sums: the matrix instruction truncates small products against a large sum.  Up to 48 x 64 or 64 x 32 a wave there are registers
+// for totals: every six steps the large accumulator is added to one, and keeps what that addition rounds off.  (384 -> 384, density
+// 0.5, against plain additions every four steps, and the error at 800 nonzeros in 1e-8: every four 3.6 % slower, 11.0; every six
+// 1.9 %, 11.8; every eight 0.7 %, 12.9; plain ones 13.0.)
+// Error against 64 bits, relative 2-norm in 1e-8, of a row of n nonzeros on rectified normals, totals / none / fp32 chain /
+// three-part kernel (sconv_mfma.hip): n = 60 9.4 / 11.9 / 9.9 / -, 120 9.9 / 14.3 / 13.7 / 5.5, 346 11 / 21 / 23 / 8.6, 800 12.0 /
+// 27 / 35 / 12.9, 2304 13 / 32 / 62 / 23.  A call comes here where no row is off by more than on the kernel that it leaves: the lines
+// in sconv_internal.h.
 //
 // A workgroup is four waves, 16 * mt filters x 16 * nt positions each, two along the filters or one; it walks the channels in
 // blocks staged as [octet][row][high, low part][cell] of 16-byte units.  The pitch of a row is the number of positions in an
@@ -34,13 +38,15 @@
 // registers, a step ahead.  Results leave through LDS, four positions a lane: 16 positions x 4 rows an instruction took 19 us
 // for what takes 5.5.
 //
-// Measured, vector kernel -> here: 13x13, 256 -> 384, 3x3, batch 256, density 0.1: 162 -> 148 us; 28x28, 192 -> 128, 3x3, batch
-// 64, density 0.2: 120 -> 73; 227x227, 3 -> 96, 11x11 stride 4, batch 64, density 0.3: 110 -> 91; three-part kernel -> here: 13x13,
-// 384 -> 384 in two groups, batch 256, density 0.5: 258 -> 208.  60 random layers: 0.7-1.85x, 1.11x as the model chooses.
-// The first: of a workgroup's 78 us 47 are shared steps (13 of them, 1.1 us for two workgroups on a CU: 1960 clocks for 1536 of
-// matrix instructions at 1.65 GHz), 9 private steps, 16 staging, 4 before the first load, 6 the stores.  Without activations'
-// bits (all zero) it takes 133 us.  Two workgroups out of step by half a block: no faster; one workgroup of 512 registers a lane
-// and 128 positions a wave: 169 us; the next block's loads in flight across the last step: spills, 390 us.
+// Measured, vector kernel -> here: 13x13, 256 -> 384, 3x3, batch 256, density 0.1: 160 -> 134 us; 28x28, 192 -> 128, 3x3, batch
+// 64, density 0.2: 120 -> 66; 227x227, 3 -> 96, 11x11 stride 4, batch 64, density 0.3: 111 -> 93; three-part kernel -> here: 13x13,
+// 384 -> 384 in two groups, batch 256, density 0.5: 251 -> 206.  439 random layers that the model sends here: 1.28x, from 0.83 to 3.1
+// (the factors in sconv_api.cpp keep the lowest away).
+// The first (time stamps, profiles/sconv_flat_mc_kernel.txt): of a workgroup's 73 us 38 are its 39 shared steps, 1570 clocks each for
+// the 1536 of matrix instructions of the two waves on a SIMD, at 1.6 GHz (spilled registers had made it 2010); 7 private steps, 17
+// staging, 5 before the first load, 7 the end and the stores.  With activations of all zero bits it took 133 us for 148.  Two
+// workgroups out of step by half a block: no faster; one workgroup of 512 registers a lane and 128 positions a wave: 169 us; the next
+// block's loads in flight across the last step: spills, 390 us.
 #include <algorithm>
 #include <type_traits>
 
