@@ -559,6 +559,9 @@ static bool free_choice(const sconv_csr *h)
 // How far the matrix-core kernel's model is trusted against the flat-stream kernel's (GatherShape::margin for the gather
 // kernels).  Of 4100 random calls it was chosen for, 7 take more than 2 % longer than on the flat-stream kernel (at most 14 %).
 static const double kMfmaMargin = 1.15;
+// The column kernel against a gather kernel: of six random calls that left it at 1.15 two took 2-4 % longer.  Over 420 random layers of
+// one tap (seed fixed beforehand) 64 go to the column kernel: 32 from the staged one 1.32x, 26 from the flat streams 1.61x, none of those slower.
+static const double kColumnGatherMargin = 1.25;
 
 // The flat streams on the matrix cores against the same on the vector units and against the three-part kernel.  Of 357 random
 // calls that went there from the former at 1.0, 12 took more than 2 % longer, two of them more than 10 %; at 1.01 it is 6 of 341,
@@ -609,6 +612,21 @@ static const sconv_csr::Choice &choose_kernel(sconv_csr *h, bool fc, int N, doub
         if (three_parts ? c.mc.us * kFlatMcMfmaMargin < c.mfma.us : c.mc.us * kFlatMcMargin < lds_us * (h->phased ? kFlatPhasedReadsLow : 1.0)) c.kind = sconv_csr::kFlatMc;
     } else {
         c.mc = FlatMcTiling();
+    }
+    // Layers of one tap: the column kernel takes what the staged one would take, in no fewer parts, and of the rest what is faster there
+    // with sums no further from the exact ones: a gather kernel's of short rows (fully connected ones are kept in 64 bits), the vector
+    // units' unless they make many more parts.  (Flat streams that are on the matrix cores stay there, also where the column kernel
+    // is faster: 400 -> 64, 28x28, batch 100, density 0.3 takes 61.5 us, and would take 33.6.)
+    if (c.mfma.one_tap && c.kind == sconv_csr::kFlatMc) {
+        choose_mfma_column(h->desc, N, c.mfma.splits, c.mfma);
+    } else if (c.mfma.one_tap) {
+        const bool staged = c.kind == sconv_csr::kMfma;
+        MfmaTiling m = c.mfma;
+        choose_mfma_column(h->desc, N, staged ? m.splits : 1, m);
+        const bool near = c.kind == sconv_csr::kGather ? !fc && h->max_row_nnz <= SCONV_MFMA_GATHER_ROW : lds_splits <= SCONV_MFMA_CHAIN_PARTS * m.splits;
+        if (!staged && !near) choose_mfma_column(h->desc, N, c.mfma.splits, m);   // (for the tuner, as it was)
+        c.mfma = m;
+        if (near && m.us * (c.kind == sconv_csr::kGather ? kColumnGatherMargin : kMfmaMargin) < best) c.kind = sconv_csr::kMfma;
     }
     if (fc) make_room(alt.choice_of_n); // (a convolution's choices make room with its tilings, in plan_lds)
     return alt.choice_of_n[N] = c;

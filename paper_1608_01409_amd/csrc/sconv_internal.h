@@ -138,6 +138,8 @@ GatherShape choose_fc_gather(const sconv_desc &d, int N, double avg_row_nnz, int
 // from call to call.
 struct MfmaTiling {
     bool phased;             // channels are phase images picked out of the input (unpadded strided layers)
+    bool one_tap;            // one tap, stride 1: sconv_mfma_column_kernel can take it
+    bool column = false;     // and takes it
     int mt = 0, nt = 0;      // a workgroup takes 32 * mt filters and 128 * nt positions
     int nt_max;              // 1 where 256 positions are too many for LDS, or 128 serve better
     int splits;              // workgroups along the channel blocks (partial sums, added by a launch of their own)
@@ -161,6 +163,13 @@ struct MfmaTiling {
 // costs a workgroup a pass over its positions (2-3 us).
 #define SCONV_MFMA_SHORT_ROW 4
 #define SCONV_MFMA_SHORT_SHARE 16
+// Up to so many nonzeros a row a sum on the matrix cores is no further from the exact one than the gather kernel's of four positions
+// (relative 2-norm in 1e-8 on rectified normals: 48 3.8 / 4.8, 64 4.2 / 5.0, 80 4.6-4.9 / 4.8, 128 5.4 / 4.9; plain normals: 64 5.4 / 5.9, 80 5.9 / 5.9;
+// at 72 one random layer with a bias had 4.1 / 3.9).
+#define SCONV_MFMA_GATHER_ROW 48
+// The flat streams' chains in so many parts reach what one on the matrix cores has (in 1e-8: 64 nonzeros 4.2, eight parts of eight
+// 4.2; 256: 7.0, of 32 7.3; 16 parts of 16 5.9).
+#define SCONV_MFMA_CHAIN_PARTS 8
 struct PackedMfma {
     std::vector<uint16_t> wfrag;  // [group][32-row tile][step][part][lane][8], one spare step behind
     std::vector<int32_t> uoff;    // [2 * steps] + [2 * steps_last]
@@ -171,6 +180,8 @@ bool mfma_weight_ok(float v);
 sconv_desc mfma_desc(const sconv_desc &d);
 // The layer's tiling (mt, nt and us for a batch of N); false if the kernel cannot take the layer.
 bool choose_mfma(const sconv_desc &d, int N, MfmaTiling &t);
+// The same layer on the column kernel (t.one_tap), in at least so many parts.
+void choose_mfma_column(const sconv_desc &d, int N, int min_splits, MfmaTiling &t);
 int pack_mfma(const sconv_desc &d, const Canonical &c, const MfmaTiling &t, PackedMfma &out);
 
 // Flat streams on the matrix cores (sconv_flat_mc.hip).  The packing depends only on the layer: nt and splits may change from

@@ -20,7 +20,7 @@
 // a third has the large ones alone at another scale, a fourth counts which outputs have a stored weight on an infinity or NaN.
 // 13x13, 384 -> 384 in two groups, 3x3, batch 256, density 0.5: 250-264 us with ordinary and with tiny activations, 695-770 us
 // with infinities, NaN or values above 2^111 in every workgroup (flat-stream kernel 530; sums over the CSR arrays instead of
-// the further passes took 40 ms).  1x1, 192 -> 64, 28x28, batch 64, density 0.3: 21 and 61-85 us (flat-stream kernel 31).
+// the further passes took 40 ms).  1x1, 192 -> 64, 28x28, batch 64, density 0.3, through LDS: 21 and 61-85 us (flat-stream kernel 31).
 //
 // Implicit GEMM: rows = filters of a group, columns = output positions counted through the batch, depth = taps x
 // channels.  A workgroup takes 32*MT filters and 128*NT positions and walks the channels in blocks of 8*g8.  The input
@@ -35,7 +35,7 @@
 // Measured: 13x13, 384 -> 384 in two groups, 3x3, batch 256, density 0.5: flat-stream kernel 530 us, here 250-264 us as the
 // clocks allow, 344 GFLOP of bf16 products at 1.30-1.38 PFLOP/s (a large library product reaches 1.24).  Counters: matrix cores
 // busy 59 % of the cycles, LDS bank conflicts 40 % of the LDS cycles, L2 hit rate 75 %.  Of 281 us at an earlier state staging
-// was 37, weights from L2 instead of L1 10, bank conflicts 7.  1x1, batch 64: 32.0 -> 21.1 us, matrix cores busy 10 %.
+// was 37, weights from L2 instead of L1 10, bank conflicts 7.
 #include <algorithm>
 #include <type_traits>
 
@@ -82,8 +82,8 @@ struct MfmaArgs {
     long long out_img, out_row;
     int goff_mul;            // floats per unit of the CSR's offsets
     int short_rows;          // there are rows of 1 to SCONV_MFMA_SHORT_ROW - 1 nonzeros
-    int wide;                // four neighbouring cells are 16 consecutive bytes of the input: 1 along rows, 2 along the positions
-    int quads;               // wide = 1: fours of cells per row, the last one back by what it would pass the row's end
+    int wide;                // four neighbouring cells of a row are 16 consecutive bytes of the input
+    int quads;               // fours of cells per row, the last one back by what it would pass the row's end
     FastDiv d_units, d_splits, d_mt, d_ohw, d_ow, d_wl, d_rowimg, d_quads;
 };
 
@@ -189,12 +189,11 @@ struct Four {
 // again = false: a workgroup's sums, stored with the epilogue, or without it and true if some are not finite.
 // again = true: those sums once more (see above).
 template <int MT, int NT, bool again>
-static __device__ __forceinline__ bool multiply_tile(const MfmaArgs &a, int bid, char *lds)
+static __device__ __forceinline__ bool multiply_tile(const MfmaArgs &a, const Tile &tile, char *lds)
 {
     constexpr int kBatch = 4;
     const int lane = threadIdx.x & 63, half = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-    const Tile tile = tile_of(a, bid);
     const int ptile = tile.ptile, split = tile.split, g = tile.g, mt = tile.mt;
     const int b_first = split * a.blk_split, b_end = min(b_first + a.blk_split, a.nblk);   // this workgroup's channel blocks
 
@@ -226,18 +225,17 @@ static __device__ __forceinline__ bool multiply_tile(const MfmaArgs &a, int bid,
     // wide: per four of cells also where they go in LDS; what no four covers is padding and stays zero
     uint2 *four = reinterpret_cast<uint2 *>(voff);
     const bool wide = !again && a.wide;
-    const int n_fours = !wide ? 0 : a.wide == 1 ? fdiv(cells, a.d_wl) * a.quads : cells >> 2;
-    if (wide && a.wide == 1)
+    const int n_fours = wide ? fdiv(cells, a.d_wl) * a.quads : 0;
+    if (wide)
         for (int i = threadIdx.x; i < a.g8 * a.plane * 3; i += 256) reinterpret_cast<uint4 *>(lds)[i] = make_uint4(0, 0, 0, 0);
     for (int i = threadIdx.x; i < (wide ? n_fours : a.plane); i += 256) {
         int row, col;            // of the cell, or of the first of four
-        if (wide && a.wide == 1) {
+        if (wide) {
             row = fdiv(i, a.d_quads);
             col = a.pad + min((i - row * a.quads) * 4, a.W - 4);
         } else {
-            const int cell = wide ? i * 4 : i;
-            row = fdiv(cell, a.d_wl);
-            col = cell - row * a.Wl;
+            row = fdiv(i, a.d_wl);
+            col = i - row * a.Wl;
         }
         int n = 0, yp = y_first * a.lstep + row;
         if (row >= rows_first) {
@@ -551,10 +549,9 @@ static __device__ __forceinline__ bool multiply_tile(const MfmaArgs &a, int bid,
 
 // The short rows of a workgroup, over what it has stored; of several parts the first holds the whole sum.
 template <int MT, int NT>
-static __device__ __forceinline__ void sum_short_rows(const MfmaArgs &a, int bid)
+static __device__ __forceinline__ void sum_short_rows(const MfmaArgs &a, const Tile &t)
 {
     const int lane = threadIdx.x & 63;
-    const Tile t = tile_of(a, bid);
     const int kl = t.mt * MT * 32 + lane, row = t.g * a.Kg + min(kl, a.Kg - 1), nnz = a.rowptr[row + 1] - a.rowptr[row];
     unsigned long long rows = __ballot(lane < 32 * MT && kl < a.Kg && nnz > 0 && nnz < SCONV_MFMA_SHORT_ROW);
     __syncthreads();
@@ -569,12 +566,10 @@ static __device__ __forceinline__ void sum_short_rows(const MfmaArgs &a, int bid
     }
 }
 
+// What is left to do for a few workgroups: sums that were not finite, short rows.
 template <int MT, int NT>
-__global__ void __launch_bounds__(256, 2) sconv_mfma_kernel(const MfmaArgs a)
+static __device__ __forceinline__ void finish_tile(const MfmaArgs &a, bool bad, char *lds)
 {
-    extern __shared__ uint4 smem[];
-    char *lds = reinterpret_cast<char *>(smem);
-    const bool bad = multiply_tile<MT, NT, false>(a, blockIdx.x, lds);
     if (!bad && !a.short_rows) return;
     // The rare rest reads the arguments again, out of the compiler's sight: with their values kept for it the first pass spills
     // scalar registers (13x13, 384 -> 384 in two groups, density 0.5, batch 256: 263 us instead of 251).
@@ -582,14 +577,190 @@ __global__ void __launch_bounds__(256, 2) sconv_mfma_kernel(const MfmaArgs a)
     int bid = blockIdx.x;
     asm volatile("" : "+s"(args), "+s"(bid));
     const MfmaArgs &b = *(const MfmaArgs *)(const __attribute__((address_space(4))) MfmaArgs *)args;
-    if (bad) multiply_tile<MT, NT, true>(b, bid, lds);
-    if (b.short_rows) sum_short_rows<MT, NT>(b, bid);
+    const Tile tile = tile_of(b, bid);
+    if (bad) multiply_tile<MT, NT, true>(b, tile, lds);
+    if (b.short_rows) sum_short_rows<MT, NT>(b, tile);
 }
 
 template <int MT, int NT>
-static int launch_mfma_inst(const MfmaArgs &a, int grid, int lds_bytes, hipStream_t s, int *hip_err)
+__global__ void __launch_bounds__(256, 2) sconv_mfma_kernel(const MfmaArgs a)
 {
-    auto kern = sconv_mfma_kernel<MT, NT>;
+    extern __shared__ uint4 smem[];
+    char *lds = reinterpret_cast<char *>(smem);
+    const bool bad = multiply_tile<MT, NT, false>(a, tile_of(a, blockIdx.x), lds);
+    finish_tile<MT, NT>(a, bad, lds);
+}
+
+// Layers of one tap at stride 1, fully connected ones among them (sconv_mfma_column_kernel).  No activation is used at two
+// positions of a workgroup, so LDS saves no load: a lane loads the 8 channels x 1 position that it feeds to the matrix instruction,
+// with the same split, the same products and the same order of them as above (same bits).  No barrier, no table; a step's loads are
+// asked for two steps before, in straight code: where a branch may leave some out the compiler waits for more of them than a step
+// needs (16.2 us for 15.2), so a last step of fewer than 16 channels (kShort) has registers of its own, loaded at the beginning.
+// What bounds it: the address unit, 14 load instructions of 16 clocks a wave and step where the matrix cores need 384 / 4, then
+// launch and stores, one round of few waves.  192 -> 64, 28x28, batch 64, density 0.3: through LDS 20.5 us, here 15.2 (floor 10); 512 -> 128,
+// 28x28, batch 32: 35.0 -> 25.5; 512 -> 512, 14x14, batch 64: 64.0 -> 48.9; fully connected 2048 -> 512, batch 256: 18.7 -> 13.8.
+// Not taken: weights through LDS, two steps at a time (a barrier every two steps: 17.8 us in the first layer), loads four steps ahead (16.3),
+// two positions a lane (18.0; 512 -> 512 44.8), 128 filters a wave (23.3).
+template <int MT, bool kShort>
+static __device__ __forceinline__ bool column_tile(const MfmaArgs &a, const Tile &tile, char *lds)
+{
+    constexpr int D = 2;                     // steps loaded ahead (even: the split activations alternate)
+    const int lane = threadIdx.x & 63, half = lane >> 5, lane16 = lane * 16;
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    volatile int *flag = reinterpret_cast<volatile int *>(lds);
+    if (threadIdx.x == 0) *flag = 0;
+    const int b_first = tile.split * a.blk_split, b_end = min(b_first + a.blk_split, a.nblk);
+    const int first_step = b_first * a.steps, total = (b_end - b_first) * a.steps - (b_end == a.nblk ? a.steps - a.steps_last : 0);
+    const int full = kShort ? min(total, a.c_virtual / 16 - first_step) : total;   // steps of 16 channels; one of fewer may follow
+    const int p0 = tile.ptile * 128, n_first = fdiv(p0, a.d_ohw), p = p0 + wave * 32 + (lane & 31);
+    const int n = fdiv(min(p, a.P - 1), a.d_ohw), q = min(p, a.P - 1) - n * a.OHW;
+    const bool there = p < a.P;
+    int4v rsrc, wrsrc;
+    {
+        const long long first = n_first * a.in_img + tile.g * a.in_group;
+        const unsigned long long ip = (unsigned long long)(a.in + first);
+        rsrc.x = __builtin_amdgcn_readfirstlane((int)(unsigned)ip);
+        rsrc.y = __builtin_amdgcn_readfirstlane((int)(unsigned)(ip >> 32));
+        rsrc.z = __builtin_amdgcn_readfirstlane((int)min((a.in_floats - first) * 4, 0x7fffffffll));
+        rsrc.w = 0x00020000;
+    }
+    {
+        const size_t first = (size_t)(tile.g * a.n_tiles32 + tile.mt * MT) * a.total_steps + first_step;
+        const unsigned long long wp = (unsigned long long)(a.wfrag + first * 192);
+        wrsrc.x = __builtin_amdgcn_readfirstlane((int)(unsigned)wp);
+        wrsrc.y = __builtin_amdgcn_readfirstlane((int)(unsigned)(wp >> 32));
+        wrsrc.z = __builtin_amdgcn_readfirstlane(((MT - 1) * a.total_steps + total) * 3072);
+        wrsrc.w = 0x00020000;
+    }
+    // (a position past the last one reads beyond the buffer's end: 0)
+    const unsigned from = (there ? (unsigned)((n - n_first) * (int)a.in_img + q) * 4u : 0x80000000u) + (unsigned)(half * 8 * a.in_ch4);
+    struct X {
+        float v[8];
+    };
+    bf16x8 A[D][MT][3], B[2][3];
+    X x[D], tail;
+    int x_step = 0, a_step = 0;              // asked for next; past the last one that one again
+    // (without a full step its first channel eight times, not used: the others may not exist)
+    const int last = kShort ? max(full - 1, 0) : full - 1, ch4 = kShort && full == 0 ? 0 : a.in_ch4;
+    auto load_x = [&](X &x) INLINE {
+        int so = (first_step + min(x_step, last)) * 16 * a.in_ch4;
+#pragma unroll
+        for (int i = 0; i < 8; ++i, so += ch4) x.v[i] = mfma_buffer_load(rsrc, (int)from, so, 0);
+        ++x_step;
+    };
+    auto load_a = [&](bf16x8 (&A)[MT][3]) INLINE {
+#pragma unroll
+        for (int m = 0; m < MT; ++m)
+#pragma unroll
+            for (int s = 0; s < 3; ++s)
+                A[m][s] = __builtin_bit_cast(bf16x8, mfma_buffer_load4(wrsrc, lane16 + s * 1024, (m * a.total_steps + min(a_step, total - 1)) * 3072, 0));
+        ++a_step;
+    };
+    auto split = [&](bf16x8 (&B)[3], const X &x) INLINE {
+        uint4 h, m, l;
+        split8(x.v, h, m, l);
+        B[0] = __builtin_bit_cast(bf16x8, h);
+        B[1] = __builtin_bit_cast(bf16x8, m);
+        B[2] = __builtin_bit_cast(bf16x8, l);
+    };
+    f32x16 acc[MT], cor[MT];
+#pragma unroll
+    for (int m = 0; m < MT; ++m)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[m][r] = cor[m][r] = 0.f;
+    auto multiply = [&](const bf16x8 (&A)[MT][3], const bf16x8 (&B)[3]) INLINE {
+#define SCONV_MFMA(D, PA, PB) \
+    _Pragma("unroll") for (int m = 0; m < MT; ++m) D[m] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(A[m][PA], B[PB], D[m], 0, 0, 0);
+        SCONV_MFMA(acc, 0, 0)
+        SCONV_MFMA(cor, 1, 0)
+        SCONV_MFMA(cor, 2, 0)
+        SCONV_MFMA(cor, 0, 1)
+        SCONV_MFMA(cor, 1, 1)
+        SCONV_MFMA(cor, 0, 2)
+#undef SCONV_MFMA
+    };
+#pragma unroll
+    for (int j = 0; j < D; ++j) {
+        load_x(x[j]);
+        load_a(A[j]);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    if constexpr (kShort) {
+        const int c0 = (first_step + full) * 16, limit = full < total ? a.c_virtual : 0;
+#pragma unroll
+        for (int i = 0; i < 8; ++i)          // a channel past the last one: 0
+            tail.v[i] = mfma_buffer_load(rsrc, (int)(c0 + i + 8 * half < limit ? from : 0x80000000u), c0 + i < limit ? (c0 + i) * a.in_ch4 : 0, 0);
+    }
+    split(B[0], x[0]);
+    load_x(x[0]);
+    __builtin_amdgcn_sched_barrier(0);
+    // (the next step's activations are split between this step's matrix instructions)
+    auto step = [&](int j) INLINE {
+        split(B[(j + 1) & 1], x[(j + 1) % D]);
+        multiply(A[j], B[j & 1]);
+        __builtin_amdgcn_sched_barrier(0);
+        load_x(x[(j + 1) % D]);
+        load_a(A[j]);
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    int i = 0;
+    for (; i + D <= full; i += D) {
+#pragma unroll
+        for (int j = 0; j < D; ++j) step(j);
+    }
+    const int left = full - i;
+#pragma unroll
+    for (int j = 0; j < D - 1; ++j)
+        if (left > j) step(j);
+    if (kShort && full < total) {
+        bf16x8 T[3];
+        split(T, tail);
+#pragma unroll
+        for (int j = 0; j < D; ++j)
+            if (left == j) multiply(A[j], T);
+    }
+    float zero = 0.f;                        // NaN once a sum is not finite
+#pragma unroll
+    for (int m = 0; m < MT; ++m)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            acc[m][r] += cor[m][r];
+            zero = __builtin_fmaf(acc[m][r], 0.f, zero);
+        }
+    __syncthreads();                         // (the flag is cleared)
+    if (zero != 0.f) *flag = 1;
+    __syncthreads();
+    const bool bad = *flag != 0, bias = a.bias && !bad, relu = a.relu && !bad;
+    const int k0 = tile.g * a.Kg + tile.mt * (MT * 32), rows = a.Kg - tile.mt * (MT * 32) - 4 * half;  // rows: this lane's, counted as below
+    const bool whole = a.Kg >= (tile.mt + 1) * (MT * 32);
+    char *base = reinterpret_cast<char *>(a.out + tile.split * a.split_stride + n_first * a.out_img + k0 * a.out_row);
+    const unsigned at = (unsigned)((n - n_first) * (int)a.out_img + q + 4 * half * (int)a.out_row) * 4u;
+    if (there) {
+#pragma unroll
+        for (int m = 0; m < MT; ++m)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const int kl = m * 32 + 8 * (r >> 2) + (r & 3);
+                if (!whole && kl >= rows) continue;
+                float v = acc[m][r];
+                if (bias) v += a.bias[k0 + 4 * half + kl];
+                *reinterpret_cast<float *>(base + kl * a.out_row * 4 + at) = relu ? fmaxf(v, 0.f) : v;
+            }
+    }
+    return bad;
+}
+
+template <int MT, bool kShort>
+__global__ void __launch_bounds__(256, 2) sconv_mfma_column_kernel(const MfmaArgs a)
+{
+    extern __shared__ uint4 smem[];
+    char *lds = reinterpret_cast<char *>(smem);
+    const bool bad = column_tile<MT, kShort>(a, tile_of(a, blockIdx.x), lds);
+    finish_tile<MT, 1>(a, bad, lds);
+}
+
+static int launch_mfma_inst(void (*kern)(const MfmaArgs), const MfmaArgs &a, int grid, int lds_bytes, hipStream_t s, int *hip_err)
+{
     const int rc = allow_full_lds(reinterpret_cast<const void *>(kern), hip_err);
     if (rc) return rc;
     hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(256), lds_bytes, s, a);
@@ -645,24 +816,30 @@ int launch_mfma(const sconv_desc &layer, const MfmaTiling &t, const DeviceMfma &
     }
     a.quads = (d.W + 3) / 4;
     // (a four's table entry has 8 bytes, a cell's 4: a row's fours need no more room)
-    a.wide = t.cstep == 1 && d.W >= 4 && t.Wl >= d.W + d.pad && 2 * a.quads <= t.Wl ? 1
-             : t.cstep == 1 && t.Wl == 1 && t.Rr == 1 && t.lstep == 1 && d.pad == 0 && (feature_major ? N : a.OHW) % 4 == 0 ? 2 : 0;
+    a.wide = t.cstep == 1 && d.W >= 4 && t.Wl >= d.W + d.pad && 2 * a.quads <= t.Wl;
     a.d_quads = make_fastdiv(a.quads, 1024);
     // what the kernel assumes
     if (t.plane > 1024 || t.total_steps > (1 << 18) || (int64_t)t.g8 * t.plane * 48 + 8 * (t.steps + t.steps_last) + 4 * t.plane > t.lds_bytes || t.g8 > 16 || t.nt > t.nt_max) return SCONV_ERR_PLAN;
-    const int units = t.n_mtiles * d.groups * t.splits;
+    const int units = a.n_mtiles * d.groups * t.splits;
     const int64_t grid = (int64_t)a.n_ptiles * units;
     if (grid > 0x7fffffff) return SCONV_ERR_RANGE;
     a.d_units = make_fastdiv(units, std::max<int64_t>(grid / 8, 8 * (int64_t)units));
     a.d_splits = make_fastdiv(t.splits, units);
-    a.d_mt = make_fastdiv(t.n_mtiles, units);
+    a.d_mt = make_fastdiv(a.n_mtiles, units);
     a.d_ohw = make_fastdiv(a.OHW, P + bn);
     a.d_ow = make_fastdiv(a.OW, a.OHW);
     a.d_wl = make_fastdiv(a.Wl, 1025);
     a.d_rowimg = make_fastdiv(a.row_img, 1024);
     hipStream_t s = static_cast<hipStream_t>(stream);
-#define X(M, NN) if (t.mt == M && t.nt == NN) return launch_mfma_inst<M, NN>(a, (int)grid, t.lds_bytes, s, hip_err);
-    X(1, 1) X(1, 2) X(2, 1) X(2, 2)
+    if (t.column && (!t.one_tap || t.nt != 1 || (t.nblk > 1 && t.g8 % 2) || t.mt > t.n_tiles32)) return SCONV_ERR_PLAN;
+#define X(M, NN) \
+    if (t.mt == M && t.nt == NN) \
+        return launch_mfma_inst(!t.column ? sconv_mfma_kernel<M, NN> : a.c_virtual % 16 ? sconv_mfma_column_kernel<M, true> : sconv_mfma_column_kernel<M, false>, \
+                                a, (int)grid, t.lds_bytes, s, hip_err);
+    X(1, 1) X(2, 1)
+#undef X
+#define X(M, NN) if (t.mt == M && t.nt == NN) return launch_mfma_inst(sconv_mfma_kernel<M, NN>, a, (int)grid, t.lds_bytes, s, hip_err);
+    X(1, 2) X(2, 2)
 #undef X
     return SCONV_ERR_PLAN;
 }
