@@ -143,6 +143,7 @@ class Csr:
         self._h = C.c_void_p(handle)
         self.layer = layer
         self._dims = None
+        self._native = None   # what _sconv_call takes it by, once the first call has been checked here
         self._destroy = lib().sconv_destroy_csr   # module globals may be gone when __del__ runs at exit
 
     def __del__(self):
@@ -152,6 +153,7 @@ class Csr:
         if getattr(self, "_h", None):
             self._destroy(self._h)
             self._h = None
+        self._native = None
 
     @property
     def handle(self):
@@ -165,6 +167,13 @@ class Csr:
             L = self.layer
             self._dims = (L.C, L.H, L.W), (L.K, oh.value, ow.value)
         return self._dims
+
+    def prepare_native(self):
+        if self._native is None and self._h:
+            in_dims, out_dims = self.dims()
+            L = lib()
+            calls = (C.cast(f, C.c_void_p).value for f in (L.sconv_forward, L.sconv_forward_noalloc, L.sconv_forward_fused, L.sconv_fc_forward))
+            self._native = _call.layer(self._h.value, *calls, _torch._C._cuda_getDevice, _raw_stream, *in_dims, *out_dims)
 
 
 def sconv_create_csr(layer, dense_w: np.ndarray, plan=None) -> Csr:
@@ -235,18 +244,22 @@ def sconv_csr_unpack(csr: Csr, which: int):
 
 _torch = None
 _raw_stream = None
+_call = None   # the native calls (csrc/sconv_call.cpp); they decline what is not the ordinary case
 
 
 def _use_torch():
     """torch, imported on the first call that is handed tensors (the host-only calls do not need it)."""
-    global _torch, _raw_stream
+    global _torch, _raw_stream, _call
     if _torch is None:
         import torch
 
         # the current stream's handle without building a Stream object around it, where this torch has the call
         _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None) or (
             lambda index: torch.cuda.current_stream(index).cuda_stream)
-        _torch = torch    # last: a thread that finds it uses both
+        from . import _sconv_call
+
+        _call = _sconv_call
+        _torch = torch    # last: a thread that finds it uses all of them
     return _torch
 
 
@@ -279,6 +292,7 @@ def _conv_buffers(csr: Csr, x, out, stream):
         out = torch.empty((N, *out_dims), dtype=torch.float32, device=x.device)
     assert _is_f32(out)
     assert out.shape == (N, *out_dims)
+    csr.prepare_native()
     return N, out, _stream_of(x, stream)
 
 
@@ -291,6 +305,7 @@ def _fc_buffers(csr: Csr, x_t, out_t, bias, stream):
         out_t = torch.empty((L.K, N), dtype=torch.float32, device=x_t.device)
     assert _is_f32(out_t) and out_t.shape == (L.K, N)
     _check_bias(csr, bias)
+    csr.prepare_native()
     return N, out_t, _stream_of(x_t, stream)
 
 
@@ -302,6 +317,12 @@ def _check_bias(csr: Csr, bias):
 
 def sconv_forward(csr: Csr, x, out=None, stream=None):
     """x: contiguous fp32 CUDA tensor [N,C,H,W]; returns/overwrites out [N,K,OH,OW] on the same device."""
+    if csr._native is not None and stream is None:
+        rc = _call.forward(csr._native, x, out)
+        if rc == SCONV_OK:
+            return out
+        if rc is not None:
+            raise SconvError(rc, f"sconv_forward (hip error {lib().sconv_last_hip_error(csr.handle)})")
     N, out, s = _conv_buffers(csr, x, out, stream)
     rc = _launch(x, lib().sconv_forward, csr.handle, x.data_ptr(), out.data_ptr(), N, s)
     if rc != SCONV_OK:
@@ -313,6 +334,12 @@ def sconv_forward_noalloc(csr: Csr, x, out, stream=None):
     """sconv_forward without any allocation: `out` must be given, and the handle prepared by an earlier
     sconv_forward call with the same batch size."""
     assert out is not None
+    if csr._native is not None and stream is None:
+        rc = _call.noalloc(csr._native, x, out)
+        if rc == SCONV_OK:
+            return out
+        if rc is not None:
+            raise SconvError(rc, f"sconv_forward_noalloc (hip error {lib().sconv_last_hip_error(csr.handle)})")
     N, out, s = _conv_buffers(csr, x, out, stream)
     rc = _launch(x, lib().sconv_forward_noalloc, csr.handle, x.data_ptr(), out.data_ptr(), N, s)
     if rc != SCONV_OK:
@@ -341,6 +368,12 @@ def sconv_tune(csr: Csr, x, out=None, max_plans=8, stream=None):
 def sconv_forward_fused(csr: Csr, x, bias=None, relu=False, out=None, stream=None):
     """sconv_forward followed, inside the kernel where it can, by out = max(out + bias[k], 0); bias: fp32 CUDA
     tensor [K] or None."""
+    if csr._native is not None and stream is None:
+        rc = _call.fused(csr._native, x, bias, relu, out)
+        if rc == SCONV_OK:
+            return out
+        if rc is not None:
+            raise SconvError(rc, f"sconv_forward_fused (hip error {lib().sconv_last_hip_error(csr.handle)})")
     N, out, s = _conv_buffers(csr, x, out, stream)
     _check_bias(csr, bias)
     rc = _launch(x, lib().sconv_forward_fused, csr.handle, x.data_ptr(), out.data_ptr(), N,
@@ -364,6 +397,12 @@ def sconv_fc_plan(csr: Csr, N: int) -> dict:
 
 def sconv_fc_forward(csr: Csr, x_t, bias=None, relu=False, out_t=None, stream=None):
     """x_t: contiguous fp32 CUDA tensor [C][N] (feature-major); returns/overwrites out_t [K][N]."""
+    if csr._native is not None and stream is None:
+        rc = _call.fc(csr._native, x_t, bias, relu, out_t)
+        if rc == SCONV_OK:
+            return out_t
+        if rc is not None:
+            raise SconvError(rc, f"sconv_fc_forward (hip error {lib().sconv_last_hip_error(csr.handle)})")
     N, out_t, s = _fc_buffers(csr, x_t, out_t, bias, stream)
     rc = _launch(x_t, lib().sconv_fc_forward, csr.handle, x_t.data_ptr(), out_t.data_ptr(), N,
                  bias.data_ptr() if bias is not None else None, int(bool(relu)), s)

@@ -1,4 +1,4 @@
-"""Build libsconv.so (hipcc, gfx950) in-tree, next to this file."""
+"""Build libsconv.so (hipcc, gfx950) and the binding's native calls (g++) in-tree, next to this file."""
 from __future__ import annotations
 
 import os
@@ -9,6 +9,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libsconv.so")
+CALL = os.path.join(HERE, "_sconv_call.so")
 SOURCES = ["sconv_api.cpp", "sconv_host.cpp", "sconv_kernels.hip", "sconv_gather.hip", "sconv_mfma.hip", "sconv_flat_mc.hip"]
 # -packed-fp32-ops is switched off: the packed FP32 forms are not to be generated for this machine.
 DEVICE_FLAGS = ["--offload-arch=gfx950", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
@@ -29,7 +30,25 @@ def build(verbose: bool = False) -> str:
         raise RuntimeError("hipcc failed:\n" + err)
     if verbose and err.strip():
         print(err, file=sys.stderr)
+    build_call()
     return LIB
+
+
+def build_call() -> str:
+    """_sconv_call.so, what binding.py calls the library through: the headers of the torch it will read tensors of."""
+    import sysconfig
+
+    import torch
+    from torch.utils import cpp_extension
+
+    torch_lib = os.path.join(os.path.dirname(torch.__file__), "lib")
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch.compiled_with_cxx11_abi())}",
+           *[f"-I{d}" for d in (sysconfig.get_paths()["include"], *cpp_extension.include_paths())],
+           os.path.join(CSRC, "sconv_call.cpp"), "-o", CALL, f"-L{torch_lib}", f"-Wl,-rpath,{torch_lib}", "-lc10", "-ltorch_cpu", "-ltorch_python"]
+    res = subprocess.run(cmd, capture_output=True, text=True)
+    if res.returncode != 0:
+        raise RuntimeError("g++ failed:\n" + res.stderr)
+    return CALL
 
 
 def build_ceilings(hipcc: str | None = None) -> str:
