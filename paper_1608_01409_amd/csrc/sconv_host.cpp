@@ -881,6 +881,15 @@ bool gather4_fits(const sconv_desc &d)
     return d.stride == 1 && d.C >= 3 && (int64_t)d.H * d.W > (int64_t)d.pad * d.W + d.pad + 2;
 }
 
+// Its fours of positions are counted through the image instead of through each row.  (Fewer than four positions a row would pass more
+// than one row's end.)
+bool gather4_flat(const sconv_desc &d, int N)
+{
+    const Geometry g = geometry(d);
+    const int64_t by_image = (int64_t)N * ceil_div(g.OH * g.OW, 4), by_row = (int64_t)N * g.OH * ceil_div(g.OW, 4);
+    return g.OW == d.W && g.OW >= 4 && (by_image + 63) / 64 < (by_row + 63) / 64;
+}
+
 int pack_gather(const sconv_desc &d, const Canonical &c, PackedGather &out)
 {
     const Geometry g = geometry(d);
@@ -978,7 +987,7 @@ GatherShape choose_gather(const sconv_desc &d, int N, double avg_row_nnz, int ma
 {
     const Geometry g = geometry(d);
     const bool four = gather4_fits(d);
-    const double P = four ? (double)N * g.OH * ceil_div(g.OW, 4) : (double)N * g.OH * g.OW;
+    const double P = four ? (double)N * g.OH * ceil_div(g.OW, 4) : (double)N * g.OH * g.OW; // (counted through the image they are fewer: up to a fifth less)
     GatherShape best = {0, 0, 0.0, 0.0};
     for (int t = 1; t <= (four ? 1 : 2); ++t)
         for (int split = 1; split <= 8; split *= 2) {
