@@ -587,7 +587,7 @@ static const sconv_csr::Choice &choose_kernel(sconv_csr *h, bool fc, int N, doub
     sconv_csr::Alternatives &alt = fc ? h->fc_alt : h->conv_alt;
     auto known = alt.choice_of_n.find(N);
     if (known != alt.choice_of_n.end()) return known->second;
-    sconv_csr::Choice c = {sconv_csr::kLds, {0, 0, 0.0, 0.0}, {}, {}, false};
+    sconv_csr::Choice c = {sconv_csr::kLds, {0, 0, 0.0, 0.0, 0.0}, {}, {}, false};
     double best = lds_us; // (a tiling the cost model gave no time keeps the call)
     if (fc ? fc_gather_fits(h->desc, N) : gather_fits(h->desc, N)) {
         c.gather = fc ? choose_fc_gather(h->desc, N, avg_row_nnz(h), h->max_row_nnz) : choose_gather(h->desc, N, avg_row_nnz(h), h->max_row_nnz);
@@ -628,6 +628,8 @@ static const sconv_csr::Choice &choose_kernel(sconv_csr *h, bool fc, int N, doub
         c.mfma = m;
         if (near && m.us * (c.kind == sconv_csr::kGather ? kColumnGatherMargin : kMfmaMargin) < best) c.kind = sconv_csr::kMfma;
     }
+    // What is left to the vector units after all that, the gather kernel of four positions takes with less of a margin.
+    if (c.kind == sconv_csr::kLds && c.gather.flat_us > 0 && c.gather.flat_us < lds_us) c.kind = sconv_csr::kGather;
     if (fc) make_room(alt.choice_of_n); // (a convolution's choices make room with its tilings, in plan_lds)
     return alt.choice_of_n[N] = c;
 }

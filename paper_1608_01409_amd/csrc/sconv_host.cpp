@@ -988,7 +988,7 @@ GatherShape choose_gather(const sconv_desc &d, int N, double avg_row_nnz, int ma
     const Geometry g = geometry(d);
     const bool four = gather4_fits(d);
     const double P = four ? (double)N * g.OH * ceil_div(g.OW, 4) : (double)N * g.OH * g.OW; // (counted through the image they are fewer: up to a fifth less)
-    GatherShape best = {0, 0, 0.0, 0.0};
+    GatherShape best = {0, 0, 0.0, 0.0, 0.0};
     for (int t = 1; t <= (four ? 1 : 2); ++t)
         for (int split = 1; split <= 8; split *= 2) {
             const double tiles = std::ceil(P / (64.0 * t)), chunks = std::max(1.0, std::ceil(avg_row_nnz / SCONV_GATHER_CHUNK + 0.4));
@@ -1003,7 +1003,7 @@ GatherShape choose_gather(const sconv_desc &d, int N, double avg_row_nnz, int ma
                 lat = 0.28 * chunks_wave * std::sqrt((double)t);
             }
             const double us = 3.0 + std::max(thr, lat) + 0.35 * std::min(thr, lat);
-            if (best.t == 0 || us < best.us) best = GatherShape{t, split, us, 1.25};
+            if (best.t == 0 || us < best.us) best = GatherShape{t, split, us, 1.25, 0.0};
         }
     // 1.25 (of 260 random calls 2 then come here wrongly by more than 2 % and 16 stay away wrongly by more than 5 %; 5 and 9 at
     // 1.15), and more where the model reads low.  19953 random calls that it sent to these kernels were timed in turn against the flat-stream
@@ -1018,6 +1018,16 @@ GatherShape choose_gather(const sconv_desc &d, int N, double avg_row_nnz, int ma
         const double wgs = std::ceil(P / (64.0 * best.t)) * ceil_div(d.K, rows);
         if (max_row_nnz >= 3.0 * avg_row_nnz + SCONV_GATHER_CHUNK && ceil_div(max_row_nnz, SCONV_GATHER_CHUNK * best.split) > 8) best.margin = 1.5;
         if (wgs > 256 && wgs < 320) best.margin = 1.75;
+        // Against the flat streams on the vector units the four-position kernel is trusted further where its rows are level and the launch
+        // is short (the input then comes from L2).  Of 2775 random calls 110 move there at 1.08 that stayed at 1.25: 1.16x, 11 of them more
+        // than 2 % slower, three more than 10 % (one of skewed rows, 0.66x, which has since been left out); in an earlier draw 1.17x at 1.15,
+        // 1.09x between 1.15 and 1.1, 1.05x below; skewed rows down to 0.59x, strided layers to 0.74x, long launches to 0.81x.  384 -> 256 in two
+        // groups, 13x13, batch 16, density 0.1: 26.1 -> 21.5 us.  (Against the matrix cores 1.25 stays: 40 of 42 such calls were slower on the
+        // gather kernel, 0.68x.)
+        if (four && best.margin == 1.25 && max_row_nnz < 2.0 * avg_row_nnz + SCONV_GATHER_CHUNK && best.us <= 40.0) {
+            const double by_image = gather4_flat(d, N) ? std::ceil((double)N * ceil_div(g.OH * g.OW, 4) / 64.0) / std::ceil(P / 64.0) : 1.0;
+            best.flat_us = 1.08 * (3.0 + (best.us - 3.0) * by_image);
+        }
     }
     return best;
 }
@@ -1028,7 +1038,7 @@ GatherShape choose_gather(const sconv_desc &d, int N, double avg_row_nnz, int ma
 GatherShape choose_fc_gather(const sconv_desc &d, int N, double avg_row_nnz, int max_row_nnz)
 {
     const int n4 = N / 4;
-    GatherShape best = {0, 0, 0.0, 0.0};
+    GatherShape best = {0, 0, 0.0, 0.0, 0.0};
     for (int t = 1; t <= 32 && t < 2 * n4; t *= 2)
         for (int split = 1; split <= 16; split *= 4) {
             const double per_round = 4.0 * (64 / t) * split;
@@ -1037,7 +1047,7 @@ GatherShape choose_fc_gather(const sconv_desc &d, int N, double avg_row_nnz, int
             const double thr = 0.03e-3 * waves + (0.05e-3 + 0.23e-3 / t) * waves * rounds * 4.0;
             const double lat = 0.28 * std::ceil(max_row_nnz / per_round);
             const double us = 2.9 + std::max(thr, lat) + 0.35 * std::min(thr, lat);
-            if (best.t == 0 || us < best.us) best = GatherShape{t, split, us, 1.2};
+            if (best.t == 0 || us < best.us) best = GatherShape{t, split, us, 1.2, 0.0};
         }
     // Workgroups of 16 waves with long pieces of memory per nonzero, more of them than CUs: the model reads 30-40 % low.  Of 9809
     // random calls timed in turn against the flat-stream kernel 25 took more than 5 % longer with 1.2, 6 do with 1.5 here.

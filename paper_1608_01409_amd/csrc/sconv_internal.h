@@ -125,6 +125,7 @@ struct GatherShape {
     int t, split;
     double us;                     // what the launch is expected to take
     double margin;                 // its time counts with this factor when kernels are compared: how far the model is trusted here
+    double flat_us;                // its time with the factor that counts against the flat streams on the vector units alone (0: as above)
 };
 int pack_gather(const sconv_desc &d, const Canonical &c, PackedGather &out);
 int pack_fc_gather(const sconv_desc &d, const Canonical &c, PackedGather &out);
