@@ -88,6 +88,7 @@ struct FlatMcArgs {
     int Rr, Wl, row_img;     // filter rows in cells, cells per staged row, staged rows of a whole image
     int g8, nblk, c_virtual;
     int plane;               // cells that are staged at most, a multiple of 64
+    int run_until;           // phase form with runs: first position of the first workgroup whose fours of columns may pass the input's end
     int wide;                // four neighbouring cells are 16 consecutive bytes of the input: 1 along rows, 2 along the positions
     int quads;               // wide = 1: fours of cells per row, the last one back by what it would pass the row's end
     int pitch, part, octet;  // 16-byte units of LDS from one row of cells, high to low part, one channel octet to the next
@@ -373,6 +374,19 @@ static __device__ __forceinline__ bool mc_tile(const FlatMcArgs &a, int bid, cha
         for (int j = 0; j < kBatch; ++j) {
             const int item = min(i0 + 4 * j, items - 1), o = fdiv(item, d_pieces), piece = item - o * pieces, c = b * a.g8 * 8 + o * 8;
             const unsigned vo = i0 + 4 * j < items ? table[piece * 64 + lane].x : 0x80000000u;
+            // Phases of a stride of 4 or 8: four channels a load, side by side in the input.  One a load and 16 bytes from lane to lane
+            // the address unit saw four times the instructions and every line four times: 3 -> 96, 227x227, 11x11 stride 4, batch
+            // 64: 94 -> 88 us.
+            if (p0 < a.run_until) {
+#pragma unroll
+                for (int i = 0; i < 8; i += 4) {
+                    const int co = choff[c + i];
+                    const f32x4 r = __builtin_bit_cast(f32x4, mc_buffer_load4(rsrc, (int)(vo | ((unsigned)co & 0x80000000u)), co & 0x7fffffff, 0));
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) v.x[j][i + e] = r[e];
+                }
+                continue;
+            }
             int co[8];
             if (a.choff) {
 #pragma unroll
@@ -860,6 +874,14 @@ int launch_flat_mc(const sconv_desc &layer, const FlatMcTiling &t, const DeviceL
     a.wide = t.cstep == 1 && d.W >= 4 && t.Wl >= d.W + d.pad ? 1 : t.cstep == 1 && t.Wl == 1 && t.Rr == 1 && t.lstep == 1 && d.pad == 0 && a.OHW % 4 == 0 ? 2 : 0;
     const int bn = 16 * t.nt * (t.wr == 2 ? 2 : 4);
     a.n_ptiles = (int)((P + bn - 1) / bn);
+    // (from the last position's first input row in the last channel to behind the last column that its cells take of the last row)
+    auto passes_end = [&](int64_t p1) {
+        const int64_t n = p1 / a.OHW, y = (p1 - n * a.OHW) / a.OW;
+        return n * d.C * HW + (d.C - 1) * HW + (y + t.Rr) * t.cstep * d.W + (int64_t)t.Wl * t.cstep > (int64_t)N * d.C * HW;
+    };
+    int run_tiles = t.runs ? a.n_ptiles : 0;
+    while (run_tiles > 0 && passes_end(std::min(run_tiles * (int64_t)bn, P) - 1)) --run_tiles;
+    a.run_until = run_tiles * bn;
     a.n_mtiles = t.n_units / t.wr;
     a.n_units = t.n_units;
     a.groups = d.groups;

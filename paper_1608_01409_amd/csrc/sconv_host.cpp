@@ -1372,6 +1372,7 @@ bool choose_flat_mc(const sconv_desc &layer, const Canonical &csr, int N, bool f
         FlatMcTiling c;
         const int s = phased ? d.stride : 1;
         c.phased = phased != 0;
+        c.runs = phased && s % 4 == 0 && d.S >= s;
         c.cstep = s;
         c.lstep = phased ? 1 : d.stride;
         c.Rr = ceil_div(d.R, s);
@@ -1550,7 +1551,7 @@ int pack_flat_mc(const sconv_desc &layer, const Canonical &c, FlatMcTiling &t, P
     }
     for (size_t col = 0; col < col_slot.size(); ++col) {
         const int fs = (int)(col % d.S), fr = (int)(col / d.S % d.R), cl = (int)(col / ((size_t)d.R * d.S));
-        const int cv = t.phased ? ((fr % s) * s + fs % s) * g.Cg + cl : cl;
+        const int ph = (fr % s) * s + fs % s, cv = !t.phased ? cl : t.runs ? cl * s * s + ph : ph * g.Cg + cl;
         const int oct = cv / 8, b = oct / t.g8, o8 = std::min(t.g8, octets - b * t.g8);
         const int tap = (fr / s) * t.Sr + fs / s;
         col_slot[col] = (block_first[b] + tap * o8 + oct - b * t.g8) * 8 + cv % 8;
@@ -1732,7 +1733,7 @@ int pack_flat_mc(const sconv_desc &layer, const Canonical &c, FlatMcTiling &t, P
     t.small_sum = (float)std::ldexp(std::sqrt(*std::max_element(norm.begin(), norm.end())), t.wexp - 8);
     if (t.phased)
         for (int cv = 0; cv < octets * 8; ++cv) {
-            const int ph = cv / g.Cg, cl = cv % g.Cg;
+            const int ph = t.runs ? cv % (s * s) : cv / g.Cg, cl = t.runs ? cv / (s * s) : cv % g.Cg;
             const bool there = cv < t.c_virtual && ph / s < d.R && ph % s < d.S;
             out.choff.push_back(there ? ((cl * d.H + ph / s) * d.W + ph % s) * 4 : SCONV_MFMA_NO_CHANNEL);
         }

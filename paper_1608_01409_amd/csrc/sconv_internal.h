@@ -190,6 +190,8 @@ int pack_mfma(const sconv_desc &d, const Canonical &c, const MfmaTiling &t, Pack
 // call to call.
 struct FlatMcTiling {
     bool phased;             // as in MfmaTiling
+    bool runs;               // phased, stride a multiple of four: channel [input channel][row][column] of the phases, so that four
+                             // channels of a cell lie side by side in the input; else [row][column][input channel]
     int mt = 0, nt = 0;      // a wave takes 16 * mt filters and 16 * nt positions
     int wr;                  // waves along the filters: 2 (then 2 along the positions) or 1 (then 4)
     int nt_max;              // 2 where 64 positions a wave are too many for LDS

@@ -169,7 +169,7 @@ static void check(const sconv_desc &layer, int N, double density, bool skewed, b
                                     continue;
                                 }
                                 const int k = p.row_of[(size_t)u * rows + m * 16 + row], cv = (b * t.g8 + ol) * 8 + (e / 2) * 4 + place;
-                                const int ph = t.phased ? cv / g.Cg : 0, cl = t.phased ? cv % g.Cg : cv;
+                                const int ph = !t.phased ? 0 : t.runs ? cv % (s * s) : cv / g.Cg, cl = !t.phased ? cv : t.runs ? cv / (s * s) : cv % g.Cg;
                                 const int fr = tr * s + ph / s, fs = ts * s + ph % s;
                                 if (k < 0 || cv >= t.c_virtual || fr >= d.R || fs >= d.S) {
                                     CHECK(false, "a weight that the layer does not have: %s", what);
