@@ -23,7 +23,7 @@ import sys
 from collections import defaultdict
 
 MAIN = ("sconv_lds2_kernel", "sconv_lds_kernel", "sconv_direct_kernel", "sconv_gather_kernel", "sconv_gather4_kernel", "sconv_fc_gather_kernel",
-        "sconv_mfma_kernel", "sconv_flat_mc_kernel")
+        "sconv_mfma_kernel", "sconv_mfma_column_kernel", "sconv_flat_mc_kernel")
 CEIL = dict(fma_lanes=59.0, lds_b_clk=253.7, copy_tbs=4.83, l2_read_tbs=34.5)   # per CU per clock; whole chip
 
 
