@@ -614,8 +614,9 @@ static const sconv_csr::Choice &choose_kernel(sconv_csr *h, bool fc, int N, doub
         c.mc = FlatMcTiling();
     }
     // Layers of one tap: the column kernel takes what the staged one would take, in no fewer parts, and of the rest what is faster there
-    // with sums no further from the exact ones: a gather kernel's of short rows (fully connected ones are kept in 64 bits), the vector
-    // units' unless they make many more parts.  (Flat streams that are on the matrix cores stay there, also where the column kernel
+    // with sums no further from the exact ones: the four-position gather kernel's of short rows (the other gather kernels keep theirs in
+    // 64 bits: 64 -> 1024, 1x1 images, batch 512, rows of up to 41, 2.5e-8 where the matrix cores have 3.8e-8), the vector units' unless
+    // they make many more parts.  (Flat streams that are on the matrix cores stay there, also where the column kernel
     // is faster: 400 -> 64, 28x28, batch 100, density 0.3 takes 61.5 us, and would take 33.6.)
     if (c.mfma.one_tap && c.kind == sconv_csr::kFlatMc) {
         choose_mfma_column(h->desc, N, c.mfma.splits, c.mfma);
@@ -623,7 +624,7 @@ static const sconv_csr::Choice &choose_kernel(sconv_csr *h, bool fc, int N, doub
         const bool staged = c.kind == sconv_csr::kMfma;
         MfmaTiling m = c.mfma;
         choose_mfma_column(h->desc, N, staged ? m.splits : 1, m);
-        const bool near = c.kind == sconv_csr::kGather ? !fc && h->max_row_nnz <= SCONV_MFMA_GATHER_ROW : lds_splits <= SCONV_MFMA_CHAIN_PARTS * m.splits;
+        const bool near = c.kind == sconv_csr::kGather ? !fc && gather4_fits(h->desc) && h->max_row_nnz <= SCONV_MFMA_GATHER_ROW : lds_splits <= SCONV_MFMA_CHAIN_PARTS * m.splits;
         if (!staged && !near) choose_mfma_column(h->desc, N, c.mfma.splits, m);   // (for the tuner, as it was)
         c.mfma = m;
         if (near && m.us * (c.kind == sconv_csr::kGather ? kColumnGatherMargin : kMfmaMargin) < best) c.kind = sconv_csr::kMfma;

@@ -524,6 +524,22 @@ static void gather_limits()
     sconv_destroy_csr(h);
 }
 
+// Layers of one tap go to the matrix cores only where the sums come no further from the exact ones.
+static void one_tap_limits()
+{
+    // images of one and two positions: the gather kernel that keeps its sums in 64 bits
+    struct Conv {
+        sconv_desc d;
+        int N;
+        double density;
+    };
+    for (const Conv &c : {Conv{{64, 1, 1, 1024, 1, 1, 1, 0, 1}, 512, 0.5}, {{64, 1, 2, 1024, 1, 1, 1, 0, 1}, 256, 0.5}}) {
+        sconv_csr *h = make(c.d, c.density);
+        CHECK(forward(h, c.N) == "gather", "C%d %dx%d K%d N=%d: %s", c.d.C, c.d.H, c.d.W, c.d.K, c.N, launched.c_str());
+        sconv_destroy_csr(h);
+    }
+}
+
 int main(int argc, char **argv)
 {
     const std::string what = argc > 1 ? argv[1] : "";
@@ -536,6 +552,7 @@ int main(int argc, char **argv)
     else if (what == "routes") routes();
     else if (what == "flat_mc") flat_mc();
     else if (what == "gather_limits") gather_limits();
+    else if (what == "one_tap_limits") one_tap_limits();
     else if (what == "unpacked_tilings") unpacked_tilings();
     else return 2;
     std::printf("%ld failures\n", failures);

@@ -67,3 +67,8 @@ def test_a_tiling_that_no_call_runs_is_not_packed(program):
 
 def test_the_flat_streams_on_the_matrix_cores(program):
     run(program, "flat_mc")
+
+
+def test_layers_of_one_tap_keep_their_precision(program):
+    """The column kernel takes no call from a kernel whose sums are closer to the exact ones."""
+    run(program, "one_tap_limits")
