@@ -1107,7 +1107,7 @@ static int plan_fc(sconv_csr *h, int N, const sconv_csr::Planned *force = nullpt
 // The same decision for the fully connected entry point, against the tiling just planned.
 static const sconv_csr::Choice &choose_fc_kernel(sconv_csr *h, int N)
 {
-    if (free_choice(h) && h->requested.kernel == 0) return choose_kernel(h, true, N, h->fc_flat.t.us, 1);
+    if (free_choice(h) && h->requested.kernel == 0) return choose_kernel(h, true, N, h->fc_flat.t.us, h->fc_flat.t.p.splits);
     static const sconv_csr::Choice lds = {sconv_csr::kLds, {0, 0, 0.0, 0.0}, {}, {}, false};
     return lds;
 }

@@ -538,6 +538,10 @@ static void one_tap_limits()
         CHECK(forward(h, c.N) == "gather", "C%d %dx%d K%d N=%d: %s", c.d.C, c.d.H, c.d.W, c.d.K, c.N, launched.c_str());
         sconv_destroy_csr(h);
     }
+    // fully connected flat streams of 12 parts, against one part of 246 to 276 nonzeros
+    sconv_csr *h = make({295, 1, 1, 253, 1, 1, 1, 0, 1}, 0.9);
+    CHECK(fc(h, 712) == FLAT2, "295 -> 253, batch 712: %s", launched.c_str());
+    sconv_destroy_csr(h);
 }
 
 int main(int argc, char **argv)
