@@ -48,6 +48,7 @@ typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef short s16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float float4u __attribute__((ext_vector_type(4), aligned(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 using const_u32 = const __attribute__((address_space(4))) unsigned;
 using const_i32 = const __attribute__((address_space(4))) int;
@@ -719,6 +720,23 @@ static __device__ __forceinline__ bool column_tile(const MfmaArgs &a, const Tile
         for (int j = 0; j < D; ++j)
             if (left == j) multiply(A[j], T);
     }
+    const int k0 = tile.g * a.Kg + tile.mt * (MT * 32), rows = a.Kg - tile.mt * (MT * 32) - 4 * half;  // rows: this lane's, counted as below
+    const bool whole = a.Kg >= (tile.mt + 1) * (MT * 32);
+    // The bias is there before the first sum is stored: loaded between the stores, row by row, each of them waited for the stores before
+    // it (57 -> 400, 55x55, batch 17: 70.3 us; now 50.4).
+    float4u add[MT][4];
+    if (a.bias) {
+#pragma unroll
+        for (int m = 0; m < MT; ++m)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const float *from = a.bias + k0 + 4 * half;
+                if (whole) add[m][i] = *reinterpret_cast<const float4u *>(from + m * 32 + 8 * i);
+                else
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) add[m][i][e] = from[min(m * 32 + 8 * i + e, rows - 1)];   // (rows - 1 is the group's last)
+            }
+    }
     float zero = 0.f;                        // NaN once a sum is not finite
 #pragma unroll
     for (int m = 0; m < MT; ++m)
@@ -731,8 +749,6 @@ static __device__ __forceinline__ bool column_tile(const MfmaArgs &a, const Tile
     if (zero != 0.f) *flag = 1;
     __syncthreads();
     const bool bad = *flag != 0, bias = a.bias && !bad, relu = a.relu && !bad;
-    const int k0 = tile.g * a.Kg + tile.mt * (MT * 32), rows = a.Kg - tile.mt * (MT * 32) - 4 * half;  // rows: this lane's, counted as below
-    const bool whole = a.Kg >= (tile.mt + 1) * (MT * 32);
     char *base = reinterpret_cast<char *>(a.out + tile.split * a.split_stride + n_first * a.out_img + k0 * a.out_row);
     const unsigned at = (unsigned)((n - n_first) * (int)a.out_img + q + 4 * half * (int)a.out_row) * 4u;
     if (there) {
@@ -743,7 +759,7 @@ static __device__ __forceinline__ bool column_tile(const MfmaArgs &a, const Tile
                 const int kl = m * 32 + 8 * (r >> 2) + (r & 3);
                 if (!whole && kl >= rows) continue;
                 float v = acc[m][r];
-                if (bias) v += a.bias[k0 + 4 * half + kl];
+                if (bias) v += add[m][r >> 2][r & 3];
                 *reinterpret_cast<float *>(base + kl * a.out_row * 4 + at) = relu ? fmaxf(v, 0.f) : v;
             }
     }
