@@ -597,6 +597,7 @@ static const sconv_csr::Choice &choose_kernel(sconv_csr *h, bool fc, int N, doub
             best = us;
         }
     }
+    const sconv_csr::Kind without = c.kind;
     if (h->split_exact && h->short_rows * SCONV_MFMA_SHORT_SHARE <= h->desc.K && mfma_fits(h->desc, N, fc) && choose_mfma(h->desc, N, c.mfma)) {
         if (c.mfma.us * kMfmaMargin < best) c.kind = sconv_csr::kMfma;
     } else {
@@ -618,16 +619,16 @@ static const sconv_csr::Choice &choose_kernel(sconv_csr *h, bool fc, int N, doub
     // 64 bits: 64 -> 1024, 1x1 images, batch 512, rows of up to 41, 2.5e-8 where the matrix cores have 3.8e-8), the vector units' unless
     // they make many more parts.  (Flat streams that are on the matrix cores stay there, also where the column kernel
     // is faster: 400 -> 64, 28x28, batch 100, density 0.3 takes 61.5 us, and would take 33.6.)
-    if (c.mfma.one_tap && c.kind == sconv_csr::kFlatMc) {
-        choose_mfma_column(h->desc, N, c.mfma.splits, c.mfma);
-    } else if (c.mfma.one_tap) {
-        const bool staged = c.kind == sconv_csr::kMfma;
+    if (c.mfma.one_tap) {
+        const bool staged = c.kind == sconv_csr::kMfma, flat_mc = c.kind == sconv_csr::kFlatMc;
+        const int parts = c.mfma.splits;
         MfmaTiling m = c.mfma;
-        choose_mfma_column(h->desc, N, staged ? m.splits : 1, m);
+        bool can = choose_mfma_column(h->desc, N, staged || flat_mc ? parts : 1, m);
         const bool near = c.kind == sconv_csr::kGather ? !fc && gather4_fits(h->desc) && h->max_row_nnz <= SCONV_MFMA_GATHER_ROW : lds_splits <= SCONV_MFMA_CHAIN_PARTS * m.splits;
-        if (!staged && !near) choose_mfma_column(h->desc, N, c.mfma.splits, m);   // (for the tuner, as it was)
-        c.mfma = m;
-        if (near && m.us * (c.kind == sconv_csr::kGather ? kColumnGatherMargin : kMfmaMargin) < best) c.kind = sconv_csr::kMfma;
+        if (!staged && !near) can = choose_mfma_column(h->desc, N, parts, m);   // (for the tuner, as it was)
+        c.mfma = can ? m : MfmaTiling();
+        if (staged) c.kind = can ? sconv_csr::kMfma : without;
+        else if (can && !flat_mc && near && m.us * (c.kind == sconv_csr::kGather ? kColumnGatherMargin : kMfmaMargin) < best) c.kind = sconv_csr::kMfma;
     }
     // What is left to the vector units after all that, the gather kernel of four positions takes with less of a margin.
     if (c.kind == sconv_csr::kLds && c.gather.flat_us > 0 && c.gather.flat_us < lds_us) c.kind = sconv_csr::kGather;

@@ -1184,7 +1184,7 @@ bool choose_mfma(const sconv_desc &layer, int N, MfmaTiling &t)
     return true;
 }
 
-void choose_mfma_column(const sconv_desc &d, int N, int min_splits, MfmaTiling &t)
+bool choose_mfma_column(const sconv_desc &d, int N, int min_splits, MfmaTiling &t)
 {
     const Geometry g = geometry(d);
     const double P = (double)N * g.OH * g.OW, in_bytes = 4.0 * P * d.C, out_bytes = 4.0 * P * d.K;
@@ -1228,6 +1228,7 @@ void choose_mfma_column(const sconv_desc &d, int N, int min_splits, MfmaTiling &
                 t.n_mtiles = n_mtiles;
             }
         }
+    return t.us > 0;
 }
 
 int pack_mfma(const sconv_desc &d, const Canonical &c, const MfmaTiling &t, PackedMfma &out)

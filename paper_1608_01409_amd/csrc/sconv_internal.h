@@ -182,8 +182,9 @@ bool mfma_weight_ok(float v);
 sconv_desc mfma_desc(const sconv_desc &d);
 // The layer's tiling (mt, nt and us for a batch of N); false if the kernel cannot take the layer.
 bool choose_mfma(const sconv_desc &d, int N, MfmaTiling &t);
-// The same layer on the column kernel (t.one_tap), in at least so many parts.
-void choose_mfma_column(const sconv_desc &d, int N, int min_splits, MfmaTiling &t);
+// The same layer on the column kernel (t.one_tap), in at least so many parts; false, and not to be launched, if it cannot be cut so.
+// The blocks depend only on the layer.
+bool choose_mfma_column(const sconv_desc &d, int N, int min_splits, MfmaTiling &t);
 int pack_mfma(const sconv_desc &d, const Canonical &c, const MfmaTiling &t, PackedMfma &out);
 
 // Flat streams on the matrix cores (sconv_flat_mc.hip).  The packing depends only on the layer: nt and splits may change from

@@ -154,10 +154,8 @@ static void fc_gather_cases()
 
 // sconv_mfma_kernel: fragments read back to (filter, column) through the depth octets' offsets and the channel table, the
 // three parts added up.  Every weight once (a stored zero as -0), zeros everywhere else, offsets inside the staged block.
-static void check_mfma(const sconv_desc &layer, int N, int keep, bool small_weights)
+static void check_mfma_packing(const sconv_desc &layer, const MfmaTiling &t, int keep, bool small_weights)
 {
-    MfmaTiling t;
-    if (validate_desc(layer) != SCONV_OK || !choose_mfma(layer, N, t)) return;
     const sconv_desc d = mfma_desc(layer);
     const Geometry g = geometry(d);
     Canonical c = make_csr(layer, keep);
@@ -221,6 +219,51 @@ static void check_mfma(const sconv_desc &layer, int N, int keep, bool small_weig
     for (char t : there) CHECK(!t, "%s: a weight that is not stored", name(layer));
 }
 
+// The column kernel's tiling: blocks of whole steps that depend on the layer alone, no part without blocks, a block in LDS.
+static bool check_column(const sconv_desc &layer, int N, const MfmaTiling &staged, int min_splits, MfmaTiling &t)
+{
+    t = staged;
+    const bool ok = choose_mfma_column(layer, N, min_splits, t);
+    CHECK(ok, "%s N=%d: no tiling of %d parts or more", name(layer), N, min_splits);
+    if (!ok) return false;
+    const int octets = (t.c_virtual + 7) / 8, g8_last = octets - (t.nblk - 1) * t.g8, blk_split = (t.nblk + t.splits - 1) / t.splits;
+    CHECK(t.column && t.nt == 1 && (t.mt == 1 || t.mt == 2) && t.mt <= t.n_tiles32 && t.us > 0, "%s", name(layer));
+    CHECK(t.g8 >= 1 && t.g8 <= 16 && (t.nblk == 1 || t.g8 % 2 == 0) && g8_last >= 1 && g8_last <= t.g8, "%s: %d blocks of %d octets", name(layer), t.nblk, t.g8);
+    CHECK(t.steps == (t.g8 + 1) / 2 && t.steps_last == (g8_last + 1) / 2 && t.total_steps == (t.nblk - 1) * t.steps + t.steps_last, "%s: steps", name(layer));
+    CHECK(t.total_steps == (t.c_virtual + 15) / 16, "%s: steps of 16 channels", name(layer));
+    CHECK(t.splits >= min_splits && (t.splits - 1) * blk_split < t.nblk, "%s N=%d: %d parts of %d blocks", name(layer), N, t.splits, t.nblk);
+    CHECK(t.lds_bytes >= t.g8 * t.plane * 48 + 8 * (t.steps + t.steps_last) + 4 * t.plane && t.lds_bytes <= 80 * 1024, "%s: %d bytes of LDS", name(layer), t.lds_bytes);
+    return true;
+}
+
+static void check_mfma(const sconv_desc &layer, int N, int keep, bool small_weights)
+{
+    MfmaTiling t, column, other;
+    if (validate_desc(layer) != SCONV_OK || !choose_mfma(layer, N, t)) return;
+    check_mfma_packing(layer, t, keep, small_weights);
+    if (!t.one_tap || !check_column(layer, N, t, 1, column)) return;
+    check_mfma_packing(layer, column, keep, small_weights);
+    if (choose_mfma(layer, 4 * N, t) && check_column(layer, 4 * N, t, t.splits, other))
+        CHECK(other.g8 == column.g8 && other.nblk == column.nblk, "%s: another packing for another batch size", name(layer));
+}
+
+// Every number of channels finds a column tiling with the parts that the staged kernel would make.
+static void column_cases()
+{
+    for (int C = 1; C <= 2600; C += C < 600 ? 1 : 7)
+        for (int K : {24, 200})
+            for (int N : {1, 8, 64, 1000}) {
+                const sconv_desc conv = {C, 7, 7, K, 1, 1, 1, 0, 1}, fc = {C, 1, 1, K, 1, 1, 1, 0, 1};
+                for (const sconv_desc &d : {conv, fc}) {
+                    MfmaTiling t, column;
+                    if (!choose_mfma(d, N, t)) continue;
+                    CHECK(t.one_tap, "%s", name(d));
+                    check_column(d, N, t, 1, column);
+                    check_column(d, N, t, t.splits, column);
+                }
+            }
+}
+
 static void mfma_cases()
 {
     for (int C : {1, 3, 8, 13, 40})
@@ -237,6 +280,8 @@ static void mfma_cases()
     check_mfma({301, 16, 16, 40, 3, 3, 2, 1, 1}, 7, 11, true);
     check_mfma({200, 14, 14, 70, 1, 1, 1, 0, 1}, 60, 4, true);
     check_mfma({777, 1, 1, 100, 1, 1, 1, 0, 1}, 1024, 9, true);
+    for (int C : {15, 17, 41, 96, 100, 101, 202, 250, 777}) check_mfma({2 * C, 9, 11, 66, 1, 1, 1, 0, 2}, 12, 9, C % 2 == 1);
+    column_cases();
 }
 
 int main(int argc, char **argv)
