@@ -559,9 +559,9 @@ static bool free_choice(const sconv_csr *h)
 // How far the matrix-core kernel's model is trusted against the flat-stream kernel's (GatherShape::margin for the gather
 // kernels).  Of 4100 random calls it was chosen for, 7 take more than 2 % longer than on the flat-stream kernel (at most 14 %).
 static const double kMfmaMargin = 1.15;
-// The column kernel against a gather kernel: of six random calls that left it at 1.15 two took 2-4 % longer.  Over 420 random layers of
-// one tap (seed fixed beforehand) 64 go to the column kernel: 32 from the staged one 1.32x, 26 from the flat streams 1.61x, none of those slower.
-static const double kColumnGatherMargin = 1.25;
+// The column kernel against a gather kernel, whose model reads a quarter high for such rows: of 120 random calls that left it at 1.25 13 took
+// 2-18 % longer, of 34 at 1.45 none (1.43x).
+static const double kColumnGatherMargin = 1.45;
 
 // The flat streams on the matrix cores against the same on the vector units and against the three-part kernel.  Of 357 random
 // calls that went there from the former at 1.0, 12 took more than 2 % longer, two of them more than 10 %; at 1.01 it is 6 of 341,
@@ -617,14 +617,16 @@ static const sconv_csr::Choice &choose_kernel(sconv_csr *h, bool fc, int N, doub
     // Layers of one tap: the column kernel takes what the staged one would take, in no fewer parts, and of the rest what is faster there
     // with sums no further from the exact ones: the four-position gather kernel's of short rows (the other gather kernels keep theirs in
     // 64 bits: 64 -> 1024, 1x1 images, batch 512, rows of up to 41, 2.5e-8 where the matrix cores have 3.8e-8), the vector units' unless
-    // they make many more parts.  (Flat streams that are on the matrix cores stay there, also where the column kernel
-    // is faster: 400 -> 64, 28x28, batch 100, density 0.3 takes 61.5 us, and would take 33.6.)
+    // they make many more parts.  Layers with short rows stay: each of those is a pass over a workgroup's positions that no model counts
+    // (of 25 random calls that left with some, 9 took 2-49 % longer).  (Flat streams that are on the matrix cores stay there, also where the
+    // column kernel is faster: 400 -> 64, 28x28, batch 100, density 0.3 takes 61.5 us, and would take 33.6.)
     if (c.mfma.one_tap) {
         const bool staged = c.kind == sconv_csr::kMfma, flat_mc = c.kind == sconv_csr::kFlatMc;
         const int parts = c.mfma.splits;
         MfmaTiling m = c.mfma;
         bool can = choose_mfma_column(h->desc, N, staged || flat_mc ? parts : 1, m);
-        const bool near = c.kind == sconv_csr::kGather ? !fc && gather4_fits(h->desc) && h->max_row_nnz <= SCONV_MFMA_GATHER_ROW : lds_splits <= SCONV_MFMA_CHAIN_PARTS * m.splits;
+        const bool near = !h->short_rows && (c.kind == sconv_csr::kGather ? !fc && gather4_fits(h->desc) && h->max_row_nnz <= SCONV_MFMA_GATHER_ROW
+                                                                          : lds_splits <= SCONV_MFMA_CHAIN_PARTS * m.splits);
         if (!staged && !near) can = choose_mfma_column(h->desc, N, parts, m);   // (for the tuner, as it was)
         c.mfma = can ? m : MfmaTiling();
         if (staged) c.kind = can ? sconv_csr::kMfma : without;

@@ -542,6 +542,26 @@ static void one_tap_limits()
     sconv_csr *h = make({295, 1, 1, 253, 1, 1, 1, 0, 1}, 0.9);
     CHECK(fc(h, 712) == FLAT2, "295 -> 253, batch 712: %s", launched.c_str());
     sconv_destroy_csr(h);
+    // calls that measured slower on the column kernel stay (rows of few nonzeros, rows of one to three among them), others go
+    struct Rows {
+        sconv_desc d;
+        int N;
+        std::vector<int> nnz;
+        bool column;
+    };
+    const std::vector<Rows> calls = {
+        {{235, 56, 56, 98, 1, 1, 1, 0, 1}, 41, {12, 20, 21, 33}, false},      // 47.6 us on the gather kernel, 51.6
+        {{129, 41, 41, 61, 1, 1, 1, 0, 1}, 46, {6, 13, 14, 20}, false},       // 18.1, 19.9
+        {{98, 33, 33, 447, 1, 1, 1, 0, 1}, 10, {2, 81, 5, 9, 5, 9, 5, 9, 5, 9, 5, 9, 9, 9, 9, 9, 9, 9, 9, 9, 9, 9, 9, 9, 9, 9}, false}, // flat streams 18.5, 24.3
+        {{113, 54, 54, 332, 1, 1, 1, 0, 1}, 5, {14, 25, 39, 23}, true},       // gather kernel 25.0, 17.0
+        {{192, 28, 28, 64, 1, 1, 1, 0, 1}, 64, {58}, true},                   // 15.4
+    };
+    for (const Rows &c : calls) {
+        sconv_csr *g = rows_of(c.d, c.nnz);
+        const bool column = forward(g, c.N) == "mfma";
+        CHECK(column == c.column, "C%d %dx%d K%d N=%d: %s", c.d.C, c.d.H, c.d.W, c.d.K, c.N, launched.c_str());
+        sconv_destroy_csr(g);
+    }
 }
 
 int main(int argc, char **argv)
