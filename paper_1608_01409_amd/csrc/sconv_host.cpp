@@ -1015,19 +1015,23 @@ GatherShape choose_gather(const sconv_desc &d, int N, double avg_row_nnz, int ma
     // before, 15 after), and the 276 calls that change kernel take as long in sum.
     if (best.t > 0) {
         const int rows = best.split >= 4 ? 1 : 4 / best.split;
-        const double wgs = std::ceil(P / (64.0 * best.t)) * ceil_div(d.K, rows);
+        const double tiles = std::ceil(P / (64.0 * best.t)), groups = ceil_div(d.K, rows), wgs = tiles * groups;
         if (max_row_nnz >= 3.0 * avg_row_nnz + SCONV_GATHER_CHUNK && ceil_div(max_row_nnz, SCONV_GATHER_CHUNK * best.split) > 8) best.margin = 1.5;
+        // (By rows also where the fours are counted through the image, which leaves fewer workgroups: 216 -> 35, 18x18, batch 5, 280 and 245 of
+        // them, stays at 24.3 us and would take 15.1.)
         if (wgs > 256 && wgs < 320) best.margin = 1.75;
-        // Against the flat streams on the vector units the four-position kernel is trusted further where its rows are level and the launch
-        // is short (the input then comes from L2).  Of 2775 random calls 110 move there at 1.08 that stayed at 1.25: 1.16x, 11 of them more
-        // than 2 % slower, three more than 10 % (one of skewed rows, 0.66x, which has since been left out); in an earlier draw 1.17x at 1.15,
-        // 1.09x between 1.15 and 1.1, 1.05x below; skewed rows down to 0.59x, strided layers to 0.74x, long launches to 0.81x.  384 -> 256 in two
-        // groups, 13x13, batch 16, density 0.1: 26.1 -> 21.5 us.  (Against the matrix cores 1.25 stays: 40 of 42 such calls were slower on the
-        // gather kernel, 0.68x.)
-        if (four && best.margin == 1.25 && max_row_nnz < 2.0 * avg_row_nnz + SCONV_GATHER_CHUNK && best.us <= 40.0) {
-            const double by_image = gather4_flat(d, N) ? std::ceil((double)N * ceil_div(g.OH * g.OW, 4) / 64.0) / std::ceil(P / 64.0) : 1.0;
-            best.flat_us = 1.08 * (3.0 + (best.us - 3.0) * by_image);
-        }
+        // Against the flat streams on the vector units the four-position kernel is trusted further where the launch is short, its rows are
+        // level and the model is good: few nonzeros a row, or many filters over an input of at most 16 MB.  Of 515 random calls of level rows
+        // above 1.08 28 were more than 2 % slower there, down to 0.80x (1.24x on average); of the 310 of them that these rules leave it is 4
+        // (1.31x), and of 295 of another draw 3, down to 0.96x (1.30x).  With more than 16 nonzeros a row and fewer filters a quarter of
+        // those between 1.08 and 1.16 were slower.  384 -> 256 in two groups, 13x13, batch 16, density 0.1: 25.3 -> 22.7 us.  (Strided layers:
+        // down to 0.74x; long launches 0.81x.  Against the matrix cores 1.25 stays: 40 of 42 such calls were slower on the gather kernel,
+        // 0.68x.)
+        const bool reused = avg_row_nnz < 16.0 || (d.K >= 128 && 4.0 * N * d.C * d.H * d.W <= 16e6);
+        const double launched = four && gather4_flat(d, N) ? std::ceil((double)N * ceil_div(g.OH * g.OW, 4) / 64.0) : tiles;
+        if (four && reused && best.margin == 1.25 && best.split < 8 && !(launched * groups > 256 && launched * groups < 320) &&
+            max_row_nnz < 2.0 * avg_row_nnz + SCONV_GATHER_CHUNK && best.us <= 40.0)
+            best.flat_us = 1.08 * (3.0 + (best.us - 3.0) * launched / tiles);
     }
     return best;
 }
