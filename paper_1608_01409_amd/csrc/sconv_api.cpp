@@ -559,10 +559,10 @@ static bool free_choice(const sconv_csr *h)
 // How far the matrix-core kernel's model is trusted against the flat-stream kernel's (GatherShape::margin for the gather
 // kernels).  Of 4100 random calls it was chosen for, 7 take more than 2 % longer than on the flat-stream kernel (at most 14 %).
 static const double kMfmaMargin = 1.15;
-// The column kernel against a gather kernel, whose model reads a quarter high for rows this short, a little less from 25 nonzeros on: of 120
-// random calls that left it at 1.25 13 took 2-18 % longer, of 47 at these none (1.39x).
-static const double kColumnGatherMargin = 1.45, kColumnGatherMarginLonger = 1.35;
-static const double kColumnLongerRows = 25.0;
+// The column kernel against a gather kernel, whose model reads high for short rows: of 120 random calls that left it at 1.25 13 took 2-18 %
+// longer (1.25x on average); with the larger factor where rows have fewer than 16 nonzeros on average 4 of 97, 2-8 % (1.31x).
+static const double kColumnGatherMargin = 1.25, kColumnGatherMarginShort = 1.45;
+static const double kColumnShortRows = 16.0;
 
 // The flat streams on the matrix cores against the same on the vector units and against the three-part kernel.  Of 357 random
 // calls that went there from the former at 1.0, 12 took more than 2 % longer, two of them more than 10 %; at 1.01 it is 6 of 341,
@@ -628,7 +628,7 @@ static const sconv_csr::Choice &choose_kernel(sconv_csr *h, bool fc, int N, doub
         bool can = choose_mfma_column(h->desc, N, staged || flat_mc ? parts : 1, m);
         const bool near = !h->short_rows && (c.kind == sconv_csr::kGather ? !fc && gather4_fits(h->desc) && h->max_row_nnz <= SCONV_MFMA_GATHER_ROW
                                                                           : lds_splits <= SCONV_MFMA_CHAIN_PARTS * m.splits);
-        const double margin = c.kind != sconv_csr::kGather ? kMfmaMargin : avg_row_nnz(h) < kColumnLongerRows ? kColumnGatherMargin : kColumnGatherMarginLonger;
+        const double margin = c.kind != sconv_csr::kGather ? kMfmaMargin : avg_row_nnz(h) < kColumnShortRows ? kColumnGatherMarginShort : kColumnGatherMargin;
         if (!staged && !near) can = choose_mfma_column(h->desc, N, parts, m);   // (for the tuner, as it was)
         c.mfma = can ? m : MfmaTiling();
         if (staged) c.kind = can ? sconv_csr::kMfma : without;

@@ -1020,18 +1020,17 @@ GatherShape choose_gather(const sconv_desc &d, int N, double avg_row_nnz, int ma
         // (By rows also where the fours are counted through the image, which leaves fewer workgroups: 216 -> 35, 18x18, batch 5, 280 and 245 of
         // them, stays at 24.3 us and would take 15.1.)
         if (wgs > 256 && wgs < 320) best.margin = 1.75;
-        // Against the flat streams on the vector units the four-position kernel is trusted further where the launch is short, its rows are
-        // level and the model is good: few nonzeros a row, or many filters over an input of at most 16 MB.  Of 515 random calls of level rows
-        // above 1.08 28 were more than 2 % slower there, down to 0.80x (1.24x on average); of the 310 of them that these rules leave it is 4
-        // (1.31x), and of 295 of another draw 3, down to 0.96x (1.30x).  With more than 16 nonzeros a row and fewer filters a quarter of
-        // those between 1.08 and 1.16 were slower.  384 -> 256 in two groups, 13x13, batch 16, density 0.1: 25.3 -> 22.7 us.  (Strided layers:
-        // down to 0.74x; long launches 0.81x.  Against the matrix cores 1.25 stays: 40 of 42 such calls were slower on the gather kernel,
-        // 0.68x.)
-        const bool reused = avg_row_nnz < 16.0 || (d.K >= 128 && 4.0 * N * d.C * d.H * d.W <= 16e6);
+        // Against the flat streams on the vector units the four-position kernel is trusted further where the launch is short and its rows are
+        // level.  Of 515 random calls that moved there at 1.08 28 were more than 2 % slower, down to 0.80x (1.24x on average).  Left out since:
+        // rows over eight waves, rows of 16 nonzeros and more over an input of more than 16 MB, and below 1.12 those over few filters: 69 calls,
+        // 16 of them slower (1.07x); of the others 12 are (1.27x), and of 408 of another draw 8, down to 0.90x (1.28x).  384 -> 256 in two groups, 13x13, batch 16,
+        // density 0.1: 25.3 -> 22.7 us.  (Strided layers: down to 0.74x; long launches 0.81x.  Against the matrix cores 1.25 stays: 40 of 42
+        // such calls were slower on the gather kernel, 0.68x.)
+        const bool few = avg_row_nnz < 16.0;
         const double launched = four && gather4_flat(d, N) ? std::ceil((double)N * ceil_div(g.OH * g.OW, 4) / 64.0) : tiles;
-        if (four && reused && best.margin == 1.25 && best.split < 8 && !(launched * groups > 256 && launched * groups < 320) &&
+        if (four && best.margin == 1.25 && best.split < 8 && (few || 4.0 * N * d.C * d.H * d.W <= 16e6) && !(launched * groups > 256 && launched * groups < 320) &&
             max_row_nnz < 2.0 * avg_row_nnz + SCONV_GATHER_CHUNK && best.us <= 40.0)
-            best.flat_us = 1.08 * (3.0 + (best.us - 3.0) * launched / tiles);
+            best.flat_us = (few || d.K >= 64 ? 1.08 : 1.12) * (3.0 + (best.us - 3.0) * launched / tiles);
     }
     return best;
 }

@@ -556,7 +556,7 @@ static void one_tap_limits()
         bool column;
     };
     const std::vector<Rows> calls = {
-        {{235, 56, 56, 98, 1, 1, 1, 0, 1}, 41, {12, 20, 21, 33}, false},      // 47.6 us on the gather kernel, 51.6
+        {{334, 26, 26, 118, 1, 1, 1, 0, 2}, 44, {7, 14, 15, 23}, false},      // 15.5 us on the gather kernel, 16.6
         {{129, 41, 41, 61, 1, 1, 1, 0, 1}, 46, {6, 13, 14, 20}, false},       // 18.1, 19.9
         {{98, 33, 33, 447, 1, 1, 1, 0, 1}, 10, {2, 81, 5, 9, 5, 9, 5, 9, 5, 9, 5, 9, 9, 9, 9, 9, 9, 9, 9, 9, 9, 9, 9, 9, 9, 9}, false}, // flat streams 18.5, 24.3
         {{113, 54, 54, 332, 1, 1, 1, 0, 1}, 5, {14, 25, 39, 23}, true},       // gather kernel 25.0, 17.0
