@@ -1015,22 +1015,22 @@ GatherShape choose_gather(const sconv_desc &d, int N, double avg_row_nnz, int ma
     // before, 15 after), and the 276 calls that change kernel take as long in sum.
     if (best.t > 0) {
         const int rows = best.split >= 4 ? 1 : 4 / best.split;
-        const double tiles = std::ceil(P / (64.0 * best.t)), groups = ceil_div(d.K, rows), wgs = tiles * groups;
+        const double tiles = std::ceil(P / (64.0 * best.t)), wgs = tiles * ceil_div(d.K, rows);
         if (max_row_nnz >= 3.0 * avg_row_nnz + SCONV_GATHER_CHUNK && ceil_div(max_row_nnz, SCONV_GATHER_CHUNK * best.split) > 8) best.margin = 1.5;
         // (By rows also where the fours are counted through the image, which leaves fewer workgroups: 216 -> 35, 18x18, batch 5, 280 and 245 of
         // them, stays at 24.3 us and would take 15.1.)
         if (wgs > 256 && wgs < 320) best.margin = 1.75;
-        // Against the flat streams on the vector units the four-position kernel is trusted further where the launch is short and its rows are
-        // level.  Of 515 random calls that moved there at 1.08 28 were more than 2 % slower, down to 0.80x (1.24x on average).  Left out since:
-        // rows over eight waves, rows of 16 nonzeros and more over an input of more than 16 MB, and below 1.12 those over few filters: 69 calls,
-        // 16 of them slower (1.07x); of the others 12 are (1.27x), and of 408 of another draw 8, down to 0.90x (1.28x).  384 -> 256 in two groups, 13x13, batch 16,
-        // density 0.1: 25.3 -> 22.7 us.  (Strided layers: down to 0.74x; long launches 0.81x.  Against the matrix cores 1.25 stays: 40 of 42
-        // such calls were slower on the gather kernel, 0.68x.)
-        const bool few = avg_row_nnz < 16.0;
-        const double launched = four && gather4_flat(d, N) ? std::ceil((double)N * ceil_div(g.OH * g.OW, 4) / 64.0) : tiles;
-        if (four && best.margin == 1.25 && best.split < 8 && (few || 4.0 * N * d.C * d.H * d.W <= 16e6) && !(launched * groups > 256 && launched * groups < 320) &&
-            max_row_nnz < 2.0 * avg_row_nnz + SCONV_GATHER_CHUNK && best.us <= 40.0)
-            best.flat_us = (few || d.K >= 64 ? 1.08 : 1.12) * (3.0 + (best.us - 3.0) * launched / tiles);
+        // Against the flat streams on the vector units the four-position kernel is trusted further where its rows are level and the launch
+        // is short (the input then comes from L2).  Of 996 random calls that moved there at 1.08 50 were more than 2 % slower, down to 0.77x
+        // (1.24x on average).  Left out since: long rows of several taps over more input than L2 holds (15 of the 35 below 1.25 were
+        // slower, 1.01x on average) and below 1.2 rows over eight waves (3 of 4).  384 -> 256 in two groups, 13x13, batch 16, density 0.1:
+        // 25.3 -> 22.7 us.  (Skewed rows: down to 0.59x, strided layers to 0.74x, long launches to 0.81x.  Against the matrix cores 1.25 stays:
+        // 40 of 42 such calls were slower on the gather kernel, 0.68x.)
+        const bool large = d.R * d.S > 1 && avg_row_nnz >= 16.0 && 4.0 * N * d.C * d.H * d.W > 20e6;
+        if (four && !large && best.margin == 1.25 && max_row_nnz < 2.0 * avg_row_nnz + SCONV_GATHER_CHUNK && best.us <= 40.0) {
+            const double by_image = gather4_flat(d, N) ? std::ceil((double)N * ceil_div(g.OH * g.OW, 4) / 64.0) / tiles : 1.0;
+            best.flat_us = (best.split == 8 ? 1.2 : 1.08) * (3.0 + (best.us - 3.0) * by_image);
+        }
     }
     return best;
 }
