@@ -140,4 +140,9 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "_sconv_call", nullptr, -1, methods
 
 } // namespace
 
-PyMODINIT_FUNC PyInit__sconv_call() { return PyModule_Create(&module); }
+PyMODINIT_FUNC PyInit__sconv_call()
+{
+    PyObject *m = PyModule_Create(&module);
+    if (m && PyModule_AddStringConstant(m, "torch_version", SCONV_TORCH_VERSION)) Py_CLEAR(m);
+    return m;
+}
