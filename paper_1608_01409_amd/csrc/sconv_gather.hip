@@ -222,7 +222,8 @@ int launch_gather(const sconv_desc &d, const DeviceGather &dev, const GatherShap
 // (what that brings into a window is masked like padding), and the fours may be counted through the whole image: 13x13 is 43 of them
 // instead of 52.  They are where that takes fewer waves (14x14, 68 -> 96, batch 10, density 0.41: 11.6 -> 10.2 us; with as many it is
 // up to 5 % slower).  A wave's head: a lane's four masks are runs of bits and a product (bit by bit they were most of it), and the stream's
-// first chunk is on its way meanwhile: 256 -> 384, 13x13, batch 1 7.0 -> 6.8 us; random layers of 4-20 us 1.00-1.11x, 1.03x on average.
+// first chunk is on its way meanwhile: random layers of 4-20 us 1.00-1.11x, 1.03x on average (256 -> 384, 13x13, batch 1, 7.0 and 6.8 us,
+// is within what its runs differ by).
 struct Gather4Args {
     const unsigned *ent;     // like GatherArgs::ent, the low five bits being the tap itself
     const int *rows;         // per row: first entry, chunks of eight, edge entries behind them
@@ -304,7 +305,6 @@ __global__ void __launch_bounds__(SPLIT > 4 ? SPLIT * 64 : 256) sconv_gather4_ke
         rsrc.y = __builtin_amdgcn_readfirstlane((int)(unsigned)(ip >> 32));
         rsrc.z = __builtin_amdgcn_readfirstlane(a.rec_bytes);
         rsrc.w = 0x00020000;
-        // The first of the wave's edge entries goes ahead of everything (most waves have one or none): its loads would wait alone at the end.
         for (int c = c0; c < c1; ++c) {
             e += 2 * U;                                       // the stream ends with a spare chunk
 #pragma unroll

@@ -89,6 +89,17 @@ static void check_gather(const sconv_desc &d, int N, int keep)
         CHECK(at >= shift && at + 4 <= rec && at % 4 == 0, "%s N=%d: byte %ld of %ld", name(d), N, (long)at, (long)rec);
         return at >= shift && at + 4 <= rec ? in[(at - shift) / 4] : 0.f;
     };
+    // Bits of the taps that lie inside the image, as the four-position kernel makes them from a position's row and column.
+    auto rows_at = [&](int y) {
+        uint32_t ones = 0;
+        for (int r = 0; r < d.R; ++r) ones |= 1u << r * d.S;
+        const int r0 = std::min(std::max(d.pad - y, 0), d.R), r1 = std::min(std::max(d.H + d.pad - y, 0), d.R);
+        return ((1u << r1 * d.S) - 1u) & ~((1u << r0 * d.S) - 1u) & ones;
+    };
+    auto cols_at = [&](int x) {
+        const int s0 = std::min(std::max(d.pad - x, 0), d.S), s1 = std::min(std::max(d.W + d.pad - x, 0), d.S);
+        return ((1u << s1) - 1u) & ~((1u << s0) - 1u);
+    };
     for (int k = 0; k < d.K; ++k) {
         const int j0 = four ? p.rowptr[3 * k] : p.rowptr[k];
         const int n_main = four ? p.rowptr[3 * k + 1] * SCONV_GATHER_CHUNK : p.rowptr[k + 1] - j0, n_edge = four ? p.rowptr[3 * k + 2] : 0;
@@ -113,9 +124,39 @@ static void check_gather(const sconv_desc &d, int N, int keep)
                         }
                         if (seen) sum += (double)bits(p.ent[j]) * load(base + so);
                     }
+                    if (four)
+                        for (int tap = 0; tap < d.R * d.S; ++tap) {
+                            const int iy = y - d.pad + tap / d.S, ix = x - d.pad + tap % d.S;
+                            CHECK((cols_at(x) * rows_at(y) >> tap & 1) == (iy >= 0 && iy < d.H && ix >= 0 && ix < d.W), "%s: tap %d at %d %d", name(d), tap, y, x);
+                        }
                     const double want = reference(d, c, in, n, k, y, x);
                     CHECK(sum == want, "%s N=%d output %d %d %d %d: %g instead of %g", name(d), N, n, k, y, x, sum, want);
                 }
+        // fours of positions counted through the image: they pass the end of a row, and of the image
+        if (!four || g.OW != d.W || g.OW < 4) continue;
+        for (int n = 0; n < N; ++n)
+            for (int x0 = 0; x0 < g.OH * g.OW; x0 += 4) {
+                const int y = x0 / g.OW, x = x0 - y * g.OW;
+                uint32_t valid[4];
+                for (int i = 0; i < 4; ++i) {
+                    const bool over = x + i >= g.OW;
+                    valid[i] = x0 + i < g.OH * g.OW ? cols_at(over ? x + i - g.OW : x + i) * rows_at(over ? y + 1 : y) : 0;
+                }
+                double sum[4] = {};
+                for (int j = j0; j < j0 + n_main + n_edge; ++j) {
+                    const uint32_t ctl = (uint32_t)(p.ent[j] >> 32);
+                    const int64_t base = ((int64_t)n * d.C * d.H * d.W + x0) * 4, so = ctl >> 3 & ~3u;
+                    for (int i = 0; i < 4; ++i) {
+                        const bool seen = valid[i] >> (ctl & 31) & 1;
+                        const float v = j < j0 + n_main || seen ? load(base + so + 4 * i) : 0.f;
+                        if (seen) sum[i] += (double)bits(p.ent[j]) * v;
+                    }
+                }
+                for (int i = 0; i < 4 && x0 + i < g.OH * g.OW; ++i) {
+                    const double want = reference(d, c, in, n, k, (x0 + i) / g.OW, (x0 + i) % g.OW);
+                    CHECK(sum[i] == want, "%s N=%d output %d %d at %d: %g instead of %g", name(d), N, n, k, x0 + i, sum[i], want);
+                }
+            }
     }
 }
 
@@ -133,6 +174,9 @@ static void gather_cases()
                                     for (int N = 1; N <= 2; ++N) check_gather({C, H, W, 2, R, S, stride, pad, groups}, N, (H + S) % 2 ? 11 : 5);
     check_gather({512, 1, 1, 3, 3, 3, 1, 1, 1}, 1, 11);
     check_gather({64, 7, 6, 5, 3, 3, 1, 1, 2}, 3, 4);
+    for (int W : {4, 5, 6, 7, 9, 13})
+        for (int R : {1, 2, 3, 5})
+            for (int S : {1, 3, 5, 7}) check_gather({4, 6, W, 2, R, S, 1, S / 2, W % 2 ? 1 : 2}, 2, W % 3 ? 11 : 6);
     check_gather({6, 9, 7, 4, 31, 1, 1, 15, 1}, 1, 11);
     check_gather({6, 1, 2, 4, 31, 1, 2, 15, 1}, 1, 11);
     check_gather({5, 2, 1, 4, 1, 31, 1, 15, 1}, 1, 11);
