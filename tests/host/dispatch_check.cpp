@@ -59,10 +59,12 @@ int launch_fc_gather(const sconv_desc &, const DeviceGather &dev, const GatherSh
     if (!dev.ent) std::abort();
     return ran("fc_gather");
 }
-int launch_mfma(const sconv_desc &, const MfmaTiling &, const DeviceMfma &dev, const DeviceDirect &direct, const float *, float *, int, bool,
+static bool column; // the last launch on the matrix cores was the column kernel's
+int launch_mfma(const sconv_desc &, const MfmaTiling &t, const DeviceMfma &dev, const DeviceDirect &direct, const float *, float *, int, bool,
                 const Epilogue &, int64_t, void *, int *)
 {
     if (!dev.wfrag || (dev.short_rows && !direct.trip)) std::abort();
+    column = t.column;
     return ran("mfma");
 }
 int launch_flat_mc(const sconv_desc &, const FlatMcTiling &t, const DeviceLds &dev, const float *, float *, int, const Epilogue &, int64_t, void *, int *)
@@ -569,6 +571,31 @@ static void one_tap_limits()
     }
 }
 
+// Layers of one tap are the column kernel's on the matrix cores, all others the staged one's.
+static void column_calls()
+{
+    // those of test_gpu_mfma_column.py
+    for (const std::vector<int> &c : {std::vector<int>{15, 40, 40, 32, 1, 30}, {17, 40, 40, 32, 1, 30}, {32, 19, 23, 65, 1, 30}, {33, 9, 11, 65, 1, 80},
+                                      {41, 31, 7, 97, 1, 60}, {96, 28, 28, 70, 2, 33}, {100, 21, 21, 129, 1, 23}, {202, 13, 13, 130, 2, 128}, {250, 11, 13, 64, 1, 150}}) {
+        sconv_csr *h = make({c[0], c[1], c[2], c[3], 1, 1, 1, 0, c[4]}, 0.9);
+        column = false;
+        CHECK(forward(h, c[5]).compare(0, 4, "mfma") == 0 && column, "C%d %dx%d K%d: %s, column %d", c[0], c[1], c[2], c[3], launched.c_str(), column);
+        sconv_destroy_csr(h);
+    }
+    for (const std::vector<int> &c : {std::vector<int>{100, 512, 1020}, {777, 1000, 1020}, {2050, 300, 260}, {140, 3000, 128}}) {
+        sconv_csr *h = make({c[0], 1, 1, c[1], 1, 1, 1, 0, 1}, 0.9);
+        column = false;
+        CHECK(fc(h, c[2]).compare(0, 4, "mfma") == 0 && column, "fc %d -> %d, batch %d: %s, column %d", c[0], c[1], c[2], launched.c_str(), column);
+        sconv_destroy_csr(h);
+    }
+    for (const sconv_desc &d : {sconv_desc{64, 13, 13, 64, 3, 3, 1, 1, 1}, sconv_desc{128, 14, 14, 128, 2, 1, 1, 0, 1}}) {
+        sconv_csr *h = make(d, 0.7);
+        column = true;
+        CHECK(forward(h, 128).compare(0, 4, "mfma") == 0 && !column, "C%d %dx%d stride %d: %s, column %d", d.C, d.R, d.S, d.stride, launched.c_str(), column);
+        sconv_destroy_csr(h);
+    }
+}
+
 int main(int argc, char **argv)
 {
     const std::string what = argc > 1 ? argv[1] : "";
@@ -581,6 +608,7 @@ int main(int argc, char **argv)
     else if (what == "routes") routes();
     else if (what == "flat_mc") flat_mc();
     else if (what == "gather_limits") gather_limits();
+    else if (what == "column_calls") column_calls();
     else if (what == "one_tap_limits") one_tap_limits();
     else if (what == "unpacked_tilings") unpacked_tilings();
     else return 2;

@@ -21,6 +21,9 @@ SHAPES = [
     (12, 75, 101, 144, 12, 4, 4, 0, 1, 150, 0.23),   # one tap along a row
     (11, 25, 97, 87, 6, 9, 4, 0, 1, 150, 0.48),      # few rows
     (12, 97, 109, 270, 12, 13, 8, 0, 2, 150, 0.36),  # eight columns a row of the phases
+    (39, 53, 30, 196, 3, 10, 4, 0, 1, 61, 0.37),     # fewer filter rows than the stride: fours of phases that no weight has
+    (34, 32, 83, 273, 2, 8, 4, 0, 1, 115, 0.588),
+    (34, 22, 94, 285, 7, 18, 8, 0, 1, 71, 0.139),
 ]
 
 

@@ -72,3 +72,8 @@ def test_the_flat_streams_on_the_matrix_cores(program):
 def test_layers_of_one_tap_keep_their_precision(program):
     """The column kernel takes no call from a kernel whose sums are closer to the exact ones."""
     run(program, "one_tap_limits")
+
+
+def test_layers_of_one_tap_run_the_column_kernel(program):
+    """The route names the matrix cores for both of its kernels: which of them a call launches is seen here."""
+    run(program, "column_calls")
