@@ -255,7 +255,7 @@ def _native_calls(torch):
         from . import _sconv_call
     except ImportError:
         return None
-    return _sconv_call if getattr(_sconv_call, "torch_version", None) == str(torch.__version__) else None
+    return _sconv_call if getattr(_sconv_call, "torch_version", None) == str(getattr(torch, "__version__", None)) else None
 
 
 def _use_torch():
