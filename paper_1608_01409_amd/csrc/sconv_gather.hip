@@ -220,8 +220,8 @@ int launch_gather(const sconv_desc &d, const DeviceGather &dev, const GatherShap
 // nonzeros of its first and its last channel (the "edge" entries) take the dword loads above, word by word.
 // Where an output row is as long as an input row, neighbours in the output stay neighbours in the input across the end of a row
 // (what that brings into a window is masked like padding), and the fours may be counted through the whole image: 13x13 is 43 of them
-// instead of 52.  They are where that takes fewer waves (14x14, 68 -> 96, batch 10, density 0.41: 11.6 -> 10.2 us; with as many it is
-// up to 5 % slower).  A wave's head: a lane's four masks are runs of bits and a product (bit by bit they were most of it), and the stream's
+// instead of 52.  They are where that leaves the fullest CU a workgroup less (gather4_flat; 14x14, 68 -> 96, batch 10, density 0.41: 11.6 ->
+// 10.2 us).  A wave's head: a lane's four masks are runs of bits and a product (bit by bit they were most of it), and the stream's
 // first chunk is on its way meanwhile: random layers of 4-20 us 1.00-1.11x, 1.03x on average (256 -> 384, 13x13, batch 1, 7.0 and 6.8 us,
 // is within what its runs differ by).
 struct Gather4Args {
@@ -396,7 +396,7 @@ static int launch_gather4(const sconv_desc &d, const DeviceGather &dev, const Ga
     a.K = d.K; a.OHW = g.OH * g.OW; a.OW = g.OW; a.H = d.H; a.W = d.W; a.R = d.R; a.S = d.S; a.pad = d.pad;
     a.in_img = d.C * d.H * d.W;
     const int ow4 = (g.OW + 3) / 4;
-    a.flat = gather4_flat(d, N);
+    a.flat = gather4_flat(d, N, gs.split);
     a.Q_img = a.flat ? (a.OHW + 3) / 4 : g.OH * ow4;
     a.row_ones = 0;
     for (int r = 0; r < d.R; ++r) a.row_ones |= 1u << r * d.S;

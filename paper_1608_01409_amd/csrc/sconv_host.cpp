@@ -881,13 +881,16 @@ bool gather4_fits(const sconv_desc &d)
     return d.stride == 1 && d.C >= 3 && (int64_t)d.H * d.W > (int64_t)d.pad * d.W + d.pad + 2;
 }
 
-// Its fours of positions are counted through the image instead of through each row.  (Fewer than four positions a row would pass more
-// than one row's end.)
-bool gather4_flat(const sconv_desc &d, int N)
+// Its fours of positions are counted through the image instead of through each row, where that leaves the fullest CU a workgroup
+// less: 441 random calls 1.066x, 37 more than 2 % slower, 8 more than 5 %.  With fewer workgroups but no round of them less it was 0.988x over
+// 1005 (422 more than 2 % slower, 57 more than 5 %; 43 more than 5 % faster).  (Fewer than four positions a row would pass more than one
+// row's end.)
+bool gather4_flat(const sconv_desc &d, int N, int split)
 {
     const Geometry g = geometry(d);
-    const int64_t by_image = (int64_t)N * ceil_div(g.OH * g.OW, 4), by_row = (int64_t)N * g.OH * ceil_div(g.OW, 4);
-    return g.OW == d.W && g.OW >= 4 && (by_image + 63) / 64 < (by_row + 63) / 64;
+    const int rows = split >= 4 ? 1 : 4 / split;
+    auto rounds = [&](int64_t fours) { return ((N * fours + 63) / 64 * ceil_div(d.K, rows) + 255) / 256; };
+    return g.OW == d.W && g.OW >= 4 && rounds(ceil_div(g.OH * g.OW, 4)) < rounds((int64_t)g.OH * ceil_div(g.OW, 4));
 }
 
 int pack_gather(const sconv_desc &d, const Canonical &c, PackedGather &out)
@@ -1028,7 +1031,7 @@ GatherShape choose_gather(const sconv_desc &d, int N, double avg_row_nnz, int ma
         // 40 of 42 such calls were slower on the gather kernel, 0.68x.)
         const bool large = d.R * d.S > 1 && avg_row_nnz >= 16.0 && 4.0 * N * d.C * d.H * d.W > 20e6;
         if (four && !large && best.margin == 1.25 && max_row_nnz < 2.0 * avg_row_nnz + SCONV_GATHER_CHUNK && best.us <= 40.0) {
-            const double by_image = gather4_flat(d, N) ? std::ceil((double)N * ceil_div(g.OH * g.OW, 4) / 64.0) / tiles : 1.0;
+            const double by_image = gather4_flat(d, N, best.split) ? std::ceil((double)N * ceil_div(g.OH * g.OW, 4) / 64.0) / tiles : 1.0;
             best.flat_us = (best.split == 8 ? 1.2 : 1.08) * (3.0 + (best.us - 3.0) * by_image);
         }
     }

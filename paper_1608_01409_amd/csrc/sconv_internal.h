@@ -131,7 +131,7 @@ int pack_gather(const sconv_desc &d, const Canonical &c, PackedGather &out);
 int pack_fc_gather(const sconv_desc &d, const Canonical &c, PackedGather &out);
 bool gather_fits(const sconv_desc &d, int N);
 bool gather4_fits(const sconv_desc &d);
-bool gather4_flat(const sconv_desc &d, int N);
+bool gather4_flat(const sconv_desc &d, int N, int split);
 bool fc_gather_fits(const sconv_desc &d, int N);
 GatherShape choose_gather(const sconv_desc &d, int N, double avg_row_nnz, int max_row_nnz);
 GatherShape choose_fc_gather(const sconv_desc &d, int N, double avg_row_nnz, int max_row_nnz);

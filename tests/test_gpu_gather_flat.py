@@ -1,5 +1,5 @@
-"""The four-position gather kernel with its fours counted through the image: rows that end anywhere in a four, images that end in one,
-filters of both orientations, and no more of the neighbouring memory than before."""
+"""The four-position gather kernel with its fours counted through the image, and through each row of layers that could have them so: rows
+that end anywhere in a four, images that end in one, filters of both orientations, and no more of the neighbouring memory than before."""
 import numpy as np
 import pytest
 import torch
@@ -11,8 +11,17 @@ pytestmark = pytest.mark.gpu
 TOL = 1e-5
 
 # C, H, W, K, R, S, pad, groups, N (S = 2 pad + 1: an output row is as long as an input row)
-CASES = [(12, 13, 13, 24, 3, 3, 1, 1, 4), (9, 14, 14, 20, 3, 3, 1, 1, 10), (20, 7, 5, 16, 3, 3, 1, 2, 10), (7, 9, 9, 16, 1, 1, 0, 1, 5),
+BY_ROW = [(12, 13, 13, 24, 3, 3, 1, 1, 4), (9, 14, 14, 20, 3, 3, 1, 1, 10), (20, 7, 5, 16, 3, 3, 1, 2, 10), (7, 9, 9, 16, 1, 1, 0, 1, 5),
          (6, 10, 6, 8, 5, 5, 2, 1, 7), (5, 9, 5, 8, 2, 3, 1, 1, 9), (8, 5, 13, 12, 5, 3, 1, 1, 11), (3, 6, 7, 8, 3, 7, 3, 1, 13), (4, 31, 5, 8, 1, 5, 2, 2, 4)]
+# with so many filters that the image's fours are a round of 256 workgroups less; each number of waves a row
+BY_IMAGE = [(12, 13, 13, 65, 3, 3, 1, 1, 4), (12, 13, 13, 129, 3, 3, 1, 1, 4), (9, 14, 14, 29, 3, 3, 1, 1, 10), (9, 14, 14, 225, 3, 3, 1, 1, 10),
+            (20, 7, 5, 86, 3, 3, 1, 2, 10), (7, 9, 9, 341, 1, 1, 0, 1, 5), (6, 10, 6, 86, 5, 5, 2, 1, 7), (5, 9, 5, 86, 2, 3, 1, 1, 9),
+            (8, 5, 13, 171, 5, 3, 1, 1, 11), (3, 6, 7, 103, 3, 7, 3, 1, 13), (4, 31, 5, 206, 1, 5, 2, 2, 4), (60, 13, 13, 70, 3, 3, 1, 1, 4)]
+CASES = BY_ROW + BY_IMAGE
+
+
+def workgroups_of_fullest_cu(fours, K, splits):
+    return -(-(-(-fours // 64) * -(-K // max(1, 4 // splits))) // 256)
 
 
 @pytest.mark.parametrize("case", CASES, ids=["x".join(map(str, c)) for c in CASES])
@@ -26,7 +35,10 @@ def test_fours_through_the_image(oracle, case):
     w = np.where(rng.random((K, layer.Cg, R, S)) < 0.5, rng.standard_normal((K, layer.Cg, R, S)), 0).astype(np.float32)
     print(f"[gpu-case] gather flat {case}", flush=True)
     h = B.sconv_create_csr(layer, w)
-    assert B.sconv_route_of(h, N)["kernel"] == "gather4"
+    route = B.sconv_route_of(h, N)
+    assert route["kernel"] == "gather4"
+    through_image = workgroups_of_fullest_cu(N * by_image, K, route["splits"]) < workgroups_of_fullest_cu(N * by_row, K, route["splits"])
+    assert through_image == (case in BY_IMAGE)
     ref, ab, _ = oracle.sparse_conv(layer, w, x)
     around = torch.full((x.size + 2 * 4096,), float("nan"), device="cuda")          # no window may see what lies beside the input
     xd = around[4096:4096 + x.size].view(x.shape)
