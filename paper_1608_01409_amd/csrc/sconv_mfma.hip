@@ -597,8 +597,9 @@ __global__ void __launch_bounds__(256, 2) sconv_mfma_kernel(const MfmaArgs a)
 // with the same split, the same products and the same order of them as above (same bits).  No barrier, no table; a step's loads are
 // asked for two steps before, in straight code: where a branch may leave some out the compiler waits for more of them than a step
 // needs (16.2 us for 15.2), so a last step of fewer than 16 channels (kShort) has registers of its own, loaded at the beginning.
-// What bounds it: the address unit, 14 load instructions of 16 clocks a wave and step where the matrix cores need 384 / 4, then
-// launch and stores, one round of few waves.  192 -> 64, 28x28, batch 64, density 0.3: through LDS 20.5 us, here 15.2 (floor 10); 512 -> 128,
+// What bounds it: the address unit is the busiest (14 load instructions a wave and step, 14 clocks each, where the matrix cores need
+// 384 / 4), for 33 % of the first layer's launch on average, 42 % on a CU with two workgroups (matrix cores 13 %); the rest is one round of few
+// waves: launch, first loads, stores.  192 -> 64, 28x28, batch 64, density 0.3: through LDS 20.5 us, here 15.2 (floor 10); 512 -> 128,
 // 28x28, batch 32: 35.0 -> 25.5; 512 -> 512, 14x14, batch 64: 64.0 -> 48.9; fully connected 2048 -> 512, batch 256: 18.7 -> 13.8.
 // Not taken: weights through LDS, two steps at a time (a barrier every two steps: 17.8 us in the first layer), loads four steps ahead (16.3),
 // two positions a lane (18.0; 512 -> 512 44.8), 128 filters a wave (23.3).

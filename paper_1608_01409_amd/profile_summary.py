@@ -6,7 +6,7 @@ layer's kernel, which bench.py reports as roofline.traffic).
     python -m paper_1608_01409_amd.profile_summary RAW_DIR OUT_FILE [--traffic-json PATH]
 
 RAW_DIR holds one sub-directory per profiler run: kt (kernel trace), fetch (FETCH_SIZE), write (WRITE_SIZE),
-sq1, sq2, sq3 (SQ counters), l2 (TCC request counters), each with the profiler's CSV files and the log.json that
+sq1, sq2, sq3 (SQ counters), l2 (TCC request counters), ta (address unit), each with the profiler's CSV files and the log.json that
 profile_run.py wrote for that run (which forward call launched which dispatches).  Dispatches are attributed to
 layers from the end of the run backwards, so launches that precede the log (library set-up) do not matter.  The
 byte counters and the L2 request counters are scaled by what the same counter reads for the plain device copy
@@ -173,6 +173,13 @@ def main() -> int:
         if "TCC_HIT_sum" in l2 and "TCC_MISS_sum" in l2:
             lines.append("  hit rate                   " + "  ".join(
                 f"{l} {l2['TCC_HIT_sum'].get(l, 0.0) / max(1.0, l2['TCC_HIT_sum'].get(l, 0.0) + l2['TCC_MISS_sum'].get(l, 0.0)):.1%}" for l in layers))
+        lines.append("")
+    ta, _, _ = counters(raw, "ta")
+    if ta.get("TA_TA_BUSY_sum") and ta.get("GRBM_GUI_ACTIVE"):
+        lines.append("address unit (TA, one a CU) per launch: share of the kernel's cycles it is busy, mean over 256 CUs; load instructions from buffers")
+        for l in layers:
+            cyc = ta["GRBM_GUI_ACTIVE"].get(l, 0.0) / 8.0
+            lines.append(f"  {l:16s} {ta['TA_TA_BUSY_sum'].get(l, 0.0) / max(1.0, cyc * 256.0):6.1%}  {ta.get('TA_BUFFER_READ_WAVEFRONTS_sum', {}).get(l, 0.0):.4g}")
         lines.append("")
     if sq1 and sq2 and "GRBM_GUI_ACTIVE" in sq1:
         lines.append("derived per layer, each beside its ceiling (kernel cycles = GRBM_GUI_ACTIVE / 8 XCDs; SQ instruction counters "
