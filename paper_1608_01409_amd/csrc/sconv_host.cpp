@@ -1032,7 +1032,9 @@ GatherShape choose_gather(const sconv_desc &d, int N, double avg_row_nnz, int ma
         // matrix cores 1.25 stays: 40 of 42 such calls were slower on the gather kernel, 0.68x.)
         const bool large = d.R * d.S > 1 && avg_row_nnz >= 16.0 && 4.0 * N * d.C * d.H * d.W > 20e6;
         if (four && !large && best.margin == 1.25 && max_row_nnz < 2.0 * avg_row_nnz + SCONV_GATHER_CHUNK && best.us <= 40.0) {
-            const double by_image = gather4_flat(d, N, best.split) ? std::ceil((double)N * ceil_div(g.OH * g.OW, 4) / 64.0) / tiles : 1.0;
+            // (what fours through the image would take counts, however they are counted: the model reads high where output rows leave fours
+            // partly empty; 50 random calls that this brings 1.19x, 5 of them more than 2 % slower)
+            const double by_image = g.OW == d.W && g.OW >= 4 ? std::ceil((double)N * ceil_div(g.OH * g.OW, 4) / 64.0) / tiles : 1.0;
             best.flat_us = (best.split == 8 ? 1.2 : 1.08) * (3.0 + (best.us - 3.0) * by_image);
         }
     }

@@ -518,6 +518,8 @@ static void gather_limits()
         {{260, 21, 21, 16, 3, 3, 1, 1, 2}, 19, {690, 721, 751}, false},  // rows over eight waves: 21.1, 18.2
         {{384, 13, 13, 256, 3, 3, 1, 1, 2}, 16, {140, 173, 200}, true},  // 22.7, 25.3
         {{39, 53, 53, 58, 3, 3, 1, 1, 1}, 59, {3, 4, 6}, true},          // 20.7, 22.6
+        {{80, 7, 7, 152, 1, 1, 1, 0, 1}, 139, {1}, true},                // fours through the image, or through each row: 4.9, 8.6
+        {{52, 7, 7, 103, 3, 3, 1, 1, 1}, 197, {5, 6, 7}, true},          // 5.5, 8.4
     };
     for (const Conv &c : convs) {
         sconv_csr *h = rows_of(c.d, c.nnz);
