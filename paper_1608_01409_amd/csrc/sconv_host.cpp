@@ -1024,18 +1024,16 @@ GatherShape choose_gather(const sconv_desc &d, int N, double avg_row_nnz, int ma
         // them, stays at 24.3 us and would take 15.1.)
         if (wgs > 256 && wgs < 320) best.margin = 1.75;
         // Against the flat streams on the vector units the four-position kernel is trusted further where its rows are level and the launch
-        // is short (the input then comes from L2).  Of 996 random calls that moved there at 1.08 50 were more than 2 % slower, down to 0.77x
-        // (1.24x on average).  Left out since: long rows of several taps over more input than L2 holds (15 of the 35 below 1.25 were
-        // slower, 1.01x on average) and below 1.2 rows over eight waves (3 of 4).  Of 161 of a later draw 6 are slower, down to 0.74x (1.28x;
-        // rows of 16 and more nonzeros of one tap over more than 50 MB, nine calls of two draws: 0.95x).  384 -> 256 in two groups, 13x13,
-        // batch 16, density 0.1: 25.3 -> 22.7 us.  (Skewed rows: down to 0.59x, strided layers to 0.74x, long launches to 0.81x.  Against the
-        // matrix cores 1.25 stays: 40 of 42 such calls were slower on the gather kernel, 0.68x.)
-        const bool large = d.R * d.S > 1 && avg_row_nnz >= 16.0 && 4.0 * N * d.C * d.H * d.W > 20e6;
-        if (four && !large && best.margin == 1.25 && max_row_nnz < 2.0 * avg_row_nnz + SCONV_GATHER_CHUNK && best.us <= 40.0) {
-            // (what fours through the image would take counts, however they are counted: the model reads high where output rows leave fours
-            // partly empty; 50 random calls that this brings 1.19x, 5 of them more than 2 % slower)
+        // is short (the input then comes from L2), and its model reads high where output rows leave fours partly empty: what fours through the
+        // image would take counts, however they are counted (50 random calls that this brings 1.19x, 5 of them more than 2 % slower).  Of
+        // 996 random calls that moved there at 1.08 50 were more than 2 % slower, down to 0.77x (1.24x on average), of 161 of a later draw 6, down
+        // to 0.74x (1.28x); their sums are half as far from the exact ones.  Not taken: to leave out long rows of several taps over more than
+        // 20 MB (15 of 35 calls slower on the gather kernel, 1.01x on average, 6 of 21 of another draw, 1.02x), rows over eight waves (3 of 4; 1 of
+        // 5, 1.03x).  384 -> 256 in two groups, 13x13, batch 16, density 0.1: 25.3 -> 22.7 us.  (Skewed rows: down to 0.59x, strided layers to
+        // 0.74x, long launches to 0.81x.  Against the matrix cores 1.25 stays: 40 of 42 such calls were slower on the gather kernel, 0.68x.)
+        if (four && best.margin == 1.25 && max_row_nnz < 2.0 * avg_row_nnz + SCONV_GATHER_CHUNK && best.us <= 40.0) {
             const double by_image = g.OW == d.W && g.OW >= 4 ? std::ceil((double)N * ceil_div(g.OH * g.OW, 4) / 64.0) / tiles : 1.0;
-            best.flat_us = (best.split == 8 ? 1.2 : 1.08) * (3.0 + (best.us - 3.0) * by_image);
+            best.flat_us = 1.08 * (3.0 + (best.us - 3.0) * by_image);
         }
     }
     return best;

@@ -513,9 +513,6 @@ static void gather_limits()
         {{216, 18, 18, 35, 3, 3, 1, 1, 1}, 5, {1419}, false},          // 280 workgroups: 27.0 us, 24.6
         {{216, 18, 18, 32, 3, 3, 1, 1, 1}, 5, {1419}, true},           // 256
         {{256, 13, 13, 384, 3, 3, 1, 1, 1}, 1, {230}, true},
-        {{453, 14, 14, 35, 3, 3, 1, 1, 1}, 162, {167, 196, 219}, false}, // long rows over 58 MB: 44.0 us, 35.3
-        {{386, 15, 15, 59, 3, 3, 1, 1, 1}, 182, {64, 81, 100}, false},   // 42.0, 35.8
-        {{260, 21, 21, 16, 3, 3, 1, 1, 2}, 19, {690, 721, 751}, false},  // rows over eight waves: 21.1, 18.2
         {{384, 13, 13, 256, 3, 3, 1, 1, 2}, 16, {140, 173, 200}, true},  // 22.7, 25.3
         {{39, 53, 53, 58, 3, 3, 1, 1, 1}, 59, {3, 4, 6}, true},          // 20.7, 22.6
         {{80, 7, 7, 152, 1, 1, 1, 0, 1}, 139, {1}, true},                // fours through the image, or through each row: 4.9, 8.6
