@@ -623,11 +623,11 @@ static const sconv_csr::Choice &choose_kernel(sconv_csr *h, bool fc, int N, doub
     // column kernel is faster: 400 -> 64, 28x28, batch 100, density 0.3 takes 61.5 us, and would take 33.6.)
     if (c.mfma.one_tap) {
         const bool staged = c.kind == sconv_csr::kMfma, flat_mc = c.kind == sconv_csr::kFlatMc;
-        const int parts = c.mfma.splits;
+        const int parts = c.mfma.splits, chain_parts = SCONV_MFMA_CHAIN_PARTS * (h->max_row_nnz <= SCONV_MFMA_CHAIN_ROW ? 2 : 1);
         MfmaTiling m = c.mfma;
         bool can = choose_mfma_column(h->desc, N, staged || flat_mc ? parts : 1, m);
         const bool near = !h->short_rows && (c.kind == sconv_csr::kGather ? !fc && gather4_fits(h->desc) && h->max_row_nnz <= SCONV_MFMA_GATHER_ROW
-                                                                          : lds_splits <= SCONV_MFMA_CHAIN_PARTS * m.splits);
+                                                                          : lds_splits <= chain_parts * m.splits);
         const double margin = c.kind != sconv_csr::kGather ? kMfmaMargin : avg_row_nnz(h) < kColumnShortRows ? kColumnGatherMarginShort : kColumnGatherMargin;
         if (!staged && !near) can = choose_mfma_column(h->desc, N, parts, m);   // (for the tuner, as it was)
         c.mfma = can ? m : MfmaTiling();

@@ -169,8 +169,11 @@ struct MfmaTiling {
 // (relative 2-norm in 1e-8 on rectified normals: 48 3.8 / 4.8, 64 4.2 / 5.0, 80 4.6-4.9 / 4.8, 128 5.4 / 4.9; plain normals: 64 5.4 / 5.9, 80 5.9 / 5.9;
 // at 72 one random layer with a bias had 4.1 / 3.9).
 #define SCONV_MFMA_GATHER_ROW 48
-// The flat streams' chains in so many parts reach what one on the matrix cores has (in 1e-8: 64 nonzeros 4.2, eight parts of eight
-// 4.2; 256: 7.0, of 32 7.3; 16 parts of 16 5.9).
+// A sum in one chain on the matrix cores is no further from the exact one than the flat streams' in up to so many parts, and in up to twice as
+// many where rows have at most SCONV_MFMA_CHAIN_ROW nonzeros: adding the parts up rounds as well (in 1e-8 on rectified normals, here / there: 64
+// nonzeros 4.1 / 10.4 in one part, 6.9 in four and five, 7.5 in eleven; 256 7.1 / 9.8 in eight, 9.3 in eleven; fully connected 265 7.2 / 9.4 in
+// twelve, 385 8.7 / 10.3 in sixteen; 512 in three parts 7.0 / 10.9 in fifteen).
+#define SCONV_MFMA_CHAIN_ROW 512
 #define SCONV_MFMA_CHAIN_PARTS 8
 struct PackedMfma {
     std::vector<uint16_t> wfrag;  // [group][32-row tile][step][part][lane][8], one spare step behind

@@ -130,8 +130,9 @@ def test_no_further_from_the_exact_sums_than_the_gather_kernel(C, hw, K, N, dens
     assert relative(rows(B.sconv_forward_fused(h, xd, bias, False)), with_bias) <= relative((sums + bias.double()[:, None]).float(), with_bias)
 
 
-# C, K, N, density: fully connected calls that it takes from flat streams of 1, 4, 6, 8 and 32 parts
-@pytest.mark.parametrize("C,K,N,density", [(268, 3276, 480, 0.1558), (210, 3785, 344, 0.5432), (238, 1351, 812, 0.5591), (770, 1513, 144, 0.9151), (2263, 240, 476, 0.4298)])
+# C, K, N, density: fully connected calls that it takes from flat streams of 1, 4, 6, 8 and 32 parts; from 12 and 16 in one
+@pytest.mark.parametrize("C,K,N,density", [(268, 3276, 480, 0.1558), (210, 3785, 344, 0.5432), (238, 1351, 812, 0.5591), (770, 1513, 144, 0.9151), (2263, 240, 476, 0.4298),
+                                         (295, 253, 712, 0.9), (350, 470, 596, 0.407), (402, 491, 720, 0.96)])
 def test_no_further_from_the_exact_sums_than_the_flat_streams(C, K, N, density):
     layer = B.fc_layer(C, K)
     w, x, bias, exact = exact_and_inputs(layer, N, density, C)
